@@ -54,7 +54,6 @@ void BatchCoef::set(hipStream_t s, int nb_, const double* const* a, const int* K
     for (int i = 0; i <= K[c]; ++i) A[(size_t)i * nb + c] = a[c][i];
   host = A;
   this->K.assign(K, K + nb);
-  upload(dK, this->K.data(), this->K.size(), s);
   std::vector<float> A32(A.begin(), A.end());
   upload(d64, A.data(), A.size(), s);
   upload(d32, A32.data(), A32.size(), s);
@@ -80,7 +79,7 @@ void filter_apply_batch_on(hipStream_t s, const ChainBatch& bt, const BatchCoef&
   // column-major
   const int var = batch_variant<T>(s, bt);
   if (var == 5) {
-    chain_lds_filter<T>(s, bt, A, co.dK.as<int>(), v, w);
+    chain_res_batch<T>(s, bt, A, K, v, w, bufA, bufB);
     return;
   }
   if (var == 4) {
@@ -186,15 +185,14 @@ void BatchFilter::form(polfed_ctx* c, const std::vector<SolveRun*>& runs) {
   bt.set_scale(Ec.data(), dE.data());
   co.set(c->stream, nb, a.data(), K.data());
   // the step kernel is picked before run() records the recurrence
-  if (fp32)
-    (void)batch_variant<float>(c->stream, bt);
-  else
-    (void)batch_variant<double>(c->stream, bt);
+  const int var =
+      fp32 ? batch_variant<float>(c->stream, bt) : batch_variant<double>(c->stream, bt);
   graph.reset();
   graph_pref = runs[0]->p.graph;
   mode = kTimeDirect;
   if (graph_pref == 2 || co.Kmax < 8 || co.Kmax > kGraphMaxSteps) mode = kDirect;
   if (graph_pref == 1 && mode == kTimeDirect) mode = kGraph;
+  if (var == 5 && mode == kTimeDirect) mode = kDirect;  // a few launches in all
   if (mode == kTimeDirect) {
     // the way an earlier batch of this pattern, width, precision and order
     // (to a factor of two) chose

@@ -34,7 +34,7 @@ void BlockWs::init(polfed_ctx* ctx, const polfed_op* op, int s_, bool fp32_,
   w.alloc(n * sizeof(double));
   save.alloc(n * sizeof(double));
   const size_t tb = fp32 ? sizeof(float) : sizeof(double);
-  bA.alloc(n * tb);
+  bA.alloc(filter_buf_bytes((int64_t)n, tb));
   bB.alloc(n * tb);
   if (fp32) {
     v32.alloc(n * sizeof(float));

@@ -675,6 +675,7 @@ polfed_status polfed_op_set_kernel(polfed_op* op, int precision, int variant, in
                 "no staged-tile kernel of this shape for this chain length and precision");
     }
     op->tuned[pi] = variant;
+    op->forced[pi] = variant >= 0;
     if (chosen) *chosen = op->tuned[pi];
     return POLFED_OK;
   });
@@ -861,12 +862,12 @@ polfed_status polfed_filter_apply(polfed_ctx* ctx, const polfed_op* op, double E
     CtxLock lk(ctx);
     const int64_t D = op->D;
     if (precision == POLFED_FP64) {
-      DevBuf A(std::max<int64_t>(D, 1) * sizeof(double)), Bb(std::max<int64_t>(D, 1) * sizeof(double));
+      DevBuf A(filter_buf_bytes(D, sizeof(double))), Bb(std::max<int64_t>(D, 1) * sizeof(double));
       filter_apply<double>(ctx, op, E_c, dE, a, K, static_cast<const double*>(v),
                            static_cast<double*>(w), A.as<double>(), Bb.as<double>());
       HIPC(hipStreamSynchronize(ctx->stream));
     } else {
-      DevBuf A(std::max<int64_t>(D, 1) * sizeof(float)), Bb(std::max<int64_t>(D, 1) * sizeof(float));
+      DevBuf A(filter_buf_bytes(D, sizeof(float))), Bb(std::max<int64_t>(D, 1) * sizeof(float));
       filter_apply<float>(ctx, op, E_c, dE, a, K, static_cast<const float*>(v),
                           static_cast<float*>(w), A.as<float>(), Bb.as<float>());
       HIPC(hipStreamSynchronize(ctx->stream));

@@ -1158,11 +1158,15 @@ static int tuned_variant(hipStream_t s, const polfed_op* op) {
   const std::string pkey = std::string(sizeof(T) == 8 ? "step64" : "step32");
   {
     const int v = pattern_choice(op, pkey);
-    if (v >= 0) return op->tuned[pi] = v;
+    if (v >= 0) {
+      chain_res_prepare(s, op, pi == 1);
+      return op->tuned[pi] = v;
+    }
   }
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   HIPC(hipStreamIsCapturing(s, &cs));
   if (cs != hipStreamCaptureStatusNone) return 0;
+  chain_res_prepare(s, op, pi == 1);  // the tables of the resident filter
   const size_t n = (size_t)op->D;
   DevBuf bv(n * sizeof(T)), bb1(n * sizeof(T)), bb2(n * sizeof(T));
   HIPC(hipMemsetAsync(bv.get(), 0, n * sizeof(T), s));

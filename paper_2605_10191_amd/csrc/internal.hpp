@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cstdint>
 #include <cstdio>
@@ -299,6 +300,7 @@ enum class Model { Chain, Qsun, Csr, Qrem };
 // Opaque handles of the C ABI.
 namespace polfed {
 struct Server;
+struct ResTable;
 }
 
 struct polfed_ctx {
@@ -318,6 +320,9 @@ struct polfed_ctx {
   // "<pattern>|<what>"; guarded by tune_mu
   std::mutex tune_mu;
   std::map<std::string, int> pattern_tuned;
+  // tables of the resident recurrence per chain pattern and slab count, owned
+  // by the operators of the pattern; guarded by tune_mu
+  std::map<std::string, std::weak_ptr<polfed::ResTable>> res_tables;
   // reusable workspaces
   polfed::DevBuf scratch_red;  // reduction partials
   polfed::DevBuf scratch_scalar;
@@ -417,6 +422,12 @@ struct polfed_op {
   // step-kernel variant picked by timing on first use, per precision
   // (-1: not tuned yet, 0: segment kernel, 1 + i: tile kernel tiles[i])
   mutable int tuned[2] = {-1, -1};
+  // the step-kernel variant was set by the caller, per precision: filters
+  // then run on that kernel
+  bool forced[2] = {false, false};
+  // tables of the resident recurrence by slab count (guarded by ctx->tune_mu)
+  mutable std::map<int, std::shared_ptr<polfed::ResTable>> res_tables;
+  polfed::DevBuf d_fields;  // 32 site terms and the constant (FP64)
   // POLFED_PRECISION_AUTO resolved for this operator (-1: not timed yet)
   mutable int auto_precision = -1;
   std::vector<double> split_dseg;  // uniform diagonal part of each segment
@@ -459,6 +470,8 @@ struct ChainBatch {
   DevBuf fab64, fab32;    // [nb][64] low-bit field sums (bits 0-4 | 5-9)
   DevBuf dseg64, dseg32;  // [nseg][nb] uniform diagonal part per segment
   DevBuf sc64, sc32;      // [2][nb] sigma = 2/dE, tau = -2 E_c/dE
+  DevBuf fields;          // [nb][33] site terms and constant (resident kernel)
+  DevBuf res_state;       // team state of the resident kernel
   std::vector<double> E_c, dE;  // host copies of each column's rescaling
   void init(polfed_ctx* c, const polfed_op* const* o, int n);
   void set_scale(const double* E_c, const double* dE);
@@ -474,19 +487,92 @@ void chain_batch_step(hipStream_t s, const ChainBatch& bt, int64_t ld, bool fina
 // columns per launch), 2, 3 interleaved blocks (element (r, c) at r nb + c;
 // 2 or 4 workgroups per compute unit), 4 column-major blocks with every
 // column stepped by its operator's own tuned single-column kernel (the
-// staged-tile kernels of long chains), 5 the LDS-resident whole filter
-// (one workgroup per column; short chains).  Not while the stream is
+// staged-tile kernels of long chains), 5 the resident recurrence (the whole
+// filter in one launch, see resident.hip).  Not while the stream is
 // captured (returns 0 then, without keeping it).
 template <typename T>
 int batch_variant(hipStream_t s, const ChainBatch& bt);
-// Variant 5: the whole filter of every column in LDS (one workgroup per
-// column, a barrier between steps), for short chains.  A: (Kmax + 1) x nb
-// coefficients, Kc: device int32 orders; v, w column-major D x nb.
+// Chains of which variant 5 can be forced: those of which two vectors and the
+// tables of one column fit the LDS of a compute unit.
 template <typename T>
 bool chain_lds_filter_fits(const polfed_op* op0);
+// Resident recurrence (resident.hip): the K steps of a column or a pair of
+// columns in one launch, by a team of workgroups on one XCD.
+constexpr int kResThreads = 512;  // up to 256 VGPRs a lane for the rows' state
+constexpr int kResMaxL = 20;
+constexpr int kResMaxPairRows = 3;  // rows a thread of a pair of columns
+constexpr int kResMaxRows = 6;      // rows a thread of a single column
+constexpr int kResMaxSlabs = 32;
+constexpr int kResTeamsPerXcd = 16;
+struct ResTeam {
+  int joined, n, group[2];
+  int pad0[12];
+  int flag[kResMaxSlabs];  // barriers each member has reached
+};
+struct ResState {
+  int slots[16 * 16];  // workgroups that joined, per XCD, a cache line apart
+  int queue, err;
+  int pad[14];
+  ResTeam teams[16 * kResTeamsPerXcd];
+};
+// Entries of the slab tables: an LDS row, kResFar | row of another slab, or
+// kResNone.
+constexpr uint32_t kResFar = 1u << 31, kResNone = 0xFFFFFFFFu;
+struct ResBuild {
+  int L, N, periodic, sep, nslab, R, nl, nh;
+  int64_t D;
+  const uint32_t* binom;
+  uint32_t* slot;   // [nslab][R][nl + nh + 1][threads]
+  uint32_t* state;  // [D]
+  int32_t* counts;  // most hops of a row inside its slab, most leaving it
+};
 template <typename T>
-void chain_lds_filter(hipStream_t s, const ChainBatch& bt, const T* A, const int* Kc, const T* v,
-                      T* w);
+struct ResArgs {
+  int L, N, periodic, sep, nb, nslab, teams_per_xcd, pairs, ngrp, field_cols;
+  int R, nl, nh, rows_cap;  // of the tables; LDS row rows_cap holds a zero
+  int i_top, i_bot, first, lda;
+  int64_t D;
+  double t_in, t_pb, vzz;
+  const uint32_t* slot;
+  const uint32_t* state;
+  const double* fields;  // [field_cols][33]: 32 site terms, constant
+  const T* sc;           // [2][nb]: sigma, tau
+  const T* A;            // [K + 1][lda] coefficients
+  const T* v;
+  T *w, *X, *Y;
+  ResState* st;
+};
+
+// Slab tables of a chain pattern for one number of slabs.
+struct ResTable {
+  int nslab = 0, R = 0, nl = 0, nh = 0, rows = 0, sep = 0;
+  DevBuf slot, state;
+};
+// Whether filters of op in this precision run as one resident launch (short
+// matrix-free chains whose step kernel is not forced); builds the tables for
+// it (not while s is captured); the bytes such a filter needs behind the D
+// elements of its first recurrence buffer.
+bool chain_res_applies(const polfed_op* op, bool fp32);
+void chain_res_prepare(hipStream_t s, const polfed_op* op, bool fp32);
+size_t chain_res_tail();
+// Steps from which a filter goes that way: the resident launch itself
+// (joining, tables, two small kernels) takes about 20 us.
+constexpr int kResMinSteps = 16;
+constexpr int kResChunk = 8192;  // steps of one launch
+// Bytes of a filter's first recurrence buffer for n elements.
+inline size_t filter_buf_bytes(int64_t n, size_t elem) {
+  return (size_t)std::max<int64_t>(n, 1) * elem + chain_res_tail();
+}
+// The filter as one resident launch; false (nothing done) where it does not
+// apply or K is small.
+template <typename T>
+bool chain_res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const double* a,
+                      int K, const T* v, T* w, T* bufA, T* bufB);
+bool chain_res_batch_fits(hipStream_t s, const polfed_op* op0, int nb);
+template <typename T>
+void chain_res_batch(hipStream_t s, const ChainBatch& bt, const T* A, int K, const T* v, T* w,
+                     T* bufA, T* bufB);
+
 // One step with variant var; v column-major (column stride D) when vcm,
 // else in the variant's layout; out column-major when ocm.
 template <typename T>

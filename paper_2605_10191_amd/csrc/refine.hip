@@ -111,7 +111,7 @@ void refine(SolveRun& run, Extracted& ex, double theta_min) {
   const double lock_tol = 0.1 * run.tol_resid;
   if (n == 0) return;
   const size_t n32 = (size_t)D * n * sizeof(float), n64 = (size_t)D * n * sizeof(double);
-  DevBuf r32(n32), z32(n32), bA(n32), bB(n32), Ua(n64), HUa(n64), W(n64), HW(n64), tmp(n64),
+  DevBuf r32(n32), z32(n32), bA(filter_buf_bytes(D * n, sizeof(float))), bB(n32), Ua(n64), HUa(n64), W(n64), HW(n64), tmp(n64),
       dE, dP;
   const bool batched = op->model == Model::Chain && !op->pattern_key.empty() && op->split_nseg > 0;
   std::vector<std::vector<double>> q(n, std::vector<double>(std::max(K, 1)));

@@ -1,0 +1,805 @@
+// Resident Clenshaw recurrence of a chain operator: the K steps of one column
+// (or of two interleaved columns) in ONE launch, by a team of workgroups that
+// live on one XCD.
+//
+// What bounds short chains is not bytes but the launch of every step: at
+// L = 18 a step's vectors are 389 KB a column, 0.2 us of HBM time, yet a step
+// took 4 to 6 us alone and 17.4 us for 13 columns, whose interleaved block
+// outgrows an XCD's 4 MB L2.  Here every member of a team owns a fixed slab
+// of rows for the whole recurrence, so
+//   - v, b_{i+1}, b_{i+2}, the diagonal and the target of every hop of its
+//     rows stay in registers: a step decodes nothing and streams nothing;
+//   - the slab of b_{i+1} sits in LDS, where most hops land; the hops that
+//     leave the slab gather from the team's vector in global memory, which
+//     the team's own L2 holds (copying those rows into LDS first, so that all
+//     hops are LDS reads, measured slower: it adds a barrier to each step);
+//   - a step ends with a barrier of the team's members (0.9 us for 32 of
+//     them; a launch in a replayed graph takes 1.6 us before it does
+//     anything) instead of a kernel boundary.
+// Measured (FP64, us a step, before -> here): one column at L = 12 3.6 -> 1.0,
+// L = 16 4 -> 2.0, L = 18 5 -> 3.5; 16 columns at L = 14 4.1 -> 1.6; 13 columns
+// at L = 18 17.3 -> 5.1, of which the barrier and the gathers' round trip are
+// 1.3 and the LDS reads of the hops most of the rest.
+// The columns are spread over the eight XCDs, so no data crosses them.
+//
+// Teams form from the workgroups that are running: a workgroup reads the XCD
+// it is on and joins that XCD's next team; the first member closes the team
+// when it is full or after a bounded time, and a workgroup that comes later
+// leaves at once.  So a barrier only ever waits for workgroups that run, no
+// matter what else the device executes, and a team with fewer members than
+// slabs walks several slabs a member (reloading their state) instead.  Column
+// groups are handed out by a counter, so any set of teams finishes them all.
+//
+// Members exchange data through the L2 of their XCD: a store is in it once
+// the writer's vmcnt is zero (the L1 writes through), and the readers' loads
+// bypass their L1 (agent scope).
+#include <algorithm>
+
+#include <iterator>
+#include <memory>
+
+#include "chain_dev.hpp"
+#include "internal.hpp"
+
+namespace polfed {
+
+namespace {
+
+constexpr int kResClosed = 1 << 20;
+constexpr int kFieldStride = 33;  // field table of a column: 32 sites, constant
+constexpr int kAuxAgent = 16;     // load of agent scope: past the L1
+
+__device__ __forceinline__ int res_load(const int* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ int res_add(int* p, int v) {
+  return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void res_store(int* p, int v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// the XCD of this workgroup (hardware register XCC_ID, 4 bits)
+__device__ __forceinline__ int xcc_id() { return __builtin_amdgcn_s_getreg(20 | (3 << 11)) & 15; }
+
+struct TeamView {
+  ResTeam* t;
+  int n, rank;
+  int step;  // barriers passed
+  int failed;
+};
+
+// All members have stored what they wrote before; afterwards all see it.
+// between() runs once the workgroup's own LDS reads are done, while the other
+// members arrive.  Every member raises its own flag and one wave polls all of
+// them with one load.
+template <class F>
+__device__ __forceinline__ void team_barrier(TeamView& tv, int* err, F&& between) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  ++tv.step;
+  if (tv.n > 1 && threadIdx.x == 0) res_store(&tv.t->flag[tv.rank], tv.step);
+  between();
+  if (tv.n > 1 && threadIdx.x < 64 && !tv.failed) {
+    const int* f = &tv.t->flag[min((int)threadIdx.x, tv.n - 1)];
+    const long long t0 = wall_clock64();
+    while (__ballot(res_load(f) < tv.step)) {
+      // every member runs, so this ends; the bound (30 s of the 100 MHz
+      // clock) only keeps a broken device from hanging
+      if (wall_clock64() - t0 > 3000000000LL) {
+        tv.failed = 1;
+        res_store(err, 1);
+        break;
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// Joins the next team of this workgroup's XCD (nslab members); false for a
+// workgroup that came too late or is not needed.
+__device__ __forceinline__ bool team_join(ResState* st, int nslab, int teams_per_xcd, int* s_join,
+                                          TeamView& tv) {
+  if (nslab <= 1) return true;
+  if (threadIdx.x == 0) {
+    const int x = xcc_id();
+    const int slot = res_add(&st->slots[16 * x], 1);
+    const int team = slot / nslab;
+    int n = 0, rank = 0;
+    if (team < teams_per_xcd) {
+      ResTeam* t = &st->teams[x * kResTeamsPerXcd + team];
+      rank = res_add(&t->joined, 1);
+      if (rank == 0) {
+        const long long t0 = wall_clock64();
+        while (res_load(&t->joined) < nslab && wall_clock64() - t0 < 10000) {
+        }
+        n = __hip_atomic_fetch_or(&t->joined, kResClosed, __ATOMIC_RELAXED,
+                                  __HIP_MEMORY_SCOPE_AGENT);
+        res_store(&t->n, n);
+      } else if (rank < kResClosed) {
+        // the first member runs and closes the team within 100 us
+        while ((n = res_load(&t->n)) == 0) __builtin_amdgcn_s_sleep(1);
+      }
+    }
+    s_join[0] = n;
+    s_join[1] = rank;
+    s_join[2] = x * kResTeamsPerXcd + team;
+  }
+  __syncthreads();
+  tv.n = uniform(s_join[0]);
+  tv.rank = uniform(s_join[1]);
+  if (tv.n == 0 || tv.rank >= nslab) return false;
+  tv.n = min(tv.n, nslab);
+  tv.t = &st->teams[uniform(s_join[2])];
+  return true;
+}
+
+template <typename T, int G>
+struct Cols {
+  T x[G];
+};
+
+template <typename T, int G>
+__device__ __forceinline__ Cols<T, G> rload(rsrc_t r, uint32_t off) {
+  Cols<T, G> c;
+  if constexpr (G == 2)
+    bload2<T, kAuxAgent>(r, off, 0, c.x[0], c.x[1]);
+  else
+    c.x[0] = bload<T, kAuxAgent>(r, off, 0);
+  return c;
+}
+template <typename T, int G>
+__device__ __forceinline__ void rstore(const Cols<T, G>& c, rsrc_t r, uint32_t off) {
+  if constexpr (G == 2)
+    bstore2<0>(c.x[0], c.x[1], r, off, 0);
+  else
+    bstore<0>(c.x[0], r, off, 0);
+}
+template <typename T, int G>
+__device__ __forceinline__ Cols<T, G> lread(const unsigned char* b, uint32_t off) {
+  return *reinterpret_cast<const Cols<T, G>*>(b + off);
+}
+
+// Row r of slab m of D rows in nslab slabs.
+__host__ __device__ __forceinline__ int64_t slab_row(int64_t D, int nslab, int m) {
+  return D * m / nslab;
+}
+
+// ------------------------------------------------------------ tables ----
+
+// Targets of the hops of a state: f(slot, rank), slot 0 the periodic bond,
+// slot b + 1 the bond (b, b + 1).
+template <class F>
+__device__ __forceinline__ void chain_targets(int L, int periodic, uint32_t s, int64_t r,
+                                              const uint32_t* binom, F&& f) {
+  int below = 0;
+  for (int b = 0; b + 1 < L; ++b) {
+    const uint32_t sb = (s >> b) & 1u;
+    if (sb != ((s >> (b + 1)) & 1u)) {
+      const int64_t d = binom[b * kBinomN + below];
+      f(b + 1, sb ? r + d : r - d);
+    }
+    below += (int)sb;
+  }
+  if (periodic && (((s >> (L - 1)) ^ s) & 1u)) {
+    const uint32_t sp = s ^ (1u | (1u << (L - 1)));
+    int k = 0;
+    int64_t rk = 0;
+    for (int x = 0; x < L; ++x)
+      if ((sp >> x) & 1u) rk += binom[x * kBinomN + (++k)];
+    f(0, rk);
+  }
+}
+
+// The slab tables of a chain pattern: FILL = false counts (most hops of a row
+// inside its slab, most leaving it), FILL = true writes.
+// One workgroup per slab; thread t holds rows t, t + NT, ... of the slab.
+template <bool FILL>
+__global__ __launch_bounds__(kResThreads) void k_res_build(ResBuild p) {
+  __shared__ uint32_t s_binom[(kResMaxL + 1) * kBinomN];
+  for (int i = threadIdx.x; i < (kResMaxL + 1) * kBinomN; i += kResThreads) s_binom[i] = p.binom[i];
+  __syncthreads();
+  const int m = blockIdx.x;
+  const int64_t row0 = slab_row(p.D, p.nslab, m), row1 = slab_row(p.D, p.nslab, m + 1);
+  for (int j = 0; j < p.R; ++j) {
+    const int64_t r = row0 + threadIdx.x + (int64_t)kResThreads * j;
+    const bool valid = r < row1;
+    uint32_t s = 0, rr = valid ? (uint32_t)r : 0u;
+    int k = p.N;
+    for (int b = p.L - 1; b >= 0; --b) {
+      const uint32_t c = s_binom[b * kBinomN + k];
+      if (k > 0 && rr >= c) {
+        s |= 1u << b;
+        rr -= c;
+        --k;
+      }
+    }
+    // entry (m, j, slot, thread): the hops inside the slab (LDS rows), those
+    // leaving it (rows), the periodic bond.  A hop that leaves takes the slot
+    // of its bond among the bonds that leave in this wave, so that the wave's
+    // gather of a slot is one run of rows; in a wave with more such bonds
+    // than slots (at a slab's edge) each lane packs its own.
+    const int64_t per = (int64_t)(p.nl + p.nh + 1) * kResThreads;
+    const int64_t e = ((int64_t)m * p.R + j) * per + threadIdx.x;
+    uint32_t out = 0;  // bonds that leave the slab in this row
+    int nl = 0;
+    if (valid)
+      chain_targets(p.L, p.periodic, s, r, s_binom, [&](int slot, int64_t to) {
+        if (to < row0 || to >= row1) {
+          out |= 1u << slot;
+        } else if (slot == 0 && p.sep) {
+          if (FILL) p.slot[e + (int64_t)(p.nl + p.nh) * kResThreads] = (uint32_t)(to - row0);
+        } else {
+          if (FILL) p.slot[e + (int64_t)nl * kResThreads] = (uint32_t)(to - row0);
+          ++nl;
+        }
+      });
+    if (p.sep) out &= ~1u;
+    const int nh = __popc(out);
+    uint32_t any = 0;
+    for (int b = 0; b < p.L; ++b)
+      if (__ballot((out >> b) & 1u)) any |= 1u << b;
+    if (FILL && valid) {
+      const uint32_t set = __popc(any) <= p.nh ? any : out;
+      chain_targets(p.L, p.periodic, s, r, s_binom, [&](int slot, int64_t to) {
+        if (to >= row0 && to < row1) return;
+        const int k = slot == 0 && p.sep ? p.nh : __popc(set & ((1u << slot) - 1u));
+        p.slot[e + (int64_t)(p.nl + k) * kResThreads] = kResFar | (uint32_t)to;
+      });
+    }
+    if (FILL) {
+      if (valid) p.state[r] = s;
+    } else {
+      atomicMax(&p.counts[0], nl);
+      atomicMax(&p.counts[1], nh);
+    }
+  }
+}
+
+__global__ void k_res_fill(int64_t n, uint32_t v, uint32_t* p) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x)
+    p[i] = v;
+}
+
+// ------------------------------------------------------- recurrence ----
+
+// A slab's rows in registers: thread t holds rows t, t + NT, ... .  A hop is
+// the LDS byte offset of its target (of a zero where there is none) or, out
+// of the slab, the byte offset in the group's vector (past its end, which
+// reads as 0, where there is none).
+template <typename T, int NL, int NH, int R, int G>
+struct SlabState {
+  uint32_t loc[R][(NL + 1) / 2];  // two 16-bit offsets a register
+  uint32_t far[R][NH > 0 ? NH : 1], per[R];
+  Cols<T, G> v[R], b1[R], b2[R], dg[R];
+};
+constexpr uint32_t kNoRow = 0xFFFFFFF0u;  // an offset past any vector
+
+template <typename T, int NL, int NH, int R, int G>
+__device__ __forceinline__ void res_setup(const ResArgs<T>& p, SlabState<T, NL, NH, R, G>& S,
+                                          int c0, int m, const double* s_field, rsrc_t cur,
+                                          rsrc_t prev, bool no_prev, unsigned char* s_b) {
+  constexpr uint32_t RB = G * sizeof(T);
+  const int64_t row0 = slab_row(p.D, p.nslab, m), row1 = slab_row(p.D, p.nslab, m + 1);
+  const uint32_t zero = (uint32_t)p.rows_cap;
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    const int q = threadIdx.x + kResThreads * j;
+    const int64_t r = row0 + q;
+    const bool valid = r < row1;
+    // a table of fewer rows a thread than this kernel's leaves the rest idle
+    const bool have = j < p.R;
+    const uint32_t* e =
+        p.slot + ((int64_t)m * p.R + (have ? j : 0)) * (p.nl + p.nh + 1) * kResThreads + threadIdx.x;
+#pragma unroll
+    for (int b = 0; b < NL; ++b) {
+      const uint32_t x = have && b < p.nl ? e[(int64_t)b * kResThreads] : kResNone;
+      const uint32_t o = (x == kResNone ? zero : x) * RB;  // below 2^16
+      S.loc[j][b / 2] = b % 2 ? S.loc[j][b / 2] | o << 16 : o;
+    }
+#pragma unroll
+    for (int b = 0; b < NH; ++b) {
+      const uint32_t x = have && b < p.nh ? e[(int64_t)(p.nl + b) * kResThreads] : kResNone;
+      S.far[j][b] = x == kResNone ? kNoRow : (x & ~kResFar) * RB;
+    }
+    if (p.sep) {  // far targets keep their mark
+      const uint32_t x = have ? e[(int64_t)(p.nl + p.nh) * kResThreads] : kResNone;
+      S.per[j] = x == kResNone ? zero * RB : (x & kResFar) ? kResFar | (x & ~kResFar) * RB : x * RB;
+    }
+    const uint32_t s = valid ? p.state[r] : 0u;
+    const uint32_t top = (s >> (p.L - 1)) & 1u;
+    const int n11 = __popc(s & (s >> 1)) + (p.periodic ? (int)(top & s & 1u) : 0);
+#pragma unroll
+    for (int c = 0; c < G; ++c) {
+      const double* f = s_field + c * kFieldStride;
+      double d = f[32] + p.vzz * n11;
+      for (int b = 0; b < p.L; ++b) d += (s >> b) & 1u ? f[b] : 0.0;
+      const int col = c0 + c;
+      S.dg[j].x[c] = (T)((double)p.sc[col] * d + (double)p.sc[p.nb + col]);
+      S.v[j].x[c] = valid ? p.v[(int64_t)col * p.D + r] : T(0);
+    }
+    const uint32_t off = valid ? (uint32_t)r * RB : kNoRow;
+    S.b1[j] = rload<T, G>(cur, off);
+    S.b2[j] = rload<T, G>(prev, no_prev ? kNoRow : off);
+    if (valid) *reinterpret_cast<Cols<T, G>*>(s_b + (uint32_t)q * RB) = S.b1[j];
+  }
+  __syncthreads();
+}
+
+// Wave-uniform value of lane i of a register.
+template <typename T>
+__device__ __forceinline__ T lane_value(T x, int i) {
+  if constexpr (sizeof(T) == 8) {
+    int w[2];
+    __builtin_memcpy(w, &x, 8);
+    w[0] = __builtin_amdgcn_readlane(w[0], i);
+    w[1] = __builtin_amdgcn_readlane(w[1], i);
+    __builtin_memcpy(&x, w, 8);
+  } else {
+    int w;
+    __builtin_memcpy(&w, &x, 4);
+    w = __builtin_amdgcn_readlane(w, i);
+    __builtin_memcpy(&x, &w, 4);
+  }
+  return x;
+}
+
+template <typename T, int NL, int NH, int R, int G>
+__device__ __forceinline__ void res_group(const ResArgs<T>& p, int c0, TeamView& tv,
+                                          unsigned char* s_b, double* s_field, int* err) {
+  constexpr uint32_t RB = G * sizeof(T);
+  const int64_t D = p.D;
+  const int nslab = p.nslab;
+  if (threadIdx.x < G * kFieldStride)
+    s_field[threadIdx.x] =
+        p.fields[p.field_cols > 1 ? (int64_t)c0 * kFieldStride + threadIdx.x
+                                  : threadIdx.x % kFieldStride];
+  if (threadIdx.x < RB / 4)
+    reinterpret_cast<uint32_t*>(s_b + (uint32_t)p.rows_cap * RB)[threadIdx.x] = 0;
+  T* cur = p.X + (int64_t)c0 * D;
+  T* prev = p.Y + (int64_t)c0 * D;
+  if (p.first) {  // b_K = a_K v
+    for (int m = tv.rank; m < nslab; m += tv.n)
+      for (int64_t r = slab_row(D, nslab, m) + threadIdx.x; r < slab_row(D, nslab, m + 1);
+           r += kResThreads)
+#pragma unroll
+        for (int c = 0; c < G; ++c)
+          cur[r * G + c] = p.A[(int64_t)p.i_top * p.lda + c0 + c] * p.v[(int64_t)(c0 + c) * D + r];
+  }
+  team_barrier(tv, err, [] {});
+  SlabState<T, NL, NH, R, G> S;
+  const bool one = tv.n >= nslab;  // one slab a member: its state is kept
+  // hop amplitudes with the column's scale
+  T ht[G], hb[G], acf[G];
+#pragma unroll
+  for (int c = 0; c < G; ++c) {
+    const T sg = p.sc[c0 + c];
+    ht[c] = sg * (T)p.t_in;
+    hb[c] = sg * (T)p.t_pb;
+  }
+  const int lane = threadIdx.x & 63;
+  int row0 = (int)slab_row(D, nslab, tv.rank);
+  int rows = (int)slab_row(D, nslab, tv.rank + 1) - row0;
+  for (int i = p.i_top - 1; i >= p.i_bot; --i) {
+    const bool last = i == 0;
+    const T half = last ? T(0.5) : T(1);
+    // 64 steps' coefficients at a time, one a lane
+    const int ci = (p.i_top - 1 - i) & 63;
+    if (ci == 0)
+#pragma unroll
+      for (int c = 0; c < G; ++c) acf[c] = p.A[(int64_t)max(i - lane, 0) * p.lda + c0 + c];
+    T ai[G];
+#pragma unroll
+    for (int c = 0; c < G; ++c) ai[c] = lane_value(acf[c], ci);
+    const bool bad = last && res_load(err) != 0;
+    const rsrc_t rc = make_rsrc(cur, (uint32_t)(D * RB));
+    const rsrc_t ro = make_rsrc(prev, (uint32_t)(D * RB));
+    // a team of one with one slab exchanges nothing until the chunk's end
+    const bool store = nslab > 1 || i <= p.i_bot + 1;
+    for (int m = tv.rank; m < nslab; m += tv.n) {
+      if (!one) {
+        __syncthreads();  // the slab before: its LDS reads are done
+        row0 = (int)slab_row(D, nslab, m);
+        rows = (int)slab_row(D, nslab, m + 1) - row0;
+      }
+      if (!one || i == p.i_top - 1)
+        res_setup<T, NL, NH, R, G>(p, S, c0, m, s_field, rc, ro, p.first && i == p.i_top - 1, s_b);
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        // the hops that leave the slab on their way while the others are summed
+        Cols<T, G> g[NH > 0 ? NH : 1], x[NL];
+#pragma unroll
+        for (int b = 0; b < NH; ++b) g[b] = rload<T, G>(rc, S.far[j][b]);
+#pragma unroll
+        for (int b = 0; b < NL; ++b)
+          x[b] = lread<T, G>(s_b, b % 2 ? S.loc[j][b / 2] >> 16 : S.loc[j][b / 2] & 0xFFFFu);
+        Cols<T, G> acc{}, hp{};
+#pragma unroll
+        for (int b = 0; b < NL; ++b)
+#pragma unroll
+          for (int c = 0; c < G; ++c) acc.x[c] += x[b].x[c];
+        if (p.sep) {
+          const uint32_t o = S.per[j];
+          hp = (o & kResFar) ? rload<T, G>(rc, o & ~kResFar) : lread<T, G>(s_b, o);
+        }
+#pragma unroll
+        for (int b = 0; b < NH; ++b)
+#pragma unroll
+          for (int c = 0; c < G; ++c) acc.x[c] += g[b].x[c];
+        Cols<T, G> o;
+#pragma unroll
+        for (int c = 0; c < G; ++c)
+          o.x[c] = half * (S.dg[j].x[c] * S.b1[j].x[c] + ht[c] * acc.x[c] + hb[c] * hp.x[c]) -
+                   S.b2[j].x[c] + ai[c] * S.v[j].x[c];
+        const int q = threadIdx.x + kResThreads * j;
+        if (q < rows) {
+          if (last) {
+#pragma unroll
+            for (int c = 0; c < G; ++c)
+              p.w[(int64_t)(c0 + c) * D + row0 + q] = bad ? T(NAN) : o.x[c];
+          } else if (store) {
+            rstore<T, G>(o, ro, (uint32_t)(row0 + q) * RB);
+          }
+        }
+        S.b2[j] = S.b1[j];
+        S.b1[j] = o;
+      }
+    }
+    if (last) break;
+    team_barrier(tv, err, [&] {
+      if (!one) return;
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        const int q = threadIdx.x + kResThreads * j;
+        if (q < rows) *reinterpret_cast<Cols<T, G>*>(s_b + (uint32_t)q * RB) = S.b1[j];
+      }
+    });
+    T* t = cur;
+    cur = prev;
+    prev = t;
+  }
+}
+
+template <typename T, int NL, int NH, int R>
+__global__ __launch_bounds__(kResThreads) void k_chain_res(ResArgs<T> p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ double s_field[2 * kFieldStride];
+  __shared__ int s_join[4];
+  TeamView tv{nullptr, 1, 0, 0, 0};
+  if (!team_join(p.st, p.nslab, p.teams_per_xcd, s_join, tv)) return;
+  for (int round = 0;; ++round) {
+    if (threadIdx.x == 0 && tv.rank == 0) {
+      const int g = res_add(&p.st->queue, 1);
+      if (tv.n > 1)
+        res_store(&tv.t->group[round & 1], g);
+      else
+        s_join[3] = g;
+    }
+    team_barrier(tv, &p.st->err, [] {});
+    const int g = uniform(tv.n > 1 ? res_load(&tv.t->group[round & 1]) : s_join[3]);
+    if (g >= p.ngrp) return;
+    // pairs of columns first, then single ones
+    if constexpr (R <= kResMaxPairRows) {
+      if (g < p.pairs)
+        res_group<T, NL, NH, R, 2>(p, 2 * g, tv, smem, s_field, &p.st->err);
+      else
+        res_group<T, NL, NH, R, 1>(p, p.pairs + g, tv, smem, s_field, &p.st->err);
+    } else {
+      res_group<T, NL, NH, R, 1>(p, g, tv, smem, s_field, &p.st->err);
+    }
+    __syncthreads();
+  }
+}
+
+// Clears the team state and writes a chunk's coefficients (kernel arguments,
+// so that the call can be captured and needs no copy from host memory).
+template <typename T>
+struct CoefPack {
+  static constexpr int kN = 440;
+  T a[kN];
+};
+template <typename T>
+__global__ __launch_bounds__(256) void k_res_begin(ResState* st, T* sc, T sigma, T tau) {
+  int* p = reinterpret_cast<int*>(st);
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < (int)(sizeof(ResState) / 4);
+       i += gridDim.x * 256)
+    p[i] = 0;
+  if (sc && blockIdx.x == 0 && threadIdx.x == 0) {
+    sc[0] = sigma;
+    sc[1] = tau;
+  }
+}
+template <typename T>
+__global__ __launch_bounds__(512) void k_res_coef(CoefPack<T> c, int n, T* out) {
+  if ((int)threadIdx.x < n) out[threadIdx.x] = c.a[threadIdx.x];
+}
+
+// A[0 .. top - bot] = a[bot .. top]
+template <typename T>
+void put_coefs(hipStream_t s, const double* a, int bot, int top, T* A) {
+  CoefPack<T> c;
+  for (int i = bot; i <= top; i += CoefPack<T>::kN) {
+    const int n = std::min(CoefPack<T>::kN, top - i + 1);
+    for (int k = 0; k < n; ++k) c.a[k] = (T)a[i + k];
+    hipLaunchKernelGGL((k_res_coef<T>), dim3(1), dim3(512), 0, s, c, n, A + (i - bot));
+  }
+  HIPC(hipGetLastError());
+}
+
+// How the columns of a batch go to teams: slabs of a column (a power of two),
+// pairs of columns sharing a team, rows a thread.
+struct ResShape {
+  int nslab = 0, pairs = 0, ngrp = 0, teams = 0, R = 0;
+  double us = 1e30;  // of a step, by the model below
+};
+
+int res_rows(int64_t D, int nslab) { return (int)((D + nslab - 1) / nslab); }
+int res_r(int64_t D, int nslab) { return (res_rows(D, nslab) + kResThreads - 1) / kResThreads; }
+
+// Measured on an MI355X (FP64, us a step): slabs 1, 8, 16, 32 with one row a
+// thread 1.0 (two rows), 1.4, 1.6, 2.0; another row a thread adds 0.75, with
+// a pair of columns 1.2.  The model below follows these within 15% and picks
+// the cheapest shape: one workgroup up to 1,024 rows, one row a thread as
+// long as 32 slabs allow it, pairs once there are more columns than teams.
+ResShape res_shape(int64_t D, int nb) {
+  ResShape best;
+  for (int nslab = 1; nslab <= kResMaxSlabs; nslab *= 2) {
+    const int R = res_r(D, nslab);
+    if (R > kResMaxRows || (nslab == 1 && R > 2)) continue;
+    const int teams = nslab == 1 ? 256 : 8 * std::min(kResMaxSlabs / nslab, kResTeamsPerXcd);
+    const double base = nslab == 1 ? 0.3 : 0.5 + 0.0235 * nslab;
+    for (int pair = 0; pair < 2; ++pair) {
+      ResShape x;
+      x.nslab = nslab;
+      x.teams = teams;
+      x.R = R;
+      if (pair && R > kResMaxPairRows) continue;
+      const int per = pair ? 2 : 1;
+      const int rounds = (nb + per * teams - 1) / (per * teams);
+      if (pair) {
+        // as many single columns as the rounds have room for
+        x.pairs = std::max(0, nb - rounds * teams);
+        if (x.pairs == 0) continue;
+      }
+      x.ngrp = nb - x.pairs;
+      x.us = rounds * (base + (pair ? 1.2 : 0.75) * R);
+      if (x.us < best.us) best = x;
+    }
+  }
+  return best;
+}
+
+// An instantiation that covers a table.
+bool res_instance(const ResTable& t) {
+  if (t.nh == 0) return t.R <= 2 && t.nl <= 12;
+  if (t.R <= 3) return t.nl <= 14 && t.nh <= 10;
+  return t.nl <= 15 && t.nh <= 11;
+}
+
+template <typename T>
+void res_launch(hipStream_t s, const ResTable& t, unsigned grid, size_t shm, const ResArgs<T>& a) {
+  const dim3 g(grid), b(kResThreads);
+#define POLFED_RES(NL_, NH_, R_)                                             \
+  if (t.nl <= NL_ && t.nh <= NH_ && t.R <= R_) {                             \
+    hipLaunchKernelGGL((k_chain_res<T, NL_, NH_, R_>), g, b, shm, s, a);     \
+    HIPC(hipGetLastError());                                                 \
+    return;                                                                  \
+  }
+  POLFED_RES(12, 0, 1)
+  POLFED_RES(12, 0, 2)
+  POLFED_RES(10, 6, 1)
+  POLFED_RES(14, 10, 1)
+  POLFED_RES(14, 10, 2)
+  POLFED_RES(14, 10, 3)
+  POLFED_RES(15, 11, 6)
+#undef POLFED_RES
+  fail(POLFED_ERR_INVALID, "resident recurrence: no kernel for this table");
+}
+
+std::shared_ptr<ResTable> build_table(hipStream_t s, const polfed_op* op, int nslab) {
+  TallyScope untallied(nullptr);  // lives as long as the pattern's operators
+  auto t = std::make_shared<ResTable>();
+  t->nslab = nslab;
+  t->R = res_r(op->D, nslab);
+  t->rows = res_rows(op->D, nslab);
+  t->sep = op->periodic && op->t_pb != op->t_in ? 1 : 0;
+  ResBuild b{};
+  b.L = op->L;
+  b.N = op->N;
+  b.periodic = op->periodic;
+  b.sep = t->sep;
+  b.nslab = nslab;
+  b.R = t->R;
+  b.D = op->D;
+  b.binom = op->d_binom.as<uint32_t>();
+  DevBuf cnt(2 * sizeof(int32_t));
+  b.counts = cnt.as<int32_t>();
+  hipLaunchKernelGGL(k_res_fill, dim3(1), dim3(64), 0, s, (int64_t)2, 0u, cnt.as<uint32_t>());
+  hipLaunchKernelGGL(k_res_build<false>, dim3((unsigned)nslab), dim3(kResThreads), 0, s, b);
+  HIPC(hipGetLastError());
+  int32_t h[2];
+  HIPC(hipMemcpyAsync(h, cnt.get(), sizeof h, hipMemcpyDeviceToHost, s));
+  HIPC(hipStreamSynchronize(s));
+  t->nl = b.nl = h[0];
+  t->nh = b.nh = h[1];
+  const size_t n = (size_t)nslab * t->R * (t->nl + t->nh + 1) * kResThreads;
+  t->slot.alloc(n * sizeof(uint32_t));
+  t->state.alloc((size_t)op->D * sizeof(uint32_t));
+  b.slot = t->slot.as<uint32_t>();
+  b.state = t->state.as<uint32_t>();
+  hipLaunchKernelGGL(k_res_fill, dim3(256), dim3(256), 0, s, (int64_t)n, kResNone, b.slot);
+  hipLaunchKernelGGL(k_res_build<true>, dim3((unsigned)nslab), dim3(kResThreads), 0, s, b);
+  HIPC(hipGetLastError());
+  HIPC(hipStreamSynchronize(s));
+  return t;
+}
+
+// The table of op's pattern for this many slabs: shared by the operators of
+// the pattern on the context, freed with the last of them.  One that op does
+// not hold yet is looked up and built only with `build`, and not while the
+// stream is captured (null then).
+std::shared_ptr<ResTable> res_table(hipStream_t s, const polfed_op* op, int nslab, bool build) {
+  polfed_ctx* ctx = op->ctx;
+  const std::string key = op->pattern_key + "|" + std::to_string(nslab);
+  std::lock_guard<std::mutex> lk(ctx->tune_mu);
+  auto& mine = op->res_tables[nslab];
+  if (mine || !build) return mine;
+  auto& shared = ctx->res_tables[key];
+  if ((mine = shared.lock())) return mine;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  HIPC(hipStreamIsCapturing(s, &cs));
+  if (cs != hipStreamCaptureStatusNone) return nullptr;
+  for (auto it = ctx->res_tables.begin(); it != ctx->res_tables.end();)
+    it = it->second.expired() && it->first != key ? ctx->res_tables.erase(it) : std::next(it);
+  mine = build_table(s, op, nslab);
+  ctx->res_tables[key] = mine;
+  return mine;
+}
+
+bool res_chain(const polfed_op* op) {
+  return op->model == Model::Chain && op->storage == POLFED_MATRIX_FREE && op->split_nseg > 0 &&
+         op->L <= kResMaxL && op->D >= 1 && !op->pattern_key.empty();
+}
+
+// One chunk after another of a recurrence of order K; put(c) supplies the
+// coefficients A of steps i0 .. i1 (and clears the state).
+template <typename T, class Put>
+void res_run(hipStream_t s, const ResTable& t, const ResShape& x, ResArgs<T> a, int K, int chunk,
+             Put&& put) {
+  a.sep = t.sep;
+  a.nslab = t.nslab;
+  a.R = t.R;
+  a.nl = t.nl;
+  a.nh = t.nh;
+  a.rows_cap = t.rows;
+  a.slot = t.slot.template as<uint32_t>();
+  a.state = t.state.template as<uint32_t>();
+  a.pairs = x.pairs;
+  a.ngrp = x.ngrp;
+  a.teams_per_xcd = t.nslab == 1 ? 1 : std::min(x.teams / 8, (x.ngrp + 7) / 8);
+  const unsigned grid = t.nslab == 1 ? (unsigned)std::min(x.ngrp, 1024)
+                                     : (unsigned)(8 * a.teams_per_xcd * t.nslab);
+  const size_t shm = ((size_t)(t.rows + 1) * (x.pairs ? 2 : 1) * sizeof(T) + 15) / 16 * 16;
+  for (int top = K; top > 0;) {
+    const int bot = std::max(0, top - chunk);
+    a.i_top = top;
+    a.i_bot = bot;
+    a.first = top == K;
+    put(a, top, bot);
+    res_launch<T>(s, t, grid, shm, a);
+    if ((top - bot) % 2) std::swap(a.X, a.Y);
+    top = bot;
+  }
+}
+
+}  // namespace
+
+// A single column: where a thread holds at most three rows (D <= 49,152).
+// With six rows a step takes 7.7 us, more than a launch of the step kernel.
+bool chain_res_applies(const polfed_op* op, bool fp32) {
+  if (!res_chain(op) || op->forced[fp32 ? 1 : 0]) return false;
+  return res_shape(op->D, 1).R <= 3 && res_shape(op->D, 1).nslab > 0;
+}
+
+void chain_res_prepare(hipStream_t s, const polfed_op* op, bool fp32) {
+  if (chain_res_applies(op, fp32)) (void)res_table(s, op, res_shape(op->D, 1).nslab, true);
+}
+
+size_t chain_res_tail() {
+  return 256 + sizeof(ResState) + 256 + (size_t)(kResChunk + 1) * sizeof(double);
+}
+
+template <typename T>
+bool chain_res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const double* a,
+                      int K, const T* v, T* w, T* bufA, T* bufB) {
+  if (K < kResMinSteps || !chain_res_applies(op, sizeof(T) == 4)) return false;
+  const ResShape x = res_shape(op->D, 1);
+  const auto t = res_table(s, op, x.nslab, false);
+  if (!t || !res_instance(*t)) return false;
+  // the state, the scale and a chunk's coefficients lie behind bufA
+  uintptr_t p = ((uintptr_t)(bufA + op->D) + 255) / 256 * 256;
+  ResState* st = (ResState*)p;
+  T* sc = (T*)(p + (sizeof(ResState) + 255) / 256 * 256);
+  T* A = sc + 32;
+  ResArgs<T> r{};
+  r.L = op->L;
+  r.N = op->N;
+  r.periodic = op->periodic;
+  r.nb = 1;
+  r.field_cols = 1;
+  r.lda = 1;
+  r.D = op->D;
+  r.t_in = op->t_in;
+  r.t_pb = op->t_pb;
+  r.vzz = op->vzz;
+  r.fields = op->d_fields.template as<double>();
+  r.sc = sc;
+  r.v = v;
+  r.w = w;
+  r.X = bufA;
+  r.Y = bufB;
+  r.st = st;
+  const T sigma = (T)(2.0 / dE), tau = (T)(-2.0 * E_c / dE);
+  res_run(s, *t, x, r, K, kResChunk, [&](ResArgs<T>& q, int top, int bot) {
+    hipLaunchKernelGGL((k_res_begin<T>), dim3(8), dim3(256), 0, s, st, sc, sigma, tau);
+    put_coefs<T>(s, a, bot, top, A);
+    q.A = A - bot;  // indexed by the step
+  });
+  return true;
+}
+
+template bool chain_res_filter<double>(hipStream_t, const polfed_op*, double, double,
+                                       const double*, int, const double*, double*, double*,
+                                       double*);
+template bool chain_res_filter<float>(hipStream_t, const polfed_op*, double, double,
+                                      const double*, int, const float*, float*, float*, float*);
+
+bool chain_res_batch_fits(hipStream_t s, const polfed_op* op0, int nb) {
+  if (!res_chain(op0)) return false;
+  const ResShape x = res_shape(op0->D, nb);
+  if (x.nslab == 0) return false;
+  const auto t = res_table(s, op0, x.nslab, true);
+  return t && res_instance(*t);
+}
+
+// Variant 5 of a batch: every column's recurrence of order K (coefficients
+// past a column's own order are zero, so its vectors stay zero until there).
+template <typename T>
+void chain_res_batch(hipStream_t s, const ChainBatch& bt, const T* A, int K, const T* v, T* w,
+                     T* bufA, T* bufB) {
+  const polfed_op* op0 = bt.ops[0];
+  const ResShape x = res_shape(op0->D, bt.nb);
+  const auto t = x.nslab ? res_table(s, op0, x.nslab, true) : nullptr;
+  REQUIRE(t && res_instance(*t), "batch: no resident recurrence for this chain");
+  ResArgs<T> r{};
+  r.L = op0->L;
+  r.N = op0->N;
+  r.periodic = op0->periodic;
+  r.nb = bt.nb;
+  r.field_cols = bt.nb;
+  r.lda = bt.nb;
+  r.D = op0->D;
+  r.t_in = op0->t_in;
+  r.t_pb = op0->t_pb;
+  r.vzz = op0->vzz;
+  r.fields = bt.fields.template as<double>();
+  r.sc = (const T*)(sizeof(T) == 8 ? bt.sc64.get() : bt.sc32.get());
+  r.A = A;
+  r.v = v;
+  r.w = w;
+  r.X = bufA;
+  r.Y = bufB;
+  r.st = bt.res_state.template as<ResState>();
+  res_run(s, *t, x, r, K, kResChunk, [&](ResArgs<T>& q, int, int) {
+    hipLaunchKernelGGL((k_res_begin<T>), dim3(8), dim3(256), 0, s, q.st, (T*)nullptr, T(0), T(0));
+    HIPC(hipGetLastError());
+  });
+}
+
+template void chain_res_batch<double>(hipStream_t, const ChainBatch&, const double*, int,
+                                      const double*, double*, double*, double*);
+template void chain_res_batch<float>(hipStream_t, const ChainBatch&, const float*, int,
+                                     const float*, float*, float*, float*);
+
+}  // namespace polfed

@@ -39,7 +39,7 @@ struct Ws {
     flag.alloc(sizeof(int));
     HIPC(hipMemsetAsync(flag.get(), 0, sizeof(int), s));
     const size_t tb = fp32 ? sizeof(float) : sizeof(double);
-    bA.alloc(std::max<int64_t>(D, 1) * tb);
+    bA.alloc(filter_buf_bytes(D, tb));
     bB.alloc(std::max<int64_t>(D, 1) * tb);
     if (fp32) {
       v32.alloc(std::max<int64_t>(D, 1) * sizeof(float));
@@ -88,7 +88,6 @@ struct BatchCoef {
   int nb = 0, Kmax = 0;
   std::vector<double> host;  // (Kmax + 1) x nb, column c of row i = a_c[i]
   std::vector<int> K;        // each column's own order
-  DevBuf dK;                 // the same on the device (int32)
   void set(hipStream_t s, int nb, const double* const* a, const int* K);
 };
 

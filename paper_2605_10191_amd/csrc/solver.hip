@@ -93,6 +93,14 @@ void filter_apply_on(hipStream_t s, const polfed_op* op, double E_c, double dE,
     scale_t<T>(s, D, (T)a[0], v, w);
     return;
   }
+  if (K >= kResMinSteps && chain_res_applies(op, sizeof(T) == 4)) {
+    // one resident launch; its tables are built when the step kernel is
+    // chosen, on the operator's first step
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    HIPC(hipStreamIsCapturing(s, &cs));
+    if (cs == hipStreamCaptureStatusNone) op_tune(s, op, sizeof(T) == 4);
+    if (chain_res_filter<T>(s, op, E_c, dE, a, K, v, w, bufA, bufB)) return;
+  }
   scale_t<T>(s, D, (T)a[K], v, bufA);  // b_K
   const T* cur = bufA;                  // b_{i+1}
   T* prev = nullptr;                    // b_{i+2}
@@ -534,7 +542,7 @@ size_t SolveRun::bytes_at(int64_t D_, int m, int n, bool f32) {
   size_t b = (M + 2) * vec + (nseg * (M + 1) + 8192 + 3 * (M + 2)) * 8;
   // w, the filter's two recurrence buffers, the FP32 copies of v and w,
   // and the fixed graph input (FP64)
-  b += vec + (f32 ? 4 * D * 4 : 3 * vec);
+  b += vec + (f32 ? 4 * D * 4 : 3 * vec) + chain_res_tail();
   // check and extraction: the tridiagonal eigenvectors (M x M), the chosen
   // ones (M x n), the projected matrix and its eigenvectors, partial sums,
   // the split sums of the projection product
@@ -601,6 +609,8 @@ void SolveRun::filter_self() {
   const int64_t D = op->D;
   if (mode == kTimeDirect && (p.graph == 2 || pl.K < 8 || pl.K > kGraphMaxSteps)) mode = kDirect;
   if (mode == kTimeDirect && p.graph == 1) mode = kGraph;
+  // a resident filter is a few launches in all
+  if (mode == kTimeDirect && pl.K >= kResMinSteps && chain_res_applies(op, fp32)) mode = kDirect;
   const bool use_graph = mode == kTimeGraph || mode == kGraph;
   if (use_graph && !graph.ready()) {
     if (!fp32) vst.alloc((size_t)std::max<int64_t>(D, 1) * sizeof(double));
@@ -881,7 +891,7 @@ void SolveRun::fallback_fp64() {
   graph.reset();
   mode = (p.graph == 2 || pl.K < 8 || pl.K > kGraphMaxSteps) ? kDirect
                                                              : (p.graph == 1 ? kGraph : kTimeDirect);
-  ws.bA.alloc((size_t)std::max<int64_t>(D, 1) * sizeof(double));
+  ws.bA.alloc(filter_buf_bytes(D, sizeof(double)));
   ws.bB.alloc((size_t)std::max<int64_t>(D, 1) * sizeof(double));
   k = 0;
   brk_from = 1;
@@ -970,13 +980,13 @@ void lanczos_step(polfed_ctx* ctx, const polfed_op* op, double E_c, double dE,
   if (precision == POLFED_FP32) {
     float* v32 = static_cast<float*>(ctx_scratch(ctx, 4, nd * sizeof(float)));
     float* w32 = static_cast<float*>(ctx_scratch(ctx, 5, nd * sizeof(float)));
-    float* bA = static_cast<float*>(ctx_scratch(ctx, 6, nd * sizeof(float)));
+    float* bA = static_cast<float*>(ctx_scratch(ctx, 6, filter_buf_bytes(D, sizeof(float))));
     float* bB = static_cast<float*>(ctx_scratch(ctx, 7, nd * sizeof(float)));
     dev_copy_d2f(s, D, vk, v32);
     filter_apply<float>(ctx, op, E_c, dE, a, K, v32, w32, bA, bB);
     dev_copy_f2d(s, D, w32, w);
   } else {
-    double* bA = static_cast<double*>(ctx_scratch(ctx, 6, nd * sizeof(double)));
+    double* bA = static_cast<double*>(ctx_scratch(ctx, 6, filter_buf_bytes(D, sizeof(double))));
     double* bB = static_cast<double*>(ctx_scratch(ctx, 7, nd * sizeof(double)));
     filter_apply<double>(ctx, op, E_c, dE, a, K, vk, w, bA, bB);
   }
