@@ -499,6 +499,7 @@ bool chain_lds_filter_fits(const polfed_op* op0);
 // Resident recurrence (resident.hip): the K steps of a column or a pair of
 // columns in one launch, by a team of workgroups on one XCD.
 constexpr int kResThreads = 512;  // up to 256 VGPRs a lane for the rows' state
+constexpr int kResWaves = kResThreads / 64;
 constexpr int kResMaxL = 20;
 constexpr int kResMaxPairRows = 3;  // rows a thread of a pair of columns
 constexpr int kResMaxRows = 6;      // rows a thread of a single column
@@ -541,6 +542,8 @@ struct ResArgs {
   const T* v;
   T *w, *X, *Y;
   ResState* st;
+  double* part;  // moments: partial products; i_all: the last step's index
+  int i_all;
 };
 
 // Slab tables of a chain pattern for one number of slabs.
@@ -569,6 +572,11 @@ template <typename T>
 bool chain_res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const double* a,
                       int K, const T* v, T* w, T* bufA, T* bufB);
 bool chain_res_batch_fits(hipStream_t s, const polfed_op* op0, int nb);
+// Products of the Chebyshev vectors t_n(H~) v of nb columns (kpm.hip).
+bool chain_res_moments_fit(hipStream_t s, const polfed_op* op, int nb);
+size_t chain_res_moments_bytes(const polfed_op* op, int M, int nb);
+void chain_res_moments(hipStream_t s, const polfed_op* op, double E_c, double dE, int M, int nb,
+                       const double* v, double* X, double* Y, void* ws, double* dots);
 template <typename T>
 void chain_res_batch(hipStream_t s, const ChainBatch& bt, const T* A, int K, const T* v, T* w,
                      T* bufA, T* bufB);
@@ -672,6 +680,8 @@ namespace polfed {
 // (vector c with seed + c), scaled to unit variance.
 void kpm_moments(polfed_ctx* ctx, const polfed_op* op, double E_c, double dE, int N, int R,
                  const double* rvecs, uint64_t seed, double* mu);
+// Device bytes kpm_moments holds for R vectors of op (besides rvecs).
+size_t kpm_workspace(const polfed_op* op, int N, int R);
 void kpm_density(const double* mu, int N, const double* x, int nx, double* rho);
 // argmax of the KPM density over the Chebyshev nodes of 4096 that lie in [lo, hi]
 double kpm_maxdos(const double* mu, int N, double lo, double hi);

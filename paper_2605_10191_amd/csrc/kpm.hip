@@ -2,9 +2,17 @@
 // and App. B): stochastic Chebyshev moments mu_n = Tr T_n(H~), estimated as
 // the mean over R random vectors r of <r|T_n(H~)|r>, and the Jackson-damped
 // density rho_KPM(x) = [mu_0 g_0 + 2 sum_{n>=1} mu_n g_n T_n(x)] /
-// (pi sqrt(1 - x^2)).  The recurrence t_{n+1} = 2 H~ t_n - t_{n-1} is the
-// fused Clenshaw step with a = 0 (out = sigma H t_n + tau t_n - t_{n-1},
-// written over t_{n-1}), so the moments run on the same kernels as the filter.
+// (pi sqrt(1 - x^2)).
+//
+// With t_n = T_n(H~) r, the product rules of the Chebyshev polynomials (2 T_m
+// T_n = T_{m+n} + T_{m-n}) give two moments of a vector per step,
+//     <r|t_{2n}> = 2 <t_n|t_n> - <r|r>,
+//     <r|t_{2n+1}> = 2 <t_{n+1}|t_n> - <r|t_1>,
+// so N moments take N / 2 steps.  On short chains all vectors go through the
+// resident recurrence at once, with the products formed in it: 200 moments of
+// 32 vectors at L = 17 take 0.76 ms; with a step and two product launches per
+// moment and vector they took 71 ms.  Elsewhere the recurrence is the fused step kernel
+// (a = 0, written over t_{n-1}) followed by one launch for both products.
 #include <algorithm>
 #include <cmath>
 
@@ -12,52 +20,173 @@
 
 namespace polfed {
 
+namespace {
+
+constexpr int kKpmCols = 64;       // vectors of one resident launch
+constexpr int kDotBlocks = 512;    // partial sums of a product
+
+// vector c: uniform on [-sqrt 3, sqrt 3) (zero mean, unit variance), drawn as
+// dev_random does from seed + c
+__global__ void k_kpm_vectors(int64_t D, int nb, uint64_t seed, double* y) {
+  const double w = sqrt(3.0);
+  const int64_t n = D * nb;
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
+       e += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t c = e / D, i = e - c * D;
+    uint64_t z = seed + (uint64_t)c + 0x9E3779B97F4A7C15ull * (uint64_t)(i + 1);
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    z ^= z >> 31;
+    y[e] = w * ((double)(z >> 11) * (2.0 / 9007199254740992.0) - 1.0);
+  }
+}
+
+// part[0][block] = sums of x x, part[1][block] = of x y (y may be null).
+__global__ __launch_bounds__(256) void k_dot_pair(int64_t n, const double* __restrict__ x,
+                                                  const double* __restrict__ y, double* part) {
+  __shared__ double red[8];
+  double a = 0, b = 0;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const double t = x[i];
+    a += t * t;
+    if (y) b += t * y[i];
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    a += __shfl_down(a, off, 64);
+    b += __shfl_down(b, off, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[threadIdx.x >> 6] = a;
+    red[4 + (threadIdx.x >> 6)] = b;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    double t = 0;
+    for (int i = 0; i < 4; ++i) t += red[4 * threadIdx.x + i];
+    part[threadIdx.x * gridDim.x + blockIdx.x] = t;
+  }
+}
+
+// out[k] = sum of part[k n .. k n + n), one wave a sum
+__global__ __launch_bounds__(256) void k_sum_rows(const double* part, int n, int64_t count,
+                                                  double* out) {
+  const int64_t k = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (k >= count) return;
+  double t = 0;
+  for (int i = threadIdx.x & 63; i < n; i += 64) t += part[k * n + i];
+  for (int off = 32; off > 0; off >>= 1) t += __shfl_down(t, off, 64);
+  if ((threadIdx.x & 63) == 0) out[k] = t;
+}
+
+void draw_vectors(hipStream_t s, int64_t D, int nb, uint64_t seed, double* y) {
+  const int64_t n = D * nb;
+  if (!n) return;
+  const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>(8192, (n + 255) / 256));
+  hipLaunchKernelGGL(k_kpm_vectors, dim3(g), dim3(256), 0, s, D, nb, seed, y);
+  HIPC(hipGetLastError());
+}
+
+int dot_blocks(int64_t D) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>(kDotBlocks, (D + 1023) / 1024));
+}
+
+void dot_pair(hipStream_t s, int64_t D, const double* x, const double* y, double* part) {
+  hipLaunchKernelGGL(k_dot_pair, dim3((unsigned)dot_blocks(D)), dim3(256), 0, s, D, x, y, part);
+  HIPC(hipGetLastError());
+}
+
+}  // namespace
+
+size_t kpm_workspace(const polfed_op* op, int N, int R) {
+  const size_t D = (size_t)std::max<int64_t>(op->D, 1), M = (size_t)(N / 2);
+  const size_t nb = (size_t)std::min(R, kKpmCols);
+  const size_t dots = 2 * (M + 1) * kDotBlocks * 8;
+  const bool res = op->model == Model::Chain && op->L <= kResMaxL;
+  return std::max(3 * D * 8 + dots,
+                  res ? 3 * D * nb * 8 + dots + chain_res_moments_bytes(op, (int)M, (int)nb) : 0);
+}
+
 void kpm_moments(polfed_ctx* ctx, const polfed_op* op, double E_c, double dE, int N, int R,
                  const double* rvecs, uint64_t seed, double* mu) {
   REQUIRE(N >= 1 && R >= 1, "kpm: need N >= 1 moments and R >= 1 vectors");
   REQUIRE(dE > 0 && std::isfinite(dE) && std::isfinite(E_c), "kpm: need finite E_c, dE > 0");
   hipStream_t s = ctx->stream;
   const int64_t D = op->D;
+  const int M = N / 2;  // steps
   const size_t nd = (size_t)std::max<int64_t>(D, 1);
-  DevBuf r(nd * sizeof(double)), ta(nd * sizeof(double)), tb(nd * sizeof(double)),
-      dots((size_t)N * R * sizeof(double)), part(8192 * sizeof(double));
-  for (int c = 0; c < R; ++c) {
-    const double* rv;
-    if (rvecs) {
-      rv = rvecs + (size_t)c * D;
-    } else {
-      // uniform on [-sqrt 3, sqrt 3): zero mean, unit variance
-      dev_random(s, D, seed + (uint64_t)c, r.as<double>());
-      dev_axpby(s, D, 0.0, r.as<double>(), std::sqrt(3.0), r.as<double>());
-      rv = r.as<double>();
+  std::fill(mu, mu + N, 0.0);
+  // the moments of one vector from m0 = <t_0|t_0> and its products of step n
+  auto add = [&](double m0, auto&& same, auto&& next) {
+    const double m1 = N > 1 ? next(1) : 0.0;
+    mu[0] += m0;
+    if (N > 1) mu[1] += m1;
+    for (int n = 1; 2 * n < N; ++n) mu[2 * n] += 2.0 * same(n) - m0;
+    for (int n = 1; 2 * n + 1 < N; ++n) mu[2 * n + 1] += 2.0 * next(n + 1) - m1;
+  };
+  const int cols = std::min(R, kKpmCols);
+  if (M >= 4 && D >= 1 && chain_res_moments_fit(s, op, cols)) {
+    DevBuf v, X(nd * cols * sizeof(double)), Y(nd * cols * sizeof(double)),
+        ws(chain_res_moments_bytes(op, M, cols));
+    const int g = dot_blocks(D);
+    DevBuf part((size_t)cols * 2 * g * sizeof(double)), d0((size_t)cols * 2 * sizeof(double));
+    if (!rvecs) v.alloc(nd * cols * sizeof(double));
+    std::vector<double> dots((size_t)M * 2 * cols), h0((size_t)2 * cols);
+    for (int c0 = 0; c0 < R; c0 += cols) {
+      const int nb = std::min(cols, R - c0);
+      const double* vc = rvecs ? rvecs + (size_t)c0 * D : v.as<double>();
+      if (!rvecs) draw_vectors(s, D, nb, seed + (uint64_t)c0, v.as<double>());
+      for (int c = 0; c < nb; ++c)
+        dot_pair(s, D, vc + (size_t)c * D, nullptr, part.as<double>() + (size_t)c * 2 * g);
+      hipLaunchKernelGGL(k_sum_rows, dim3((unsigned)((2 * nb + 3) / 4)), dim3(256), 0, s,
+                         part.as<double>(), g, (int64_t)2 * nb, d0.as<double>());
+      HIPC(hipGetLastError());
+      HIPC(hipMemcpyAsync(h0.data(), d0.get(), (size_t)2 * nb * sizeof(double),
+                          hipMemcpyDeviceToHost, s));
+      chain_res_moments(s, op, E_c, dE, M, nb, vc, X.as<double>(), Y.as<double>(), ws.get(),
+                        dots.data());
+      for (int c = 0; c < nb; ++c)
+        add(h0[2 * c], [&](int n) { return dots[((size_t)(n - 1) * 2) * nb + c]; },
+            [&](int n) { return dots[((size_t)(n - 1) * 2 + 1) * nb + c]; });
     }
-    double* out = dots.as<double>() + (size_t)c * N;
-    // t_0 = r
-    dev_dot(s, D, rv, rv, part.as<double>(), 1024, out, 0);
-    if (N == 1) continue;
-    // t_1 = H~ r into ta
-    op_step<double>(s, op, 1.0 / dE, -E_c / dE, 0.0, nullptr, rv, nullptr, ta.as<double>());
-    dev_dot(s, D, rv, ta.as<double>(), part.as<double>(), 1024, out + 1, 0);
-    // t_{n+1} = 2 H~ t_n - t_{n-1}: cur = t_n, prev = t_{n-1} (prev is
-    // overwritten); t_0 is r itself, so the first update writes to tb
-    const double* cur = ta.as<double>();
-    const double* prev = rv;
-    for (int n = 2; n < N; ++n) {
-      double* nxt = (prev == rv) ? tb.as<double>() : const_cast<double*>(prev);
-      op_step<double>(s, op, 2.0 / dE, -2.0 * E_c / dE, 0.0, nullptr, cur, prev, nxt);
-      dev_dot(s, D, rv, nxt, part.as<double>(), 1024, out + n, 0);
-      prev = cur;
-      cur = nxt;
+  } else {
+    const int g = dot_blocks(D);
+    const size_t row = (size_t)2 * g;
+    DevBuf r, ta(nd * sizeof(double)), tb(nd * sizeof(double)),
+        part((size_t)(M + 1) * row * sizeof(double)),
+        sums((size_t)(M + 1) * 2 * R * sizeof(double));
+    if (!rvecs) r.alloc(nd * sizeof(double));
+    for (int c = 0; c < R; ++c) {
+      const double* rv = rvecs ? rvecs + (size_t)c * D : r.as<double>();
+      if (!rvecs) draw_vectors(s, D, 1, seed + (uint64_t)c, r.as<double>());
+      double* pr = part.as<double>();
+      dot_pair(s, D, rv, nullptr, pr);
+      // cur = t_n, prev = t_{n-1} (overwritten; t_0 is r itself, so the first
+      // update writes to tb)
+      const double* cur = rv;
+      const double* prev = nullptr;
+      for (int n = 1; n <= M; ++n) {
+        const double f = n == 1 ? 1.0 : 2.0;
+        double* nxt = n == 1 ? ta.as<double>()
+                             : (prev == rv ? tb.as<double>() : const_cast<double*>(prev));
+        op_step<double>(s, op, f / dE, -f * E_c / dE, 0.0, nullptr, cur, prev, nxt);
+        dot_pair(s, D, nxt, cur, pr + (size_t)n * row);
+        prev = cur;
+        cur = nxt;
+      }
+      const int64_t count = (int64_t)(M + 1) * 2;
+      hipLaunchKernelGGL(k_sum_rows, dim3((unsigned)((count + 3) / 4)), dim3(256), 0, s, pr, g,
+                         count, sums.as<double>() + (size_t)c * count);
+      HIPC(hipGetLastError());
+    }
+    std::vector<double> h((size_t)(M + 1) * 2 * R);
+    HIPC(hipMemcpyAsync(h.data(), sums.get(), h.size() * sizeof(double), hipMemcpyDeviceToHost, s));
+    HIPC(hipStreamSynchronize(s));
+    for (int c = 0; c < R; ++c) {
+      const double* q = h.data() + (size_t)c * (M + 1) * 2;
+      add(q[0], [&](int n) { return q[2 * n]; }, [&](int n) { return q[2 * n + 1]; });
     }
   }
-  std::vector<double> h((size_t)N * R);
-  HIPC(hipMemcpyAsync(h.data(), dots.get(), h.size() * sizeof(double), hipMemcpyDeviceToHost, s));
-  HIPC(hipStreamSynchronize(s));
-  for (int n = 0; n < N; ++n) {
-    double acc = 0;
-    for (int c = 0; c < R; ++c) acc += h[(size_t)c * N + n];
-    mu[n] = acc / R;
-  }
+  for (int n = 0; n < N; ++n) mu[n] /= R;
 }
 
 // Jackson factors g_n for N moments (App. B eq. kernels_jackson_and_lorenz).

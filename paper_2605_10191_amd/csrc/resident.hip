@@ -345,7 +345,33 @@ __device__ __forceinline__ T lane_value(T x, int i) {
   return x;
 }
 
-template <typename T, int NL, int NH, int R, int G>
+// Sums of the wave's x[0..n) over its lanes, value k in lane k * 64 / n
+// (n a power of two): each step halves the values a lane carries until one is
+// left, so 2 values take 6 exchanges instead of 12.
+template <int n>
+__device__ __forceinline__ double wave_sums(double (&x)[n]) {
+  const int lane = threadIdx.x & 63;
+  int off = 32;
+#pragma unroll
+  for (int m = n; m > 1; m /= 2, off /= 2) {
+    const bool up = lane & off;
+#pragma unroll
+    for (int k = 0; k < m / 2; ++k) {
+      const double give = up ? x[k] : x[k + m / 2];
+      const double keep = up ? x[k + m / 2] : x[k];
+      x[k] = keep + __shfl_xor(give, off, 64);
+    }
+  }
+  for (; off > 0; off /= 2) x[0] += __shfl_xor(x[0], off, 64);
+  return x[0];
+}
+
+// MOM: the Chebyshev vectors t_0 = v, t_1 = H~ t_0, t_{n+1} = 2 H~ t_n -
+// t_{n-1} instead of the filter (no coefficients), n = i_top - i steps done
+// after step i, with the products <t_n|t_n> and <t_{n-1}|t_n> of each step:
+// a wave's sums go to part[n][2][column][slab][wave] while the team's other
+// members reach the barrier.
+template <typename T, int NL, int NH, int R, int G, bool MOM>
 __device__ __forceinline__ void res_group(const ResArgs<T>& p, int c0, TeamView& tv,
                                           unsigned char* s_b, double* s_field, int* err) {
   constexpr uint32_t RB = G * sizeof(T);
@@ -365,7 +391,8 @@ __device__ __forceinline__ void res_group(const ResArgs<T>& p, int c0, TeamView&
            r += kResThreads)
 #pragma unroll
         for (int c = 0; c < G; ++c)
-          cur[r * G + c] = p.A[(int64_t)p.i_top * p.lda + c0 + c] * p.v[(int64_t)(c0 + c) * D + r];
+          cur[r * G + c] = (MOM ? T(1) : p.A[(int64_t)p.i_top * p.lda + c0 + c]) *
+                           p.v[(int64_t)(c0 + c) * D + r];
   }
   team_barrier(tv, err, [] {});
   SlabState<T, NL, NH, R, G> S;
@@ -382,16 +409,26 @@ __device__ __forceinline__ void res_group(const ResArgs<T>& p, int c0, TeamView&
   int row0 = (int)slab_row(D, nslab, tv.rank);
   int rows = (int)slab_row(D, nslab, tv.rank + 1) - row0;
   for (int i = p.i_top - 1; i >= p.i_bot; --i) {
-    const bool last = i == 0;
-    const T half = last ? T(0.5) : T(1);
+    const bool last = !MOM && i == 0;
+    const T half = (MOM ? p.first && i == p.i_top - 1 : last) ? T(0.5) : T(1);
     // 64 steps' coefficients at a time, one a lane
     const int ci = (p.i_top - 1 - i) & 63;
-    if (ci == 0)
+    if (!MOM && ci == 0)
 #pragma unroll
       for (int c = 0; c < G; ++c) acf[c] = p.A[(int64_t)max(i - lane, 0) * p.lda + c0 + c];
     T ai[G];
 #pragma unroll
-    for (int c = 0; c < G; ++c) ai[c] = lane_value(acf[c], ci);
+    for (int c = 0; c < G; ++c) ai[c] = MOM ? T(0) : lane_value(acf[c], ci);
+    double dots[2 * G] = {};
+    auto flush = [&](int m) {  // this wave's sums over the rows of slab m
+      const double s = wave_sums<2 * G>(dots);
+      const int k = lane / (32 / G);  // value k: product k / G of column k % G
+      if (lane % (32 / G) == 0)
+        p.part[((((int64_t)p.i_all - i) * 2 + k / G) * p.nb + c0 + k % G) * nslab * kResWaves +
+               m * kResWaves + (threadIdx.x >> 6)] = s;
+#pragma unroll
+      for (int q = 0; q < 2 * G; ++q) dots[q] = 0;
+    };
     const bool bad = last && res_load(err) != 0;
     const rsrc_t rc = make_rsrc(cur, (uint32_t)(D * RB));
     const rsrc_t ro = make_rsrc(prev, (uint32_t)(D * RB));
@@ -431,7 +468,14 @@ __device__ __forceinline__ void res_group(const ResArgs<T>& p, int c0, TeamView&
 #pragma unroll
         for (int c = 0; c < G; ++c)
           o.x[c] = half * (S.dg[j].x[c] * S.b1[j].x[c] + ht[c] * acc.x[c] + hb[c] * hp.x[c]) -
-                   S.b2[j].x[c] + ai[c] * S.v[j].x[c];
+                   S.b2[j].x[c] + (MOM ? T(0) : ai[c] * S.v[j].x[c]);
+        if constexpr (MOM) {  // a row past the slab's end is 0 throughout
+#pragma unroll
+          for (int c = 0; c < G; ++c) {
+            dots[c] += (double)o.x[c] * (double)o.x[c];
+            dots[G + c] += (double)o.x[c] * (double)S.b1[j].x[c];
+          }
+        }
         const int q = threadIdx.x + kResThreads * j;
         if (q < rows) {
           if (last) {
@@ -445,10 +489,12 @@ __device__ __forceinline__ void res_group(const ResArgs<T>& p, int c0, TeamView&
         S.b2[j] = S.b1[j];
         S.b1[j] = o;
       }
+      if (MOM && !one) flush(m);
     }
     if (last) break;
     team_barrier(tv, err, [&] {
       if (!one) return;
+      if (MOM) flush(tv.rank);
 #pragma unroll
       for (int j = 0; j < R; ++j) {
         const int q = threadIdx.x + kResThreads * j;
@@ -461,7 +507,7 @@ __device__ __forceinline__ void res_group(const ResArgs<T>& p, int c0, TeamView&
   }
 }
 
-template <typename T, int NL, int NH, int R>
+template <typename T, int NL, int NH, int R, bool MOM>
 __global__ __launch_bounds__(kResThreads) void k_chain_res(ResArgs<T> p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ double s_field[2 * kFieldStride];
@@ -482,11 +528,11 @@ __global__ __launch_bounds__(kResThreads) void k_chain_res(ResArgs<T> p) {
     // pairs of columns first, then single ones
     if constexpr (R <= kResMaxPairRows) {
       if (g < p.pairs)
-        res_group<T, NL, NH, R, 2>(p, 2 * g, tv, smem, s_field, &p.st->err);
+        res_group<T, NL, NH, R, 2, MOM>(p, 2 * g, tv, smem, s_field, &p.st->err);
       else
-        res_group<T, NL, NH, R, 1>(p, p.pairs + g, tv, smem, s_field, &p.st->err);
+        res_group<T, NL, NH, R, 1, MOM>(p, p.pairs + g, tv, smem, s_field, &p.st->err);
     } else {
-      res_group<T, NL, NH, R, 1>(p, g, tv, smem, s_field, &p.st->err);
+      res_group<T, NL, NH, R, 1, MOM>(p, g, tv, smem, s_field, &p.st->err);
     }
     __syncthreads();
   }
@@ -500,15 +546,17 @@ struct CoefPack {
   T a[kN];
 };
 template <typename T>
-__global__ __launch_bounds__(256) void k_res_begin(ResState* st, T* sc, T sigma, T tau) {
+__global__ __launch_bounds__(256) void k_res_begin(ResState* st, T* sc, T sigma, T tau,
+                                                   int nb) {
   int* p = reinterpret_cast<int*>(st);
   for (int i = blockIdx.x * 256 + threadIdx.x; i < (int)(sizeof(ResState) / 4);
        i += gridDim.x * 256)
     p[i] = 0;
-  if (sc && blockIdx.x == 0 && threadIdx.x == 0) {
-    sc[0] = sigma;
-    sc[1] = tau;
-  }
+  if (sc && blockIdx.x == 0)
+    for (int c = threadIdx.x; c < nb; c += 256) {
+      sc[c] = sigma;
+      sc[nb + c] = tau;
+    }
 }
 template <typename T>
 __global__ __launch_bounds__(512) void k_res_coef(CoefPack<T> c, int n, T* out) {
@@ -577,12 +625,12 @@ bool res_instance(const ResTable& t) {
   return t.nl <= 15 && t.nh <= 11;
 }
 
-template <typename T>
+template <typename T, bool MOM>
 void res_launch(hipStream_t s, const ResTable& t, unsigned grid, size_t shm, const ResArgs<T>& a) {
   const dim3 g(grid), b(kResThreads);
 #define POLFED_RES(NL_, NH_, R_)                                             \
   if (t.nl <= NL_ && t.nh <= NH_ && t.R <= R_) {                             \
-    hipLaunchKernelGGL((k_chain_res<T, NL_, NH_, R_>), g, b, shm, s, a);     \
+    hipLaunchKernelGGL((k_chain_res<T, NL_, NH_, R_, MOM>), g, b, shm, s, a); \
     HIPC(hipGetLastError());                                                 \
     return;                                                                  \
   }
@@ -664,7 +712,7 @@ bool res_chain(const polfed_op* op) {
 
 // One chunk after another of a recurrence of order K; put(c) supplies the
 // coefficients A of steps i0 .. i1 (and clears the state).
-template <typename T, class Put>
+template <bool MOM = false, typename T, class Put>
 void res_run(hipStream_t s, const ResTable& t, const ResShape& x, ResArgs<T> a, int K, int chunk,
              Put&& put) {
   a.sep = t.sep;
@@ -687,7 +735,7 @@ void res_run(hipStream_t s, const ResTable& t, const ResShape& x, ResArgs<T> a, 
     a.i_bot = bot;
     a.first = top == K;
     put(a, top, bot);
-    res_launch<T>(s, t, grid, shm, a);
+    res_launch<T, MOM>(s, t, grid, shm, a);
     if ((top - bot) % 2) std::swap(a.X, a.Y);
     top = bot;
   }
@@ -741,8 +789,8 @@ bool chain_res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE,
   r.Y = bufB;
   r.st = st;
   const T sigma = (T)(2.0 / dE), tau = (T)(-2.0 * E_c / dE);
-  res_run(s, *t, x, r, K, kResChunk, [&](ResArgs<T>& q, int top, int bot) {
-    hipLaunchKernelGGL((k_res_begin<T>), dim3(8), dim3(256), 0, s, st, sc, sigma, tau);
+  res_run<false>(s, *t, x, r, K, kResChunk, [&](ResArgs<T>& q, int top, int bot) {
+    hipLaunchKernelGGL((k_res_begin<T>), dim3(8), dim3(256), 0, s, st, sc, sigma, tau, 1);
     put_coefs<T>(s, a, bot, top, A);
     q.A = A - bot;  // indexed by the step
   });
@@ -791,10 +839,74 @@ void chain_res_batch(hipStream_t s, const ChainBatch& bt, const T* A, int K, con
   r.X = bufA;
   r.Y = bufB;
   r.st = bt.res_state.template as<ResState>();
-  res_run(s, *t, x, r, K, kResChunk, [&](ResArgs<T>& q, int, int) {
-    hipLaunchKernelGGL((k_res_begin<T>), dim3(8), dim3(256), 0, s, q.st, (T*)nullptr, T(0), T(0));
+  res_run<false>(s, *t, x, r, K, kResChunk, [&](ResArgs<T>& q, int, int) {
+    hipLaunchKernelGGL((k_res_begin<T>), dim3(8), dim3(256), 0, s, q.st, (T*)nullptr, T(0), T(0),
+                       0);
     HIPC(hipGetLastError());
   });
+}
+
+// out[k] = sum of part[k * n .. k * n + n), one wave a sum.
+__global__ __launch_bounds__(256) void k_res_sum(const double* part, int n, int64_t count,
+                                                 double* out) {
+  const int64_t k = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (k >= count) return;
+  double x = 0;
+  for (int i = threadIdx.x & 63; i < n; i += 64) x += part[k * n + i];
+  for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off, 64);
+  if ((threadIdx.x & 63) == 0) out[k] = x;
+}
+
+bool chain_res_moments_fit(hipStream_t s, const polfed_op* op, int nb) {
+  return !op->forced[0] && chain_res_batch_fits(s, op, nb);
+}
+
+size_t chain_res_moments_bytes(const polfed_op* op, int M, int nb) {
+  const ResShape x = res_shape(op->D, nb);
+  const size_t sums = (size_t)M * 2 * nb;
+  return sizeof(ResState) + 4096 + (sums * x.nslab * kResWaves + sums) * sizeof(double);
+}
+
+// dots[n - 1][0] = <t_n|t_n>, dots[n - 1][1] = <t_{n-1}|t_n> of every column
+// for n = 1 .. M (host, [M][2][nb]); v: D x nb, X and Y: its two buffers.
+void chain_res_moments(hipStream_t s, const polfed_op* op, double E_c, double dE, int M, int nb,
+                       const double* v, double* X, double* Y, void* ws, double* dots) {
+  const ResShape x = res_shape(op->D, nb);
+  const auto t = res_table(s, op, x.nslab, true);
+  REQUIRE(t && res_instance(*t), "kpm: no resident recurrence for this chain");
+  ResState* st = (ResState*)ws;
+  double* sc = (double*)((unsigned char*)ws + (sizeof(ResState) + 255) / 256 * 256);
+  double* sums = sc + 2 * nb + 32;
+  const int64_t count = (int64_t)M * 2 * nb;
+  ResArgs<double> r{};
+  r.L = op->L;
+  r.N = op->N;
+  r.periodic = op->periodic;
+  r.nb = nb;
+  r.field_cols = 1;
+  r.lda = nb;
+  r.D = op->D;
+  r.t_in = op->t_in;
+  r.t_pb = op->t_pb;
+  r.vzz = op->vzz;
+  r.fields = op->d_fields.as<double>();
+  r.sc = sc;
+  r.v = v;
+  r.X = X;
+  r.Y = Y;
+  r.st = st;
+  r.part = sums + count;
+  r.i_all = M - 1;
+  res_run<true>(s, *t, x, r, M, kResChunk, [&](ResArgs<double>& q, int, int) {
+    hipLaunchKernelGGL((k_res_begin<double>), dim3(8), dim3(256), 0, s, q.st, sc, 2.0 / dE,
+                       -2.0 * E_c / dE, nb);
+    HIPC(hipGetLastError());
+  });
+  hipLaunchKernelGGL(k_res_sum, dim3((unsigned)((count + 3) / 4)), dim3(256), 0, s, r.part,
+                     t->nslab * kResWaves, count, sums);
+  HIPC(hipGetLastError());
+  HIPC(hipMemcpyAsync(dots, sums, (size_t)count * sizeof(double), hipMemcpyDeviceToHost, s));
+  HIPC(hipStreamSynchronize(s));
 }
 
 template void chain_res_batch<double>(hipStream_t, const ChainBatch&, const double*, int,

@@ -561,6 +561,8 @@ size_t SolveRun::footprint(const polfed_op* op, const polfed_params& p) {
   const int n_want = (int)std::min<int64_t>(op->D, n_ev + g);
   const int M = (int)std::min<int64_t>(op->D, expected_krylov_dim(n_want, 1, p.eta > 0 ? p.eta : 1.5));
   size_t b = bytes_at(op->D, M, n_want, f32);
+  if (p.kpm_moments > 0)  // before the basis is allocated
+    b = std::max(b, kpm_workspace(op, p.kpm_moments, p.kpm_vectors > 0 ? p.kpm_vectors : 100));
   if (!(p.E_max > p.E_min)) {
     // the bounds Lanczos before it: its basis of up to 300 steps, w and the
     // two recurrence buffers of its work space

@@ -12,7 +12,7 @@ import pytest
 
 import workloads as wl
 from oracle import filter as flt
-from oracle import models
+from oracle import kpm, models
 from tests.test_gpu_batch import filter_tol
 from tests.test_gpu_parity import ctx, dev, host, pk, say  # noqa: F401
 
@@ -113,3 +113,19 @@ def test_streams_side_by_side(pk):
     for i in range(6):
         for w in got[i]:
             assert np.array_equal(host(w), alone[i])
+
+
+@pytest.mark.parametrize("L,N,periodic,R", [(12, 6, True, 3), (13, 6, False, 17), (16, 8, True, 9),
+                                            (14, 5, True, 70)])
+def test_kpm_moments(pk, ctx, L, N, periodic, R):
+    """Moments from the resident recurrence (one workgroup, teams, pairs of
+    vectors, more vectors than one launch takes) for odd, even and the
+    smallest numbers of them."""
+    say(f"kpm L={L} N={N} R={R}")
+    op, H = chain(pk, ctx, "tv" if L == 16 else "xxz", L, N, periodic, 9)
+    v = np.random.default_rng(2).standard_normal((R, op.D))
+    E_c, dE = 0.2, 2.6 * L
+    ref = kpm.moments(H, E_c, dE, v.T, 61)
+    for n in (1, 2, 3, 7, 8, 9, 60, 61):
+        got = pk.kpm_moments(op, E_c, dE, n, R, dev(v))
+        assert np.max(np.abs(got - ref[:n])) <= 1e-11 * op.D, n
