@@ -552,10 +552,10 @@ struct ResTable {
   DevBuf slot, state;
 };
 // Whether filters of op in this precision run as one resident launch (short
-// matrix-free chains whose step kernel is not forced); builds the tables for
-// it (not while s is captured); the bytes such a filter needs behind the D
-// elements of its first recurrence buffer.
-bool chain_res_applies(const polfed_op* op, bool fp32);
+// matrix-free chains whose step kernel is not forced, quantum suns); builds a
+// chain's tables for it (not while s is captured); the bytes such a filter
+// needs behind the D elements of its first recurrence buffer.
+bool res_applies(const polfed_op* op, bool fp32);
 void chain_res_prepare(hipStream_t s, const polfed_op* op, bool fp32);
 size_t chain_res_tail();
 // Steps from which a filter goes that way: the resident launch itself
@@ -569,7 +569,7 @@ inline size_t filter_buf_bytes(int64_t n, size_t elem) {
 // The filter as one resident launch; false (nothing done) where it does not
 // apply or K is small.
 template <typename T>
-bool chain_res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const double* a,
+bool res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const double* a,
                       int K, const T* v, T* w, T* bufA, T* bufB);
 bool chain_res_batch_fits(hipStream_t s, const polfed_op* op0, int nb);
 // Products of the Chebyshev vectors t_n(H~) v of nb columns (kpm.hip).

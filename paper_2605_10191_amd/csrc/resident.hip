@@ -538,6 +538,186 @@ __global__ __launch_bounds__(kResThreads) void k_chain_res(ResArgs<T> p) {
   }
 }
 
+// The quantum sun: row = dot state << L | outer bits.  A slab fixes the top
+// outer bits, so the whole dot matrix and the rays of the other outer spins
+// stay inside it; a ray of a top spin gathers from another slab, at the same
+// place for all lanes but the bit.  A thread holds DG dot states of one
+// setting of the slab's outer bits (ITEMS settings), so the ND values of a
+// setting are read once for DG rows; ND <= 8 keeps the thread's rows of the
+// dot matrix in registers (ND = 0: any size, read from LDS).  At 3 + 13 spins
+// (FP64) a step takes 4.4 us, 7.6 as a launch: the barrier and the gathers'
+// round trip about 2, 1.3 the 2.6 MB that the five top rays gather from one
+// XCD's L2, 0.9 the LDS reads.
+template <typename T>
+struct QsunRes {
+  QsunDev q;
+  int sbits, i_top, i_bot, first;
+  T sigma, tau;
+  const T *A, *v;
+  T *w, *X, *Y;
+  ResState* st;
+};
+
+constexpr int kQsunSlabBits = 5;
+
+template <typename T, int DG, int ITEMS, int ND>
+__global__ __launch_bounds__(kResThreads) void k_qsun_res(QsunRes<T> p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ int s_join[4];
+  __shared__ T s_amp[kQsunMaxL];
+  constexpr uint32_t TB = sizeof(T);
+  const int L = p.q.L, nd = 1 << p.q.N, nslab = 1 << p.sbits;
+  const int lo = L - p.sbits, nob = 1 << lo;  // outer bits inside a slab
+  TeamView tv{nullptr, 1, 0, 0, 0};
+  if (!team_join(p.st, nslab, 1, s_join, tv)) return;
+  // the first team takes the column
+  if (threadIdx.x == 0 && tv.rank == 0) {
+    const int g = res_add(&p.st->queue, 1);
+    if (tv.n > 1)
+      res_store(&tv.t->group[0], g);
+    else
+      s_join[3] = g;
+  }
+  int* err = &p.st->err;
+  team_barrier(tv, err, [] {});
+  if (uniform(tv.n > 1 ? res_load(&tv.t->group[0]) : s_join[3]) > 0) return;
+  T* s_b = reinterpret_cast<T*>(smem);           // [nd][nob]
+  T* s_h = s_b + ((size_t)nd << lo);             // [nd][nd], scaled
+  for (int i = threadIdx.x; i < nd * nd; i += kResThreads) s_h[i] = (T)(p.sigma * p.q.hdot[i]);
+  if ((int)threadIdx.x < L) s_amp[threadIdx.x] = (T)(p.sigma * p.q.ray_amp[threadIdx.x]);
+  T* cur = p.X;
+  T* prev = p.Y;
+  const int64_t D = p.q.D;
+  const int items = (nd / DG) << lo;
+  auto row = [&](int m, int d, int o) { return ((uint32_t)d << L) | ((uint32_t)m << lo) | (uint32_t)o; };
+  if (p.first) {
+    const T a = p.A[p.i_top];
+    for (int m = tv.rank; m < nslab; m += tv.n)
+      for (int i = threadIdx.x; i < (nd << lo); i += kResThreads) {
+        const uint32_t r = row(m, i >> lo, i & (nob - 1));
+        cur[r] = a * p.v[r];
+      }
+  }
+  team_barrier(tv, err, [] {});
+  T h[ITEMS][DG][ND > 0 ? ND : 1], v[ITEMS][DG], b1[ITEMS][DG], b2[ITEMS][DG], dg[ITEMS], acf = 0;
+  const bool one = tv.n >= nslab;
+  const int lane = threadIdx.x & 63;
+  for (int i = p.i_top - 1; i >= p.i_bot; --i) {
+    const bool last = i == 0;
+    const T half = last ? T(0.5) : T(1);
+    const int ci = (p.i_top - 1 - i) & 63;
+    if (ci == 0) acf = p.A[max(i - lane, 0)];
+    const T ai = lane_value(acf, ci);
+    const bool bad = last && res_load(err) != 0;
+    const bool store = nslab > 1 || i <= p.i_bot + 1;
+    const rsrc_t rc = make_rsrc(cur, (uint32_t)(D * TB)), ro = make_rsrc(prev, (uint32_t)(D * TB));
+    for (int m = tv.rank; m < nslab; m += tv.n) {
+      if (!one) __syncthreads();  // the slab before: its LDS reads are done
+      if (!one || i == p.i_top - 1) {
+#pragma unroll
+        for (int t = 0; t < ITEMS; ++t) {
+          const int it = threadIdx.x + kResThreads * t, o = it & (nob - 1), d0 = (it >> lo) * DG;
+          const bool valid = it < items;
+          const uint32_t ob = ((uint32_t)m << lo) | (uint32_t)o;
+          const double* f = p.q.ftab;
+          const double fs = f[ob & 255u] + f[256 + ((ob >> 8) & 255u)] +
+                            f[512 + ((ob >> 16) & 255u)] + f[768 + (ob >> 24)];
+          dg[t] = (T)(p.sigma * (p.q.c0 + fs) + p.tau);
+#pragma unroll
+          for (int d = 0; d < DG; ++d) {
+            const uint32_t r = valid ? row(m, d0 + d, o) : 0u, off = valid ? r * TB : kNoRow;
+            v[t][d] = valid ? p.v[r] : T(0);
+            b1[t][d] = rload<T, 1>(rc, off).x[0];
+            b2[t][d] = rload<T, 1>(ro, p.first && i == p.i_top - 1 ? kNoRow : off).x[0];
+            if (valid) s_b[((d0 + d) << lo) + o] = b1[t][d];
+            if constexpr (ND > 0) {
+#pragma unroll
+              for (int e = 0; e < ND; ++e) h[t][d][e] = valid ? s_h[(d0 + d) * ND + e] : T(0);
+            }
+          }
+        }
+        __syncthreads();
+      }
+#pragma unroll
+      for (int t = 0; t < ITEMS; ++t) {
+        const int it = threadIdx.x + kResThreads * t, o = it & (nob - 1), d0 = (it >> lo) * DG;
+        const bool valid = it < items;
+        const int dv = valid ? d0 : 0;
+        T acc[DG];
+#pragma unroll
+        for (int d = 0; d < DG; ++d) acc[d] = dg[t] * b1[t][d];
+        // rays of the top outer spins on their way from other slabs
+        T x[kQsunSlabBits][DG];
+#pragma unroll
+        for (int u = 0; u < kQsunSlabBits; ++u)
+#pragma unroll
+          for (int d = 0; d < DG; ++d)
+            x[u][d] = rload<T, 1>(rc, valid && u < p.sbits
+                                          ? (row(m, d0 + d, o) ^ p.q.ray_mask[min(lo + u, L - 1)]) * TB
+                                          : kNoRow).x[0];
+        // meanwhile the dot matrix and the rays inside the slab
+        if constexpr (ND > 0) {
+          T y[ND];
+#pragma unroll
+          for (int e = 0; e < ND; ++e) y[e] = s_b[(e << lo) + o];
+#pragma unroll
+          for (int d = 0; d < DG; ++d)
+#pragma unroll
+            for (int e = 0; e < ND; ++e) acc[d] += h[t][d][e] * y[e];
+        } else {
+#pragma unroll 4
+          for (int e = 0; e < nd; ++e) {
+            const T y = s_b[(e << lo) + o];
+#pragma unroll
+            for (int d = 0; d < DG; ++d) acc[d] += s_h[(dv + d) * nd + e] * y;
+          }
+        }
+#pragma unroll 4
+        for (int k = 0; k < lo; ++k) {
+          const int dm = (int)(p.q.ray_mask[k] >> L);
+          const T am = s_amp[k];
+          const int oo = o ^ (1 << k);
+#pragma unroll
+          for (int d = 0; d < DG; ++d) acc[d] += am * s_b[(((dv + d) ^ dm) << lo) + oo];
+        }
+#pragma unroll
+        for (int u = 0; u < kQsunSlabBits; ++u) {
+          const T am = s_amp[min(lo + u, L - 1)];
+#pragma unroll
+          for (int d = 0; d < DG; ++d) acc[d] += am * x[u][d];
+        }
+#pragma unroll
+        for (int d = 0; d < DG; ++d) {
+          const T out = half * acc[d] - b2[t][d] + ai * v[t][d];
+          if (valid) {
+            const uint32_t r = row(m, d0 + d, o);
+            if (last)
+              p.w[r] = bad ? T(NAN) : out;
+            else if (store)
+              bstore<0>(out, ro, r * TB, 0);
+          }
+          b2[t][d] = b1[t][d];
+          b1[t][d] = out;
+        }
+      }
+    }
+    if (last) break;
+    team_barrier(tv, err, [&] {
+      if (!one) return;
+#pragma unroll
+      for (int t = 0; t < ITEMS; ++t) {
+        const int it = threadIdx.x + kResThreads * t, o = it & (nob - 1), d0 = (it >> lo) * DG;
+#pragma unroll
+        for (int d = 0; d < DG; ++d)
+          if (it < items) s_b[((d0 + d) << lo) + o] = b1[t][d];
+      }
+    });
+    T* t = cur;
+    cur = prev;
+    prev = t;
+  }
+}
+
 // Clears the team state and writes a chunk's coefficients (kernel arguments,
 // so that the call can be captured and needs no copy from host memory).
 template <typename T>
@@ -745,7 +925,7 @@ void res_run(hipStream_t s, const ResTable& t, const ResShape& x, ResArgs<T> a, 
 
 // A single column: where a thread holds at most three rows (D <= 49,152).
 // With six rows a step takes 7.7 us, more than a launch of the step kernel.
-bool chain_res_applies(const polfed_op* op, bool fp32) {
+static bool chain_res_applies(const polfed_op* op, bool fp32) {
   if (!res_chain(op) || op->forced[fp32 ? 1 : 0]) return false;
   return res_shape(op->D, 1).R <= 3 && res_shape(op->D, 1).nslab > 0;
 }
@@ -759,7 +939,7 @@ size_t chain_res_tail() {
 }
 
 template <typename T>
-bool chain_res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const double* a,
+static bool chain_res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const double* a,
                       int K, const T* v, T* w, T* bufA, T* bufB) {
   if (K < kResMinSteps || !chain_res_applies(op, sizeof(T) == 4)) return false;
   const ResShape x = res_shape(op->D, 1);
@@ -797,11 +977,85 @@ bool chain_res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE,
   return true;
 }
 
-template bool chain_res_filter<double>(hipStream_t, const polfed_op*, double, double,
-                                       const double*, int, const double*, double*, double*,
-                                       double*);
-template bool chain_res_filter<float>(hipStream_t, const polfed_op*, double, double,
-                                      const double*, int, const float*, float*, float*, float*);
+// Quantum sun: slabs so that a thread has one item of DG rows, at most 32 of
+// them, then up to four items; single-workgroup up to 2,048 rows.
+static int qsun_slab_bits(const polfed_op* op) {
+  const int dg = std::min(2, op->N_dot);
+  return std::max(0, std::min({op->N_dot + op->L - 9 - dg, kQsunSlabBits, op->L - 1}));
+}
+static int qsun_items(const polfed_op* op) {
+  const int dg = std::min(2, op->N_dot);
+  const int64_t n = (int64_t)1 << (op->N_dot + op->L - qsun_slab_bits(op) - dg);
+  return (int)((n + kResThreads - 1) / kResThreads);
+}
+static bool qsun_res_applies(const polfed_op* op) {
+  return op->model == Model::Qsun && op->storage == POLFED_MATRIX_FREE && qsun_items(op) <= 4;
+}
+
+bool res_applies(const polfed_op* op, bool fp32) {
+  return chain_res_applies(op, fp32) || qsun_res_applies(op);
+}
+
+template <typename T>
+bool res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const double* a, int K,
+                const T* v, T* w, T* bufA, T* bufB) {
+  if (chain_res_filter<T>(s, op, E_c, dE, a, K, v, w, bufA, bufB)) return true;
+  if (K < kResMinSteps || !qsun_res_applies(op)) return false;
+  const int items = qsun_items(op), N = op->N_dot;
+  QsunRes<T> r{};
+  r.q = op->qsun();
+  r.sbits = qsun_slab_bits(op);
+  r.sigma = (T)(2.0 / dE);
+  r.tau = (T)(-2.0 * E_c / dE);
+  r.v = v;
+  r.w = w;
+  r.X = bufA;
+  r.Y = bufB;
+  uintptr_t p = ((uintptr_t)(bufA + op->D) + 255) / 256 * 256;
+  r.st = (ResState*)p;
+  T* A = (T*)(p + (sizeof(ResState) + 255) / 256 * 256);
+  const unsigned grid = r.sbits ? 8u << r.sbits : 1u;
+  const size_t nd = (size_t)1 << N;
+  const size_t shm = ((nd << (op->L - r.sbits)) + nd * nd) * sizeof(T);
+  for (int top = K; top > 0;) {
+    const int bot = std::max(0, top - kResChunk);
+    r.i_top = top;
+    r.i_bot = bot;
+    r.first = top == K;
+    hipLaunchKernelGGL((k_res_begin<T>), dim3(8), dim3(256), 0, s, r.st, (T*)nullptr, T(0), T(0),
+                       0);
+    put_coefs<T>(s, a, bot, top, A);
+    r.A = A - bot;
+#define POLFED_QSUN(DG_, IT_, ND_)                                                                \
+  hipLaunchKernelGGL((k_qsun_res<T, DG_, IT_, ND_>), dim3(grid), dim3(kResThreads), shm, s, r)
+    if (N == 1 && items == 1)
+      POLFED_QSUN(2, 1, 2);
+    else if (N == 2 && items == 1)
+      POLFED_QSUN(4, 1, 4);
+    else if (N == 3 && items == 1)
+      POLFED_QSUN(4, 1, 8);
+    else if (N == 3 && items == 2)
+      POLFED_QSUN(4, 2, 8);
+    else if (N == 1)
+      POLFED_QSUN(2, 4, 0);
+    else if (items == 1)
+      POLFED_QSUN(4, 1, 0);
+    else if (items == 2)
+      POLFED_QSUN(4, 2, 0);
+    else
+      POLFED_QSUN(4, 4, 0);
+#undef POLFED_QSUN
+    HIPC(hipGetLastError());
+    if ((top - bot) % 2) std::swap(r.X, r.Y);
+    top = bot;
+  }
+  return true;
+}
+
+template bool res_filter<double>(hipStream_t, const polfed_op*, double, double, const double*, int,
+                                 const double*, double*, double*, double*);
+template bool res_filter<float>(hipStream_t, const polfed_op*, double, double, const double*, int,
+                                const float*, float*, float*, float*);
 
 bool chain_res_batch_fits(hipStream_t s, const polfed_op* op0, int nb) {
   if (!res_chain(op0)) return false;

@@ -93,13 +93,13 @@ void filter_apply_on(hipStream_t s, const polfed_op* op, double E_c, double dE,
     scale_t<T>(s, D, (T)a[0], v, w);
     return;
   }
-  if (K >= kResMinSteps && chain_res_applies(op, sizeof(T) == 4)) {
+  if (K >= kResMinSteps && res_applies(op, sizeof(T) == 4)) {
     // one resident launch; its tables are built when the step kernel is
     // chosen, on the operator's first step
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     HIPC(hipStreamIsCapturing(s, &cs));
     if (cs == hipStreamCaptureStatusNone) op_tune(s, op, sizeof(T) == 4);
-    if (chain_res_filter<T>(s, op, E_c, dE, a, K, v, w, bufA, bufB)) return;
+    if (res_filter<T>(s, op, E_c, dE, a, K, v, w, bufA, bufB)) return;
   }
   scale_t<T>(s, D, (T)a[K], v, bufA);  // b_K
   const T* cur = bufA;                  // b_{i+1}
@@ -612,7 +612,7 @@ void SolveRun::filter_self() {
   if (mode == kTimeDirect && (p.graph == 2 || pl.K < 8 || pl.K > kGraphMaxSteps)) mode = kDirect;
   if (mode == kTimeDirect && p.graph == 1) mode = kGraph;
   // a resident filter is a few launches in all
-  if (mode == kTimeDirect && pl.K >= kResMinSteps && chain_res_applies(op, fp32)) mode = kDirect;
+  if (mode == kTimeDirect && pl.K >= kResMinSteps && res_applies(op, fp32)) mode = kDirect;
   const bool use_graph = mode == kTimeGraph || mode == kGraph;
   if (use_graph && !graph.ready()) {
     if (!fp32) vst.alloc((size_t)std::max<int64_t>(D, 1) * sizeof(double));

@@ -14,7 +14,7 @@ import workloads as wl
 from oracle import filter as flt
 from oracle import kpm, models
 from tests.test_gpu_batch import filter_tol
-from tests.test_gpu_parity import ctx, dev, host, pk, say  # noqa: F401
+from tests.test_gpu_parity import ctx, dev, host, pk, qsun_case, say  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -129,3 +129,21 @@ def test_kpm_moments(pk, ctx, L, N, periodic, R):
     for n in (1, 2, 3, 7, 8, 9, 60, 61):
         got = pk.kpm_moments(op, E_c, dE, n, R, dev(v))
         assert np.max(np.abs(got - ref[:n])) <= 1e-11 * op.D, n
+
+
+# rows 4 (below a wave), 256, 2048 (one workgroup), 4096 to 65536 (slabs of
+# one item a thread), 131072 and 262144 (two and four items), every dot size
+@pytest.mark.parametrize("N,L", [(1, 1), (2, 6), (3, 8), (1, 11), (2, 11), (4, 8), (3, 13), (5, 9),
+                                 (6, 6), (1, 16), (3, 14), (5, 12), (2, 16), (3, 15)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_quantum_sun(pk, ctx, N, L, prec):
+    say(f"resident quantum sun {N}+{L} {prec}")
+    q, H = qsun_case(N, L, 3)
+    op = pk.Operator.qsun(ctx, N, L, q["A"], 1.0, 1.0, 0.75, q["u"], q["n_of_j"], q["h"])
+    p, dt = (pk.FP64, torch.float64) if prec == "fp64" else (pk.FP32, torch.float32)
+    v = np.random.default_rng(1).standard_normal(op.D)
+    E_c, dE = 0.1, 1.2 * L + 8.0
+    for K in (16, 47):
+        a = flt.coefficients(0.15, K)
+        w = pk.filter_apply(op, E_c, dE, a, dev(v, dt), p)
+        check(host(w), flt.apply_filter(H, E_c, dE, a, v), K, prec)
