@@ -105,6 +105,13 @@ void build_chain_split(polfed_op* op) {
     }
     w[4] = idle;
     w[5] = hi_off[hi ^ 1] - hoff;
+    // the joining hop of a row moves the particle between the bits Lb - 1 and
+    // Lb past no other one, so it changes the rank by +-binom(Lb - 1, m) with
+    // m the particles below: the same for every row of the block that can hop
+    if (hi & 1)
+      w[7] = need < Lb ? -(int32_t)host_binom()[(Lb - 1) * kBinomN + need] : 0;
+    else
+      w[7] = need > 0 ? (int32_t)host_binom()[(Lb - 1) * kBinomN + need - 1] : 0;
     w[6] = hi_off[hi ^ (1LL << (Lh - 1))] - hoff;
     std::memcpy(&w[8], &dhi, sizeof(double));
     const int nseg_hi = (bs + kChainSegRows - 1) / kChainSegRows;
@@ -347,71 +354,89 @@ __global__ __launch_bounds__(256) void k_chain_split(
   }
 }
 
-// Paired variant: lane l holds the adjacent rows 2l and 2l + 1 of a segment,
-// so every coalesced access (block staging, high-part gathers, v, b_{i+2}
-// and the store) moves both rows in one 16-byte instruction, halving the
-// vector-memory instructions per row.  Loads past the segment's end read
-// other rows (unused) or fall outside the buffer (read as 0); stores are
-// guarded per row.
-template <typename T, int L>
-__global__ __launch_bounds__(256) void k_chain_pair(
-    ChainSplitDev c, T sigma, T tau, T a, const T* __restrict__ v,
-    const T* __restrict__ b1, const T* b2, T* out, int nxcd,
-    const int32_t* __restrict__ recs) {
+// Direct kernel: a wavefront takes one segment, lane l the adjacent rows 2l
+// and 2l + 1, so that every coalesced access moves both rows in one 16-byte
+// instruction.  Made for chains where a wavefront runs one or two segments a
+// launch (L = 19 to 21: a step is then a chain of round trips, not bytes):
+//   - a row's low-part tables are read from global memory in list order (26
+//     bytes a row, coalesced) with the rest, instead of a 27 KB copy into LDS
+//     per workgroup that everything else waits for;
+//   - the joining bond is one more gather at a wave-uniform row offset (see
+//     build_chain_split), so only the periodic bond waits for the tables.
+// With MULTI the columns of a column-major block are spread over the XCDs
+// (8, 4, 2 or 1 of them a column), so a column's gathers stay in its XCDs'
+// L2; each column has its operator's records and tables.
+//
+// Measured (FP64, L = 20, us a step): 4 columns 13.5 (interleaved) -> 9.6, one
+// column 6.0 (segment kernel) -> 5.0 in a graph, 6.1 -> 5.8 launched one by
+// one; from L = 22 the tile kernels are faster.
+//
+// Loads past the segment's end read other rows (unused) or fall outside the
+// buffer (read as 0); stores are guarded per row.
+template <typename T, int L, bool MULTI>
+__global__ __launch_bounds__(256) void k_chain_direct(
+    ChainSplitDev c, T sigma, T tau, T a, const ChainCol* __restrict__ cols, int ncol, int nb,
+    const T* __restrict__ sc, const T* __restrict__ acoef, T half, const T* __restrict__ v,
+    const T* __restrict__ b1, const T* b2, T* out, int nxcd, int xpc) {
   constexpr int Lb = (L / 2 < kChainLoBits) ? L / 2 : kChainLoBits;
   constexpr int Lh = L - Lb;
   constexpr int NLO = 1 << Lb;
   constexpr int NH = Lh - 1;
   constexpr int NL = Lb - 1;
   constexpr int SPL = kChainStageRows / 128;  // staged row pairs per lane
-  constexpr int BLOB = chain_blob_bytes(NLO, (int)sizeof(T));
-  constexpr int CHUNKS = BLOB / 16;
   constexpr uint32_t TB = sizeof(T);
   using u4 = __attribute__((ext_vector_type(4))) uint32_t;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  {
-    const u4* src = reinterpret_cast<const u4*>(sizeof(T) == 8 ? c.blob64 : c.blob32);
-    u4* dst = reinterpret_cast<u4*>(smem);
-    constexpr int PER = (CHUNKS + 255) / 256;
-    u4 tmp[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int i = threadIdx.x + 256 * k;
-      if (i < CHUNKS) tmp[k] = src[i];
-    }
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int i = threadIdx.x + 256 * k;
-      if (i < CHUNKS) dst[i] = tmp[k];
-    }
-  }
-  const u4* s_np = reinterpret_cast<const u4*>(smem);
-  const T* s_dlo = reinterpret_cast<const T*>(smem + 16 * NLO);
-  const uint16_t* s_lo = reinterpret_cast<const uint16_t*>(s_dlo + NLO);
-  T* stage = reinterpret_cast<T*>(smem + BLOB) + (threadIdx.x >> 6) * kChainStageRows;
-  __syncthreads();
-
+  __shared__ __attribute__((aligned(16))) T s_stage[4 * kChainStageRows];
+  T* stage = s_stage + (threadIdx.x >> 6) * kChainStageRows;
   const int xcd = blockIdx.x % nxcd;
-  const int blocks_x = gridDim.x / nxcd;
-  const int64_t s_begin = c.nseg * xcd / nxcd, s_end = c.nseg * (xcd + 1) / nxcd;
-  const int wpb = blockDim.x >> 6;
-  const int64_t wstride = (int64_t)blocks_x * wpb;
   const int lane = threadIdx.x & 63;
   const T vzz = (T)c.vzz, t_in = (T)c.t_in, t_pb = (T)c.t_pb;
   const uint32_t vbytes = (uint32_t)(c.D * TB);
-  const rsrc_t rb1 = make_rsrc(b1, vbytes), rv = make_rsrc(v, v ? vbytes : 0),
-               rb2 = make_rsrc(b2, b2 ? vbytes : 0), rout = make_rsrc(out, vbytes);
-  int64_t si = s_begin + (int64_t)(blockIdx.x / nxcd) * wpb + uniform(threadIdx.x >> 6);
-  if (si >= s_end) return;
-  for (; si < s_end; si += wstride) {
-    const SegRec<NH> cur = load_rec<NH>(recs + (int64_t)uniform((int)si) * kChainRecWords);
+  // this XCD's share: segments [s_begin, s_begin + nsx) of the columns
+  // first, first + step, ...
+  const int part = MULTI ? xcd % xpc : xcd, parts = MULTI ? xpc : nxcd;
+  const int s_begin = (int)(c.nseg * part / parts);
+  const int nsx = (int)(c.nseg * (part + 1) / parts) - s_begin;
+  const int first = MULTI ? xcd / xpc : 0, step = MULTI ? nxcd / xpc : 1;
+  const int ncx = MULTI ? (ncol - first + step - 1) / step : 1;
+  const int64_t items = (int64_t)nsx * max(ncx, 0);
+  const int64_t stride = (int64_t)(gridDim.x / nxcd) * 4;
+  for (int64_t it = (int64_t)(blockIdx.x / nxcd) * 4 + uniform(threadIdx.x >> 6); it < items;
+       it += stride) {
+    const int k = MULTI ? (int)(it / nsx) : 0;
+    const int si = uniform(s_begin + (int)(it - (int64_t)k * nsx));
+    const int col = uniform(first + k * step);
+    const int64_t coff = MULTI ? (int64_t)col * c.D : 0;
+    const int32_t* recs = MULTI ? cols[col].rec : c.rec;
+    const unsigned char* blob = reinterpret_cast<const unsigned char*>(
+        sizeof(T) == 8 ? (MULTI ? cols[col].blobl64 : c.blobl64)
+                       : (MULTI ? cols[col].blobl32 : c.blobl32));
+    const rsrc_t rb1 = make_rsrc(b1 + coff, vbytes), rv = make_rsrc(v ? v + coff : b1, v ? vbytes : 0),
+                 rb2 = make_rsrc(b2 ? b2 + coff : b1, b2 ? vbytes : 0),
+                 rout = make_rsrc(out + coff, vbytes);
+    const rsrc_t rnp = make_rsrc(blob, 16 * NLO), rdl = make_rsrc(blob + 16 * NLO, TB * NLO),
+                 rlo = make_rsrc(blob + (16 + TB) * NLO, 2 * NLO);
+    const int32_t* rec = recs + (int64_t)si * kChainRecWords;
+    const SegRec<NH> cur = load_rec<NH>(rec);
+    const int d_near = uniform(rec[7]);
     const int hi0 = cur.flags & 1, hitop = (cur.flags >> 1) & 1;
     const int bs = (cur.flags >> 2) & 1023, st = (cur.flags >> 12) & 1023;
     const int blk0 = cur.row0 - st;
     const uint32_t so_blk = (uint32_t)blk0 * TB, so_row = (uint32_t)cur.row0 * TB;
     const uint32_t pair_off = (uint32_t)(2 * lane) * TB;
-    // stage the block: pairs of rows
-    T sg[SPL][2];
+    // the lane's two rows, clamped into the segment, and their tables
+    int jj[2], lo[2];
+    u4 np[2];
+    T dl[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      jj[i] = min(2 * lane + i, cur.len - 1);
+      const uint32_t q = (uint32_t)(cur.lidx + jj[i]);
+      np[i] = __builtin_amdgcn_raw_buffer_load_b128(rnp, 16 * q, 0, 0);
+      lo[i] = __builtin_amdgcn_raw_buffer_load_b16(rlo, 2 * q, 0, 0);
+      dl[i] = bload<T>(rdl, TB * q, 0);
+    }
+    T sg[SPL][2], g_hi[NH > 0 ? NH : 1][2], g_j[2], vv[2], bt[2];
 #pragma unroll
     for (int m = 0; m < SPL; ++m) {
       if (128 * m < bs)
@@ -419,19 +444,6 @@ __global__ __launch_bounds__(256) void k_chain_pair(
       else
         sg[m][0] = sg[m][1] = T(0);
     }
-    // the lane's two rows, clamped into the segment
-    int jj[2], lo[2];
-    u4 np[2];
-    bool act_j[2], act_p[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      jj[i] = min(2 * lane + i, cur.len - 1);
-      lo[i] = s_lo[cur.lidx + jj[i]];
-      np[i] = s_np[lo[i]];
-      act_j[i] = ((lo[i] >> (Lb - 1)) & 1) != hi0;
-      act_p[i] = c.periodic && ((lo[i] & 1) != hitop);
-    }
-    T g_hi[NH > 0 ? NH : 1][2], g_j[2], g_p[2], vv[2], bt[2];
 #pragma unroll
     for (int b = 0; b < NH; ++b) {
       if (cur.dh[b] != 0)
@@ -439,13 +451,10 @@ __global__ __launch_bounds__(256) void k_chain_pair(
       else
         g_hi[b][0] = g_hi[b][1] = T(0);
     }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int rj = (int)((np[i][2] >> 8) & 255u);
-      const int rp = (int)((np[i][2] >> 16) & 255u);
-      g_j[i] = act_j[i] ? bload<T>(rb1, (uint32_t)(blk0 + cur.d_join + rj) * TB, 0) : T(0);
-      g_p[i] = act_p[i] ? bload<T>(rb1, (uint32_t)(blk0 + cur.d_pbc + rp) * TB, 0) : T(0);
-    }
+    if (d_near != 0)
+      bload2<T>(rb1, pair_off + (uint32_t)((cur.row0 + d_near) * (int)TB), 0, g_j[0], g_j[1]);
+    else
+      g_j[0] = g_j[1] = T(0);
     if (v)
       bload2<T, kAuxNT>(rv, pair_off, so_row, vv[0], vv[1]);
     else
@@ -454,6 +463,15 @@ __global__ __launch_bounds__(256) void k_chain_pair(
       bload2<T, kAuxNT>(rb2, pair_off, so_row, bt[0], bt[1]);
     else
       bt[0] = bt[1] = T(0);
+    bool act_j[2], act_p[2];
+    T g_p[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      act_j[i] = ((lo[i] >> (Lb - 1)) & 1) != hi0;
+      act_p[i] = c.periodic && ((lo[i] & 1) != hitop);
+      const int rp = (int)((np[i][2] >> 16) & 255u);
+      g_p[i] = act_p[i] ? bload<T>(rb1, (uint32_t)(blk0 + cur.d_pbc + rp) * TB, 0) : T(0);
+    }
     wave_sync();  // the previous segment's LDS reads are done
 #pragma unroll
     for (int m = 0; m < SPL; ++m) {
@@ -464,6 +482,8 @@ __global__ __launch_bounds__(256) void k_chain_pair(
       }
     }
     wave_sync();
+    const T sig = MULTI ? half * sc[col] : sigma, ta = MULTI ? half * sc[nb + col] : tau;
+    const T ac = MULTI ? (acoef ? acoef[col] : T(0)) : a;
     T o[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -479,10 +499,10 @@ __global__ __launch_bounds__(256) void k_chain_pair(
       hop += act_j[i] ? g_j[i] : T(0);
       const int lo_top = (l >> (Lb - 1)) & 1, lo0 = l & 1;
       const int n11x = (lo_top & hi0) + (c.periodic ? (hitop & lo0) : 0);
-      const T dg = s_dlo[l] + (T)cur.dhi + vzz * (T)n11x;
+      const T dg = dl[i] + (T)cur.dhi + vzz * (T)n11x;
       const T acc = dg * bo + t_in * hop + (act_p[i] ? t_pb * g_p[i] : T(0));
-      o[i] = sigma * acc + tau * bo - bt[i];
-      if (v) o[i] += a * vv[i];
+      o[i] = sig * acc + ta * bo - bt[i];
+      if (v) o[i] += ac * vv[i];
     }
     const int r0 = 2 * lane;
     if (r0 + 1 < cur.len)
@@ -493,25 +513,65 @@ __global__ __launch_bounds__(256) void k_chain_pair(
 }
 
 template <typename T, int L>
-static void launch_pair(hipStream_t s, const polfed_op* op, T sigma, T tau, T a, const T* v,
-                        const T* b1, const T* b2, T* out) {
-  constexpr int Lb = (L / 2 < kChainLoBits) ? L / 2 : kChainLoBits;
-  constexpr int NLO = 1 << Lb;
-  const size_t shm = chain_blob_bytes(NLO, (int)sizeof(T)) + 4 * kChainStageRows * sizeof(T);
-  const int bpc = std::max(1, std::min(kChainBlocksPerCU, (int)(kLdsPerCU / shm)));
+static void launch_direct(hipStream_t s, const polfed_op* op, T sigma, T tau, T a, const T* v,
+                          const T* b1, const T* b2, T* out) {
   ChainSplitDev c = op->chain_split();
-  const int64_t blocks_needed = (c.nseg + 3) / 4;
-  int64_t grid = std::min<int64_t>(blocks_needed, (int64_t)op->ctx->n_cu * bpc);
+  int64_t grid = std::min<int64_t>((c.nseg + 3) / 4, (int64_t)op->ctx->n_cu * kChainBlocksPerCU);
   int nxcd = 1;
   if (grid >= 64) {
-    grid -= grid % 8;
+    grid = (grid + 7) / 8 * 8;
     nxcd = 8;
   }
   grid = std::max<int64_t>(grid, 1);
-  hipLaunchKernelGGL((k_chain_pair<T, L>), dim3((unsigned)grid), dim3(256), shm, s, c, sigma,
-                     tau, a, v, b1, b2, out, nxcd, c.rec);
+  hipLaunchKernelGGL((k_chain_direct<T, L, false>), dim3((unsigned)grid), dim3(256), 0, s, c, sigma,
+                     tau, a, (const ChainCol*)nullptr, 1, 1, (const T*)nullptr, (const T*)nullptr,
+                     T(1), v, b1, b2, out, nxcd, 1);
   HIPC(hipGetLastError());
 }
+
+// Columns [col0, col0 + ncol) of a batch, one step (see k_chain_direct).
+template <typename T, int L>
+static void launch_direct_cols(hipStream_t s, const ChainBatch& bt, int col0, int ncol, T half,
+                               const T* acoef, const T* v, const T* b1, const T* b2, T* out) {
+  const polfed_op* op0 = bt.ops[0];
+  ChainSplitDev c = op0->chain_split();
+  int xpc = 8;
+  while (xpc > 1 && xpc * ncol > 8) xpc /= 2;
+  const int64_t per = (c.nseg / xpc + 1) * ((ncol + 8 / xpc - 1) / (8 / xpc));  // items of an XCD
+  int64_t grid = 8 * std::min<int64_t>((per + 3) / 4, (int64_t)op0->ctx->n_cu * kChainBlocksPerCU / 8);
+  const bool f64 = sizeof(T) == 8;
+  const T* sc = (const T*)(f64 ? bt.sc64.get() : bt.sc32.get());
+  const size_t o = (size_t)col0 * op0->D;
+  hipLaunchKernelGGL((k_chain_direct<T, L, true>), dim3((unsigned)std::max<int64_t>(grid, 8)),
+                     dim3(256), 0, s, c, T(0), T(0), T(0), bt.cols.as<ChainCol>() + col0, ncol,
+                     bt.nb, sc + col0, acoef ? acoef + col0 : nullptr, half, v ? v + o : nullptr,
+                     b1 + o, b2 ? b2 + o : nullptr, out + o, 8, xpc);
+  HIPC(hipGetLastError());
+}
+
+template <typename T>
+void chain_direct_cols(hipStream_t s, const ChainBatch& bt, int col0, int ncol, T half,
+                       const T* acoef, const T* v, const T* b1, const T* b2, T* out) {
+  switch (bt.ops[0]->L) {
+#define POLFED_CASE(LL)                                                                     \
+  case LL:                                                                                  \
+    launch_direct_cols<T, LL>(s, bt, col0, ncol, half, acoef, v, b1, b2, out);              \
+    break;
+    POLFED_CASE(4) POLFED_CASE(5) POLFED_CASE(6) POLFED_CASE(7) POLFED_CASE(8)
+    POLFED_CASE(9) POLFED_CASE(10) POLFED_CASE(11) POLFED_CASE(12) POLFED_CASE(13)
+    POLFED_CASE(14) POLFED_CASE(15) POLFED_CASE(16) POLFED_CASE(17) POLFED_CASE(18)
+    POLFED_CASE(19) POLFED_CASE(20) POLFED_CASE(21) POLFED_CASE(22) POLFED_CASE(23)
+    POLFED_CASE(24) POLFED_CASE(25) POLFED_CASE(26) POLFED_CASE(27) POLFED_CASE(28)
+#undef POLFED_CASE
+    default: fail(POLFED_ERR_INVALID, "batch: chain length outside 4..28");
+  }
+}
+template void chain_direct_cols<double>(hipStream_t, const ChainBatch&, int, int, double,
+                                        const double*, const double*, const double*,
+                                        const double*, double*);
+template void chain_direct_cols<float>(hipStream_t, const ChainBatch&, int, int, float,
+                                       const float*, const float*, const float*, const float*,
+                                       float*);
 
 // Tile variant for long chains: a workgroup stages a whole tile of 2^KT
 // consecutive high parts of b_{i+1} in LDS (one coalesced read of its rows),
@@ -1110,7 +1170,7 @@ static bool launch_variant(hipStream_t s, const polfed_op* op, int var, T sigma,
     return true;
   }
   if (var == 3) {
-    launch_pair<T, L>(s, op, sigma, tau, a, v, b1, b2, out);
+    launch_direct<T, L>(s, op, sigma, tau, a, v, b1, b2, out);
     return true;
   }
   if (var == 4) {

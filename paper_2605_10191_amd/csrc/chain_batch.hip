@@ -24,163 +24,6 @@
 
 namespace polfed {
 
-template <typename T, int L>
-__global__ __launch_bounds__(256) void k_chain_split_batch(
-    ChainSplitDev c, int nb, int col0, int ncols, int64_t ld, T half,
-    const T* __restrict__ fab, const T* __restrict__ dseg, const T* __restrict__ sc,
-    const T* __restrict__ acoef, const T* __restrict__ v, const T* __restrict__ b1,
-    const T* b2, T* out, int nxcd, const int32_t* __restrict__ recs) {
-  constexpr int Lb = (L / 2 < kChainLoBits) ? L / 2 : kChainLoBits;
-  constexpr int Lh = L - Lb;
-  constexpr int NLO = 1 << Lb;
-  constexpr int NH = Lh - 1;
-  constexpr int NL = Lb - 1;
-  constexpr int SPL2 = kChainStageRows / 128;  // staged row pairs per lane
-  constexpr int BLOB = chain_blob_bytes(NLO, (int)sizeof(T));
-  constexpr int CHUNKS = BLOB / 16;
-  constexpr uint32_t TB = sizeof(T);
-  using u4 = __attribute__((ext_vector_type(4))) uint32_t;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  {
-    const u4* src = reinterpret_cast<const u4*>(sizeof(T) == 8 ? c.blob64 : c.blob32);
-    u4* dst = reinterpret_cast<u4*>(smem);
-    constexpr int PER = (CHUNKS + 255) / 256;
-    u4 tmp[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int i = threadIdx.x + 256 * k;
-      if (i < CHUNKS) tmp[k] = src[i];
-    }
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int i = threadIdx.x + 256 * k;
-      if (i < CHUNKS) dst[i] = tmp[k];
-    }
-  }
-  T* s_fab = reinterpret_cast<T*>(smem + BLOB);
-  for (int i = threadIdx.x; i < ncols * 64; i += 256) s_fab[i] = fab[(int64_t)col0 * 64 + i];
-  const u4* s_np = reinterpret_cast<const u4*>(smem);
-  const uint16_t* s_lo = reinterpret_cast<const uint16_t*>(smem + 16 * NLO + TB * NLO);
-  T* stage = s_fab + ncols * 64 + (threadIdx.x >> 6) * kChainStageRows;
-  __syncthreads();
-
-  const int xcd = blockIdx.x % nxcd;
-  const int blocks_x = gridDim.x / nxcd;
-  const int64_t s_begin = c.nseg * xcd / nxcd, s_end = c.nseg * (xcd + 1) / nxcd;
-  const int wpb = blockDim.x >> 6;
-  const int64_t wstride = (int64_t)blocks_x * wpb;
-  const int lane = threadIdx.x & 63;
-  const T vzz = (T)c.vzz, t_in = (T)c.t_in, t_pb = (T)c.t_pb;
-  const uint32_t vbytes = (uint32_t)(c.D * TB);
-  int64_t si = s_begin + (int64_t)(blockIdx.x / nxcd) * wpb + uniform(threadIdx.x >> 6);
-  if (si >= s_end) return;
-  for (; si < s_end; si += wstride) {
-    const SegRec<NH> cur = load_rec<NH>(recs + (int64_t)uniform((int)si) * kChainRecWords);
-    const int hi0 = cur.flags & 1, hitop = (cur.flags >> 1) & 1;
-    const int bs = (cur.flags >> 2) & 1023, st = (cur.flags >> 12) & 1023;
-    const int blk0 = cur.row0 - st;
-    const uint32_t so_blk = (uint32_t)blk0 * TB, so_row = (uint32_t)cur.row0 * TB;
-    // per-row decoding shared by all columns: lane l holds the adjacent rows
-    // 2l and 2l + 1 (clamped into the segment)
-    int jj[2], lo[2], gj[2], gp[2];
-    u4 np[2];
-    bool act_j[2], act_p[2];
-    T zz[2], nidle[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      jj[i] = min(2 * lane + i, cur.len - 1);
-      const int l = s_lo[cur.lidx + jj[i]];
-      lo[i] = l;
-      np[i] = s_np[l];
-      act_j[i] = ((l >> (Lb - 1)) & 1) != hi0;
-      act_p[i] = c.periodic && ((l & 1) != hitop);
-      const int rj = (int)((np[i][2] >> 8) & 255u);
-      const int rp = (int)((np[i][2] >> 16) & 255u);
-      gj[i] = blk0 + cur.d_join + rj;
-      gp[i] = blk0 + cur.d_pbc + rp;
-      const int xlo = (l ^ (l >> 1)) & ((1 << NL) - 1);
-      nidle[i] = (T)(NL - __popc(xlo));
-      const int n11x = ((l >> (Lb - 1)) & 1 & hi0) + (c.periodic ? (hitop & l & 1) : 0);
-      zz[i] = vzz * (T)(__popc(l & (l >> 1)) + n11x);
-    }
-    const uint32_t pair_off = (uint32_t)(2 * lane) * TB;
-    const int r0 = 2 * lane;
-#pragma unroll 1
-    for (int cc = 0; cc < ncols; ++cc) {
-      const int col = col0 + cc;
-      const int64_t coff = (int64_t)col * ld;
-      const T sig = sc[col] * half, ta = sc[nb + col] * half;
-      const T ac = acoef ? acoef[col] : T(0);
-      const T dsg = dseg[si * nb + col];
-      const rsrc_t rb1 = make_rsrc(b1 + coff, vbytes);
-      const rsrc_t rv = make_rsrc(v ? v + coff : nullptr, v ? vbytes : 0);
-      const rsrc_t rb2 = make_rsrc(b2 ? b2 + coff : nullptr, b2 ? vbytes : 0);
-      const rsrc_t rout = make_rsrc(out + coff, vbytes);
-      T sg[SPL2][2];
-#pragma unroll
-      for (int m = 0; m < SPL2; ++m) {
-        if (128 * m < bs)
-          bload2<T>(rb1, pair_off + (uint32_t)(128 * m) * TB, so_blk, sg[m][0], sg[m][1]);
-        else
-          sg[m][0] = sg[m][1] = T(0);
-      }
-      T g_hi[NH > 0 ? NH : 1][2], g_j[2], g_p[2], vv[2], bt[2];
-#pragma unroll
-      for (int b = 0; b < NH; ++b) {
-        if (cur.dh[b] != 0)
-          bload2<T>(rb1, pair_off, (uint32_t)(cur.row0 + cur.dh[b]) * TB, g_hi[b][0], g_hi[b][1]);
-        else
-          g_hi[b][0] = g_hi[b][1] = T(0);
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        g_j[i] = act_j[i] ? bload<T>(rb1, (uint32_t)gj[i] * TB, 0) : T(0);
-        g_p[i] = act_p[i] ? bload<T>(rb1, (uint32_t)gp[i] * TB, 0) : T(0);
-      }
-      if (v)
-        bload2<T, kAuxNT>(rv, pair_off, so_row, vv[0], vv[1]);
-      else
-        vv[0] = vv[1] = T(0);
-      if (b2)
-        bload2<T, kAuxNT>(rb2, pair_off, so_row, bt[0], bt[1]);
-      else
-        bt[0] = bt[1] = T(0);
-      wave_sync();  // the previous column's (or segment's) LDS reads are done
-#pragma unroll
-      for (int m = 0; m < SPL2; ++m) {
-        const int r = 128 * m + 2 * lane;
-        if (r < bs) {
-          stage[r] = sg[m][0];
-          if (r + 1 < bs) stage[r + 1] = sg[m][1];
-        }
-      }
-      wave_sync();
-      const T* fa = s_fab + cc * 64;
-      T o[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int l = lo[i];
-        const T bo = stage[st + jj[i]];
-        T hop = 0;
-#pragma unroll
-        for (int b = 0; b < NL; ++b) hop += stage[(np[i][b >> 2] >> (8 * (b & 3))) & 255u];
-#pragma unroll
-        for (int b = 0; b < NH; ++b) hop += g_hi[b][i];
-        hop -= nidle[i] * bo;
-        hop += act_j[i] ? g_j[i] : T(0);
-        const T dg = zz[i] + fa[l & 31] + fa[32 + (l >> 5)] + dsg;
-        const T acc = dg * bo + t_in * hop + (act_p[i] ? t_pb * g_p[i] : T(0));
-        o[i] = sig * acc + ta * bo - bt[i];
-        if (v) o[i] += ac * vv[i];
-      }
-      if (r0 + 1 < cur.len)
-        bstore2<kAuxNT>(o[0], o[1], rout, pair_off, so_row);
-      else if (r0 < cur.len)
-        bstore<kAuxNT>(o[0], rout, pair_off, so_row);
-    }
-  }
-}
-
 // Interleaved multi-column step.  The recurrence blocks are stored with the
 // columns of a row side by side: element (row r, column c) at X[r nb + c].
 // A wavefront takes one (segment, column group) item, a group being the
@@ -621,34 +464,6 @@ static void launch_rows(hipStream_t s, const polfed_op* op0, const ChainBatch& b
   HIPC(hipGetLastError());
 }
 
-template <typename T, int L>
-static void launch_batch(hipStream_t s, const polfed_op* op0, const ChainBatch& bt,
-                         int col0, int ncols, int64_t ld, int bpc, T half, const T* acoef,
-                         const T* v, const T* b1, const T* b2, T* out) {
-  constexpr int Lb = (L / 2 < kChainLoBits) ? L / 2 : kChainLoBits;
-  constexpr int NLO = 1 << Lb;
-  const size_t shm = chain_blob_bytes(NLO, (int)sizeof(T)) +
-                     (size_t)ncols * 64 * sizeof(T) + 4 * kChainStageRows * sizeof(T);
-  bpc = std::max(1, std::min(bpc, batch_bpc_fit(shm)));
-  ChainSplitDev c = op0->chain_split();
-  const int64_t blocks_needed = (c.nseg + 3) / 4;
-  int64_t grid = std::min<int64_t>(blocks_needed, (int64_t)op0->ctx->n_cu * bpc);
-  int nxcd = 1;
-  if (grid >= 64) {
-    grid -= grid % 8;
-    nxcd = 8;
-  }
-  grid = std::max<int64_t>(grid, 1);
-  const bool f64 = sizeof(T) == 8;
-  hipLaunchKernelGGL((k_chain_split_batch<T, L>), dim3((unsigned)grid), dim3(256), shm, s, c,
-                     bt.nb, col0, ncols, ld, half,
-                     (const T*)(f64 ? bt.fab64.get() : bt.fab32.get()),
-                     (const T*)(f64 ? bt.dseg64.get() : bt.dseg32.get()),
-                     (const T*)(f64 ? bt.sc64.get() : bt.sc32.get()), acoef, v, b1, b2, out,
-                     nxcd, c.rec);
-  HIPC(hipGetLastError());
-}
-
 void ChainBatch::init(polfed_ctx* c, const polfed_op* const* o, int n) {
   REQUIRE(n >= 1, "batch: need at least one operator");
   ctx = c;
@@ -684,6 +499,10 @@ void ChainBatch::init(polfed_ctx* c, const polfed_op* const* o, int n) {
   }
   upload(fields, fl.data(), fl.size(), s);
   res_state.alloc(sizeof(ResState));
+  std::vector<ChainCol> cd(n);
+  for (int i = 0; i < n; ++i)
+    cd[i] = {ops[i]->d_rec.as<int32_t>(), ops[i]->d_blobl64.get(), ops[i]->d_blobl32.get()};
+  upload(cols, cd.data(), cd.size(), s);
   sc64.alloc((size_t)2 * n * sizeof(double));
   sc32.alloc((size_t)2 * n * sizeof(float));
   HIPC(hipStreamSynchronize(s));
@@ -772,24 +591,9 @@ static void batch_step_var(hipStream_t s, const ChainBatch& bt, int var, bool fi
     }
     return;
   }
-  const int per = var == 0 ? 16 : 8;
-  for (int col0 = 0; col0 < bt.nb; col0 += per) {
-    const int ncols = std::min(per, bt.nb - col0);
-    switch (op0->L) {
-#define POLFED_CASE(LL)                                                                     \
-  case LL:                                                                                  \
-    launch_batch<T, LL>(s, op0, bt, col0, ncols, ld, kChainBlocksPerCU, half, acoef, v, b1, \
-                        b2, out);                                                           \
-    break;
-      POLFED_CASE(4) POLFED_CASE(5) POLFED_CASE(6) POLFED_CASE(7) POLFED_CASE(8)
-      POLFED_CASE(9) POLFED_CASE(10) POLFED_CASE(11) POLFED_CASE(12) POLFED_CASE(13)
-      POLFED_CASE(14) POLFED_CASE(15) POLFED_CASE(16) POLFED_CASE(17) POLFED_CASE(18)
-      POLFED_CASE(19) POLFED_CASE(20) POLFED_CASE(21) POLFED_CASE(22) POLFED_CASE(23)
-      POLFED_CASE(24) POLFED_CASE(25) POLFED_CASE(26) POLFED_CASE(27) POLFED_CASE(28)
-#undef POLFED_CASE
-      default: fail(POLFED_ERR_INVALID, "batch: chain length outside 4..28");
-    }
-  }
+  const int per = var == 0 ? bt.nb : 8;
+  for (int col0 = 0; col0 < bt.nb; col0 += per)
+    chain_direct_cols<T>(s, bt, col0, std::min(per, bt.nb - col0), half, acoef, v, b1, b2, out);
 }
 
 template <typename T>

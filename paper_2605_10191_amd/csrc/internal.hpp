@@ -259,6 +259,12 @@ struct ChainSplitDev {
   int64_t nseg;
 };
 
+// A column of a column-major batch: its operator's records and tables.
+struct ChainCol {
+  const int32_t* rec;
+  const void *blobl64, *blobl32;
+};
+
 constexpr int kQsunMaxL = 31;
 // Quantum sun in the full space: index = dot_state << L | outer_bits.
 struct QsunDev {
@@ -471,6 +477,7 @@ struct ChainBatch {
   DevBuf dseg64, dseg32;  // [nseg][nb] uniform diagonal part per segment
   DevBuf sc64, sc32;      // [2][nb] sigma = 2/dE, tau = -2 E_c/dE
   DevBuf fields;          // [nb][33] site terms and constant (resident kernel)
+  DevBuf cols;            // [nb] ChainCol
   DevBuf res_state;       // team state of the resident kernel
   std::vector<double> E_c, dE;  // host copies of each column's rescaling
   void init(polfed_ctx* c, const polfed_op* const* o, int n);
@@ -482,6 +489,11 @@ struct ChainBatch {
 template <typename T>
 void chain_batch_step(hipStream_t s, const ChainBatch& bt, int64_t ld, bool final_step,
                       const T* acoef, const T* v, const T* b1, const T* b2, T* out);
+// One step of columns [col0, col0 + ncol) of column-major blocks with the
+// columns spread over the XCDs (chain.hip).
+template <typename T>
+void chain_direct_cols(hipStream_t s, const ChainBatch& bt, int col0, int ncol, T half,
+                       const T* acoef, const T* v, const T* b1, const T* b2, T* out);
 // The multi-column step kernel picked by timing for this batch width and
 // precision (kept per operator pattern): 0, 1 column-major blocks (16 or 8
 // columns per launch), 2, 3 interleaved blocks (element (r, c) at r nb + c;
