@@ -186,7 +186,7 @@ __global__ __launch_bounds__(256) void k_chain_ilv(
       } else if (VCM) {
 #pragma unroll
         for (int q = 0; q < G; ++q)
-          vv[i].x[q] = q < w ? bload<T, kAuxNT>(rv, row * TB, (uint32_t)(c0 + q) * cbytes) : T(0);
+          vv[i].x[q] = q < w ? bload<T>(rv, row * TB, (uint32_t)(c0 + q) * cbytes) : T(0);
       } else {
         vv[i] = gload<T>(rv, row * rowb + cb, 0, w);
       }
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(256) void k_chain_rows(
       if (vcm) {
 #pragma unroll
         for (int q = 0; q < G; ++q)
-          vv.x[q] = q < ww ? bload<T, kAuxNT>(rv, row * TB, (uint32_t)(c0 + q) * cbytes) : T(0);
+          vv.x[q] = q < ww ? bload<T>(rv, row * TB, (uint32_t)(c0 + q) * cbytes) : T(0);
       } else {
         vv = gload<T>(rv, row * rowb + cb, 0, ww);
       }

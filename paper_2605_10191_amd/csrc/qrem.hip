@@ -76,9 +76,9 @@ __global__ __launch_bounds__(kQremThreads) void k_qrem_step(
           s1 += g1;
         }
         T e0, e1, v0 = T(0), v1 = T(0), c0 = T(0), c1 = T(0);
-        bload2<T, kAuxNT>(rE, vo, toff, e0, e1);
-        if (v) bload2<T, kAuxNT>(rv, vo, toff, v0, v1);
-        if (b2) bload2<T, kAuxNT>(rb2, vo, toff, c0, c1);
+        bload2<T>(rE, vo, toff, e0, e1);
+        if (v) bload2<T>(rv, vo, toff, v0, v1);
+        if (b2) bload2<T>(rb2, vo, toff, c0, c1);
         const T h0 = e0 * x[j][0] - gamma * s0, h1 = e1 * x[j][1] - gamma * s1;
         const T o0 = a * v0 + sigma * h0 + tau * x[j][0] - c0;
         const T o1 = a * v1 + sigma * h1 + tau * x[j][1] - c1;
@@ -130,7 +130,7 @@ __global__ __launch_bounds__(kQremThreads) void k_qrem_step_multi(
       if (q < NP) {
         const uint32_t vo = (uint32_t)(2 * q) * W;
         T e0, e1;
-        bload2<T, kAuxNT>(rE, vo, toff, e0, e1);
+        bload2<T>(rE, vo, toff, e0, e1);
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
           const rsrc_t rb1 = make_rsrc(b1 + (size_t)c * D, vbytes);
@@ -151,8 +151,8 @@ __global__ __launch_bounds__(kQremThreads) void k_qrem_step_multi(
             s1 += g1;
           }
           T v0 = T(0), v1 = T(0), c0 = T(0), c1 = T(0);
-          if (v) bload2<T, kAuxNT>(make_rsrc(v + (size_t)c * D, vbytes), vo, toff, v0, v1);
-          if (b2) bload2<T, kAuxNT>(make_rsrc(b2 + (size_t)c * D, vbytes), vo, toff, c0, c1);
+          if (v) bload2<T>(make_rsrc(v + (size_t)c * D, vbytes), vo, toff, v0, v1);
+          if (b2) bload2<T>(make_rsrc(b2 + (size_t)c * D, vbytes), vo, toff, c0, c1);
           const T h0 = e0 * x[c][j][0] - gamma * s0, h1 = e1 * x[c][j][1] - gamma * s1;
           const T o0 = a * v0 + sigma * h0 + tau * x[c][j][0] - c0;
           const T o1 = a * v1 + sigma * h1 + tau * x[c][j][1] - c1;
