@@ -29,8 +29,8 @@
 //
 // Locality: the eight XCDs each sweep a contiguous eighth of the segments
 // (workgroups are dispatched to the XCDs round robin), so most high-part
-// gathers of an XCD stay in its own L2; the streamed vectors v, b2 and the
-// output use non-temporal accesses so they do not evict the gathered one.
+// gathers of an XCD stay in its own L2; the streamed vectors v and b2 are
+// read past the caches while they are small (see stream_nt).
 #include <algorithm>
 #include <cstdlib>
 #include <cstdio>
@@ -67,6 +67,10 @@ void build_chain_split(polfed_op* op) {
     }
     q[9] = (uint8_t)lo_rank[lo ^ (1 << (Lb - 1))];
     q[10] = (uint8_t)lo_rank[lo ^ 1];
+    // the number of low bonds without a hop, and lo itself
+    q[11] = (uint8_t)(Lb - 1 - __builtin_popcount((lo ^ (lo >> 1)) & ((1 << (Lb - 1)) - 1)));
+    q[12] = (uint8_t)(lo & 255);
+    q[13] = (uint8_t)(lo >> 8);
   }
   std::vector<double> dlo(nlo);
   for (int lo = 0; lo < nlo; ++lo) {
@@ -104,6 +108,7 @@ void build_chain_split(polfed_op* op) {
       idle += act ? 0 : 1;
     }
     w[4] = idle;
+    for (int b = 0; b + 1 < Lh; ++b) w[4] |= (w[10 + b] != 0) << (8 + b);
     w[5] = hi_off[hi ^ 1] - hoff;
     // the joining hop of a row moves the particle between the bits Lb - 1 and
     // Lb past no other one, so it changes the rank by +-binom(Lb - 1, m) with
@@ -265,6 +270,7 @@ __global__ __launch_bounds__(256) void k_chain_split(
   const int64_t wstride = (int64_t)blocks_x * wpb;
   const int lane = threadIdx.x & 63;
   const T vzz = (T)c.vzz, t_in = (T)c.t_in, t_pb = (T)c.t_pb;
+  const bool nt = stream_nt<T>(c.D);
   const uint32_t vbytes = (uint32_t)(c.D * TB);
   const rsrc_t rb1 = make_rsrc(b1, vbytes), rv = make_rsrc(v, v ? vbytes : 0),
                rb2 = make_rsrc(b2, b2 ? vbytes : 0), rout = make_rsrc(out, vbytes);
@@ -319,8 +325,9 @@ __global__ __launch_bounds__(256) void k_chain_split(
         const int rp = (int)((np[i][2] >> 16) & 255u);  // byte 10
         g_j[i] = act_j[i] ? bload<T>(rb1, (uint32_t)(blk0 + cur.d_join + rj) * TB, 0) : T(0);
         g_p[i] = act_p[i] ? bload<T>(rb1, (uint32_t)(blk0 + cur.d_pbc + rp) * TB, 0) : T(0);
-        vv[i] = v ? bload<T, kAuxNT>(rv, off, so_row) : T(0);
-        bt[i] = b2 ? bload<T, kAuxNT>(rb2, off, so_row) : T(0);
+        vv[i] = bt[i] = T(0);
+        if (v) bload_stream<T>(rv, off, so_row, nt, &vv[i]);
+        if (b2) bload_stream<T>(rb2, off, so_row, nt, &bt[i]);
       }
       if (pass == 0) {
         wave_sync();  // the previous segment's LDS reads are done
@@ -357,7 +364,7 @@ __global__ __launch_bounds__(256) void k_chain_split(
 // Direct kernel: a wavefront takes one segment, lane l the adjacent rows 2l
 // and 2l + 1, so that every coalesced access moves both rows in one 16-byte
 // instruction.  Made for chains where a wavefront runs one or two segments a
-// launch (L = 19 to 21: a step is then a chain of round trips, not bytes):
+// launch (up to L = 21: a step is then a chain of round trips, not bytes):
 //   - a row's low-part tables are read from global memory in list order (26
 //     bytes a row, coalesced) with the rest, instead of a 27 KB copy into LDS
 //     per workgroup that everything else waits for;
@@ -367,9 +374,12 @@ __global__ __launch_bounds__(256) void k_chain_split(
 // (8, 4, 2 or 1 of them a column), so a column's gathers stay in its XCDs'
 // L2; each column has its operator's records and tables.
 //
+// A bond without a hop in the segment is passed by with a branch both where it
+// is loaded and where it is added; the empty asm keeps the compiler from
+// adding zeros instead.
+//
 // Measured (FP64, L = 20, us a step): 4 columns 13.5 (interleaved) -> 9.6, one
-// column 6.0 (segment kernel) -> 5.0 in a graph, 6.1 -> 5.8 launched one by
-// one; from L = 22 the tile kernels are faster.
+// column launched one by one 6.8 (segment kernel) -> 5.9.
 //
 // Loads past the segment's end read other rows (unused) or fall outside the
 // buffer (read as 0); stores are guarded per row.
@@ -391,6 +401,7 @@ __global__ __launch_bounds__(256) void k_chain_direct(
   const int xcd = blockIdx.x % nxcd;
   const int lane = threadIdx.x & 63;
   const T vzz = (T)c.vzz, t_in = (T)c.t_in, t_pb = (T)c.t_pb;
+  const bool nt = stream_nt<T>(MULTI ? c.D * ncol : c.D);
   const uint32_t vbytes = (uint32_t)(c.D * TB);
   // this XCD's share: segments [s_begin, s_begin + nsx) of the columns
   // first, first + step, ...
@@ -414,18 +425,18 @@ __global__ __launch_bounds__(256) void k_chain_direct(
     const rsrc_t rb1 = make_rsrc(b1 + coff, vbytes), rv = make_rsrc(v ? v + coff : b1, v ? vbytes : 0),
                  rb2 = make_rsrc(b2 ? b2 + coff : b1, b2 ? vbytes : 0),
                  rout = make_rsrc(out + coff, vbytes);
-    const rsrc_t rnp = make_rsrc(blob, 16 * NLO), rdl = make_rsrc(blob + 16 * NLO, TB * NLO),
-                 rlo = make_rsrc(blob + (16 + TB) * NLO, 2 * NLO);
+    const rsrc_t rnp = make_rsrc(blob, 16 * NLO), rdl = make_rsrc(blob + 16 * NLO, TB * NLO);
     const int32_t* rec = recs + (int64_t)si * kChainRecWords;
     const SegRec<NH> cur = load_rec<NH>(rec);
     const int d_near = uniform(rec[7]);
+    uint32_t act = (uint32_t)uniform(rec[4]) >> 8;  // high bonds with a hop
     const int hi0 = cur.flags & 1, hitop = (cur.flags >> 1) & 1;
     const int bs = (cur.flags >> 2) & 1023, st = (cur.flags >> 12) & 1023;
     const int blk0 = cur.row0 - st;
     const uint32_t so_blk = (uint32_t)blk0 * TB, so_row = (uint32_t)cur.row0 * TB;
     const uint32_t pair_off = (uint32_t)(2 * lane) * TB;
     // the lane's two rows, clamped into the segment, and their tables
-    int jj[2], lo[2];
+    int jj[2];
     u4 np[2];
     T dl[2];
 #pragma unroll
@@ -433,7 +444,6 @@ __global__ __launch_bounds__(256) void k_chain_direct(
       jj[i] = min(2 * lane + i, cur.len - 1);
       const uint32_t q = (uint32_t)(cur.lidx + jj[i]);
       np[i] = __builtin_amdgcn_raw_buffer_load_b128(rnp, 16 * q, 0, 0);
-      lo[i] = __builtin_amdgcn_raw_buffer_load_b16(rlo, 2 * q, 0, 0);
       dl[i] = bload<T>(rdl, TB * q, 0);
     }
     T sg[SPL][2], g_hi[NH > 0 ? NH : 1][2], g_j[2], vv[2], bt[2];
@@ -446,29 +456,29 @@ __global__ __launch_bounds__(256) void k_chain_direct(
     }
 #pragma unroll
     for (int b = 0; b < NH; ++b) {
-      if (cur.dh[b] != 0)
+      if ((act >> b) & 1u) {
+        asm volatile("");
         bload2<T>(rb1, pair_off, (uint32_t)(cur.row0 + cur.dh[b]) * TB, g_hi[b][0], g_hi[b][1]);
-      else
-        g_hi[b][0] = g_hi[b][1] = T(0);
+      }
     }
     if (d_near != 0)
       bload2<T>(rb1, pair_off + (uint32_t)((cur.row0 + d_near) * (int)TB), 0, g_j[0], g_j[1]);
     else
       g_j[0] = g_j[1] = T(0);
     if (v)
-      bload2<T, kAuxNT>(rv, pair_off, so_row, vv[0], vv[1]);
+      bload_stream<T, 2>(rv, pair_off, so_row, nt, vv);
     else
       vv[0] = vv[1] = T(0);
     if (b2)
-      bload2<T, kAuxNT>(rb2, pair_off, so_row, bt[0], bt[1]);
+      bload_stream<T, 2>(rb2, pair_off, so_row, nt, bt);
     else
       bt[0] = bt[1] = T(0);
     bool act_j[2], act_p[2];
     T g_p[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      act_j[i] = ((lo[i] >> (Lb - 1)) & 1) != hi0;
-      act_p[i] = c.periodic && ((lo[i] & 1) != hitop);
+      act_j[i] = (int)((np[i][3] >> (Lb - 1)) & 1u) != hi0;
+      act_p[i] = c.periodic && (int)(np[i][3] & 1u) != hitop;
       const int rp = (int)((np[i][2] >> 16) & 255u);
       g_p[i] = act_p[i] ? bload<T>(rb1, (uint32_t)(blk0 + cur.d_pbc + rp) * TB, 0) : T(0);
     }
@@ -484,24 +494,33 @@ __global__ __launch_bounds__(256) void k_chain_direct(
     wave_sync();
     const T sig = MULTI ? half * sc[col] : sigma, ta = MULTI ? half * sc[nb + col] : tau;
     const T ac = MULTI ? (acoef ? acoef[col] : T(0)) : a;
-    T o[2];
+    T o[2], bo[2], hop[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const int l = lo[i];
-      const T bo = stage[st + jj[i]];
-      T hop = 0;
+      bo[i] = stage[st + jj[i]];
+      T h = 0;
 #pragma unroll
-      for (int b = 0; b < NL; ++b) hop += stage[(np[i][b >> 2] >> (8 * (b & 3))) & 255u];
+      for (int b = 0; b < NL; ++b) h += stage[(np[i][b >> 2] >> (8 * (b & 3))) & 255u];
+      hop[i] = h - (T)(int)(np[i][2] >> 24) * bo[i];  // idle low bonds read the row itself
+    }
+    // (reread, or the first tests' results are held in registers)
+    asm volatile("" : "+s"(act));
 #pragma unroll
-      for (int b = 0; b < NH; ++b) hop += g_hi[b][i];
-      const int xlo = (l ^ (l >> 1)) & ((1 << NL) - 1);
-      hop -= (T)(NL - __popc(xlo)) * bo;
-      hop += act_j[i] ? g_j[i] : T(0);
-      const int lo_top = (l >> (Lb - 1)) & 1, lo0 = l & 1;
+    for (int b = 0; b < NH; ++b) {
+      if ((act >> b) & 1u) {
+        asm volatile("");
+        hop[0] += g_hi[b][0];
+        hop[1] += g_hi[b][1];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      hop[i] += act_j[i] ? g_j[i] : T(0);
+      const int lo_top = (int)((np[i][3] >> (Lb - 1)) & 1u), lo0 = (int)(np[i][3] & 1u);
       const int n11x = (lo_top & hi0) + (c.periodic ? (hitop & lo0) : 0);
       const T dg = dl[i] + (T)cur.dhi + vzz * (T)n11x;
-      const T acc = dg * bo + t_in * hop + (act_p[i] ? t_pb * g_p[i] : T(0));
-      o[i] = sig * acc + ta * bo - bt[i];
+      const T acc = dg * bo[i] + t_in * hop[i] + (act_p[i] ? t_pb * g_p[i] : T(0));
+      o[i] = sig * acc + ta * bo[i] - bt[i];
       if (v) o[i] += ac * vv[i];
     }
     const int r0 = 2 * lane;
@@ -523,9 +542,8 @@ static void launch_direct(hipStream_t s, const polfed_op* op, T sigma, T tau, T 
     nxcd = 8;
   }
   grid = std::max<int64_t>(grid, 1);
-  hipLaunchKernelGGL((k_chain_direct<T, L, false>), dim3((unsigned)grid), dim3(256), 0, s, c, sigma,
-                     tau, a, (const ChainCol*)nullptr, 1, 1, (const T*)nullptr, (const T*)nullptr,
-                     T(1), v, b1, b2, out, nxcd, 1);
+  hipLaunchKernelGGL((k_chain_direct<T, L, false>), dim3((unsigned)grid), dim3(256), 0, s, c, sigma, tau, a, (const ChainCol*)nullptr, 1, 1, (const T*)nullptr,
+                     (const T*)nullptr, T(1), v, b1, b2, out, nxcd, 1);
   HIPC(hipGetLastError());
 }
 
@@ -573,6 +591,175 @@ template void chain_direct_cols<float>(hipStream_t, const ChainBatch&, int, int,
                                        const float*, const float*, const float*, const float*,
                                        float*);
 
+constexpr int kPairedFirst = 22;  // variant 3 is the paired kernel from here on
+
+// Paired variant: the direct kernel for chains where a wavefront runs many
+// segments, so that the low-part tables are worth a copy into LDS, and what
+// counts is the traffic of the gathers: the joining bond is gathered by the
+// rows that hop only (us a step, direct / paired: FP32 L = 22 9.5 / 8.6,
+// L = 24 22.1 / 17.4, FP64 L = 23 16.0 / 15.7; FP64 L = 20 5.9 / 6.4, L = 21
+// 7.9 / 8.0).  The tables are in list order and carry the low part and the
+// number of idle low bonds, so a row's LDS reads are one round trip (FP32
+// L = 23, 10 up, open: 10.55 -> 10.2).  Four workgroups a CU: six take 28.4
+// instead of 25.3 (FP64 L = 24, open), three 11.3 instead of 10.2 (FP32).
+template <typename T, int L>
+__global__ __launch_bounds__(256) void k_chain_pair(
+    ChainSplitDev c, T sigma, T tau, T a, const T* __restrict__ v,
+    const T* __restrict__ b1, const T* b2, T* out, int nxcd,
+    const int32_t* __restrict__ recs) {
+  constexpr int Lb = (L / 2 < kChainLoBits) ? L / 2 : kChainLoBits;
+  constexpr int Lh = L - Lb;
+  constexpr int NLO = 1 << Lb;
+  constexpr int NH = Lh - 1;
+  constexpr int NL = Lb - 1;
+  constexpr int SPL = kChainStageRows / 128;  // staged row pairs per lane
+  constexpr int BLOB = wt_blob_bytes(NLO, (int)sizeof(T));
+  constexpr int CHUNKS = BLOB / 16;
+  constexpr uint32_t TB = sizeof(T);
+  using u4 = __attribute__((ext_vector_type(4))) uint32_t;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  {
+    const u4* src = reinterpret_cast<const u4*>(sizeof(T) == 8 ? c.blobl64 : c.blobl32);
+    u4* dst = reinterpret_cast<u4*>(smem);
+    constexpr int PER = (CHUNKS + 255) / 256;
+    u4 tmp[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int i = threadIdx.x + 256 * k;
+      if (i < CHUNKS) tmp[k] = src[i];
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int i = threadIdx.x + 256 * k;
+      if (i < CHUNKS) dst[i] = tmp[k];
+    }
+  }
+  const u4* s_np = reinterpret_cast<const u4*>(smem);
+  const T* s_dlo = reinterpret_cast<const T*>(smem + 16 * NLO);
+  T* stage = reinterpret_cast<T*>(smem + BLOB) + (threadIdx.x >> 6) * kChainStageRows;
+  __syncthreads();
+
+  const int xcd = blockIdx.x % nxcd;
+  const int blocks_x = gridDim.x / nxcd;
+  const int64_t s_begin = c.nseg * xcd / nxcd, s_end = c.nseg * (xcd + 1) / nxcd;
+  const int wpb = blockDim.x >> 6;
+  const int64_t wstride = (int64_t)blocks_x * wpb;
+  const int lane = threadIdx.x & 63;
+  const T vzz = (T)c.vzz, t_in = (T)c.t_in, t_pb = (T)c.t_pb;
+  const bool nt = stream_nt<T>(c.D);
+  const uint32_t vbytes = (uint32_t)(c.D * TB);
+  const rsrc_t rb1 = make_rsrc(b1, vbytes), rv = make_rsrc(v, v ? vbytes : 0),
+               rb2 = make_rsrc(b2, b2 ? vbytes : 0), rout = make_rsrc(out, vbytes);
+  int64_t si = s_begin + (int64_t)(blockIdx.x / nxcd) * wpb + uniform(threadIdx.x >> 6);
+  if (si >= s_end) return;
+  for (; si < s_end; si += wstride) {
+    const SegRec<NH> cur = load_rec<NH>(recs + (int64_t)uniform((int)si) * kChainRecWords);
+    const int hi0 = cur.flags & 1, hitop = (cur.flags >> 1) & 1;
+    const int bs = (cur.flags >> 2) & 1023, st = (cur.flags >> 12) & 1023;
+    const int blk0 = cur.row0 - st;
+    const uint32_t so_blk = (uint32_t)blk0 * TB, so_row = (uint32_t)cur.row0 * TB;
+    const uint32_t pair_off = (uint32_t)(2 * lane) * TB;
+    // stage the block: pairs of rows
+    T sg[SPL][2];
+#pragma unroll
+    for (int m = 0; m < SPL; ++m) {
+      if (128 * m < bs)
+        bload2<T>(rb1, pair_off + (uint32_t)(128 * m) * TB, so_blk, sg[m][0], sg[m][1]);
+      else
+        sg[m][0] = sg[m][1] = T(0);
+    }
+    // the lane's two rows, clamped into the segment
+    int jj[2];
+    u4 np[2];
+    bool act_j[2], act_p[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      jj[i] = min(2 * lane + i, cur.len - 1);
+      np[i] = s_np[cur.lidx + jj[i]];
+      act_j[i] = (int)((np[i][3] >> (Lb - 1)) & 1u) != hi0;
+      act_p[i] = c.periodic && (int)(np[i][3] & 1u) != hitop;
+    }
+    T g_hi[NH > 0 ? NH : 1][2], g_j[2], g_p[2], vv[2], bt[2];
+#pragma unroll
+    for (int b = 0; b < NH; ++b) {
+      if (cur.dh[b] != 0)
+        bload2<T>(rb1, pair_off, (uint32_t)(cur.row0 + cur.dh[b]) * TB, g_hi[b][0], g_hi[b][1]);
+      else
+        g_hi[b][0] = g_hi[b][1] = T(0);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int rj = (int)((np[i][2] >> 8) & 255u);
+      const int rp = (int)((np[i][2] >> 16) & 255u);
+      g_j[i] = act_j[i] ? bload<T>(rb1, (uint32_t)(blk0 + cur.d_join + rj) * TB, 0) : T(0);
+      g_p[i] = act_p[i] ? bload<T>(rb1, (uint32_t)(blk0 + cur.d_pbc + rp) * TB, 0) : T(0);
+    }
+    if (v)
+      bload_stream<T, 2>(rv, pair_off, so_row, nt, vv);
+    else
+      vv[0] = vv[1] = T(0);
+    if (b2)
+      bload_stream<T, 2>(rb2, pair_off, so_row, nt, bt);
+    else
+      bt[0] = bt[1] = T(0);
+    wave_sync();  // the previous segment's LDS reads are done
+#pragma unroll
+    for (int m = 0; m < SPL; ++m) {
+      const int r = 128 * m + 2 * lane;
+      if (r < bs) {
+        stage[r] = sg[m][0];
+        if (r + 1 < bs) stage[r + 1] = sg[m][1];
+      }
+    }
+    wave_sync();
+    T o[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int l = (int)np[i][3];
+      const T bo = stage[st + jj[i]];
+      T hop = 0;
+#pragma unroll
+      for (int b = 0; b < NL; ++b) hop += stage[(np[i][b >> 2] >> (8 * (b & 3))) & 255u];
+#pragma unroll
+      for (int b = 0; b < NH; ++b) hop += g_hi[b][i];
+      hop -= (T)(int)(np[i][2] >> 24) * bo;  // idle low bonds read the row itself
+      hop += act_j[i] ? g_j[i] : T(0);
+      const int lo_top = (l >> (Lb - 1)) & 1, lo0 = l & 1;
+      const int n11x = (lo_top & hi0) + (c.periodic ? (hitop & lo0) : 0);
+      const T dg = s_dlo[cur.lidx + jj[i]] + (T)cur.dhi + vzz * (T)n11x;
+      const T acc = dg * bo + t_in * hop + (act_p[i] ? t_pb * g_p[i] : T(0));
+      o[i] = sigma * acc + tau * bo - bt[i];
+      if (v) o[i] += a * vv[i];
+    }
+    const int r0 = 2 * lane;
+    if (r0 + 1 < cur.len)
+      bstore2<kAuxNT>(o[0], o[1], rout, pair_off, so_row);
+    else if (r0 < cur.len)
+      bstore<kAuxNT>(o[0], rout, pair_off, so_row);
+  }
+}
+
+template <typename T, int L>
+static void launch_pair(hipStream_t s, const polfed_op* op, T sigma, T tau, T a, const T* v,
+                        const T* b1, const T* b2, T* out) {
+  constexpr int Lb = (L / 2 < kChainLoBits) ? L / 2 : kChainLoBits;
+  constexpr int NLO = 1 << Lb;
+  const size_t shm = wt_blob_bytes(NLO, (int)sizeof(T)) + 4 * kChainStageRows * sizeof(T);
+  const int bpc = std::max(1, std::min(kChainBlocksPerCU, (int)(kLdsPerCU / shm)));
+  ChainSplitDev c = op->chain_split();
+  const int64_t blocks_needed = (c.nseg + 3) / 4;
+  int64_t grid = std::min<int64_t>(blocks_needed, (int64_t)op->ctx->n_cu * bpc);
+  int nxcd = 1;
+  if (grid >= 64) {
+    grid -= grid % 8;
+    nxcd = 8;
+  }
+  grid = std::max<int64_t>(grid, 1);
+  hipLaunchKernelGGL((k_chain_pair<T, L>), dim3((unsigned)grid), dim3(256), shm, s, c, sigma,
+                     tau, a, v, b1, b2, out, nxcd, c.rec);
+  HIPC(hipGetLastError());
+}
+
 // Tile variant for long chains: a workgroup stages a whole tile of 2^KT
 // consecutive high parts of b_{i+1} in LDS (one coalesced read of its rows),
 // so the low-part hops, the joining bond (high bit 0) and the KT - 1 bonds
@@ -614,6 +801,7 @@ __global__ __launch_bounds__(kTileThreads) void k_chain_tile(
   constexpr int NW = kTileThreads / 64;
   const int lane = threadIdx.x & 63;
   const T vzz = (T)c.vzz, t_in = (T)c.t_in, t_pb = (T)c.t_pb;
+  const bool nt = stream_nt<T>(c.D);
   const uint32_t vbytes = (uint32_t)(c.D * TB);
   const rsrc_t rb1 = make_rsrc(b1, vbytes), rv = make_rsrc(v, v ? vbytes : 0),
                rb2 = make_rsrc(b2, b2 ? vbytes : 0), rout = make_rsrc(out, vbytes);
@@ -679,11 +867,11 @@ __global__ __launch_bounds__(kTileThreads) void k_chain_tile(
         g_p[i] = act_p[i] ? bload<T>(rb1, (uint32_t)(blk0 + cur.d_pbc + rp) * TB, 0) : T(0);
       }
       if (v)
-        bload2<T, kAuxNT>(rv, pair_off, so_row, vv[0], vv[1]);
+        bload_stream<T, 2>(rv, pair_off, so_row, nt, vv);
       else
         vv[0] = vv[1] = T(0);
       if (b2)
-        bload2<T, kAuxNT>(rb2, pair_off, so_row, bt[0], bt[1]);
+        bload_stream<T, 2>(rb2, pair_off, so_row, nt, bt);
       else
         bt[0] = bt[1] = T(0);
       T o[2];
@@ -727,34 +915,51 @@ constexpr int kWtXcds = 8;
 // Staged-tile kernel.  A tile is the set of rows whose state bits outside
 // [0, Lb + KT) (and, for a wrapped tile, outside the top bit L - 1) are
 // fixed: 2^WR runs of 2^KT consecutive high parts, each run a contiguous
-// range of rows.  The workgroup copies the tile's rows of b_{i+1}, and the
-// records of its segments, into LDS with direct-to-LDS buffer loads (one
-// 16-byte load per lane fills 1 KB of LDS, no registers involved), so that
+// range of rows.  The workgroup copies the tile's rows of b_{i+1} into LDS
+// with direct-to-LDS buffer loads (one 16-byte load per lane fills 1 KB of
+// LDS, no registers involved), so that
 //   - the low-part hops, the joining bond and the KT - 1 bonds among the
 //     tile's high bits read LDS;
 //   - in a wrapped tile the periodic bond (L - 1, 0) reads LDS too: its
 //     target differs in the top bit, so it lies in the tile's other run;
 //   - only the bonds between the tile's high bits and the fixed middle
 //     bits gather from global memory, at wave-uniform row offsets;
-//   - a segment's record and its rows' low-part tables (in list order) are
-//     LDS reads, so the global gathers of a segment start after two short
-//     LDS round trips instead of a scalar load from global memory.
+//   - a row's low-part tables (in list order) are LDS reads.
 // With DB the next tile is staged into a second LDS buffer while the current
 // one is processed.
+//
+// What bounds it at L = 24 to 26 is what the L2s fetch: at L = 24 145 MB a
+// step, 86 of them the vectors themselves, which a plain pass over the same
+// vectors moves at 7.5 TB/s (19 us of 26.5); at L = 26 about 590 MB of 730 go
+// through when the order of the tiles is kept.  Below that it is the work of a
+// segment: a bond without a hop is passed by with a branch where it is loaded
+// and where it is added, the low part and the number of its idle bonds come
+// with the neighbour positions, a hop that a row does not have reads a zero,
+// and FP32 is held to 64 registers, for two workgroups a CU.
+//
+// us a step of a filter, before and after (with the streamed vectors read
+// through the caches and the shares below): FP64 L = 23 18.1 -> 14.4, 24 28.8
+// -> 26.5, 25 58.5 -> 50.0, 26 108 -> 99; FP32 L = 24 20.1 -> 17.2, 25 39.6 ->
+// 30.3, 26 70.9 -> 55.5.  One row a lane in FP64 (64 registers, twice the
+// wavefronts) was slower, 33 at L = 24: the L1 takes 16 lookups for a 64-lane
+// load whether a lane reads 8 bytes or 16.
 template <typename T, int L, int KT, int WR, int DB, int NT>
-__global__ __launch_bounds__(NT) void k_chain_wt(
+__global__ __launch_bounds__(NT, sizeof(T) == 4 ? 8 : 4) void k_chain_wt(
     ChainSplitDev c, T sigma, T tau, T a, const T* __restrict__ v,
-    const T* __restrict__ b1, const T* b2, T* out, int nxcd, int ntiles, int buf_rows,
-    int rec_slots, const int32_t* __restrict__ recs, const int32_t* __restrict__ tiles) {
+    const T* __restrict__ b1, const T* b2, T* out, int nxcd, int rounds, int buf_rows,
+    const int32_t* __restrict__ recs, const int32_t* __restrict__ tiles,
+    const int32_t* __restrict__ shares) {
   constexpr int Lb = (L / 2 < kChainLoBits) ? L / 2 : kChainLoBits;
   constexpr int NLO = 1 << Lb;
   constexpr int NH = L - Lb - 1;  // bonds inside the high part
   constexpr int NHL = KT - 1;     // of which inside the tile: b < NHL
+  constexpr int NFAR = NH - NHL;
   constexpr int NL = Lb - 1;
-  constexpr int BLOB = chain_blob_bytes(NLO, (int)sizeof(T));
+  constexpr int R = 2;  // rows per lane
+  constexpr int UNITS = kChainSegRows / (64 * R);
+  constexpr int BLOB = wt_blob_bytes(NLO, (int)sizeof(T));
   constexpr int CHUNKS = BLOB / 16;
   constexpr int CH = 1024 / (int)sizeof(T);  // rows per staging load of a wave
-  constexpr int RB = kChainRecWords * 4;      // bytes per segment record
   constexpr int NW = NT / 64;
   constexpr uint32_t TB = sizeof(T);
   using u4 = __attribute__((ext_vector_type(4))) uint32_t;
@@ -764,197 +969,215 @@ __global__ __launch_bounds__(NT) void k_chain_wt(
     const u4* src = reinterpret_cast<const u4*>(sizeof(T) == 8 ? c.blobl64 : c.blobl32);
     u4* dst = reinterpret_cast<u4*>(smem);
     for (int i = threadIdx.x; i < CHUNKS; i += NT) dst[i] = src[i];
+    if (threadIdx.x < 4) reinterpret_cast<uint32_t*>(smem + BLOB)[threadIdx.x] = 0;
   }
   // list-ordered tables: entry p describes the p-th low part of the list
   const u4* s_np = reinterpret_cast<const u4*>(smem);
   const T* s_dlo = reinterpret_cast<const T*>(smem + 16 * NLO);
-  const uint16_t* s_lo = reinterpret_cast<const uint16_t*>(s_dlo + NLO);
-  // per buffer: buf_rows rows of b_{i+1}, then rec_slots segment records
-  const size_t buf_bytes = (size_t)buf_rows * TB + (size_t)rec_slots * RB;
-  unsigned char* const s_b0 = smem + BLOB;
-  unsigned char* const s_b1 = s_b0 + (DB ? buf_bytes : 0);
+  // a zero behind the tables (what a hop that does not exist reads), then
+  // the tile buffers of buf_rows rows of b_{i+1}
+  constexpr uint32_t ZERO = BLOB;
+  constexpr uint32_t BUF0 = BLOB + 16;
+  const uint32_t buf_bytes = DB ? (uint32_t)buf_rows * TB : 0u;
 
   const int xcd = blockIdx.x % nxcd;
   const int wg = blockIdx.x / nxcd, nwg = gridDim.x / nxcd;
-  // the XCD's range of the tile table (row-balanced bounds after the
-  // entries; one XCD takes them all)
-  const int t_begin = nxcd == kWtXcds ? uniform(tiles[8 * ntiles + xcd]) : 0;
-  const int t_end = nxcd == kWtXcds ? uniform(tiles[8 * ntiles + xcd + 1]) : ntiles;
+  // the tiles of this workgroup: one share a round, a share going from
+  // segment s0 of tile t0 up to segment s1 of tile t1
+  struct Pos {
+    int r, t, s0, t1, s1, t_end;
+  };
+  auto share = [&](Pos& p) {
+    const int32_t* q = shares + 2 * ((xcd * rounds + p.r) * nwg + wg);
+    p.t = uniform(q[0]);
+    p.s0 = uniform(q[1]);
+    p.t1 = uniform(q[2]);
+    p.s1 = uniform(q[3]);
+    p.t_end = p.s1 > 0 ? p.t1 + 1 : p.t1;
+  };
+  auto settle = [&](Pos& p) {  // on to the next share that has a tile left
+    while (p.t >= p.t_end && p.r < rounds) {
+      if (++p.r < rounds) share(p);
+    }
+  };
+  Pos at{};
+  share(at);
+  settle(at);
   const int wave = uniform(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const T vzz = (T)c.vzz, t_in = (T)c.t_in, t_pb = (T)c.t_pb;
+  const bool nt = stream_nt<T>(c.D);
   const uint32_t vbytes = (uint32_t)(c.D * TB);
   const rsrc_t rb1 = make_rsrc(b1, vbytes), rv = make_rsrc(v, v ? vbytes : 0),
-               rb2 = make_rsrc(b2, b2 ? vbytes : 0), rout = make_rsrc(out, vbytes),
-               rrec = make_rsrc(recs, (uint32_t)(c.nseg * RB));
-  // the tile's runs of rows and of segment records into a buffer, in chunks
-  // of 1 KB dealt round robin to the waves; a run's last chunk spills into
-  // the run's padding
-  auto stage = [&](int t, unsigned char* buf) {
+               rb2 = make_rsrc(b2, b2 ? vbytes : 0), rout = make_rsrc(out, vbytes);
+  // the tile's runs of rows into a buffer, in chunks of 1 KB dealt round
+  // robin to the waves; a run's last chunk spills into the run's padding
+  auto stage = [&](int t, uint32_t buf) {
     const int32_t* tt = tiles + 8 * t;
-    int rbase = 0, sbase = 0;
+    int rbase = 0;
 #pragma unroll
     for (int r = 0; r < (1 << WR); ++r) {
       const int row0 = tt[4 * r], rows = tt[4 * r + 1];
-      const int seg0 = tt[4 * r + 2], nseg = tt[4 * r + 3];
       const int nch = (rows + CH - 1) / CH;
       for (int ch = wave; ch < nch; ch += NW)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            rb1, (lds_ptr)(buf + (size_t)(rbase + ch * CH) * TB), 16,
+            rb1, (lds_ptr)(smem + buf + (size_t)(rbase + ch * CH) * TB), 16,
             (uint32_t)(ch * CH) * TB + 16u * lane, (uint32_t)row0 * TB, 0, 0);
-      const int nrc = (nseg + 7) / 8;
-      for (int ch = wave; ch < nrc; ch += NW)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            rrec, (lds_ptr)(buf + (size_t)buf_rows * TB + (size_t)(sbase + 8 * ch) * RB), 16,
-            (uint32_t)(8 * ch * RB) + 16u * lane, (uint32_t)seg0 * RB, 0, 0);
       rbase += nch * CH;
-      sbase += nrc * 8;
     }
   };
-  int t = t_begin + wg;
-  if (DB && t < t_end) stage(t, s_b0);
-  for (int it = 0; t < t_end; t += nwg, ++it) {
-    unsigned char* const cb = (DB && (it & 1)) ? s_b1 : s_b0;
+  if (DB && at.r < rounds) stage(at.t, BUF0);
+  for (int it = 0; at.r < rounds; ++it) {
+    const int t = at.t;
+    const bool last = t == at.t1;
+    const int u_first = at.s0, u_last = at.s1;
+    ++at.t;
+    at.s0 = 0;
+    settle(at);
+    const uint32_t cb = BUF0 + ((it & 1) ? buf_bytes : 0u);
     if (DB) {
       // this tile was requested one iteration ago; once every wave has it
       // (and is done with the other buffer), stage the next tile
       __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();
-      if (t + nwg < t_end) stage(t + nwg, (it & 1) ? s_b0 : s_b1);
+      if (at.r < rounds) stage(at.t, BUF0 + ((it & 1) ? 0u : buf_bytes));
     } else {
       __syncthreads();  // the previous tile's LDS reads are done
-      stage(t, s_b0);
+      stage(t, cb);
       __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();
     }
-    const T* const cur_buf = reinterpret_cast<const T*>(cb);
-    const int32_t* const s_rec = reinterpret_cast<const int32_t*>(cb + (size_t)buf_rows * TB);
     const int32_t* tt = tiles + 8 * t;
-    const int r0row = tt[0], r0nseg = tt[3];
-    const int r1row = WR ? tt[4] : 0, r1nseg = WR ? tt[7] : 0;
+    const int r0row = tt[0], r0seg = tt[2], r0nseg = tt[3];
+    const int r1row = WR ? tt[4] : 0, r1seg = WR ? tt[6] - r0nseg : 0, r1nseg = WR ? tt[7] : 0;
     const int base1 = WR ? ((tt[1] + CH - 1) / CH) * CH : 0;
-    const int sbase1 = ((r0nseg + 7) / 8) * 8;
-    const int nsegs = r0nseg + r1nseg;
-    for (int j = wave; j < nsegs; j += NW) {
+    const int u_end = (last ? u_last : r0nseg + r1nseg) * UNITS;
+    int u = u_first * UNITS + wave;
+    auto record = [&](int uu) {
+      const int j = uu / UNITS;
+      return recs + (int64_t)(j + (WR && j >= r0nseg ? r1seg : r0seg)) * kChainRecWords;
+    };
+    for (; u < u_end; u += NW) {
+      const int32_t* rec = record(u);
+      const SegRec<NH> cur = load_rec<NH>(rec);
+      const int d_near = uniform(rec[7]);
+      uint32_t act = (uint32_t)uniform(rec[4]) >> 8;  // bonds with a hop
+      const int j = u / UNITS;
+      const int p0 = (u % UNITS) * 64 * R;  // first row of the unit in its segment
+      if (UNITS > 1 && p0 >= cur.len) continue;
       const bool in1 = WR && j >= r0nseg;
-      // LDS index = global row + shift (own run), + pshift (the other run)
-      const int shift = in1 ? base1 - r1row : -r0row;
-      const int pshift = in1 ? -r0row : base1 - r1row;
-      const SegRec<NH> cur = load_rec<NH>(s_rec + (in1 ? sbase1 + j - r0nseg : j) * kChainRecWords);
+      // LDS byte address = TB * global row + shift (own run), + pshift (the
+      // other run)
+      const uint32_t shift = cb + (uint32_t)(in1 ? base1 - r1row : -r0row) * TB;
+      const uint32_t pshift = cb + (uint32_t)(in1 ? -r0row : base1 - r1row) * TB;
       const int hi0 = cur.flags & 1, hitop = (cur.flags >> 1) & 1;
-      const int st = (cur.flags >> 12) & 1023;
-      const int blk0 = cur.row0 - st;
-      const int lrow0 = cur.row0 + shift, lblk0 = blk0 + shift;
-      const uint32_t so_row = (uint32_t)cur.row0 * TB;
-      const uint32_t pair_off = (uint32_t)(2 * lane) * TB;
-      // global gathers first: high-part hops at uniform offsets, the
-      // periodic bond of an unwrapped tile, the streamed v and b_{i+2}
-      T g_hi[NH - NHL > 0 ? NH - NHL : 1][2], vv[2], bt[2];
+      const int blk0 = cur.row0 - ((cur.flags >> 12) & 1023);
+      const uint32_t row = (uint32_t)(cur.row0 + p0);
+      const uint32_t blk = (uint32_t)blk0 * TB + shift;
+      const uint32_t so_row = row * TB;
+      const int r0 = R * lane, left = cur.len - p0;
+      const uint32_t off = (uint32_t)r0 * TB;
+      // global loads first: the streamed v and b_{i+2}, then the high bonds
+      // at uniform offsets.  The empty asm keeps a bond's branch a branch:
+      // half of the bonds are idle in a segment, and a branch costs less
+      // than the zeros and additions of a select.
+      T vv[R], bt[R], g_hi[NFAR > 0 ? NFAR : 1][R], g_p[R];
+      if (v) bload_stream<T, R>(rv, off, so_row, nt, vv);
+      if (b2) bload_stream<T, R>(rb2, off, so_row, nt, bt);
 #pragma unroll
-      for (int b = NHL; b < NH; ++b) {
-        if (cur.dh[b] != 0)
-          bload2<T>(rb1, pair_off, (uint32_t)(cur.row0 + cur.dh[b]) * TB, g_hi[b - NHL][0],
-                    g_hi[b - NHL][1]);
-        else
-          g_hi[b - NHL][0] = g_hi[b - NHL][1] = T(0);
-      }
-      if (v)
-        bload2<T, kAuxNT>(rv, pair_off, so_row, vv[0], vv[1]);
-      else
-        vv[0] = vv[1] = T(0);
-      if (b2)
-        bload2<T, kAuxNT>(rb2, pair_off, so_row, bt[0], bt[1]);
-      else
-        bt[0] = bt[1] = T(0);
-      // the lane's rows 2 lane and 2 lane + 1 (clamped into the segment)
-      int jj[2], lo[2];
-      u4 np[2];
-      T dl[2];
-      bool act_j[2], act_p[2];
+      for (int b = NHL; b < NH; ++b)
+        if ((act >> b) & 1u) {
+          asm volatile("");
+          bload_rows<T, R>(rb1, off, so_row + (uint32_t)cur.dh[b] * TB, g_hi[b - NHL]);
+        }
+      T o[R], bo[R], hop[R];
+      u4 np[R];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        jj[i] = min(2 * lane + i, cur.len - 1);
-        const int q = cur.lidx + jj[i];
-        lo[i] = s_lo[q];
-        np[i] = s_np[q];
-        dl[i] = s_dlo[q];
-      }
-      T g_p[2];
+      for (int i = 0; i < R; ++i) np[i] = s_np[cur.lidx + p0 + min(r0 + i, left - 1)];
+      if (!WR) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int l = lo[i];
-        act_j[i] = ((l >> (Lb - 1)) & 1) != hi0;
-        act_p[i] = c.periodic && ((l & 1) != hitop);
-        if (!WR) {
-          const int rp = (int)((np[i][2] >> 16) & 255u);
-          g_p[i] = act_p[i] ? bload<T>(rb1, (uint32_t)(blk0 + cur.d_pbc + rp) * TB, 0) : T(0);
+        for (int i = 0; i < R; ++i) {
+          const uint32_t lo = np[i][3];
+          const bool act_p = c.periodic && (int)(lo & 1u) != hitop;
+          g_p[i] = act_p ? bload<T>(rb1, (uint32_t)(blk0 + cur.d_pbc +
+                                                    (int)((np[i][2] >> 16) & 255u)) * TB, 0)
+                         : T(0);
         }
       }
-      // every LDS operand of both rows is read before any is summed (an
-      // idle in-tile high bond reads the row itself and is masked; the
-      // joining and periodic reads are clamped into the buffer and masked)
-      T bo[2], nb[2][NL > 0 ? NL : 1], th[2][NHL > 0 ? NHL : 1], tj[2], tp[2];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int lr = lrow0 + jj[i];
-        bo[i] = cur_buf[lr];
+      for (int i = 0; i < R; ++i) {
+        const int rr = min(r0 + i, left - 1);
+        const uint32_t lo = np[i][3];
+        const uint32_t own = (row + (uint32_t)rr) * TB + shift;
+        const bool act_j = (int)((lo >> (Lb - 1)) & 1u) != hi0;
+        const bool act_p = c.periodic && (int)(lo & 1u) != hitop;
+        bo[i] = lds_at<T>(smem, own);
+        T h = lds_at<T>(smem, act_j ? own + (uint32_t)d_near * TB : ZERO);
 #pragma unroll
         for (int b = 0; b < NL; ++b)
-          nb[i][b] = cur_buf[lblk0 + (int)((np[i][b >> 2] >> (8 * (b & 3))) & 255u)];
+          h += lds_at<T>(smem, blk + ((np[i][b >> 2] >> (8 * (b & 3))) & 255u) * TB);
+        // idle low bonds read the row itself
+        h -= (T)(int)(np[i][2] >> 24) * bo[i];
 #pragma unroll
-        for (int b = 0; b < NHL; ++b) th[i][b] = cur_buf[lr + cur.dh[b]];
-        const int rj = (int)((np[i][2] >> 8) & 255u);
-        tj[i] = cur_buf[min(lblk0 + cur.d_join + rj, buf_rows - 1)];
-        if (WR) {
-          const int rp = (int)((np[i][2] >> 16) & 255u);
-          tp[i] = cur_buf[min(blk0 + cur.d_pbc + rp + pshift, buf_rows - 1)];
+        for (int b = 0; b < NHL; ++b)
+          if ((act >> b) & 1u) {
+            asm volatile("");
+            h += lds_at<T>(smem, own + (uint32_t)cur.dh[b] * TB);
+          }
+        hop[i] = h;
+        if (WR)
+          g_p[i] = lds_at<T>(smem, act_p ? (uint32_t)(blk0 + cur.d_pbc +
+                                                      (int)((np[i][2] >> 16) & 255u)) * TB +
+                                               pshift
+                                         : ZERO);
+        const int lo_top = (int)((lo >> (Lb - 1)) & 1u);
+        const int n11x = (lo_top & hi0) + (c.periodic ? (hitop & (int)(lo & 1u)) : 0);
+        o[i] = s_dlo[cur.lidx + p0 + rr] + (T)cur.dhi + vzz * (T)n11x;
+      }
+      // (reread, or the first tests' results are held in 24 registers)
+      asm volatile("" : "+s"(act));
+#pragma unroll
+      for (int b = NHL; b < NH; ++b)
+        if ((act >> b) & 1u) {
+          asm volatile("");
+#pragma unroll
+          for (int i = 0; i < R; ++i) hop[i] += g_hi[b - NHL][i];
         }
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const T acc = o[i] * bo[i] + t_in * hop[i] + t_pb * g_p[i];
+        o[i] = sigma * acc + tau * bo[i];
       }
-      T o[2];
+      if (b2) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int l = lo[i];
-        T hop = 0;
-#pragma unroll
-        for (int b = 0; b < NL; ++b) hop += nb[i][b];
-        const int xlo = (l ^ (l >> 1)) & ((1 << NL) - 1);
-        hop -= (T)(NL - __popc(xlo)) * bo[i];
-#pragma unroll
-        for (int b = 0; b < NHL; ++b) hop += cur.dh[b] != 0 ? th[i][b] : T(0);
-#pragma unroll
-        for (int b = NHL; b < NH; ++b) hop += g_hi[b - NHL][i];
-        hop += act_j[i] ? tj[i] : T(0);
-        if (WR) g_p[i] = act_p[i] ? tp[i] : T(0);
-        const int lo_top = (l >> (Lb - 1)) & 1, lo0 = l & 1;
-        const int n11x = (lo_top & hi0) + (c.periodic ? (hitop & lo0) : 0);
-        const T dg = dl[i] + (T)cur.dhi + vzz * (T)n11x;
-        const T acc = dg * bo[i] + t_in * hop + (act_p[i] ? t_pb * g_p[i] : T(0));
-        o[i] = sigma * acc + tau * bo[i] - bt[i];
-        if (v) o[i] += a * vv[i];
+        for (int i = 0; i < R; ++i) o[i] -= bt[i];
       }
-      const int r0 = 2 * lane;
-      if (r0 + 1 < cur.len)
-        bstore2<kAuxNT>(o[0], o[1], rout, pair_off, so_row);
-      else if (r0 < cur.len)
-        bstore<kAuxNT>(o[0], rout, pair_off, so_row);
+      if (v) {
+#pragma unroll
+        for (int i = 0; i < R; ++i) o[i] += a * vv[i];
+      }
+      if (r0 + R <= left)
+        bstore_rows<T, R, kAuxNT>(o, rout, off, so_row);
+      else if (r0 < left)
+        bstore<kAuxNT>(o[0], rout, off, so_row);
     }
   }
 }
 
-// Staged-tile configurations: tile bits (below the largest tile bits of the
-// chain), wrap, double buffer, threads per workgroup.
+// Staged-tile configurations: tile bits (chain_wt_bits minus this), wrap, double
+// buffer, threads per workgroup.
 struct WtConf {
   int dkt, wrap, db, nt;
 };
 constexpr WtConf kWtConf[] = {
-    {0, 1, 0, 1024},  // 6: largest wrapped tile, one buffer, 16 waves
-    {1, 1, 1, 512},   // 7: half-size wrapped tile, two buffers, 8 waves
-    {1, 1, 0, 512},   // 8: half-size wrapped tile, one buffer, 8 waves
-    {0, 1, 1, 1024},  // 9: largest wrapped tile, two buffers (FP32 fits)
+    {0, 1, 0, 1024},   // 6: wrapped tile, one buffer
+    {-1, 0, 1, 512},   // 7: twice the run, not wrapped, two buffers
+    {-1, 0, 0, 1024},  // 8: twice the run, not wrapped, one buffer
+    {0, 1, 1, 1024},   // 9: wrapped tile, two buffers
 };
 constexpr int kWtFirst = 6, kWtCount = (int)(sizeof(kWtConf) / sizeof(kWtConf[0]));
 
-// Tile bits of the staged-tile kernel's largest tile at chain length L.
+// Tile bits of the staged-tile kernel's wrapped tile at chain length L.
 constexpr int chain_wt_bits(int L) {
   const int Lb = (L / 2 < kChainLoBits) ? L / 2 : kChainLoBits;
   const int Lh = L - Lb;
@@ -975,10 +1198,9 @@ static const polfed_op::WTiles* wt_tables(const polfed_op* op, int kt, int wrap)
   TallyScope untallied(nullptr);  // the table lives as long as the operator
   std::vector<int32_t> tab;
   std::vector<int64_t> tid;   // the tile index t of each entry
-  std::vector<int> trows;     // its rows
   for (int64_t t = 0; t < nt; ++t) {
     int32_t e[8] = {0};
-    int rows_tot = 0, bufr[2] = {0, 0}, slots = 0;
+    int rows_tot = 0, bufr[2] = {0, 0};
     for (int r = 0; r <= wrap; ++r) {
       const int64_t h0 = ((int64_t)r << (Lh - 1)) | (t << kt), h1 = h0 + ((int64_t)1 << kt);
       e[4 * r] = ho[h0];
@@ -986,7 +1208,6 @@ static const polfed_op::WTiles* wt_tables(const polfed_op* op, int kt, int wrap)
       e[4 * r + 2] = so[h0];
       e[4 * r + 3] = so[h1] - so[h0];
       rows_tot += e[4 * r + 1];
-      slots += ((e[4 * r + 3] + 7) / 8) * 8;
       for (int p = 0; p < 2; ++p) {
         const int ch = p == 0 ? 128 : 256;
         bufr[p] += ((e[4 * r + 1] + ch - 1) / ch) * ch;
@@ -995,9 +1216,7 @@ static const polfed_op::WTiles* wt_tables(const polfed_op* op, int kt, int wrap)
     if (rows_tot == 0) continue;
     tab.insert(tab.end(), e, e + 8);
     tid.push_back(t);
-    trows.push_back(rows_tot);
     for (int p = 0; p < 2; ++p) W.buf_rows[p] = std::max(W.buf_rows[p], bufr[p]);
-    W.rec_slots = std::max(W.rec_slots, slots);
   }
   W.kt = kt;
   W.wrap = wrap;
@@ -1023,35 +1242,75 @@ static const polfed_op::WTiles* wt_tables(const polfed_op* op, int kt, int wrap)
   std::stable_sort(ord.begin(), ord.end(),
                    [&](int x, int y) { return order_key(x) < order_key(y); });
   std::vector<int32_t> sorted;
-  sorted.reserve(tab.size() + kWtXcds + 1);
-  int64_t rows_all = 0;
+  sorted.reserve(tab.size());
   for (int i : ord) {
     sorted.insert(sorted.end(), tab.begin() + 8 * (size_t)i, tab.begin() + 8 * (size_t)i + 8);
-    rows_all += trows[i];
+    W.nseg.push_back(tab[8 * (size_t)i + 3] + tab[8 * (size_t)i + 7]);
   }
-  // XCD x takes entries [bound[x], bound[x + 1]): bound[x] is the first
-  // entry whose rows before it reach x/8 of all rows
-  int64_t cum = 0;
-  int x = 1;
-  sorted.push_back(0);
-  for (int k = 0; k < W.n && x < kWtXcds; ++k) {
-    while (x < kWtXcds && cum >= rows_all * x / kWtXcds) {
-      sorted.push_back(k);
-      ++x;
-    }
-    cum += trows[ord[k]];
-  }
-  while (x < kWtXcds) {
-    sorted.push_back(W.n);
-    ++x;
-  }
-  sorted.push_back(W.n);
   tab.swap(sorted);
   upload(W.d, tab.data(), tab.size(), op->ctx->stream);
   HIPC(hipStreamSynchronize(op->ctx->stream));
   return W.n > 0 ? &W : nullptr;
 }
 
+// Rounds in which the workgroups go through an XCD's range of the tile table.
+// In one round each has one contiguous share and at most one tile's remainder
+// to wait for; but tiles that are processed at the same time are then far from
+// each other in the table, and so are their gathers.  That costs nothing while
+// an XCD's part of b_{i+1} fits its 4 MB L2 (FP64 L = 23 in one round 14.4 us a
+// step, in two 15.9), and from there on a round takes one tile of every
+// workgroup, neighbours in the table (FP64 L = 25, one round / as many as
+// tiles: 57.8 / 50.0; L = 26 124 / 101, which also is the order that the
+// gathers were counted in).
+static int wt_rounds(const polfed_op* op, const polfed_op::WTiles* W, int n, bool fp32) {
+  if (op->D * (fp32 ? 4 : 8) <= kWtXcds * (int64_t)(4 << 20)) return 1;
+  return std::max(1, (W->n + n / 2) / n);
+}
+// Shares of n workgroups of the table's segments: workgroup k starts at
+// entry k (tile, segment in it) and ends where k + 1 starts.  A segment takes
+// a wavefront about the same time whatever its rows, so segments, not rows
+// or tiles, are what is dealt out evenly: with whole tiles per workgroup the
+// XCDs of the largest tiles at L = 24 had 98 tiles for 64 workgroups, two
+// rounds for 1.5 rounds' work.  A tile that two workgroups share is staged by
+// both.
+static const int32_t* wt_shares(const polfed_op* op, const polfed_op::WTiles* W, int n) {
+  DevBuf& d = W->shares[n];
+  if (!d.get()) {
+    TallyScope untallied(nullptr);
+    int64_t all = 0;
+    for (int x : W->nseg) all += x;
+    std::vector<int32_t> tab;
+    int64_t before = 0;  // segments of the tiles before t
+    int t = 0;
+    for (int k = 0; k <= n; ++k) {
+      const int64_t g = all * k / n;
+      while (t < W->n && before + W->nseg[t] <= g) before += W->nseg[t++];
+      tab.push_back(t);
+      tab.push_back((int32_t)(g - before));
+    }
+    upload(d, tab.data(), tab.size(), op->ctx->stream);
+    HIPC(hipStreamSynchronize(op->ctx->stream));
+  }
+  return d.as<int32_t>();
+}
+
+// LDS of a workgroup: tables, the zero, one or two tile buffers.
+static size_t wt_shm(const polfed_op* op, const polfed_op::WTiles* W, bool fp32, int db) {
+  const int tb = fp32 ? 4 : 8;
+  return wt_blob_bytes(1 << op->split_Lb, tb) + 16 +
+         (size_t)(db ? 2 : 1) * W->buf_rows[fp32 ? 1 : 0] * tb;
+}
+
+// Workgroups of a launch: as many as are resident at once, in whole XCDs.
+static int wt_grid(const polfed_op* op, const polfed_op::WTiles* W, size_t shm, int nt) {
+  const int per_cu = std::max(1, std::min((int)(kLdsPerCU / shm), 2048 / nt));
+  int64_t grid = std::min<int64_t>(W->n, (int64_t)op->ctx->n_cu * per_cu);
+  if (grid >= 64) grid -= grid % kWtXcds;
+  return (int)std::max<int64_t>(grid, 1);
+}
+
+// The variant's tables, built if they are not there yet (a later launch may
+// be under capture).
 bool chain_wt_exists(const polfed_op* op, int var, bool fp32) {
   if (op->model != Model::Chain || op->split_nseg <= 0) return false;
   if (var < kWtFirst || var >= kWtFirst + kWtCount) return false;
@@ -1060,36 +1319,28 @@ bool chain_wt_exists(const polfed_op* op, int var, bool fp32) {
   if (chain_wt_bits(op->L) == 0 || KT < 1) return false;
   const polfed_op::WTiles* W = wt_tables(op, KT, C.wrap);
   if (!W) return false;
-  const size_t tb = fp32 ? 4 : 8;
-  const size_t shm = chain_blob_bytes(1 << op->split_Lb, (int)tb) +
-                     (size_t)(C.db ? 2 : 1) * ((size_t)W->buf_rows[fp32 ? 1 : 0] * tb +
-                                               (size_t)W->rec_slots * kChainRecWords * 4);
-  return shm <= kLdsPerCU;
+  const size_t shm = wt_shm(op, W, fp32, C.db);
+  if (shm > kLdsPerCU) return false;
+  const int grid = wt_grid(op, W, shm, C.nt);
+  wt_shares(op, W, grid * wt_rounds(op, W, grid, fp32));
+  return true;
 }
 
 template <typename T, int L, int KT, int WR, int DB, int NT>
 static bool launch_wt(hipStream_t s, const polfed_op* op, T sigma, T tau, T a, const T* v,
                       const T* b1, const T* b2, T* out) {
-  constexpr int Lb = (L / 2 < kChainLoBits) ? L / 2 : kChainLoBits;
   const polfed_op::WTiles* W = wt_tables(op, KT, WR);
   if (!W) return false;
-  const int buf_rows = W->buf_rows[sizeof(T) == 8 ? 0 : 1];
-  const size_t shm = chain_blob_bytes(1 << Lb, (int)sizeof(T)) +
-                     (size_t)(DB ? 2 : 1) * ((size_t)buf_rows * sizeof(T) +
-                                              (size_t)W->rec_slots * kChainRecWords * 4);
+  const bool fp32 = sizeof(T) == 4;
+  const size_t shm = wt_shm(op, W, fp32, DB);
   if (shm > kLdsPerCU) return false;
-  const int per_cu = std::max(1, std::min((int)(kLdsPerCU / shm), 2048 / NT));
-  ChainSplitDev c = op->chain_split();
-  int64_t grid = std::min<int64_t>(W->n, (int64_t)op->ctx->n_cu * per_cu);
-  int nxcd = 1;
-  if (grid >= 64) {
-    grid -= grid % kWtXcds;
-    nxcd = kWtXcds;
-  }
-  grid = std::max<int64_t>(grid, 1);
+  const int grid = wt_grid(op, W, shm, NT);
+  const int nxcd = grid >= 64 ? kWtXcds : 1;
+  const int rounds = wt_rounds(op, W, grid, fp32);
+  const ChainSplitDev c = op->chain_split();
   hipLaunchKernelGGL((k_chain_wt<T, L, KT, WR, DB, NT>), dim3((unsigned)grid), dim3(NT), shm, s,
-                     c, sigma, tau, a, v, b1, b2, out, nxcd, W->n, buf_rows, W->rec_slots,
-                     c.rec, W->d.as<int32_t>());
+                     c, sigma, tau, a, v, b1, b2, out, nxcd, rounds, W->buf_rows[fp32 ? 1 : 0],
+                     c.rec, W->d.as<int32_t>(), wt_shares(op, W, grid * rounds));
   HIPC(hipGetLastError());
   return true;
 }
@@ -1170,7 +1421,10 @@ static bool launch_variant(hipStream_t s, const polfed_op* op, int var, T sigma,
     return true;
   }
   if (var == 3) {
-    launch_direct<T, L>(s, op, sigma, tau, a, v, b1, b2, out);
+    if constexpr (L >= kPairedFirst)
+      launch_pair<T, L>(s, op, sigma, tau, a, v, b1, b2, out);
+    else
+      launch_direct<T, L>(s, op, sigma, tau, a, v, b1, b2, out);
     return true;
   }
   if (var == 4) {

@@ -247,6 +247,9 @@ constexpr int kChainMaxHighBonds = kChainRecWords - 10;
 constexpr int chain_blob_bytes(int nlo, int tbytes) {
   return ((nlo * (16 + tbytes + 2)) + 15) / 16 * 16;
 }
+// the staged-tile kernel's part of the list-ordered image: it takes the low
+// part from its entry of the neighbour positions
+constexpr int wt_blob_bytes(int nlo, int tbytes) { return (nlo * (16 + tbytes) + 15) / 16 * 16; }
 struct ChainSplitDev {
   int64_t D;
   int N, periodic;
@@ -419,7 +422,8 @@ struct polfed_op {
   struct WTiles {
     int kt = 0, wrap = 0, n = 0;
     int buf_rows[2] = {0, 0};
-    int rec_slots = 0;  // segment records of the largest tile, runs padded to 8
+    std::vector<int> nseg;               // segments of each tile
+    mutable std::map<int, polfed::DevBuf> shares;  // by workgroups, see wt_shares
     polfed::DevBuf d;
   };
   mutable std::map<int, WTiles> wtiles;
