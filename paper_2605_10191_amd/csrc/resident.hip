@@ -990,7 +990,11 @@ static bool chain_res_filter(hipStream_t s, const polfed_op* op, double E_c, dou
 }
 
 // Quantum sun: slabs so that a thread has one item of DG rows, at most 32 of
-// them, then up to four items; single-workgroup up to 2,048 rows.
+// them, then a few items; single-workgroup up to 2,048 rows.  Where the line
+// lies, us a step, resident / a launch a step: FP64 N = 3, L = 13 (one item)
+// 4.6 / 7.8, N = 2, L = 15 (two) 8.3 / 9.1, N = 4, L = 13 (two) 9.4 / 9.2,
+// N = 5, L = 12 (two) 11.6 / 10.7; FP32 N = 5, L = 12 (two) 9.6 / 17.6,
+// N = 1, L = 16 (four) 7.8 / 12.8, N = 3, L = 15 (four) 14.7 / 13.8.
 static int qsun_slab_bits(const polfed_op* op) {
   const int dg = std::min(2, op->N_dot);
   return std::max(0, std::min({op->N_dot + op->L - 9 - dg, kQsunSlabBits, op->L - 1}));
@@ -1000,19 +1004,21 @@ static int qsun_items(const polfed_op* op) {
   const int64_t n = (int64_t)1 << (op->N_dot + op->L - qsun_slab_bits(op) - dg);
   return (int)((n + kResThreads - 1) / kResThreads);
 }
-static bool qsun_res_applies(const polfed_op* op) {
-  return op->model == Model::Qsun && op->storage == POLFED_MATRIX_FREE && qsun_items(op) <= 4;
+static bool qsun_res_applies(const polfed_op* op, bool fp32) {
+  if (op->model != Model::Qsun || op->storage != POLFED_MATRIX_FREE) return false;
+  const int most = fp32 ? (op->N_dot == 1 ? 4 : 2) : (op->N_dot <= 2 ? 2 : 1);
+  return qsun_items(op) <= most;
 }
 
 bool res_applies(const polfed_op* op, bool fp32) {
-  return chain_res_applies(op, fp32) || qsun_res_applies(op);
+  return chain_res_applies(op, fp32) || qsun_res_applies(op, fp32);
 }
 
 template <typename T>
 bool res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const double* a, int K,
                 const T* v, T* w, T* bufA, T* bufB) {
   if (chain_res_filter<T>(s, op, E_c, dE, a, K, v, w, bufA, bufB)) return true;
-  if (K < kResMinSteps || !qsun_res_applies(op)) return false;
+  if (K < kResMinSteps || !qsun_res_applies(op, sizeof(T) == 4)) return false;
   const int items = qsun_items(op), N = op->N_dot;
   QsunRes<T> r{};
   r.q = op->qsun();
@@ -1052,10 +1058,8 @@ bool res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const
       POLFED_QSUN(2, 4, 0);
     else if (items == 1)
       POLFED_QSUN(4, 1, 0);
-    else if (items == 2)
-      POLFED_QSUN(4, 2, 0);
     else
-      POLFED_QSUN(4, 4, 0);
+      POLFED_QSUN(4, 2, 0);
 #undef POLFED_QSUN
     HIPC(hipGetLastError());
     if ((top - bot) % 2) std::swap(r.X, r.Y);
