@@ -22,6 +22,7 @@
 #include <numeric>
 #include <type_traits>
 
+#include "chain_dev.hpp"
 #include "internal.hpp"
 
 namespace polfed {
@@ -262,12 +263,23 @@ __global__ __launch_bounds__(256) void k_qsun_step(
 }
 
 // -------------------------------------------------------- CSR kernel ----
-// Each block owns a run of rows whose off-diagonal entries (at most
-// kCsrStage) are first staged into LDS with coalesced loads; each lane then
-// walks its rows out of LDS and gathers b1.  A row longer than the stage is
-// a block of its own and is reduced across the block from global memory.
+// Each block owns a run of rows, one a thread, whose off-diagonal entries (at
+// most kCsrStage) are first copied into LDS with direct-to-LDS loads of 16
+// bytes a lane; each lane then walks its row out of LDS and gathers b1, eight
+// entries at a time: their columns and codes are read, the eight gathers sent
+// off and then summed in the row's order.  A row longer than the stage is a
+// block of its own and is reduced across the block from global memory.  The
+// XCDs take contiguous eighths of the blocks, so that b1 is fetched into one
+// L2 rather than into all of them.
+//
+// J1-J2 chain L = 22 (D = 705,432, 22 entries a row, mapped values, FP64): one
+// gather at a time, 256 threads for the 140 rows that fit the stage, blocks
+// dealt over the XCDs 57.7 us a step; this 27.3 (L = 20, values
+// not mapped: 28.3 -> 15.3).  Sixteen gathers in flight or 256 threads with
+// twice the stage are no faster.
 constexpr int kCsrStage = 3072;
-constexpr int kCsrRowsPerBlock = 512;
+constexpr int kCsrThreads = 128;   // and rows of a block
+constexpr int kCsrDepth = 8;       // gathers in flight a lane
 
 template <typename T>
 __device__ __forceinline__ T block_sum(T x, T* red) {
@@ -283,53 +295,90 @@ __device__ __forceinline__ T block_sum(T x, T* red) {
 }
 
 template <typename T, bool MAPPED>
-__global__ __launch_bounds__(256) void k_csr_step(
+__global__ __launch_bounds__(kCsrThreads) void k_csr_step(
     CsrDev m, T sigma, T tau, T a, const T* __restrict__ v,
     const T* __restrict__ b1, const T* b2, T* out) {
+  using lds_ptr = __attribute__((address_space(3))) void*;
+  constexpr int U = kCsrDepth;
   // the mapped variant stages one-byte codes instead of values, which
-  // leaves room for more workgroups per CU
-  using Stage = std::conditional_t<MAPPED, uint8_t, T>;
-  __shared__ int32_t scol[kCsrStage];
-  __shared__ Stage sval[kCsrStage];
-  __shared__ T red[8];
+  // leaves room for more workgroups per CU; the copies' last 1 KB chunk and
+  // the last row's last U entries reach past the stage
+  constexpr int VB = MAPPED ? 1 : (int)sizeof(T);
+  __shared__ __attribute__((aligned(16))) int32_t scol[kCsrStage + 256];
+  __shared__ __attribute__((aligned(16))) unsigned char sval[kCsrStage * VB + 1024];
+  __shared__ T red[kCsrThreads / 64];
   __shared__ T stab[MAPPED ? 256 : 1];  // value table of an optimized mapping
-  const int64_t blk = blockIdx.x;
+  const int64_t per = gridDim.x / 8;
+  const int64_t blk = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
+  if (blk >= m.nblk) return;
   const int64_t rb = m.blk_row[blk], re = m.blk_row[blk + 1];
   const int64_t z0 = m.rowptr[rb], z1 = m.rowptr[re];
   const T* val = Tab<T>::val(m);
   const T* dia = Tab<T>::diag(m);
+  const bool codes = MAPPED && m.ncode > 1;
   if constexpr (MAPPED) {
     const T* vg = Tab<T>::vtab(m);
-    for (int i = threadIdx.x; i < m.ncode; i += blockDim.x) stab[i] = vg[i];
+    for (int i = threadIdx.x; i < m.ncode; i += kCsrThreads) stab[i] = vg[i];
     __syncthreads();
   }
   const T* vt = stab;
   if (z1 - z0 <= kCsrStage) {
-    for (int64_t i = threadIdx.x; i < z1 - z0; i += blockDim.x) {
-      scol[i] = m.col[z0 + i];
-      if constexpr (MAPPED)
-        sval[i] = m.ncode == 1 ? (uint8_t)0 : m.code[z0 + i];
-      else
-        sval[i] = val[z0 + i];
+    const int n = (int)(z1 - z0);
+    const int wave = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    // codes are staged from the dword that holds the first one
+    const int c0 = MAPPED ? (int)(z0 & 3) : 0;
+    const int bytes[2] = {4 * n, MAPPED ? (codes ? (n + c0 + 3) / 4 * 4 : 0) : n * VB};
+    const rsrc_t rcol = make_rsrc(m.col + z0, bytes[0]),
+                 rval = make_rsrc(MAPPED ? (const void*)(m.code + (codes ? z0 - c0 : 0))
+                                         : (const void*)(val + z0),
+                                  bytes[1]);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      unsigned char* dst = q == 0 ? reinterpret_cast<unsigned char*>(scol) : sval;
+      for (int o = 1024 * wave; o < bytes[q]; o += 16 * kCsrThreads)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(q == 0 ? rcol : rval, (lds_ptr)(dst + o), 16,
+                                                 (uint32_t)o + 16u * lane, 0, 0, 0);
     }
+    // the row's own values, on their way with the copies
+    const int64_t r = min(rb + (int64_t)threadIdx.x, re - 1);
+    const int e0 = (int)(m.rowptr[r] - z0), e1 = (int)(m.rowptr[r + 1] - z0);
+    const T bo = b1[r], dr = dia[r];
+    const T vr = v ? v[r] : T(0), b2r = b2 ? b2[r] : T(0);
+    __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    for (int64_t r = rb + threadIdx.x; r < re; r += blockDim.x) {
-      const int64_t e0 = m.rowptr[r] - z0, e1 = m.rowptr[r + 1] - z0;
-      const T bo = b1[r];
-      T acc = dia[r] * bo;
-      for (int64_t e = e0; e < e1; ++e) {
-        T x;
-        if constexpr (MAPPED)
-          x = vt[sval[e]];
-        else
-          x = sval[e];
-        acc += x * b1[scol[e]];
+    if (rb + (int64_t)threadIdx.x >= re) return;
+    T acc = dr * bo;
+    for (int e = e0; e < e1; e += U) {
+      int64_t col[U];
+      T x[U], g[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int c = scol[e + u];  // beyond the row: another's, or nothing
+        col[u] = e + u < e1 ? (int64_t)c : r;
       }
-      T o = sigma * acc + tau * bo;
-      if (v) o += a * v[r];
-      if (b2) o -= b2[r];
-      out[r] = o;
+#pragma unroll
+      for (int u = 0; u < U; ++u) g[u] = b1[col[u]];
+      if constexpr (MAPPED) {
+        uint32_t w[U / 4 + 1];
+        const uint32_t* sc = reinterpret_cast<const uint32_t*>(sval) + ((e + c0) >> 2);
+#pragma unroll
+        for (int q = 0; q <= U / 4; ++q) w[q] = codes ? sc[q] : 0u;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          x[u] = vt[(__builtin_amdgcn_alignbyte(w[u / 4 + 1], w[u / 4], (e + c0) & 3) >>
+                     (8 * (u & 3))) & 255u];
+      } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = reinterpret_cast<const T*>(sval)[e + u];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (e + u < e1) acc += x[u] * g[u];
     }
+    T o = sigma * acc + tau * bo;
+    if (v) o += a * vr;
+    if (b2) o -= b2r;
+    out[r] = o;
   } else {
     // a single long row
     T part = 0;
@@ -362,11 +411,12 @@ void op_step(hipStream_t s, const polfed_op* op, T sigma, T tau, T a,
   if (op->D == 0) return;
   if (op->storage == POLFED_CSR) {
     CsrDev m = op->csr();
+    const unsigned grid = (unsigned)((m.nblk + 7) / 8 * 8);
     if (m.ncode > 0)
-      hipLaunchKernelGGL((k_csr_step<T, true>), dim3((unsigned)m.nblk), dim3(256), 0, s, m, sigma,
+      hipLaunchKernelGGL((k_csr_step<T, true>), dim3(grid), dim3(kCsrThreads), 0, s, m, sigma,
                          tau, a, v, b1, b2, out);
     else
-      hipLaunchKernelGGL((k_csr_step<T, false>), dim3((unsigned)m.nblk), dim3(256), 0, s, m,
+      hipLaunchKernelGGL((k_csr_step<T, false>), dim3(grid), dim3(kCsrThreads), 0, s, m,
                          sigma, tau, a, v, b1, b2, out);
     HIPC(hipGetLastError());
     return;
@@ -650,7 +700,7 @@ static void csr_blocks(const std::vector<int64_t>& rowptr, int64_t D,
   blk.push_back(0);
   while (r < D) {
     int64_t e = r, nz = 0;
-    while (e < D && e - r < kCsrRowsPerBlock) {
+    while (e < D && e - r < kCsrThreads) {
       const int64_t len = rowptr[e + 1] - rowptr[e];
       if (nz + len > kCsrStage) break;
       nz += len;
@@ -899,6 +949,7 @@ int optimize_mapping(polfed_ctx* ctx, polfed_op* op) {
   std::vector<float> tab32(tab.begin(), tab.end());
   upload(op->d_vtab, tab.data(), tab.size(), s);
   upload(op->d_vtab32, tab32.data(), tab32.size(), s);
+  code.resize((code.size() + 3) / 4 * 4);  // the step kernel reads whole dwords
   if (tab.size() > 1) upload(op->d_code, code.data(), code.size(), s);
   HIPC(hipStreamSynchronize(s));
   op->ncode = (int)tab.size();
