@@ -588,6 +588,12 @@ template <typename T>
 bool res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const double* a,
                       int K, const T* v, T* w, T* bufA, T* bufB);
 bool chain_res_batch_fits(hipStream_t s, const polfed_op* op0, int nb);
+// The filter as a matrix, for solves of short chains (see there).
+bool chain_dense_pays(const polfed_op* op, int K, int M);
+size_t chain_dense_bytes(const polfed_op* op);
+bool chain_dense_build(hipStream_t s, const polfed_op* op, double E_c, double dE, const double* a,
+                       int K, double* P, double* X, double* Y, void* ws);
+void chain_dense_apply(hipStream_t s, int64_t D, const double* P, const double* x, double* y);
 // Products of the Chebyshev vectors t_n(H~) v of nb columns (kpm.hip).
 bool chain_res_moments_fit(hipStream_t s, const polfed_op* op, int nb);
 size_t chain_res_moments_bytes(const polfed_op* op, int M, int nb);

@@ -321,7 +321,7 @@ __device__ __forceinline__ void res_setup(const ResArgs<T>& p, SlabState<T, NL, 
       for (int b = 0; b < p.L; ++b) d += (s >> b) & 1u ? f[b] : 0.0;
       const int col = c0 + c;
       S.dg[j].x[c] = (T)((double)p.sc[col] * d + (double)p.sc[p.nb + col]);
-      S.v[j].x[c] = valid ? p.v[(int64_t)col * p.D + r] : T(0);
+      S.v[j].x[c] = !valid ? T(0) : p.v ? p.v[(int64_t)col * p.D + r] : T(r == col);
     }
     const uint32_t off = valid ? (uint32_t)r * RB : kNoRow;
     S.b1[j] = rload<T, G>(cur, off);
@@ -386,6 +386,7 @@ __device__ __forceinline__ void res_group(const ResArgs<T>& p, int c0, TeamView&
   constexpr bool skip = RB == 8 && R <= 3;
   const int64_t D = p.D;
   const int nslab = p.nslab;
+  const bool lda1 = p.lda == 1;  // the same coefficients for every column
   if (threadIdx.x < G * kFieldStride)
     s_field[threadIdx.x] =
         p.fields[p.field_cols > 1 ? (int64_t)c0 * kFieldStride + threadIdx.x
@@ -400,8 +401,8 @@ __device__ __forceinline__ void res_group(const ResArgs<T>& p, int c0, TeamView&
            r += kResThreads)
 #pragma unroll
         for (int c = 0; c < G; ++c)
-          cur[r * G + c] = (MOM ? T(1) : p.A[(int64_t)p.i_top * p.lda + c0 + c]) *
-                           p.v[(int64_t)(c0 + c) * D + r];
+          cur[r * G + c] = (MOM ? T(1) : p.A[(int64_t)p.i_top * p.lda + (lda1 ? 0 : c0 + c)]) *
+                           (p.v ? p.v[(int64_t)(c0 + c) * D + r] : T(r == c0 + c));
   }
   team_barrier(tv, err, [] {});
   SlabState<T, NL, NH, R, G> S;
@@ -424,7 +425,7 @@ __device__ __forceinline__ void res_group(const ResArgs<T>& p, int c0, TeamView&
     const int ci = (p.i_top - 1 - i) & 63;
     if (!MOM && ci == 0)
 #pragma unroll
-      for (int c = 0; c < G; ++c) acf[c] = p.A[(int64_t)max(i - lane, 0) * p.lda + c0 + c];
+      for (int c = 0; c < G; ++c) acf[c] = p.A[(int64_t)max(i - lane, 0) * p.lda + (lda1 ? 0 : c0 + c)];
     T ai[G];
 #pragma unroll
     for (int c = 0; c < G; ++c) ai[c] = MOM ? T(0) : lane_value(acf[c], ci);
@@ -571,6 +572,7 @@ struct QsunRes {
 };
 
 constexpr int kQsunSlabBits = 5;
+constexpr int kDenseMaxRows = 2048;  // of a filter applied as a matrix
 
 template <typename T, int DG, int ITEMS, int ND>
 __global__ __launch_bounds__(kResThreads) void k_qsun_res(QsunRes<T> p) {
@@ -1066,6 +1068,96 @@ bool res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const
     top = bot;
   }
   return true;
+}
+
+// P(H~) as a matrix: its columns are the filter of the unit vectors, a batch
+// that fills the chip, and an application is then one product with it.  A
+// short chain's filter runs on one workgroup or one XCD however idle the rest
+// of the chip is; at L = 12 (D = 924, K = 181) an application takes 222 us,
+// the matrix of all 924 columns 0.89 ms and a product 3.4 to 4.7 us; at L = 13
+// (D = 1,716, K = 489) 590 us against 9.3 ms and 8 us.  The error of an
+// application is that of the columns, each a Clenshaw sum of the same order,
+// weighted with v (norm of the error against an 80-bit evaluation, recurrence
+// and matrix: L = 12 4.18e-16 and 4.20e-16, L = 13 4.43e-16 and 4.45e-16).
+//
+// It pays once a solve applies the filter more often than the batch takes in
+// applications; M is the expected number of them, of which a solve that
+// converges early uses somewhat more than half.  Solves, ms before and after:
+// D = 252 8.7 and 6.3, D = 924 22.7 and 10.5, D = 1,716 40.3 and 18.8, D =
+// 2,002 44.6 and 21.8; at D = 3,432 the columns would take 40 ms of the 51 that
+// the applications take.  The matrix and the two buffers of its columns stay
+// below 100 MB.
+bool chain_dense_pays(const polfed_op* op, int K, int M) {
+  if (K < kResMinSteps || op->D > kDenseMaxRows || !chain_res_applies(op, false)) return false;
+  const ResShape all = res_shape(op->D, (int)op->D);
+  return all.nslab > 0 && 0.5 * M * res_shape(op->D, 1).us > 2.0 * all.us;
+}
+
+size_t chain_dense_bytes(const polfed_op* op) {
+  return sizeof(ResState) + 4096 + (2 * (size_t)op->D + kResChunk + 1) * sizeof(double);
+}
+
+// P: D x D; X, Y: its two buffers; ws: chain_dense_bytes.
+bool chain_dense_build(hipStream_t s, const polfed_op* op, double E_c, double dE, const double* a,
+                       int K, double* P, double* X, double* Y, void* ws) {
+  const int nb = (int)op->D;
+  const ResShape x = res_shape(op->D, nb);
+  const auto t = res_table(s, op, x.nslab, true);
+  if (!t || !res_instance(*t)) return false;
+  ResState* st = (ResState*)ws;
+  double* sc = (double*)((unsigned char*)ws + (sizeof(ResState) + 255) / 256 * 256);
+  double* A = sc + 2 * nb;
+  ResArgs<double> r{};
+  r.L = op->L;
+  r.N = op->N;
+  r.periodic = op->periodic;
+  r.nb = nb;
+  r.field_cols = 1;
+  r.lda = 1;
+  r.D = op->D;
+  r.t_in = op->t_in;
+  r.t_pb = op->t_pb;
+  r.vzz = op->vzz;
+  r.fields = op->d_fields.as<double>();
+  r.sc = sc;
+  r.w = P;
+  r.X = X;
+  r.Y = Y;
+  r.st = st;
+  res_run<false>(s, *t, x, r, K, kResChunk, [&](ResArgs<double>& q, int top, int bot) {
+    hipLaunchKernelGGL((k_res_begin<double>), dim3(8), dim3(256), 0, s, q.st, sc, 2.0 / dE,
+                       -2.0 * E_c / dE, nb);
+    put_coefs<double>(s, a, bot, top, A);
+    q.A = A - bot;  // indexed by the step
+  });
+  return true;
+}
+
+// y_i = sum_j P[i D + j] x_j: a wave a row (P is symmetric to its rounding, so
+// the row is read where the column lies, contiguous), the whole chip at work.
+__global__ __launch_bounds__(256) void k_dense_mv(int D, const double* __restrict__ P,
+                                                  const double* __restrict__ x,
+                                                  double* __restrict__ y) {
+  const int i = uniform((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+  if (i >= D) return;
+  const int lane = threadIdx.x & 63;
+  const double* row = P + (int64_t)i * D;
+  double s0 = 0, s1 = 0;
+  int j = lane;
+#pragma unroll 8
+  for (; j + 64 < D; j += 128) {
+    s0 += row[j] * x[j];
+    s1 += row[j + 64] * x[j + 64];
+  }
+  if (j < D) s0 += row[j] * x[j];
+  s0 += s1;
+  for (int off = 32; off > 0; off >>= 1) s0 += __shfl_down(s0, off, 64);
+  if (lane == 0) y[i] = s0;
+}
+
+void chain_dense_apply(hipStream_t s, int64_t D, const double* P, const double* x, double* y) {
+  hipLaunchKernelGGL(k_dense_mv, dim3((unsigned)((D + 3) / 4)), dim3(256), 0, s, (int)D, P, x, y);
+  HIPC(hipGetLastError());
 }
 
 template bool res_filter<double>(hipStream_t, const polfed_op*, double, double, const double*, int,

@@ -168,6 +168,8 @@ struct SolveRun {
   DevBuf vst;  // FP64: fixed copy of v_k read by the graph
   enum { kTimeDirect, kTimeGraph, kDirect, kGraph } mode = kTimeDirect;
   float t_direct_ms = 0;
+  DevBuf dense;  // P(H~) as a matrix, from the first application on, if that pays
+  enum { kDenseAsk, kDenseNo, kDenseYes } dense_mode = kDenseAsk;
   // block Lanczos (s > 1): band holds [A_j | B_{j+1}] (2 s^2 doubles) for
   // every block step j; the filtered block lives in bw.w
   int s = 1;

@@ -532,6 +532,7 @@ void SolveRun::setup(polfed_ctx* c, const polfed_op* o, const polfed_params& prm
   done = false;
   status = POLFED_NOT_CONVERGED;
   restart_seed = 0x5EEDULL;
+  dense_mode = kDenseAsk;
   sbytes = step_bytes(op, p.precision);
 }
 
@@ -630,8 +631,26 @@ void SolveRun::filter_self() {
   HIPC(hipEventCreate(&e0));
   HIPC(hipEventCreate(&e1));
   HIPC(hipEventRecord(e0, s));
+  if (dense_mode == kDenseAsk) {
+    // not where the launch mode was chosen by the caller, nor in the server,
+    // whose admissions count the vectors only
+    dense_mode = kDenseNo;
+    if (!fp32 && mode == kDirect && p.graph == 0 && !take && chain_dense_pays(op, pl.K, cap)) {
+      op_tune(s, op, false);  // the operator's tables
+      const size_t n = (size_t)D * D * sizeof(double);
+      dense.alloc(n);
+      DevBuf X(n), Y(n), st(chain_dense_bytes(op));
+      if (chain_dense_build(s, op, pl.E_c, pl.dE, a.data(), pl.K, dense.as<double>(),
+                            X.as<double>(), Y.as<double>(), st.get()))
+        dense_mode = kDenseYes;
+      else
+        dense.release();
+    }
+  }
   if (fp32) dev_copy_d2f(s, D, B.col(k), ws.v32.as<float>());
-  if (use_graph) {
+  if (dense_mode == kDenseYes) {
+    chain_dense_apply(s, D, dense.as<double>(), B.col(k), ws.w.as<double>());
+  } else if (use_graph) {
     if (!fp32)
       HIPC(hipMemcpyAsync(vst.get(), B.col(k), (size_t)D * sizeof(double),
                           hipMemcpyDeviceToDevice, s));
@@ -891,6 +910,7 @@ void SolveRun::fallback_fp64() {
   R.fp32_fallback = 1;
   tol_ritz = 1e-10;
   graph.reset();
+  dense_mode = kDenseAsk;
   mode = (p.graph == 2 || pl.K < 8 || pl.K > kGraphMaxSteps) ? kDirect
                                                              : (p.graph == 1 ? kGraph : kTimeDirect);
   ws.bA.alloc(filter_buf_bytes(D, sizeof(double)));
