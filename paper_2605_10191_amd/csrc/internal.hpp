@@ -594,6 +594,10 @@ size_t chain_dense_bytes(const polfed_op* op);
 bool chain_dense_build(hipStream_t s, const polfed_op* op, double E_c, double dE, const double* a,
                        int K, double* P, double* X, double* Y, void* ws);
 void chain_dense_apply(hipStream_t s, int64_t D, const double* P, const double* x, double* y);
+// Two Gram-Schmidt passes, norm and scaling of a short vector in one launch;
+// partial holds 8192 doubles.  False: not the faster way, nothing done.
+bool cgs2_team(hipStream_t s, int64_t D, int k1, const double* V, double* w, double* c,
+               double* partial, int* flag, double* alpha, double* beta, double* v_next);
 // Products of the Chebyshev vectors t_n(H~) v of nb columns (kpm.hip).
 bool chain_res_moments_fit(hipStream_t s, const polfed_op* op, int nb);
 size_t chain_res_moments_bytes(const polfed_op* op, int M, int nb);

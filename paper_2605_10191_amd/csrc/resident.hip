@@ -1160,6 +1160,149 @@ void chain_dense_apply(hipStream_t s, int64_t D, const double* P, const double* 
   HIPC(hipGetLastError());
 }
 
+// ---- orthogonalization of a short vector in one launch ----
+
+// w <- w - V (V^T w) over k1 basis vectors, twice, beta = ||w||, v_next =
+// w / beta, by one team.  For short chains the eight launches that this takes
+// otherwise last 40 us whatever they move (D = 924, k1 = 70: 0.5 MB a pass).
+// V^T w is split by columns and V c by rows, so every sum lies in one member,
+// in an order that does not depend on how many members the team got: virtual
+// member m takes the columns m, m + nm, ... and the rows of slab m.  Four
+// phases and the norm take five barriers of about 1 us; a pass reads V through
+// one XCD's L2.  Measured, us a step with it, launches / this: D = 70, k1 = 30 30 / 20,
+// D = 924, k1 = 100 54 / 27, D = 3,432, k1 = 150 88 / 40, k1 = 500 256 / 118.
+constexpr int kOrthCols = 8;  // columns of V^T w at a time
+
+__global__ __launch_bounds__(kResThreads) void k_cgs2_team(
+    ResState* st, int64_t D, int k1, int nm, const double* V, double* w, double* c, double* norm,
+    int* flag, double* alpha, double* beta, double* v_next) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ int s_join[4];
+  __shared__ double s_red[kResWaves * 64];
+  double* s_c = reinterpret_cast<double*>(smem);  // [k1]
+  TeamView tv{nullptr, 1, 0, 0, 0};
+  if (!team_join(st, nm, 1, s_join, tv)) return;
+  // the first team does it
+  if (threadIdx.x == 0 && tv.rank == 0) {
+    const int g = res_add(&st->queue, 1);
+    if (tv.n > 1)
+      res_store(&tv.t->group[0], g);
+    else
+      s_join[3] = g;
+  }
+  int* err = &st->err;
+  team_barrier(tv, err, [] {});
+  if (uniform(tv.n > 1 ? res_load(&tv.t->group[0]) : s_join[3]) > 0) return;
+  const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
+  const rsrc_t rw = make_rsrc(w, (uint32_t)(D * 8)), rc = make_rsrc(c, (uint32_t)(k1 * 8)),
+               rn = make_rsrc(norm, (uint32_t)(nm * 8));
+  double a0 = 0;
+  for (int pass = 0; pass < 2; ++pass) {
+    // c = V^T w, columns m, m + nm, ...: the workgroup's threads share the rows
+    for (int m = tv.rank; m < nm; m += tv.n)
+      for (int q0 = 0; m + q0 * nm < k1; q0 += kOrthCols) {
+        double acc[kOrthCols] = {};
+#pragma unroll 2
+        for (int64_t r = threadIdx.x; r < D; r += kResThreads) {
+          const double wr = bload<double, kAuxAgent>(rw, (uint32_t)(r * 8), 0);
+#pragma unroll
+          for (int q = 0; q < kOrthCols; ++q) {
+            const int j = m + (q0 + q) * nm;
+            if (j < k1) acc[q] += V[r + (int64_t)j * D] * wr;
+          }
+        }
+        const double t = wave_sums<kOrthCols>(acc);
+        __syncthreads();
+        if (lane % (64 / kOrthCols) == 0) s_red[wave * kOrthCols + lane / (64 / kOrthCols)] = t;
+        __syncthreads();
+        const int j = m + (q0 + (int)threadIdx.x) * nm;
+        if ((int)threadIdx.x < kOrthCols && j < k1) {
+          double x = 0;
+#pragma unroll
+          for (int i = 0; i < kResWaves; ++i) x += s_red[i * kOrthCols + threadIdx.x];
+          c[j] = x;
+          if (j == k1 - 1) {  // adds up to the Lanczos alpha
+            a0 += x;
+            if (alpha && pass) alpha[0] = a0;
+          }
+        }
+      }
+    team_barrier(tv, err, [] {});
+    for (int j = threadIdx.x; j < k1; j += kResThreads)
+      s_c[j] = bload<double, kAuxAgent>(rc, (uint32_t)(j * 8), 0);
+    __syncthreads();
+    // w -= V c on the rows of slab m: a wave takes every eighth column
+    for (int m = tv.rank; m < nm; m += tv.n) {
+      const int64_t row0 = slab_row(D, nm, m), row1 = slab_row(D, nm, m + 1);
+      double sq = 0;
+      for (int64_t rb = row0; rb < row1; rb += 64) {
+        const int64_t r = min(rb + lane, row1 - 1);
+        double acc = 0;
+#pragma unroll 8
+        for (int j = wave; j < k1; j += kResWaves) acc += V[r + (int64_t)j * D] * s_c[j];
+        s_red[threadIdx.x] = acc;
+        __syncthreads();
+        if (wave == 0) {
+          double x = 0;
+#pragma unroll
+          for (int i = 0; i < kResWaves; ++i) x += s_red[64 * i + lane];
+          const double y = bload<double, kAuxAgent>(rw, (uint32_t)(r * 8), 0) - x;
+          if (rb + lane < row1) {
+            w[r] = y;
+            sq += y * y;
+          }
+        }
+        __syncthreads();
+      }
+      if (pass == 1 && wave == 0) {
+        for (int off = 32; off > 0; off >>= 1) sq += __shfl_down(sq, off, 64);
+        if (lane == 0) norm[m] = sq;
+      }
+    }
+    team_barrier(tv, err, [] {});
+  }
+  double b = bload<double, kAuxAgent>(rn, (uint32_t)(lane * 8), 0);  // 0 past the last
+  for (int off = 32; off > 0; off >>= 1) b += __shfl_xor(b, off, 64);
+  b = res_load(err) != 0 ? (double)NAN : sqrt(b);
+  const bool ok = b > 1e-300 && isfinite(b);
+  const double inv = ok ? 1.0 / b : isnan(b) && res_load(err) != 0 ? b : 0.0;
+  if (tv.rank == 0 && threadIdx.x == 0) {
+    beta[0] = b;
+    if (!ok && flag) flag[0] = 1;
+  }
+  for (int m = tv.rank; m < nm; m += tv.n)
+    for (int64_t r = slab_row(D, nm, m) + threadIdx.x; r < slab_row(D, nm, m + 1);
+         r += kResThreads)
+      v_next[r] = bload<double, kAuxAgent>(rw, (uint32_t)(r * 8), 0) * inv;
+}
+
+// Where it is the faster one.  The launches split the rows in segments of
+// 8,192, so below that they leave most of the chip idle and the line lies
+// where one XCD's path to V is the longer one (D = 3,432: 1.7 M entries 256 us
+// against 118); above, they do not (D = 12,870: 0.4 M entries 85 against 47,
+// 0.8 M 92 against 86, 1.3 M 104 against 112).  With many rows and few columns
+// the split by columns is the poor one (D = 24,310, k1 = 2: 52 against 69).
+static bool orth_team(int64_t D, int k1) {
+  return k1 >= 1 && k1 <= 4096 && D >= 1 && D <= 16384 &&
+         D * k1 <= (D <= 8192 ? 2000 : 700) * 1000;
+}
+
+bool cgs2_team(hipStream_t s, int64_t D, int k1, const double* V, double* w, double* c,
+               double* partial, int* flag, double* alpha, double* beta, double* v_next) {
+  if (!orth_team(D, k1)) return false;
+  const int nm = D * k1 > 256 * 1000 ? 32 : 16;
+  // the team state and the norm's parts lie in the partial sums' 64 KB
+  static_assert(sizeof(ResState) + 32 * sizeof(double) <= 8192 * sizeof(double), "partial");
+  ResState* st = reinterpret_cast<ResState*>(partial);
+  double* norm = reinterpret_cast<double*>(st + 1);
+  hipLaunchKernelGGL((k_res_begin<double>), dim3(8), dim3(256), 0, s, st, (double*)nullptr, 0.0,
+                     0.0, 0);
+  hipLaunchKernelGGL(k_cgs2_team, dim3(8 * nm), dim3(kResThreads), (size_t)k1 * sizeof(double), s,
+                     st, D, k1, nm, V, w, c, norm, flag, alpha, beta, v_next);
+  HIPC(hipGetLastError());
+  return true;
+}
+
 template bool res_filter<double>(hipStream_t, const polfed_op*, double, double, const double*, int,
                                  const double*, double*, double*, double*);
 template bool res_filter<float>(hipStream_t, const polfed_op*, double, double, const double*, int,

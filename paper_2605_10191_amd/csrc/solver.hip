@@ -142,6 +142,7 @@ namespace {
 void cgs2_raw(hipStream_t s, int64_t D, int k1, const double* V, double* w,
               double* c, double* partial, int64_t nseg, int* flag, double* alpha_k,
               double* beta_next, double* v_next) {
+  if (cgs2_team(s, D, k1, V, w, c, partial, flag, alpha_k, beta_next, v_next)) return;
   for (int pass = 0; pass < 2; ++pass) {
     dev_gemv_t(s, D, k1, V, D, w, partial, nseg, c, alpha_k, pass);
     dev_gemv_n_sub(s, D, k1, V, D, c, w);
