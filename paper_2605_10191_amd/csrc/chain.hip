@@ -372,7 +372,8 @@ __global__ __launch_bounds__(256) void k_chain_split(
 //     build_chain_split), so only the periodic bond waits for the tables.
 // With MULTI the columns of a column-major block are spread over the XCDs
 // (8, 4, 2 or 1 of them a column), so a column's gathers stay in its XCDs'
-// L2; each column has its operator's records and tables.
+// L2; each column has its operator's records and tables, or all have one
+// operator's (cols null: H on the columns of a block).
 //
 // A bond without a hop in the segment is passed by with a branch both where it
 // is loaded and where it is added; the empty asm keeps the compiler from
@@ -418,10 +419,11 @@ __global__ __launch_bounds__(256) void k_chain_direct(
     const int si = uniform(s_begin + (int)(it - (int64_t)k * nsx));
     const int col = uniform(first + k * step);
     const int64_t coff = MULTI ? (int64_t)col * c.D : 0;
-    const int32_t* recs = MULTI ? cols[col].rec : c.rec;
+    const bool own = MULTI && cols;  // the columns' own operators, or one for all
+    const int32_t* recs = own ? cols[col].rec : c.rec;
     const unsigned char* blob = reinterpret_cast<const unsigned char*>(
-        sizeof(T) == 8 ? (MULTI ? cols[col].blobl64 : c.blobl64)
-                       : (MULTI ? cols[col].blobl32 : c.blobl32));
+        sizeof(T) == 8 ? (own ? cols[col].blobl64 : c.blobl64)
+                       : (own ? cols[col].blobl32 : c.blobl32));
     const rsrc_t rb1 = make_rsrc(b1 + coff, vbytes), rv = make_rsrc(v ? v + coff : b1, v ? vbytes : 0),
                  rb2 = make_rsrc(b2 ? b2 + coff : b1, b2 ? vbytes : 0),
                  rout = make_rsrc(out + coff, vbytes);
@@ -492,8 +494,8 @@ __global__ __launch_bounds__(256) void k_chain_direct(
       }
     }
     wave_sync();
-    const T sig = MULTI ? half * sc[col] : sigma, ta = MULTI ? half * sc[nb + col] : tau;
-    const T ac = MULTI ? (acoef ? acoef[col] : T(0)) : a;
+    const T sig = own ? half * sc[col] : sigma, ta = own ? half * sc[nb + col] : tau;
+    const T ac = own ? (acoef ? acoef[col] : T(0)) : a;
     T o[2], bo[2], hop[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -565,6 +567,44 @@ static void launch_direct_cols(hipStream_t s, const ChainBatch& bt, int col0, in
                      bt.nb, sc + col0, acoef ? acoef + col0 : nullptr, half, v ? v + o : nullptr,
                      b1 + o, b2 ? b2 + o : nullptr, out + o, 8, xpc);
   HIPC(hipGetLastError());
+}
+
+// out = H x for n vectors of one operator, column-major.
+template <int L>
+static void launch_direct_block(hipStream_t s, const polfed_op* op, int n, const double* x,
+                                double* out) {
+  ChainSplitDev c = op->chain_split();
+  int xpc = 8;
+  while (xpc > 1 && xpc * n > 8) xpc /= 2;
+  const int64_t per = (c.nseg / xpc + 1) * ((n + 8 / xpc - 1) / (8 / xpc));  // items of an XCD
+  const int64_t grid =
+      8 * std::min<int64_t>((per + 3) / 4, (int64_t)op->ctx->n_cu * kChainBlocksPerCU / 8);
+  hipLaunchKernelGGL((k_chain_direct<double, L, true>), dim3((unsigned)std::max<int64_t>(grid, 8)),
+                     dim3(256), 0, s, c, 1.0, 0.0, 0.0, (const ChainCol*)nullptr, n, n,
+                     (const double*)nullptr, (const double*)nullptr, 1.0, (const double*)nullptr,
+                     x, (const double*)nullptr, out, 8, xpc);
+  HIPC(hipGetLastError());
+}
+
+// H on the columns of a block in one launch, where a launch a column is mostly
+// its own latency: below the paired kernel's chains (L = 20, 120 columns:
+// 180 us, a launch a column 590).  False: not done.
+bool chain_apply_block(hipStream_t s, const polfed_op* op, int n, const double* x, double* out) {
+  if (n < 2 || op->model != Model::Chain || op->storage != POLFED_MATRIX_FREE ||
+      op->split_nseg <= 0 || op->forced[0])
+    return false;
+  switch (op->L) {
+#define POLFED_CASE(LL)                           \
+  case LL:                                        \
+    launch_direct_block<LL>(s, op, n, x, out);    \
+    return true;
+    POLFED_CASE(4) POLFED_CASE(5) POLFED_CASE(6) POLFED_CASE(7) POLFED_CASE(8)
+    POLFED_CASE(9) POLFED_CASE(10) POLFED_CASE(11) POLFED_CASE(12) POLFED_CASE(13)
+    POLFED_CASE(14) POLFED_CASE(15) POLFED_CASE(16) POLFED_CASE(17) POLFED_CASE(18)
+    POLFED_CASE(19) POLFED_CASE(20) POLFED_CASE(21)
+#undef POLFED_CASE
+    default: return false;
+  }
 }
 
 template <typename T>

@@ -493,6 +493,8 @@ struct ChainBatch {
 template <typename T>
 void chain_batch_step(hipStream_t s, const ChainBatch& bt, int64_t ld, bool final_step,
                       const T* acoef, const T* v, const T* b1, const T* b2, T* out);
+// H on n vectors (column-major); false where a launch a vector is as fast.
+bool chain_apply_block(hipStream_t s, const polfed_op* op, int n, const double* x, double* out);
 // One step of columns [col0, col0 + ncol) of column-major blocks with the
 // columns spread over the XCDs (chain.hip).
 template <typename T>

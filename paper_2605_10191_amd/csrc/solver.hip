@@ -199,6 +199,12 @@ void apply_H(hipStream_t s, const polfed_op* op, const double* x, double* y) {
   op_step<double>(s, op, 1.0, 0.0, 0.0, nullptr, x, nullptr, y);
 }
 
+// Y = H X for n vectors (D x n).
+void apply_H_block(hipStream_t s, const polfed_op* op, int n, const double* X, double* Y) {
+  if (chain_apply_block(s, op, n, X, Y)) return;
+  for (int j = 0; j < n; ++j) apply_H(s, op, X + (size_t)j * op->D, Y + (size_t)j * op->D);
+}
+
 // Tridiagonal Lanczos matrix from alpha[0..m) and beta[1..m).
 void ritz_last(int m, const std::vector<double>& al, const std::vector<double>& be,
                std::vector<double>& theta, std::vector<double>& zlast) {
@@ -391,7 +397,7 @@ Extracted extract(polfed_ctx* ctx, const polfed_op* op, const Basis& B, Ws& ws, 
   Extracted ex;
   DevBuf U((size_t)D * n * sizeof(double)), HU((size_t)D * n * sizeof(double));
   dev_gemm_nn(s, D, m, n, B.V.as<double>(), D, dY.as<double>(), m, U.as<double>(), D, false);
-  for (int j = 0; j < n; ++j) apply_H(s, op, U.as<double>() + (size_t)j * D, HU.as<double>() + (size_t)j * D);
+  apply_H_block(s, op, n, U.as<double>(), HU.as<double>());
   rayleigh_ritz(s, D, n, U.as<double>(), HU.as<double>(), ws.nseg, ex);
   return ex;
 }
@@ -406,8 +412,7 @@ void extract_pairs(polfed_ctx* ctx, const polfed_op* op, const double* V, int m,
   const int64_t nseg = std::max<int64_t>(1, std::min<int64_t>(256, (D + 8191) / 8192));
   DevBuf U((size_t)D * n * sizeof(double)), HU((size_t)D * n * sizeof(double));
   dev_gemm_nn(s, D, m, n, V, D, T, m, U.as<double>(), D, false);
-  for (int j = 0; j < n; ++j)
-    apply_H(s, op, U.as<double>() + (size_t)j * D, HU.as<double>() + (size_t)j * D);
+  apply_H_block(s, op, n, U.as<double>(), HU.as<double>());
   Extracted ex;
   rayleigh_ritz(s, D, n, U.as<double>(), HU.as<double>(), nseg, ex);
   dcopy_async(s, E, ex.E.data(), (size_t)n, hipMemcpyHostToDevice);

@@ -67,3 +67,38 @@ def test_sparse_tiles(pk, ctx, L, N, periodic, prec):
         assert np.all(np.abs(got - ref) <= (L + 24) * u * mag), variant
         tried += 1
     assert tried >= 7
+
+
+@pytest.mark.parametrize("model,L,N,periodic,n", [
+    ("xxz", 4, 2, True, 3), ("tv", 9, 4, True, 2), ("xxz", 12, 6, True, 9),
+    ("xxz", 16, 3, False, 17), ("tv", 20, 4, True, 8), ("xxz", 21, 19, True, 5),
+    ("xxz", 22, 2, True, 4)])
+def test_hamiltonian_on_a_block(pk, ctx, model, L, N, periodic, n):
+    """Rayleigh-Ritz on a random orthonormal block: H applied to its columns
+    in one launch (up to L = 21) and one by one, odd and even column counts on
+    one, two, four and all XCDs a column."""
+    print(f"H on a block {model} L={L} N={N} n={n}")
+    sys.stdout.flush()
+    if model == "xxz":
+        f = wl.xxz_fields(L, 2.0, 5)
+        H, _ = models.xxz(L, N, 1.0, 1.0, f, periodic)
+        op = pk.Operator.xxz(ctx, L, N, 1.0, 1.0, f, periodic)
+    else:
+        f = wl.tv_onsite(L, 5)
+        H, _ = models.tv(L, N, 1.0, 1.0, f, periodic)
+        op = pk.Operator.tv(ctx, L, N, 1.0, 1.0, f, periodic)
+    rng = np.random.default_rng(L + n)
+    V, _ = np.linalg.qr(rng.standard_normal((op.D, n)))
+    E, U, res = pk.extract(op, torch.as_tensor(np.ascontiguousarray(V.T), device="cuda:0"),
+                           torch.as_tensor(np.eye(n), device="cuda:0"))[:3]
+    torch.cuda.synchronize()
+    ref, Z = np.linalg.eigh(V.T @ (H @ V))
+    norm = abs(H).sum(axis=1).max()
+    # a projected entry sums D products of rows of up to L + 5 terms
+    tol = (op.D + L + 10) * 2.0 ** -53 * norm * n
+    got = np.asarray(E.cpu()).ravel()
+    assert np.max(abs(np.sort(got) - ref)) <= tol
+    R = H @ (V @ Z) - (V @ Z) * ref
+    order = np.argsort(got)
+    have = np.asarray(res.cpu()).ravel()[order]
+    assert np.max(abs(have - np.linalg.norm(R, axis=0))) <= tol
