@@ -5,6 +5,7 @@
 // results do not depend on timing.
 #include <algorithm>
 
+#include "chain_dev.hpp"
 #include "internal.hpp"
 
 namespace polfed {
@@ -95,16 +96,26 @@ __global__ __launch_bounds__(kTB) void k_gemv_t(int64_t D, int k, const double* 
   }
 }
 
-// c[j] = sum of the partials of column j; the last column's value is also
-// stored to (or added to) *tail, which carries the Lanczos alpha_k.
-__global__ void k_reduce_cols(const double* part, int64_t nseg, int k, double* c,
-                              double* tail, int tail_add) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+// c[j] = sum of the partials of column j, a wave a column; the last column's
+// value is also stored to (or added to) *tail, which carries the Lanczos
+// alpha_k.
+__global__ __launch_bounds__(kTB) void k_reduce_cols(const double* part, int64_t nseg, int k,
+                                                     double* c, double* tail, int tail_add) {
+  const int j = (int)(blockIdx.x * (kTB / 64) + (threadIdx.x >> 6)), lane = threadIdx.x & 63;
   if (j >= k) return;
   double t = 0;
-  for (int64_t s = 0; s < nseg; ++s) t += part[(int64_t)j * nseg + s];
+  for (int64_t s = lane; s < nseg; s += 64) t += part[(int64_t)j * nseg + s];
+  t = wave_sum(t);
+  if (lane != 0) return;
   c[j] = t;
   if (tail && j == k - 1) tail[0] = tail_add ? tail[0] + t : t;
+}
+
+static void reduce_cols(hipStream_t s, const double* part, int64_t nseg, int k, double* c,
+                        double* tail, int tail_add) {
+  hipLaunchKernelGGL(k_reduce_cols, dim3((unsigned)((k + kTB / 64 - 1) / (kTB / 64))), dim3(kTB),
+                     0, s, part, nseg, k, c, tail, tail_add);
+  HIPC(hipGetLastError());
 }
 
 static int64_t seg_len_for(int64_t D, int64_t nseg) {
@@ -120,9 +131,8 @@ void dev_gemv_t(hipStream_t s, int64_t D, int k, const double* V, int64_t ld,
   const int64_t ns = std::max<int64_t>(1, (D + len - 1) / len);
   dim3 grid((unsigned)((k + kCols - 1) / kCols), (unsigned)ns);
   hipLaunchKernelGGL(k_gemv_t, grid, dim3(kTB), 0, s, D, k, V, ld, w, len, ns, partial);
-  hipLaunchKernelGGL(k_reduce_cols, dim3((unsigned)((k + 63) / 64)), dim3(64), 0, s,
-                     partial, ns, k, c, tail, tail_add);
   HIPC(hipGetLastError());
+  reduce_cols(s, partial, ns, k, c, tail, tail_add);
 }
 
 // ---- tall-skinny block products: C = V^T W and W -= V C for W of S <= 8
@@ -196,8 +206,7 @@ static void tall_pass(hipStream_t s, int64_t D, int k, const double* V, double* 
   const int64_t ns = std::max<int64_t>(1, (D + len - 1) / len);
   dim3 grid((unsigned)((k + kCols - 1) / kCols), (unsigned)ns);
   hipLaunchKernelGGL(k_gemm_tn_tall<S>, grid, dim3(kTB), 0, s, D, k, V, W, len, ns, partial);
-  hipLaunchKernelGGL(k_reduce_cols, dim3((unsigned)((k * S + 63) / 64)), dim3(64), 0, s, partial,
-                     ns, k * S, C, nullptr, 0);
+  reduce_cols(s, partial, ns, k * S, C, nullptr, 0);
   hipLaunchKernelGGL(k_gemm_nn_sub_tall<S>, dim3((unsigned)((D + kTB - 1) / kTB)), dim3(kTB), 0,
                      s, D, k, V, C, W);
   HIPC(hipGetLastError());
@@ -248,6 +257,111 @@ void dev_gemv_n_sub(hipStream_t s, int64_t D, int k, const double* V, int64_t ld
   hipLaunchKernelGGL(k_gemv_n_sub, dim3((unsigned)((D + kTB - 1) / kTB)), dim3(kTB), 0,
                      s, D, k, V, ld, c, w);
   HIPC(hipGetLastError());
+}
+
+// ---- w -= V c and then V^T w, V read once ----
+//
+// The second and the third product of two Gram-Schmidt passes.  Both are bound
+// by reading V (L = 24, 168 vectors: 3.6 GB at 5.2 TB/s), and both need a row
+// slab of it, so a workgroup copies S rows of all k columns into LDS (direct
+// loads, 1 KB of LDS each), updates its rows of w and adds their products to
+// one sum a thread and column, kept over the workgroup's slabs.  S rows are as
+// many as leave room for three workgroups a CU (two above 416 columns), of
+// which one computes while the others' copies are on their way; above 600
+// columns the products stay separate.  In the second product lane l starts at
+// row l of the slab, so the lanes of a column's sum read different banks.
+//
+// Measured, us an orthogonalization, four products / three: D = 2.7 M, 168
+// vectors 2,999 / 2,188, D = 0.7 M, 410 2,131 / 1,557, 600 2,848 / 2,346;
+// D = 48,620, 100 211 / 133; D = 12,870, 300 279 / 171.
+constexpr int kMidColsPer = 3;  // columns of a thread
+
+template <int S>
+__global__ __launch_bounds__(kTB) void k_gemv_n_t(int64_t D, int k, const double* V,
+                                                  const double* c, double* w, double* part) {
+  using lds_ptr = __attribute__((address_space(3))) void*;
+  constexpr int G = kTB / S;           // groups of threads over the columns
+  constexpr int CPL = 128 / S;         // columns of a 1 KB load
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int kp = (k + CPL - 1) / CPL * CPL;
+  double* sV = reinterpret_cast<double*>(smem);  // [kp][S]
+  double* sc = sV + (size_t)kp * S;              // [k]
+  __shared__ double red[kTB], sw[S];
+  const int t = threadIdx.x, lane = t & 63, wave = uniform(t >> 6);
+  for (int j = t; j < k; j += kTB) sc[j] = c[j];
+  const int row = t % S, g = t / S;
+  double acc[kMidColsPer] = {};
+  const int64_t slabs = (D + S - 1) / S;
+  for (int64_t b = blockIdx.x; b < slabs; b += gridDim.x) {
+    const int64_t r0 = b * S;
+    const int n = (int)std::min<int64_t>(S, D - r0);
+    __syncthreads();  // the previous slab's reads are done
+    double wr = 0;
+    if (t < n) wr = w[r0 + t];
+    if (n == S) {
+      for (int q = wave; q * CPL < k; q += kTB / 64) {
+        // columns past the last one are read as 0
+        const rsrc_t rv = make_rsrc(V + (int64_t)q * CPL * D + r0, 0xFFFFFFE0u);
+        const int cl = 2 * lane / S;
+        const uint32_t off = q * CPL + cl < k ? (uint32_t)(((int64_t)cl * D + 2 * lane % S) * 8)
+                                              : 0xFFFFFFF0u;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lds_ptr)(smem + 1024 * (size_t)q), 16, off,
+                                                 0, 0, 0);
+      }
+    } else {
+      for (int i = t; i < k * S; i += kTB)
+        sV[i] = i % S < n ? V[r0 + i % S + (int64_t)(i / S) * D] : 0.0;
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    double x = 0;
+#pragma unroll 4
+    for (int j = g; j < k; j += G) x += sV[j * S + row] * sc[j];
+    red[t] = x;
+    __syncthreads();
+    if (t < S) {
+      double y = 0;
+#pragma unroll
+      for (int i = 0; i < G; ++i) y += red[i * S + t];
+      y = t < n ? wr - y : 0.0;
+      if (t < n) w[r0 + t] = y;
+      sw[t] = y;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kMidColsPer; ++q) {
+      const int j = t + q * kTB;
+      if (j < k) {
+#pragma unroll 8
+        for (int i = 0; i < S; ++i) {
+          const int r = (i + t) % S;
+          acc[q] += sV[j * S + r] * sw[r];
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < kMidColsPer; ++q)
+    if (t + q * kTB < k) part[(int64_t)(t + q * kTB) * gridDim.x + blockIdx.x] = acc[q];
+}
+
+bool dev_gemv_n_t(hipStream_t s, int64_t D, int k, const double* V, double* c, double* w,
+                  double* partial, double* tail, int tail_add) {
+  if (D < kGsMidMinRows || D > (int64_t(1) << 26) || k < 8 || k > 600) return false;
+  const int S = k <= 104 ? 64 : k <= 208 ? 32 : 16;
+  const int cpl = 128 / S, kp = (k + cpl - 1) / cpl * cpl;
+  const size_t shm = ((size_t)kp * S + k) * sizeof(double);
+  const int64_t parts = gs_parts(D);
+  const dim3 grid((unsigned)parts), block(kTB);
+  if (S == 64)
+    hipLaunchKernelGGL(k_gemv_n_t<64>, grid, block, shm, s, D, k, V, c, w, partial);
+  else if (S == 32)
+    hipLaunchKernelGGL(k_gemv_n_t<32>, grid, block, shm, s, D, k, V, c, w, partial);
+  else
+    hipLaunchKernelGGL(k_gemv_n_t<16>, grid, block, shm, s, D, k, V, c, w, partial);
+  HIPC(hipGetLastError());
+  reduce_cols(s, partial, parts, k, c, tail, tail_add);
+  return true;
 }
 
 // ---- out = w / beta; a vanishing beta (breakdown) leaves zeros and raises flag ----

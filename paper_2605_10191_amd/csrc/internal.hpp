@@ -655,6 +655,16 @@ void materialize_csr(polfed_ctx* ctx, polfed_op* op);
 int64_t red_blocks(int64_t n);
 void dev_dot(hipStream_t s, int64_t n, const double* x, const double* y,
              double* partial, int64_t npart, double* out, int sqrt_out);
+// w -= V c, then c = V^T w, in one pass over V (ld = D) where the vectors are
+// long enough for it (false: nothing done); partial: gs_parts(D) doubles a
+// column, the workgroups of that pass (three a CU, of at least 64 rows) or the
+// row segments of a separate product.
+constexpr int64_t kGsMidMinRows = 1 << 13;
+inline int64_t gs_parts(int64_t D) {
+  return D >= kGsMidMinRows ? std::min<int64_t>(768, D / 64) : 1;
+}
+bool dev_gemv_n_t(hipStream_t s, int64_t D, int k, const double* V, double* c, double* w,
+                  double* partial, double* tail, int tail_add);
 void dev_gemv_t(hipStream_t s, int64_t D, int k, const double* V, int64_t ld,
                 const double* w, double* partial, int64_t nseg, double* c,
                 double* tail, int tail_add);

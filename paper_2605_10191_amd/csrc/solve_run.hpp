@@ -29,11 +29,12 @@ struct Basis {
 
 struct Ws {
   DevBuf w, c, partial, scal, flag, alpha, beta, bA, bB, v32, w32;
-  int64_t nseg = 0;
+  int64_t nseg = 0, parts = 0;
   int coef_cap = 0;
   void init(hipStream_t s, int64_t D, int max_cols, bool fp32) {
     w.alloc(std::max<int64_t>(D, 1) * sizeof(double));
     nseg = std::max<int64_t>(1, std::min<int64_t>(256, (D + 8191) / 8192));
+    parts = gs_parts(D);
     grow(s, max_cols);
     scal.alloc(64 * sizeof(double));
     flag.alloc(sizeof(int));
@@ -59,7 +60,7 @@ struct Ws {
     alpha = std::move(na);
     beta = std::move(nb);
     c.alloc((size_t)(max_cols + 1) * sizeof(double));
-    partial.alloc((size_t)nseg * (max_cols + 1) * sizeof(double) + 8192 * sizeof(double));
+    partial.alloc(((size_t)parts * (max_cols + 1) + 8192) * sizeof(double));
     coef_cap = max_cols;
   }
 };

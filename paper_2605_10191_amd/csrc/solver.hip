@@ -143,10 +143,12 @@ void cgs2_raw(hipStream_t s, int64_t D, int k1, const double* V, double* w,
               double* c, double* partial, int64_t nseg, int* flag, double* alpha_k,
               double* beta_next, double* v_next) {
   if (cgs2_team(s, D, k1, V, w, c, partial, flag, alpha_k, beta_next, v_next)) return;
-  for (int pass = 0; pass < 2; ++pass) {
-    dev_gemv_t(s, D, k1, V, D, w, partial, nseg, c, alpha_k, pass);
+  dev_gemv_t(s, D, k1, V, D, w, partial, nseg, c, alpha_k, 0);
+  if (!dev_gemv_n_t(s, D, k1, V, c, w, partial, alpha_k, 1)) {
     dev_gemv_n_sub(s, D, k1, V, D, c, w);
+    dev_gemv_t(s, D, k1, V, D, w, partial, nseg, c, alpha_k, 1);
   }
+  dev_gemv_n_sub(s, D, k1, V, D, c, w);
   dev_dot(s, D, w, w, partial, 1024, beta_next, 1);
   dev_scale_into(s, D, w, beta_next, v_next, flag);
 }
@@ -546,7 +548,7 @@ size_t SolveRun::bytes_at(int64_t D_, int m, int n, bool f32) {
   const size_t D = (size_t)std::max<int64_t>(D_, 1), vec = D * 8, M = (size_t)m, N = (size_t)n;
   const size_t nseg = (size_t)std::max<int64_t>(1, std::min<int64_t>(256, (D_ + 8191) / 8192));
   // basis (M + 2 columns) and the coefficient and partial-sum arrays
-  size_t b = (M + 2) * vec + (nseg * (M + 1) + 8192 + 3 * (M + 2)) * 8;
+  size_t b = (M + 2) * vec + ((size_t)gs_parts(D_) * (M + 1) + 8192 + 3 * (M + 2)) * 8;
   // w, the filter's two recurrence buffers, the FP32 copies of v and w,
   // and the fixed graph input (FP64)
   b += vec + (f32 ? 4 * D * 4 : 3 * vec) + chain_res_tail();
@@ -1002,7 +1004,7 @@ void lanczos_step(polfed_ctx* ctx, const polfed_op* op, double E_c, double dE,
   const int64_t nseg = std::max<int64_t>(1, std::min<int64_t>(256, (D + 8191) / 8192));
   double* c = static_cast<double*>(ctx_scratch(ctx, 1, (size_t)(k + 2) * sizeof(double)));
   double* part = static_cast<double*>(
-      ctx_scratch(ctx, 2, ((size_t)nseg * (k + 2) + 8192) * sizeof(double)));
+      ctx_scratch(ctx, 2, ((size_t)gs_parts(D) * (k + 2) + 8192) * sizeof(double)));
   int* flag = static_cast<int*>(ctx_scratch(ctx, 3, 64));
   double* vk = V + (size_t)k * D;
   if (precision == POLFED_FP32) {

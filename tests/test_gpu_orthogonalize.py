@@ -1,7 +1,8 @@
 """The orthogonalization of a Lanczos step at the sizes where its one-launch
 form begins, changes and ends: one basis vector, fewer rows than slabs, the
 change from 16 to 32 members, the largest basis of the rule and the first
-beyond it; with the identity as the filter (order 0), so that the step is the
+beyond it; of the pass that makes the two middle products at once, whose slabs
+have 64, 32 and 16 rows; with the identity as the filter (order 0), so that the step is the
 orthogonalization of v_k itself against a random basis whose v_k is not
 orthogonal to the others."""
 import sys
@@ -34,7 +35,10 @@ def ctx(pk):
 
 @pytest.mark.parametrize("L,N,k", [(4, 2, 0), (4, 2, 3), (6, 1, 4), (8, 4, 33), (12, 6, 0),
                                    (12, 6, 8), (12, 6, 276), (12, 6, 277), (14, 7, 581),
-                                   (14, 7, 582), (16, 8, 53), (16, 8, 54), (14, 6, 198)])
+                                   (14, 7, 582), (16, 8, 53), (16, 8, 54), (14, 6, 198),
+                                   (17, 8, 0), (17, 8, 6), (17, 8, 7), (17, 8, 40),
+                                   (16, 8, 103), (16, 8, 104), (16, 8, 207), (16, 8, 208),
+                                   (16, 8, 599), (16, 8, 600), (19, 9, 30)])
 def test_lanczos_step(pk, ctx, L, N, k):
     op = pk.Operator.xxz(ctx, L, N, 1.0, 1.0, wl.xxz_fields(L, 1.0, 2), True)
     D = op.D
