@@ -1276,21 +1276,24 @@ __global__ __launch_bounds__(kResThreads) void k_cgs2_team(
       v_next[r] = bload<double, kAuxAgent>(rw, (uint32_t)(r * 8), 0) * inv;
 }
 
-// Where it is the faster one.  The launches split the rows in segments of
-// 8,192, so below that they leave most of the chip idle and the line lies
-// where one XCD's path to V is the longer one (D = 3,432: 1.7 M entries 256 us
-// against 118); above, they do not (D = 12,870: 0.4 M entries 85 against 47,
-// 0.8 M 92 against 86, 1.3 M 104 against 112).  With many rows and few columns
-// the split by columns is the poor one (D = 24,310, k1 = 2: 52 against 69).
+// Where it is the faster one.  Below 8,192 rows the launches leave most of the
+// chip idle, and the line lies where one XCD's path to V is the longer one (D =
+// 3,432: 1.7 M entries 256 us against 118); above, the middle two products go
+// in one pass, and the line lies where V outgrows the XCD's L2 (D = 12,870:
+// 0.4 M entries 85 against 47, 0.6 M 63 against 82).  With many rows and few
+// columns the split by columns is the poor one (D = 24,310, k1 = 2: 52 against
+// 69).
 static bool orth_team(int64_t D, int k1) {
   return k1 >= 1 && k1 <= 4096 && D >= 1 && D <= 16384 &&
-         D * k1 <= (D <= 8192 ? 2000 : 700) * 1000;
+         D * k1 <= (D <= 8192 ? 2000 : 450) * 1000;
 }
 
 bool cgs2_team(hipStream_t s, int64_t D, int k1, const double* V, double* w, double* c,
                double* partial, int* flag, double* alpha, double* beta, double* v_next) {
   if (!orth_team(D, k1)) return false;
-  const int nm = D * k1 > 256 * 1000 ? 32 : 16;
+  // 32 members once a pass is longer than their barrier (0.21 M entries 38.0 us
+  // with 16, 31.9; 10 k entries 21.4, 22.4; eight members are no faster there)
+  const int nm = D * k1 > 100 * 1000 ? 32 : 16;
   // the team state and the norm's parts lie in the partial sums' 64 KB
   static_assert(sizeof(ResState) + 32 * sizeof(double) <= 8192 * sizeof(double), "partial");
   ResState* st = reinterpret_cast<ResState*>(partial);

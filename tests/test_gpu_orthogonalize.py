@@ -34,8 +34,8 @@ def ctx(pk):
 
 
 @pytest.mark.parametrize("L,N,k", [(4, 2, 0), (4, 2, 3), (6, 1, 4), (8, 4, 33), (12, 6, 0),
-                                   (12, 6, 8), (12, 6, 276), (12, 6, 277), (14, 7, 581),
-                                   (14, 7, 582), (16, 8, 53), (16, 8, 54), (14, 6, 198),
+                                   (12, 6, 8), (12, 6, 107), (12, 6, 108), (14, 7, 581),
+                                   (14, 7, 582), (16, 8, 33), (16, 8, 34), (14, 6, 198),
                                    (17, 8, 0), (17, 8, 6), (17, 8, 7), (17, 8, 40),
                                    (16, 8, 103), (16, 8, 104), (16, 8, 207), (16, 8, 208),
                                    (16, 8, 599), (16, 8, 600), (19, 9, 30)])
