@@ -215,36 +215,38 @@ __global__ __launch_bounds__(kResThreads) void k_res_build(ResBuild p) {
       }
     }
     // entry (m, j, slot, thread): the hops inside the slab (LDS rows), those
-    // leaving it (rows), the periodic bond.  A hop that leaves takes the slot
-    // of its bond among the bonds that leave in this wave, so that the wave's
-    // gather of a slot is one run of rows; in a wave with more such bonds
-    // than slots (at a slab's edge) each lane packs its own.
+    // leaving it (rows), the periodic bond.  A hop takes the slot of its bond
+    // among the bonds that stay in (or leave) the slab in this wave, so that
+    // the wave's access of a slot is mostly one run of rows: coalesced out of
+    // the slab, without bank conflicts in it.  In a wave with more such bonds
+    // than slots each lane packs its own.
     const int64_t per = (int64_t)(p.nl + p.nh + 1) * kResThreads;
     const int64_t e = ((int64_t)m * p.R + j) * per + threadIdx.x;
-    uint32_t out = 0;  // bonds that leave the slab in this row
-    int nl = 0;
+    uint32_t out = 0, in = 0;  // bonds that leave the slab in this row, that do not
     if (valid)
       chain_targets(p.L, p.periodic, s, r, s_binom, [&](int slot, int64_t to) {
-        if (to < row0 || to >= row1) {
+        if (to < row0 || to >= row1)
           out |= 1u << slot;
-        } else if (slot == 0 && p.sep) {
-          if (FILL) p.slot[e + (int64_t)(p.nl + p.nh) * kResThreads] = (uint32_t)(to - row0);
-        } else {
-          if (FILL) p.slot[e + (int64_t)nl * kResThreads] = (uint32_t)(to - row0);
-          ++nl;
-        }
+        else
+          in |= 1u << slot;
       });
-    if (p.sep) out &= ~1u;
-    const int nh = __popc(out);
-    uint32_t any = 0;
-    for (int b = 0; b < p.L; ++b)
-      if (__ballot((out >> b) & 1u)) any |= 1u << b;
+    const uint32_t own = p.sep ? ~1u : ~0u;  // a periodic bond of its own sign
+    const int nl = __popc(in & own), nh = __popc(out & own);
+    uint32_t any_in = 0, any_out = 0;
+    for (int b = 0; b < p.L; ++b) {
+      if (__ballot((in & own) >> b & 1u)) any_in |= 1u << b;
+      if (__ballot((out & own) >> b & 1u)) any_out |= 1u << b;
+    }
     if (FILL && valid) {
-      const uint32_t set = __popc(any) <= p.nh ? any : out;
+      const uint32_t si = __popc(any_in) <= p.nl ? any_in : in & own;
+      const uint32_t so = __popc(any_out) <= p.nh ? any_out : out & own;
       chain_targets(p.L, p.periodic, s, r, s_binom, [&](int slot, int64_t to) {
-        if (to >= row0 && to < row1) return;
-        const int k = slot == 0 && p.sep ? p.nh : __popc(set & ((1u << slot) - 1u));
-        p.slot[e + (int64_t)(p.nl + k) * kResThreads] = kResFar | (uint32_t)to;
+        const bool far = to < row0 || to >= row1;
+        const uint32_t below = (1u << slot) - 1u;
+        const int k = slot == 0 && p.sep ? p.nl + p.nh
+                      : far              ? p.nl + __popc(so & below)
+                                         : __popc(si & below);
+        p.slot[e + (int64_t)k * kResThreads] = far ? kResFar | (uint32_t)to : (uint32_t)(to - row0);
       });
     }
     if (FILL) {
@@ -863,8 +865,24 @@ std::shared_ptr<ResTable> build_table(hipStream_t s, const polfed_op* op, int ns
   int32_t h[2];
   HIPC(hipMemcpyAsync(h, cnt.get(), sizeof h, hipMemcpyDeviceToHost, s));
   HIPC(hipStreamSynchronize(s));
-  t->nl = b.nl = h[0];
-  t->nh = b.nh = h[1];
+  t->nl = h[0];
+  t->nh = h[1];
+  // as many slots inside the slab as the instantiation reads anyway: more waves
+  // then find room for every bond of their rows (FP64, us a step, packed by
+  // lane / by bond: 13 columns at L = 18 5.15 / 4.70, 32 at L = 17 5.15 / 4.75;
+  // the same where the barrier counts).  More slots out of the slab would be
+  // more loads.
+  if (t->nh == 0 && t->R <= 2 && t->nl <= 12) {
+    t->nl = 12;
+  } else if (t->R == 1 && t->nl <= 10 && t->nh <= 6) {
+    t->nl = 10;
+  } else if (t->R <= 3 && t->nl <= 14 && t->nh <= 10) {
+    t->nl = 14;
+  } else if (t->nl <= 15 && t->nh <= 11) {
+    t->nl = 15;
+  }
+  b.nl = t->nl;
+  b.nh = t->nh;
   const size_t n = (size_t)nslab * t->R * (t->nl + t->nh + 1) * kResThreads;
   t->slot.alloc(n * sizeof(uint32_t));
   t->state.alloc((size_t)op->D * sizeof(uint32_t));
