@@ -4,6 +4,7 @@
 // Krylov basis and checks), while the filter of all unfinished
 // realizations is one multi-column Clenshaw recurrence.
 #include <algorithm>
+#include <cstring>
 #include <cmath>
 #include <cstdio>
 #include <memory>
@@ -54,9 +55,13 @@ void BatchCoef::set(hipStream_t s, int nb_, const double* const* a, const int* K
     for (int i = 0; i <= K[c]; ++i) A[(size_t)i * nb + c] = a[c][i];
   host = A;
   this->K.assign(K, K + nb);
-  std::vector<float> A32(A.begin(), A.end());
-  upload(d64, A.data(), A.size(), s);
-  upload(d32, A32.data(), A32.size(), s);
+  const std::vector<float> A32(A.begin(), A.end());
+  const size_t n = A.size();
+  A.resize(n + (n + 1) / 2);  // the FP32 ones behind them, in one copy
+  std::memcpy(A.data() + n, A32.data(), n * sizeof(float));
+  upload(both, A.data(), A.size(), s);
+  d64.p = both.get();
+  d32.p = both.as<double>() + n;
   HIPC(hipStreamSynchronize(s));
 }
 

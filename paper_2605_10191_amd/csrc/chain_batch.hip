@@ -486,25 +486,33 @@ void ChainBatch::init(polfed_ctx* c, const polfed_op* const* o, int n) {
     std::copy(ops[i]->split_fab.begin(), ops[i]->split_fab.end(), fab.begin() + (size_t)i * 64);
     for (int64_t q = 0; q < nseg; ++q) dseg[(size_t)q * n + i] = ops[i]->split_dseg[q];
   }
-  hipStream_t s = ctx->stream;
-  upload(fab64, fab.data(), fab.size(), s);
-  upload(dseg64, dseg.data(), dseg.size(), s);
   std::vector<float> f32(fab.begin(), fab.end()), d32(dseg.begin(), dseg.end());
-  upload(fab32, f32.data(), f32.size(), s);
-  upload(dseg32, d32.data(), d32.size(), s);
   std::vector<double> fl((size_t)n * 33, 0.0);
   for (int i = 0; i < n; ++i) {
     std::copy(ops[i]->site_f.begin(), ops[i]->site_f.end(), fl.begin() + (size_t)i * 33);
     fl[(size_t)i * 33 + 32] = ops[i]->c0;
   }
-  upload(fields, fl.data(), fl.size(), s);
-  res_state.alloc(sizeof(ResState));
   std::vector<ChainCol> cd(n);
   for (int i = 0; i < n; ++i)
     cd[i] = {ops[i]->d_rec.as<int32_t>(), ops[i]->d_blobl64.get(), ops[i]->d_blobl32.get()};
-  upload(cols, cd.data(), cd.size(), s);
-  sc64.alloc((size_t)2 * n * sizeof(double));
-  sc32.alloc((size_t)2 * n * sizeof(float));
+  // one buffer and one copy for the tables (a copy each took 10 us of every
+  // batch call)
+  std::vector<unsigned char> host;
+  auto place = [&](const auto& v) {
+    const size_t at = (host.size() + 255) / 256 * 256, bytes = v.size() * sizeof(v[0]);
+    host.resize(at + bytes);
+    std::memcpy(host.data() + at, v.data(), bytes);
+    return at;
+  };
+  const size_t at[] = {place(fab), place(dseg), place(f32), place(d32), place(fl), place(cd)};
+  hipStream_t s = ctx->stream;
+  upload(tables, host.data(), host.size(), s);
+  DevView* const views[] = {&fab64, &dseg64, &fab32, &dseg32, &fields, &cols};
+  for (int i = 0; i < 6; ++i) views[i]->p = tables.as<unsigned char>() + at[i];
+  res_state.alloc(sizeof(ResState));
+  scales.alloc((size_t)2 * n * (sizeof(double) + sizeof(float)));
+  sc64.p = scales.get();
+  sc32.p = scales.as<double>() + 2 * n;
   HIPC(hipStreamSynchronize(s));
 }
 
@@ -516,12 +524,15 @@ void ChainBatch::set_scale(const double* E_c, const double* dE) {
     sc[i] = 2.0 / dE[i];
     sc[nb + i] = -2.0 * E_c[i] / dE[i];
   }
-  std::vector<float> s32(sc.begin(), sc.end());
+  const std::vector<float> s32(sc.begin(), sc.end());
+  const size_t n64 = sc.size();
+  sc.resize(n64 + (n64 + 1) / 2);  // the FP32 ones behind them
+  std::memcpy(sc.data() + n64, s32.data(), n64 * sizeof(float));
   this->E_c.assign(E_c, E_c + nb);
   this->dE.assign(dE, dE + nb);
   hipStream_t s = ctx->stream;
-  HIPC(hipMemcpyAsync(sc64.get(), sc.data(), sc.size() * sizeof(double), hipMemcpyHostToDevice, s));
-  HIPC(hipMemcpyAsync(sc32.get(), s32.data(), s32.size() * sizeof(float), hipMemcpyHostToDevice, s));
+  HIPC(hipMemcpyAsync(scales.get(), sc.data(), n64 * (sizeof(double) + sizeof(float)),
+                      hipMemcpyHostToDevice, s));
   HIPC(hipStreamSynchronize(s));
 }
 

@@ -473,15 +473,21 @@ void build_split_rank_tables(int L, int N, int Lb, std::vector<int32_t>& hi_off,
 
 // A batch of chain operators that share the off-diagonal pattern; column i
 // of every vector block belongs to ops[i].
+struct DevView {  // a part of a DevBuf
+  void* p = nullptr;
+  template <class T> T* as() const { return static_cast<T*>(p); }
+  void* get() const { return p; }
+};
 struct ChainBatch {
   polfed_ctx* ctx = nullptr;
   std::vector<const polfed_op*> ops;
   int nb = 0;
-  DevBuf fab64, fab32;    // [nb][64] low-bit field sums (bits 0-4 | 5-9)
-  DevBuf dseg64, dseg32;  // [nseg][nb] uniform diagonal part per segment
-  DevBuf sc64, sc32;      // [2][nb] sigma = 2/dE, tau = -2 E_c/dE
-  DevBuf fields;          // [nb][33] site terms and constant (resident kernel)
-  DevBuf cols;            // [nb] ChainCol
+  DevView fab64, fab32;    // [nb][64] low-bit field sums (bits 0-4 | 5-9)
+  DevView dseg64, dseg32;  // [nseg][nb] uniform diagonal part per segment
+  DevView sc64, sc32;      // [2][nb] sigma = 2/dE, tau = -2 E_c/dE
+  DevView fields;          // [nb][33] site terms and constant (resident kernel)
+  DevView cols;            // [nb] ChainCol
+  DevBuf tables, scales;   // what the views lie in
   DevBuf res_state;       // team state of the resident kernel
   std::vector<double> E_c, dE;  // host copies of each column's rescaling
   void init(polfed_ctx* c, const polfed_op* const* o, int n);

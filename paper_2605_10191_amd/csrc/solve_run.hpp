@@ -85,7 +85,8 @@ double step_bytes(const polfed_op* op, int precision);
 // Device coefficient table [(Kmax + 1)][nb] of a multi-column filter; column
 // c is zero above its own order K[c].
 struct BatchCoef {
-  DevBuf d64, d32;
+  DevBuf both;
+  DevView d64, d32;  // in it
   int nb = 0, Kmax = 0;
   std::vector<double> host;  // (Kmax + 1) x nb, column c of row i = a_c[i]
   std::vector<int> K;        // each column's own order
