@@ -201,16 +201,16 @@ polfed_status polfed_op_set_storage(polfed_op* op, int storage);
 /* Step-kernel variant of a matrix-free chain (XXZ, t-V) in one precision:
  * -1 = pick by timing on the next step (the default), 0 = segment kernel,
  * 1 = tile kernel with the largest tile, 2 = tile kernel with half that tile,
- * 3 = segment kernel with two adjacent rows per lane (16-byte accesses),
+ * 3 = two adjacent rows per lane (16-byte accesses; from L = 22 with the
+ * low-part tables in LDS),
  * 4 = segment kernel with each segment split between two wavefronts,
  * 5 = tile kernel with a quarter of the largest tile;
- * 6 .. 9 = staged-tile kernel (the tile's rows and segment records copied
- * to LDS by direct-to-LDS loads; the tile also spans the top state bit, so
- * the periodic bond is an LDS read): 6 the largest tile with one buffer and
- * 1024 threads, 7 half that tile with two buffers (the next tile is staged
- * while the current one is processed) and 512 threads, 8 half that tile
- * with one buffer, 9 the largest tile with two buffers (where the LDS holds
- * them, FP32);
+ * 6 .. 9 = staged-tile kernel (the tile's rows copied to LDS by
+ * direct-to-LDS loads): 6 a tile that also spans the top state bit, so that
+ * the periodic bond is an LDS read, with one buffer, 7 and 8 a tile of twice
+ * the consecutive rows without the top bit, with two buffers (the next tile is
+ * staged while the current one is processed) and with one, 9 as 6 with two
+ * buffers (where the LDS holds them);
  * -2 only reports the variant in use.
  * A variant that does not exist for the chain length and precision (tiles
  * need L >= 22) gives POLFED_ERR_INVALID.  For a quantum random energy model the variant is
@@ -222,7 +222,7 @@ polfed_status polfed_op_set_kernel(polfed_op* op, int precision, int variant, in
 /* Multi-column step kernel of batches of B chain realizations that share the
  * pattern of op (the batch's first operator), in one precision: -1 = pick by
  * timing at the next batched filter (the default), 0 / 1 = column-major
- * blocks with 16 / 8 columns per launch, 2 / 3 = interleaved blocks (the B
+ * blocks with all columns / 8 columns per launch, 2 / 3 = interleaved blocks (the B
  * columns of a row side by side, one 16-byte access per row and 2 FP64 or 4
  * FP32 columns; 2 / 4 workgroups per compute unit), 4 = every column
  * stepped by its own operator's tuned single-column kernel (the staged-tile
@@ -425,7 +425,8 @@ polfed_status polfed_block_lanczos_step(polfed_ctx* ctx, const polfed_op* op,
                                         double* Bn, int precision);
 /* Kernel polynomial method (Sec. 4.1 eq. dos_kpm, App. B): mu[n] for
  * n < N, the mean over R vectors r of <r| T_n(H~) |r> with H~ = (H - E_c)/dE,
- * by the three-term Chebyshev recurrence on the fused step kernel (FP64).
+ * by the three-term Chebyshev recurrence for the vectors, two moments a
+ * step from <t_n|t_n> and <t_{n-1}|t_n> (FP64).
  * r: device D x R column-major, or NULL: then vector c (0 <= c < R) has
  * entries sqrt(3) (2 u - 1), u = (z >> 11) / 2^53 for the splitmix64 output
  * z of seed + c at counter i + 1 (zero mean, unit variance).  mu: host [N].

@@ -405,7 +405,7 @@ class Operator:
 
     def set_batch_kernel(self, B: int, precision: int, variant: int) -> int:
         """Multi-column step kernel for batches of B realizations of this
-        pattern (-1 autotuned, 0/1 column-major with 16/8 columns per launch,
+        pattern (-1 autotuned, 0/1 column-major with all/8 columns per launch,
         2/3 interleaved with 2/4 workgroups per CU, 4 each column by its own
         single-column kernel, L >= 22, 5 the resident recurrence of short
         chains); returns the variant in use (-1 while not tuned)."""

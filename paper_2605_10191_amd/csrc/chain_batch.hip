@@ -5,11 +5,11 @@
 //     out_c = a_c v_c + h sigma_c (H_c b1_c) + h tau_c b1_c - b2_c
 // with h = 1, or 1/2 on the closing Clenshaw step.
 //
-// The row decoding of the split layout (low part, neighbour positions,
-// activity of the joining and periodic bonds, the interaction part of the
-// diagonal) is done once per segment and reused by every column.  Each lane
-// holds two adjacent rows, so the coalesced accesses move both in one
-// 16-byte instruction.  Only the
+// In the interleaved and row-group kernels here the row decoding of the split
+// layout (low part, neighbour positions, activity of the joining and periodic
+// bonds, the interaction part of the diagonal) is done once for a group of
+// columns; the column-major and resident forms are in chain.hip and
+// resident.hip.  Only the
 // field part of the diagonal is per column: the sum over the low bits comes
 // from two 32-entry LDS tables per column (bits 0-4 and 5-9) and the sum over
 // the high bits plus the constant is one wave-uniform value per segment and
@@ -536,8 +536,8 @@ void ChainBatch::set_scale(const double* E_c, const double* dE) {
   HIPC(hipStreamSynchronize(s));
 }
 
-// Multi-column step variants: 0 and 1 the column-major kernel with 16 and
-// 8 columns per launch, 2 and 3 the interleaved kernel with 2 and 4
+// Multi-column step variants: 0 and 1 the direct kernel on column-major blocks,
+// all or 8 columns per launch, 2 and 3 the interleaved kernel with 2 and 4
 // workgroups per compute unit, 4 each column by its operator's own kernel,
 // 5 the resident recurrence, 6 and 7 the row-group kernel with 4 and
 // 8 workgroups per compute unit.

@@ -223,7 +223,6 @@ constexpr int kChainLoBits = 10;      // Lb = min(10, L / 2); blocks <= 252 rows
 constexpr int kChainSegRows = 128;   // rows per wavefront segment
 constexpr int kChainStageRows = 256;  // LDS rows staged per wavefront
 constexpr int kChainBlocksPerCU = 4;  // persistent blocks per compute unit
-constexpr int kBatchMaxCols = 16;     // columns per multi-column launch
 // A filter of more Clenshaw steps than this runs as direct launches: a graph
 // of that many kernel nodes costs more to build than it saves.
 constexpr int kGraphMaxSteps = 65536;
@@ -507,7 +506,7 @@ template <typename T>
 void chain_direct_cols(hipStream_t s, const ChainBatch& bt, int col0, int ncol, T half,
                        const T* acoef, const T* v, const T* b1, const T* b2, T* out);
 // The multi-column step kernel picked by timing for this batch width and
-// precision (kept per operator pattern): 0, 1 column-major blocks (16 or 8
+// precision (kept per operator pattern): 0, 1 column-major blocks (all or 8
 // columns per launch), 2, 3 interleaved blocks (element (r, c) at r nb + c;
 // 2 or 4 workgroups per compute unit), 4 column-major blocks with every
 // column stepped by its operator's own tuned single-column kernel (the

@@ -16,9 +16,9 @@
 //   - a step ends with a barrier of the team's members (0.9 us for 32 of
 //     them; a launch in a replayed graph takes 1.6 us before it does
 //     anything) instead of a kernel boundary.
-// Measured (FP64, us a step, before -> here): one column at L = 12 3.6 -> 1.0,
-// L = 16 4 -> 2.0, L = 18 5 -> 3.5; 16 columns at L = 14 4.1 -> 1.6; 13 columns
-// at L = 18 17.3 -> 5.1, of which the barrier and the gathers' round trip are
+// Measured (FP64, us a step, before -> here): one column at L = 12 3.6 -> 1.2,
+// L = 16 3.9 -> 1.9, L = 18 4.5 -> 3.0; 13 columns at L = 14 4.2 -> 1.7; 13 columns
+// at L = 18 17.3 -> 4.5, of which the barrier and the gathers' round trip are
 // 1.3 and the LDS reads of the hops most of the rest.
 // The columns are spread over the eight XCDs, so no data crosses them.
 //
