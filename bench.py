@@ -80,9 +80,9 @@ def measured_traffic(kernel: str):
     return k.get("bytes_per_launch") if k else None
 
 
-# staged-tile variants 6-9: (tile bits below the largest, wrap, double
+# staged-tile variants 6-9: (tile bits below the wrapped tile's, wrap, double
 # buffer, threads per workgroup), as in the library's table
-WT_CONF = {6: (0, 1, 0, 1024), 7: (1, 1, 1, 512), 8: (1, 1, 0, 512), 9: (0, 1, 1, 1024)}
+WT_CONF = {6: (0, 1, 0, 1024), 7: (-1, 0, 1, 512), 8: (-1, 0, 0, 1024), 9: (0, 1, 1, 1024)}
 
 
 def step_kernel_name(op, prec, tname: str, L: int) -> str:
@@ -95,7 +95,7 @@ def step_kernel_name(op, prec, tname: str, L: int) -> str:
         kw = min(4, L - Lb - 10) - dkt
         return f"k_chain_wt<{tname}, {L}, {kw}, {wr}, {db}, {nt}>"
     if var == 3:
-        return f"k_chain_pair<{tname}, {L}>"
+        return f"k_chain_pair<{tname}, {L}>" if L >= 22 else f"k_chain_direct<{tname}, {L}, false>"
     if var == 4:
         return f"k_chain_split<{tname}, {L}, 2>"
     if var in (1, 2):
