@@ -24,6 +24,17 @@ namespace polfed {
 constexpr int kQremThreads = 512;
 constexpr int kQremMaxTileBits = 12;
 
+// Whether the streamed vectors of n elements in all (the energies, v, b_{i+1},
+// b_{i+2} and the output) are read past the caches: once they are more than the
+// 256 MB memory-side cache can keep a useful part of from step to step.  us a
+// step, past the caches / through them: FP64 L = 20 (42 MB) 13.9 / 12.3, L = 23
+// (336 MB) 111.6 / 110.0, L = 24 (671 MB) 243.8 / 252.3; FP32 L = 24 (336 MB)
+// 140.2 / 132.3, L = 25 (671 MB) 280.9 / 296.0.
+template <typename T>
+__device__ __forceinline__ bool qrem_stream_nt(int64_t n) {
+  return n * (int64_t)sizeof(T) > 500 * 1000 * 1000;
+}
+
 template <typename T, int TB>
 __global__ __launch_bounds__(kQremThreads) void k_qrem_step(
     int L, int64_t ntiles, int nxcd, T gamma, T sigma, T tau, T a, const T* __restrict__ E,
@@ -32,6 +43,7 @@ __global__ __launch_bounds__(kQremThreads) void k_qrem_step(
   constexpr int PPT = NP > kQremThreads ? NP / kQremThreads : 1;  // pairs per thread
   constexpr uint32_t W = sizeof(T);
   __shared__ __attribute__((aligned(16))) T tile[2 * NP];
+  const bool nt = qrem_stream_nt<T>(5 * (int64_t)(vbytes / W));
   const rsrc_t rb1 = make_rsrc(b1, vbytes), rE = make_rsrc(E, vbytes);
   const rsrc_t rv = make_rsrc(v ? v : b1, v ? vbytes : 0);
   const rsrc_t rb2 = make_rsrc(b2 ? b2 : b1, b2 ? vbytes : 0);
@@ -75,13 +87,13 @@ __global__ __launch_bounds__(kQremThreads) void k_qrem_step(
           s0 += g0;
           s1 += g1;
         }
-        T e0, e1, v0 = T(0), v1 = T(0), c0 = T(0), c1 = T(0);
-        bload2<T>(rE, vo, toff, e0, e1);
-        if (v) bload2<T>(rv, vo, toff, v0, v1);
-        if (b2) bload2<T>(rb2, vo, toff, c0, c1);
-        const T h0 = e0 * x[j][0] - gamma * s0, h1 = e1 * x[j][1] - gamma * s1;
-        const T o0 = a * v0 + sigma * h0 + tau * x[j][0] - c0;
-        const T o1 = a * v1 + sigma * h1 + tau * x[j][1] - c1;
+        T e[2], vv[2] = {T(0), T(0)}, c[2] = {T(0), T(0)};
+        bload_stream<T, 2>(rE, vo, toff, nt, e);
+        if (v) bload_stream<T, 2>(rv, vo, toff, nt, vv);
+        if (b2) bload_stream<T, 2>(rb2, vo, toff, nt, c);
+        const T h0 = e[0] * x[j][0] - gamma * s0, h1 = e[1] * x[j][1] - gamma * s1;
+        const T o0 = a * vv[0] + sigma * h0 + tau * x[j][0] - c[0];
+        const T o1 = a * vv[1] + sigma * h1 + tau * x[j][1] - c[1];
         bstore2<kAuxNT>(o0, o1, ro, vo, toff);
       }
     }
@@ -103,6 +115,7 @@ __global__ __launch_bounds__(kQremThreads) void k_qrem_step_multi(
   constexpr uint32_t W = sizeof(T);
   __shared__ __attribute__((aligned(16))) T tile[NC][2 * NP];
   const uint32_t vbytes = (uint32_t)(D * W);
+  const bool nt = qrem_stream_nt<T>((1 + 4 * NC) * D);
   const rsrc_t rE = make_rsrc(E, vbytes);
   const int xcd = blockIdx.x % nxcd;
   const int64_t per_xcd = gridDim.x / nxcd;
@@ -129,8 +142,8 @@ __global__ __launch_bounds__(kQremThreads) void k_qrem_step_multi(
       const int q = threadIdx.x + j * kQremThreads;
       if (q < NP) {
         const uint32_t vo = (uint32_t)(2 * q) * W;
-        T e0, e1;
-        bload2<T>(rE, vo, toff, e0, e1);
+        T e[2];
+        bload_stream<T, 2>(rE, vo, toff, nt, e);
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
           const rsrc_t rb1 = make_rsrc(b1 + (size_t)c * D, vbytes);
@@ -150,12 +163,12 @@ __global__ __launch_bounds__(kQremThreads) void k_qrem_step_multi(
             s0 += g0;
             s1 += g1;
           }
-          T v0 = T(0), v1 = T(0), c0 = T(0), c1 = T(0);
-          if (v) bload2<T>(make_rsrc(v + (size_t)c * D, vbytes), vo, toff, v0, v1);
-          if (b2) bload2<T>(make_rsrc(b2 + (size_t)c * D, vbytes), vo, toff, c0, c1);
-          const T h0 = e0 * x[c][j][0] - gamma * s0, h1 = e1 * x[c][j][1] - gamma * s1;
-          const T o0 = a * v0 + sigma * h0 + tau * x[c][j][0] - c0;
-          const T o1 = a * v1 + sigma * h1 + tau * x[c][j][1] - c1;
+          T vv[2] = {T(0), T(0)}, bt[2] = {T(0), T(0)};
+          if (v) bload_stream<T, 2>(make_rsrc(v + (size_t)c * D, vbytes), vo, toff, nt, vv);
+          if (b2) bload_stream<T, 2>(make_rsrc(b2 + (size_t)c * D, vbytes), vo, toff, nt, bt);
+          const T h0 = e[0] * x[c][j][0] - gamma * s0, h1 = e[1] * x[c][j][1] - gamma * s1;
+          const T o0 = a * vv[0] + sigma * h0 + tau * x[c][j][0] - bt[0];
+          const T o1 = a * vv[1] + sigma * h1 + tau * x[c][j][1] - bt[1];
           bstore2<kAuxNT>(o0, o1, make_rsrc(out + (size_t)c * D, vbytes), vo, toff);
         }
       }
