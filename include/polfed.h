@@ -467,6 +467,8 @@ typedef struct {
                           filter reuses the pick of an earlier batch of the
                           same chain pattern, width, precision and order to a
                           factor of two), 1 = always graph, 2 = never.
+                          With 0 a solve of a short chain (up to 2,048 rows)
+                          may compute P(H~) once as a matrix and apply that.
                           Served requests always launch directly (the
                           server's threads capture no graphs: a device
                           synchronization or synchronous copy on another

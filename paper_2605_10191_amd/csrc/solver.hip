@@ -646,10 +646,19 @@ void SolveRun::filter_self() {
     if (!fp32 && mode == kDirect && p.graph == 0 && !take && chain_dense_pays(op, pl.K, cap)) {
       op_tune(s, op, false);  // the operator's tables
       const size_t n = (size_t)D * D * sizeof(double);
-      dense.alloc(n);
-      DevBuf X(n), Y(n), st(chain_dense_bytes(op));
-      if (chain_dense_build(s, op, pl.E_c, pl.dE, a.data(), pl.K, dense.as<double>(),
-                            X.as<double>(), Y.as<double>(), st.get()))
+      DevBuf X, Y, st;
+      bool room = true;  // without the memory for it the recurrence goes on
+      try {
+        dense.alloc(n);
+        X.alloc(n);
+        Y.alloc(n);
+        st.alloc(chain_dense_bytes(op));
+      } catch (const std::exception&) {
+        (void)hipGetLastError();
+        room = false;
+      }
+      if (room && chain_dense_build(s, op, pl.E_c, pl.dE, a.data(), pl.K, dense.as<double>(),
+                                    X.as<double>(), Y.as<double>(), st.get()))
         dense_mode = kDenseYes;
       else
         dense.release();
