@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "../../include/polfed.h"
+#include "res_shape.hpp"
 
 namespace polfed {
 
@@ -519,26 +520,6 @@ int batch_variant(hipStream_t s, const ChainBatch& bt);
 // tables of one column fit the LDS of a compute unit.
 template <typename T>
 bool chain_lds_filter_fits(const polfed_op* op0);
-// Resident recurrence (resident.hip): the K steps of a column or a pair of
-// columns in one launch, by a team of workgroups on one XCD.
-constexpr int kResThreads = 512;  // up to 256 VGPRs a lane for the rows' state
-constexpr int kResWaves = kResThreads / 64;
-constexpr int kResMaxL = 20;
-constexpr int kResMaxPairRows = 3;  // rows a thread of a pair of columns
-constexpr int kResMaxRows = 6;      // rows a thread of a single column
-constexpr int kResMaxSlabs = 32;
-constexpr int kResTeamsPerXcd = 16;
-struct ResTeam {
-  int joined, n, group[2];
-  int pad0[12];
-  int flag[kResMaxSlabs];  // barriers each member has reached
-};
-struct ResState {
-  int slots[16 * 16];  // workgroups that joined, per XCD, a cache line apart
-  int queue, err;
-  int pad[14];
-  ResTeam teams[16 * kResTeamsPerXcd];
-};
 // Entries of the slab tables: an LDS row, kResFar | row of another slab, or
 // kResNone.
 constexpr uint32_t kResFar = 1u << 31, kResNone = 0xFFFFFFFFu;
@@ -606,10 +587,11 @@ void chain_dense_apply(hipStream_t s, int64_t D, const double* P, const double* 
 bool cgs2_team(hipStream_t s, int64_t D, int k1, const double* V, double* w, double* c,
                double* partial, int* flag, double* alpha, double* beta, double* v_next);
 // Products of the Chebyshev vectors t_n(H~) v of nb columns (kpm.hip).
-bool chain_res_moments_fit(hipStream_t s, const polfed_op* op, int nb);
-size_t chain_res_moments_bytes(const polfed_op* op, int M, int nb);
-void chain_res_moments(hipStream_t s, const polfed_op* op, double E_c, double dE, int M, int nb,
-                       const double* v, double* X, double* Y, void* ws, double* dots);
+bool chain_res_moments_fit(hipStream_t s, const polfed_op* op, int width);
+size_t chain_res_moments_bytes(const polfed_op* op, int M, int width);
+void chain_res_moments(hipStream_t s, const polfed_op* op, double E_c, double dE, int M, int width,
+                       int nb, const double* v, double* X, double* Y, const DevBuf& ws,
+                       double* dots);
 template <typename T>
 void chain_res_batch(hipStream_t s, const ChainBatch& bt, const T* A, int K, const T* v, T* w,
                      T* bufA, T* bufB);

@@ -142,7 +142,7 @@ void kpm_moments(polfed_ctx* ctx, const polfed_op* op, double E_c, double dE, in
       HIPC(hipGetLastError());
       HIPC(hipMemcpyAsync(h0.data(), d0.get(), (size_t)2 * nb * sizeof(double),
                           hipMemcpyDeviceToHost, s));
-      chain_res_moments(s, op, E_c, dE, M, nb, vc, X.as<double>(), Y.as<double>(), ws.get(),
+      chain_res_moments(s, op, E_c, dE, M, cols, nb, vc, X.as<double>(), Y.as<double>(), ws,
                         dots.data());
       for (int c = 0; c < nb; ++c)
         add(h0[2 * c], [&](int n) { return dots[((size_t)(n - 1) * 2) * nb + c]; },

@@ -1,0 +1,112 @@
+// Shapes and workspaces of the resident recurrence (resident.hip): how the
+// columns of a batch go to teams, and where a call's small arrays lie.  Plain
+// C++, read by the launches and by everything that sizes a buffer for them, so
+// that the two cannot differ.
+#pragma once
+
+#include <algorithm>
+#include <cstddef>
+#include <cstdint>
+
+namespace polfed {
+
+// The K steps of a column or a pair of columns in one launch, by a team of
+// workgroups on one XCD.
+constexpr int kResThreads = 512;  // up to 256 VGPRs a lane for the rows' state
+constexpr int kResWaves = kResThreads / 64;
+constexpr int kResMaxL = 20;
+constexpr int kResMaxPairRows = 3;  // rows a thread of a pair of columns
+constexpr int kResMaxRows = 6;      // rows a thread of a single column
+constexpr int kResMaxSlabs = 32;
+constexpr int kResTeamsPerXcd = 16;
+struct ResTeam {
+  int joined, n, group[2];
+  int pad0[12];
+  int flag[kResMaxSlabs];  // barriers each member has reached
+};
+struct ResState {
+  int slots[16 * 16];  // workgroups that joined, per XCD, a cache line apart
+  int queue, err;
+  int pad[14];
+  ResTeam teams[16 * kResTeamsPerXcd];
+};
+
+// Slabs of a column (a power of two), pairs of columns sharing a team, rows a
+// thread.
+struct ResShape {
+  int nslab = 0, pairs = 0, ngrp = 0, teams = 0, R = 0;
+  double us = 1e30;  // of a step, by the model below
+};
+
+inline int res_rows(int64_t D, int nslab) { return (int)((D + nslab - 1) / nslab); }
+inline int res_r(int64_t D, int nslab) {
+  return (res_rows(D, nslab) + kResThreads - 1) / kResThreads;
+}
+
+// Measured on an MI355X (FP64, us a step): slabs 1, 8, 16, 32 with one row a
+// thread 1.0 (two rows), 1.4, 1.6, 2.0; another row a thread adds 0.75, with
+// a pair of columns 1.2.  The model below follows these within 15% and picks
+// the cheapest shape: one workgroup up to 1,024 rows, one row a thread as
+// long as 32 slabs allow it, pairs once there are more columns than teams.
+// (nslab 0: none.)
+inline ResShape res_shape_at(int64_t D, int nb, int nslab) {
+  ResShape best;
+  const int R = res_r(D, nslab);
+  if (R > kResMaxRows || (nslab == 1 && R > 2)) return best;
+  const int teams = nslab == 1 ? 256 : 8 * std::min(kResMaxSlabs / nslab, kResTeamsPerXcd);
+  const double base = nslab == 1 ? 0.3 : 0.5 + 0.0235 * nslab;
+  for (int pair = 0; pair < 2; ++pair) {
+    ResShape x;
+    x.nslab = nslab;
+    x.teams = teams;
+    x.R = R;
+    if (pair && R > kResMaxPairRows) continue;
+    const int per = pair ? 2 : 1;
+    const int rounds = (nb + per * teams - 1) / (per * teams);
+    if (pair) {
+      // as many single columns as the rounds have room for
+      x.pairs = std::max(0, nb - rounds * teams);
+      if (x.pairs == 0) continue;
+    }
+    x.ngrp = nb - x.pairs;
+    x.us = rounds * (base + (pair ? 1.2 : 0.75) * R);
+    if (x.us < best.us) best = x;
+  }
+  return best;
+}
+inline ResShape res_shape(int64_t D, int nb) {
+  ResShape best;
+  for (int nslab = 1; nslab <= kResMaxSlabs; nslab *= 2) {
+    const ResShape x = res_shape_at(D, nb, nslab);
+    if (x.us < best.us) best = x;
+  }
+  return best;
+}
+
+inline size_t res_align(size_t n) { return (n + 255) / 256 * 256; }
+
+// M steps of the Chebyshev vectors of nb columns out of groups of width
+// columns (kpm.hip): the byte offsets of the scales, the sums and the partial
+// products behind the team state, and the bytes in all.  Every group takes the
+// slabs of a full one, so that a shorter last group needs no more room and
+// reads the same tables (its own best shape can have more slabs than there are
+// columns fewer: D = 5,005 4 slabs for 64 columns, 16 for 32).
+struct ResMomentsPlan {
+  ResShape shape;
+  int64_t count = 0;  // products: M x 2 x nb
+  size_t sc = 0, sums = 0, part = 0, bytes = 0;
+};
+inline ResMomentsPlan res_moments_plan(int64_t D, int M, int width, int nb) {
+  ResMomentsPlan p;
+  const int nslab = res_shape(D, width).nslab;
+  if (nslab == 0 || nb > width) return p;
+  p.shape = res_shape_at(D, nb, nslab);
+  p.count = (int64_t)M * 2 * nb;
+  p.sc = res_align(sizeof(ResState));
+  p.sums = res_align(p.sc + (size_t)2 * nb * sizeof(double));
+  p.part = p.sums + (size_t)p.count * sizeof(double);
+  p.bytes = p.part + (size_t)p.count * nslab * kResWaves * sizeof(double);
+  return p;
+}
+
+}  // namespace polfed

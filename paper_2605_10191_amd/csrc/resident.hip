@@ -771,49 +771,6 @@ void put_coefs(hipStream_t s, const double* a, int bot, int top, T* A) {
   HIPC(hipGetLastError());
 }
 
-// How the columns of a batch go to teams: slabs of a column (a power of two),
-// pairs of columns sharing a team, rows a thread.
-struct ResShape {
-  int nslab = 0, pairs = 0, ngrp = 0, teams = 0, R = 0;
-  double us = 1e30;  // of a step, by the model below
-};
-
-int res_rows(int64_t D, int nslab) { return (int)((D + nslab - 1) / nslab); }
-int res_r(int64_t D, int nslab) { return (res_rows(D, nslab) + kResThreads - 1) / kResThreads; }
-
-// Measured on an MI355X (FP64, us a step): slabs 1, 8, 16, 32 with one row a
-// thread 1.0 (two rows), 1.4, 1.6, 2.0; another row a thread adds 0.75, with
-// a pair of columns 1.2.  The model below follows these within 15% and picks
-// the cheapest shape: one workgroup up to 1,024 rows, one row a thread as
-// long as 32 slabs allow it, pairs once there are more columns than teams.
-ResShape res_shape(int64_t D, int nb) {
-  ResShape best;
-  for (int nslab = 1; nslab <= kResMaxSlabs; nslab *= 2) {
-    const int R = res_r(D, nslab);
-    if (R > kResMaxRows || (nslab == 1 && R > 2)) continue;
-    const int teams = nslab == 1 ? 256 : 8 * std::min(kResMaxSlabs / nslab, kResTeamsPerXcd);
-    const double base = nslab == 1 ? 0.3 : 0.5 + 0.0235 * nslab;
-    for (int pair = 0; pair < 2; ++pair) {
-      ResShape x;
-      x.nslab = nslab;
-      x.teams = teams;
-      x.R = R;
-      if (pair && R > kResMaxPairRows) continue;
-      const int per = pair ? 2 : 1;
-      const int rounds = (nb + per * teams - 1) / (per * teams);
-      if (pair) {
-        // as many single columns as the rounds have room for
-        x.pairs = std::max(0, nb - rounds * teams);
-        if (x.pairs == 0) continue;
-      }
-      x.ngrp = nb - x.pairs;
-      x.us = rounds * (base + (pair ? 1.2 : 0.75) * R);
-      if (x.us < best.us) best = x;
-    }
-  }
-  return best;
-}
-
 // An instantiation that covers a table.
 bool res_instance(const ResTable& t) {
   if (t.nh == 0) return t.R <= 2 && t.nl <= 12;
@@ -1383,27 +1340,30 @@ __global__ __launch_bounds__(256) void k_res_sum(const double* part, int n, int6
   if ((threadIdx.x & 63) == 0) out[k] = x;
 }
 
-bool chain_res_moments_fit(hipStream_t s, const polfed_op* op, int nb) {
-  return !op->forced[0] && chain_res_batch_fits(s, op, nb);
+bool chain_res_moments_fit(hipStream_t s, const polfed_op* op, int width) {
+  return !op->forced[0] && chain_res_batch_fits(s, op, width);
 }
 
-size_t chain_res_moments_bytes(const polfed_op* op, int M, int nb) {
-  const ResShape x = res_shape(op->D, nb);
-  const size_t sums = (size_t)M * 2 * nb;
-  return sizeof(ResState) + 4096 + (sums * x.nslab * kResWaves + sums) * sizeof(double);
+size_t chain_res_moments_bytes(const polfed_op* op, int M, int width) {
+  return res_moments_plan(op->D, M, width, width).bytes;
 }
 
 // dots[n - 1][0] = <t_n|t_n>, dots[n - 1][1] = <t_{n-1}|t_n> of every column
-// for n = 1 .. M (host, [M][2][nb]); v: D x nb, X and Y: its two buffers.
-void chain_res_moments(hipStream_t s, const polfed_op* op, double E_c, double dE, int M, int nb,
-                       const double* v, double* X, double* Y, void* ws, double* dots) {
-  const ResShape x = res_shape(op->D, nb);
+// for n = 1 .. M (host, [M][2][nb]); v: D x nb, X and Y: its two buffers; nb
+// <= width columns, ws chain_res_moments_bytes of the width.
+void chain_res_moments(hipStream_t s, const polfed_op* op, double E_c, double dE, int M, int width,
+                       int nb, const double* v, double* X, double* Y, const DevBuf& ws,
+                       double* dots) {
+  const ResMomentsPlan pl = res_moments_plan(op->D, M, width, nb);
+  const ResShape& x = pl.shape;
+  REQUIRE(x.nslab > 0 && pl.bytes <= ws.bytes(), "kpm: workspace of another width");
   const auto t = res_table(s, op, x.nslab, true);
   REQUIRE(t && res_instance(*t), "kpm: no resident recurrence for this chain");
-  ResState* st = (ResState*)ws;
-  double* sc = (double*)((unsigned char*)ws + (sizeof(ResState) + 255) / 256 * 256);
-  double* sums = sc + 2 * nb + 32;
-  const int64_t count = (int64_t)M * 2 * nb;
+  unsigned char* base = ws.as<unsigned char>();
+  ResState* st = (ResState*)base;
+  double* sc = (double*)(base + pl.sc);
+  double* sums = (double*)(base + pl.sums);
+  const int64_t count = pl.count;
   ResArgs<double> r{};
   r.L = op->L;
   r.N = op->N;
@@ -1421,7 +1381,7 @@ void chain_res_moments(hipStream_t s, const polfed_op* op, double E_c, double dE
   r.X = X;
   r.Y = Y;
   r.st = st;
-  r.part = sums + count;
+  r.part = (double*)(base + pl.part);
   r.i_all = M - 1;
   res_run<true>(s, *t, x, r, M, kResChunk, [&](ResArgs<double>& q, int, int) {
     hipLaunchKernelGGL((k_res_begin<double>), dim3(8), dim3(256), 0, s, q.st, sc, 2.0 / dE,

@@ -1,0 +1,73 @@
+"""Shapes and workspaces of the resident recurrence, on the CPU: the header that
+the launches and the buffers' sizes are computed from, compiled as it is and
+walked over every chain that takes this path (L <= 20)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2605_10191_amd", "csrc")
+
+PRELUDE = """
+#include <cstdio>
+#include <set>
+#include "res_shape.hpp"
+using namespace polfed;
+static std::set<int64_t> sizes() {  // D of the chains up to L = 20
+  std::set<int64_t> s;
+  for (int L = 2; L <= kResMaxL; ++L) {
+    int64_t d = 1;
+    for (int n = 0; n <= L; ++n) {
+      s.insert(d);
+      d = d * (L - n) / (n + 1);
+    }
+  }
+  return s;
+}
+"""
+
+
+def run_host(tmp_path, main):
+    src, exe = tmp_path / "t.cpp", tmp_path / "t"
+    src.write_text(PRELUDE + main)
+    cxx = shutil.which("g++") or "g++"
+    subprocess.run([cxx, "-std=c++17", "-O1", f"-I{CSRC}", str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+    return r.stdout
+
+
+@pytest.mark.parametrize("M", [4, 100, 2048])
+def test_groups_of_kpm_vectors_fit_one_workspace(tmp_path, M):
+    """A group of nb <= width vectors: its arrays lie one behind the other
+    inside what the full width's group asked for, and it has the slabs (and so
+    the tables) of that group."""
+    out = run_host(tmp_path, """
+int main() {
+  const int M = %d;
+  long n = 0;
+  for (int64_t D : sizes())
+    for (int width = 1; width <= 64; ++width) {
+      const ResMomentsPlan full = res_moments_plan(D, M, width, width);
+      for (int nb = 1; nb <= width; ++nb) {
+        const ResMomentsPlan p = res_moments_plan(D, M, width, nb);
+        ++n;
+        bool ok = p.shape.nslab == full.shape.nslab;
+        if (ok && p.shape.nslab) {
+          const size_t sums = (size_t)M * 2 * nb * 8;
+          ok = p.shape.ngrp + p.shape.pairs == nb && p.sc >= sizeof(ResState) &&
+               p.sums >= p.sc + 16 * (size_t)nb && p.part >= p.sums + sums &&
+               p.part + sums * p.shape.nslab * kResWaves <= full.bytes;
+        }
+        if (!ok) {
+          std::printf("D = %%ld, %%d of %%d columns\\n", (long)D, nb, width);
+          return 1;
+        }
+      }
+    }
+  std::printf("%%ld\\n", n);
+}
+""" % M)
+    assert int(out) > 50000
