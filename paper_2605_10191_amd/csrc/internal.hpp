@@ -557,18 +557,12 @@ struct ResTable {
 };
 // Whether filters of op in this precision run as one resident launch (short
 // matrix-free chains whose step kernel is not forced, quantum suns); builds a
-// chain's tables for it (not while s is captured); the bytes such a filter
-// needs behind the D elements of its first recurrence buffer.
+// chain's tables for it (not while s is captured).
 bool res_applies(const polfed_op* op, bool fp32);
 void chain_res_prepare(hipStream_t s, const polfed_op* op, bool fp32);
-size_t chain_res_tail();
-// Steps from which a filter goes that way: the resident launch itself
-// (joining, tables, two small kernels) takes about 20 us.
-constexpr int kResMinSteps = 16;
-constexpr int kResChunk = 8192;  // steps of one launch
 // Bytes of a filter's first recurrence buffer for n elements.
 inline size_t filter_buf_bytes(int64_t n, size_t elem) {
-  return (size_t)std::max<int64_t>(n, 1) * elem + chain_res_tail();
+  return (size_t)std::max<int64_t>(n, 1) * elem + ResTail::bytes;
 }
 // The filter as one resident launch; false (nothing done) where it does not
 // apply or K is small.

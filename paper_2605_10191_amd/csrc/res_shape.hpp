@@ -85,6 +85,21 @@ inline ResShape res_shape(int64_t D, int nb) {
 
 inline size_t res_align(size_t n) { return (n + 255) / 256 * 256; }
 
+// Steps from which a filter goes this way: the resident launch itself
+// (joining, tables, two small kernels) takes about 20 us.
+constexpr int kResMinSteps = 16;
+constexpr int kResChunk = 8192;  // steps of one launch
+
+// What a single column's filter keeps behind the D elements of its first
+// recurrence buffer, as byte offsets from the next multiple of 256: the team
+// state, the scale (two elements) and a chunk's coefficients.
+struct ResTail {
+  static constexpr size_t st = 0, sc = (sizeof(ResState) + 255) / 256 * 256, A = sc + 256,
+                          end = A + (size_t)(kResChunk + 1) * sizeof(double);
+  // bytes to allocate behind an element that may lie anywhere
+  static constexpr size_t bytes = 255 + end;
+};
+
 // M steps of the Chebyshev vectors of nb columns out of groups of width
 // columns (kpm.hip): the byte offsets of the scales, the sums and the partial
 // products behind the team state, and the bytes in all.  Every group takes the

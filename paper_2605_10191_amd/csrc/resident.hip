@@ -923,10 +923,6 @@ void chain_res_prepare(hipStream_t s, const polfed_op* op, bool fp32) {
   if (chain_res_applies(op, fp32)) (void)res_table(s, op, res_shape(op->D, 1).nslab, true);
 }
 
-size_t chain_res_tail() {
-  return 256 + sizeof(ResState) + 256 + (size_t)(kResChunk + 1) * sizeof(double);
-}
-
 template <typename T>
 static bool chain_res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const double* a,
                       int K, const T* v, T* w, T* bufA, T* bufB) {
@@ -934,11 +930,10 @@ static bool chain_res_filter(hipStream_t s, const polfed_op* op, double E_c, dou
   const ResShape x = res_shape(op->D, 1);
   const auto t = res_table(s, op, x.nslab, false);
   if (!t || !res_instance(*t)) return false;
-  // the state, the scale and a chunk's coefficients lie behind bufA
-  uintptr_t p = ((uintptr_t)(bufA + op->D) + 255) / 256 * 256;
-  ResState* st = (ResState*)p;
-  T* sc = (T*)(p + (sizeof(ResState) + 255) / 256 * 256);
-  T* A = sc + 32;
+  const uintptr_t p = res_align((uintptr_t)(bufA + op->D));
+  ResState* st = (ResState*)(p + ResTail::st);
+  T* sc = (T*)(p + ResTail::sc);
+  T* A = (T*)(p + ResTail::A);
   ResArgs<T> r{};
   r.L = op->L;
   r.N = op->N;
@@ -1006,9 +1001,9 @@ bool res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const
   r.w = w;
   r.X = bufA;
   r.Y = bufB;
-  uintptr_t p = ((uintptr_t)(bufA + op->D) + 255) / 256 * 256;
-  r.st = (ResState*)p;
-  T* A = (T*)(p + (sizeof(ResState) + 255) / 256 * 256);
+  const uintptr_t p = res_align((uintptr_t)(bufA + op->D));
+  r.st = (ResState*)(p + ResTail::st);
+  T* A = (T*)(p + ResTail::A);
   const unsigned grid = r.sbits ? 8u << r.sbits : 1u;
   const size_t nd = (size_t)1 << N;
   const size_t shm = ((nd << (op->L - r.sbits)) + nd * nd) * sizeof(T);

@@ -551,7 +551,7 @@ size_t SolveRun::bytes_at(int64_t D_, int m, int n, bool f32) {
   size_t b = (M + 2) * vec + ((size_t)gs_parts(D_) * (M + 1) + 8192 + 3 * (M + 2)) * 8;
   // w, the filter's two recurrence buffers, the FP32 copies of v and w,
   // and the fixed graph input (FP64)
-  b += vec + (f32 ? 4 * D * 4 : 3 * vec) + chain_res_tail();
+  b += vec + (f32 ? 4 * D * 4 : 3 * vec) + ResTail::bytes;
   // check and extraction: the tridiagonal eigenvectors (M x M), the chosen
   // ones (M x n), the projected matrix and its eigenvectors, partial sums,
   // the split sums of the projection product

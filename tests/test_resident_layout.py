@@ -71,3 +71,27 @@ int main() {
 }
 """ % M)
     assert int(out) > 50000
+
+
+def test_tail_behind_the_first_buffer_fits(tmp_path):
+    """The team state, the scale and a full chunk's coefficients end inside the
+    buffer wherever the D elements end (FP64 and FP32, D of every chain and of
+    the quantum suns), and do not overlap."""
+    run_host(tmp_path, """
+int main() {
+  std::set<int64_t> ds = sizes();
+  for (int64_t d = 1; d <= 300; ++d) ds.insert(d);
+  for (int b = 2; b <= 18; ++b) ds.insert(int64_t(1) << b);
+  static_assert(ResTail::sc >= ResTail::st + sizeof(ResState), "state");
+  static_assert(ResTail::A >= ResTail::sc + 2 * sizeof(double), "scale");
+  for (int64_t D : ds)
+    for (size_t elem : {size_t(4), size_t(8)}) {
+      const size_t at = res_align((size_t)D * elem);
+      const size_t end = at + ResTail::A + (size_t)(kResChunk + 1) * elem;
+      if (end > (size_t)D * elem + ResTail::bytes) {
+        std::printf("D = %ld, %zu bytes an element\\n", (long)D, elem);
+        return 1;
+      }
+    }
+}
+""")
