@@ -105,6 +105,11 @@ polfed_status polfed_create(int device, void* hip_stream, polfed_ctx** out);
 polfed_status polfed_destroy(polfed_ctx* ctx);
 /* Waits for all work queued on the context's stream. */
 polfed_status polfed_sync(polfed_ctx* ctx);
+/* Longest wait of the barriers inside the resident kernels (short chains and
+ * quantum suns), in seconds; 30 in a new context.  Their members all run, so
+ * it is reached only on a device that makes no progress: the call then ends
+ * with NaN in what it returns, or fails.  0 gives up at once. */
+polfed_status polfed_set_team_wait(polfed_ctx* ctx, double seconds);
 
 /* ------------------------------------------------------------------ basis
  * Sector of L-bit strings with N set bits (the U(1) sector of App. A), in

@@ -87,6 +87,7 @@ SIGNATURES = {
     "polfed_create": [_I, _P, ctypes.POINTER(_P)],
     "polfed_destroy": [_P],
     "polfed_sync": [_P],
+    "polfed_set_team_wait": [_P, _D],
     "polfed_basis_dim": [_I, _I, _I64P],
     "polfed_basis_enumerate": [_P, _I, _I, _P],
     "polfed_basis_rank": [_P, _I, _I, _P, _I64, _P],
@@ -262,6 +263,11 @@ class Context:
 
     def sync(self):
         _check(_lib.polfed_sync(self.handle))
+
+    def set_team_wait(self, seconds: float):
+        """Longest wait of the barriers inside the resident kernels (30 s in a
+        new context); a call that reaches it returns NaN or fails."""
+        _check(_lib.polfed_set_team_wait(self.handle, float(seconds)))
 
     def close(self):
         if getattr(self, "handle", None):

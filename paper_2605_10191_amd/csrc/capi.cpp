@@ -459,6 +459,15 @@ polfed_status polfed_sync(polfed_ctx* ctx) {
   });
 }
 
+polfed_status polfed_set_team_wait(polfed_ctx* ctx, double seconds) {
+  return guarded([&]() -> polfed_status {
+    CTX_OK(ctx);
+    REQUIRE(seconds >= 0 && seconds <= 3600, "team wait: need 0 .. 3600 s");
+    ctx->team_wait = (long long)(seconds * (double)kResTicksPerSecond);
+    return POLFED_OK;
+  });
+}
+
 // ---------------------------------------------------------------- basis
 
 polfed_status polfed_basis_dim(int L, int N, int64_t* D) {

@@ -318,6 +318,8 @@ struct polfed_ctx {
   bool own_stream = false;
   hipStream_t cap_stream = nullptr;  // private stream for graph capture
   int n_cu = 256;
+  // how long the teams' barriers wait (polfed_set_team_wait)
+  std::atomic<long long> team_wait{polfed::kResWait};
   std::mutex mu;  // serializes calls that use the shared workspaces
   // API calls waiting for mu (the server thread lets them in between rounds)
   std::atomic<int> api_waiting{0};
@@ -546,6 +548,7 @@ struct ResArgs {
   const T* v;
   T *w, *X, *Y;
   ResState* st;
+  long long wait;  // of a barrier
   double* part;  // moments: partial products; i_all: the last step's index
   int i_all;
 };

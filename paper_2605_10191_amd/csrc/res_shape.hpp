@@ -31,6 +31,16 @@ struct ResState {
   ResTeam teams[16 * kResTeamsPerXcd];
 };
 
+// Whether word i of a ResState is cleared before a launch: all of them before a
+// call's first one, and before the launches that go on with its recurrence all
+// but err, which says that a barrier gave up in one of those before.
+constexpr bool res_clears(size_t i, bool first) {
+  return first || i != offsetof(ResState, err) / sizeof(int);
+}
+// How long a barrier waits, in ticks of the 100 MHz clock.  Every member runs,
+// so it ends by itself; the bound only keeps a broken device from hanging.
+constexpr long long kResTicksPerSecond = 100000000, kResWait = 30 * kResTicksPerSecond;
+
 // Slabs of a column (a power of two), pairs of columns sharing a team, rows a
 // thread.
 struct ResShape {

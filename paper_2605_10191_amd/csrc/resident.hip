@@ -66,9 +66,12 @@ struct TeamView {
   int n, rank;
   int step;  // barriers passed
   int failed;
+  long long wait;  // of a barrier at most, in ticks
 };
 
-// All members have stored what they wrote before; afterwards all see it.
+// All members have stored what they wrote before; afterwards all see it.  A
+// barrier that gives up sets err and lets its member run on to the end: what
+// the call returns is then NaN or an error, never a number.
 // between() runs once the workgroup's own LDS reads are done, while the other
 // members arrive.  Every member raises its own flag and one wave polls all of
 // them with one load.
@@ -84,9 +87,7 @@ __device__ __forceinline__ void team_barrier(TeamView& tv, int* err, F&& between
     const int* f = &tv.t->flag[min((int)threadIdx.x, tv.n - 1)];
     const long long t0 = wall_clock64();
     while (__ballot(res_load(f) < tv.step)) {
-      // every member runs, so this ends; the bound (30 s of the 100 MHz
-      // clock) only keeps a broken device from hanging
-      if (wall_clock64() - t0 > 3000000000LL) {
+      if (wall_clock64() - t0 >= tv.wait) {
         tv.failed = 1;
         res_store(err, 1);
         break;
@@ -527,7 +528,7 @@ __global__ __launch_bounds__(kResThreads) void k_chain_res(ResArgs<T> p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ double s_field[2 * kFieldStride];
   __shared__ int s_join[4];
-  TeamView tv{nullptr, 1, 0, 0, 0};
+  TeamView tv{nullptr, 1, 0, 0, 0, p.wait};
   if (!team_join(p.st, p.nslab, p.teams_per_xcd, s_join, tv)) return;
   for (int round = 0;; ++round) {
     if (threadIdx.x == 0 && tv.rank == 0) {
@@ -571,6 +572,7 @@ struct QsunRes {
   const T *A, *v;
   T *w, *X, *Y;
   ResState* st;
+  long long wait;
 };
 
 constexpr int kQsunSlabBits = 5;
@@ -584,7 +586,7 @@ __global__ __launch_bounds__(kResThreads) void k_qsun_res(QsunRes<T> p) {
   constexpr uint32_t TB = sizeof(T);
   const int L = p.q.L, nd = 1 << p.q.N, nslab = 1 << p.sbits;
   const int lo = L - p.sbits, nob = 1 << lo;  // outer bits inside a slab
-  TeamView tv{nullptr, 1, 0, 0, 0};
+  TeamView tv{nullptr, 1, 0, 0, 0, p.wait};
   if (!team_join(p.st, nslab, 1, s_join, tv)) return;
   // the first team takes the column
   if (threadIdx.x == 0 && tv.rank == 0) {
@@ -734,20 +736,21 @@ __global__ __launch_bounds__(kResThreads) void k_qsun_res(QsunRes<T> p) {
   }
 }
 
-// Clears the team state and writes a chunk's coefficients (kernel arguments,
-// so that the call can be captured and needs no copy from host memory).
+// Clears the team state (see res_clears) and writes a chunk's coefficients
+// (kernel arguments, so that the call can be captured and needs no copy from
+// host memory).
 template <typename T>
 struct CoefPack {
   static constexpr int kN = 440;
   T a[kN];
 };
 template <typename T>
-__global__ __launch_bounds__(256) void k_res_begin(ResState* st, T* sc, T sigma, T tau,
+__global__ __launch_bounds__(256) void k_res_begin(ResState* st, int first, T* sc, T sigma, T tau,
                                                    int nb) {
   int* p = reinterpret_cast<int*>(st);
   for (int i = blockIdx.x * 256 + threadIdx.x; i < (int)(sizeof(ResState) / 4);
        i += gridDim.x * 256)
-    p[i] = 0;
+    if (res_clears(i, first)) p[i] = 0;
   if (sc && blockIdx.x == 0)
     for (int c = threadIdx.x; c < nb; c += 256) {
       sc[c] = sigma;
@@ -952,9 +955,10 @@ static bool chain_res_filter(hipStream_t s, const polfed_op* op, double E_c, dou
   r.X = bufA;
   r.Y = bufB;
   r.st = st;
+  r.wait = op->ctx->team_wait;
   const T sigma = (T)(2.0 / dE), tau = (T)(-2.0 * E_c / dE);
   res_run<false>(s, *t, x, r, K, kResChunk, [&](ResArgs<T>& q, int top, int bot) {
-    hipLaunchKernelGGL((k_res_begin<T>), dim3(8), dim3(256), 0, s, st, sc, sigma, tau, 1);
+    hipLaunchKernelGGL((k_res_begin<T>), dim3(8), dim3(256), 0, s, st, q.first, sc, sigma, tau, 1);
     put_coefs<T>(s, a, bot, top, A);
     q.A = A - bot;  // indexed by the step
   });
@@ -1003,6 +1007,7 @@ bool res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const
   r.Y = bufB;
   const uintptr_t p = res_align((uintptr_t)(bufA + op->D));
   r.st = (ResState*)(p + ResTail::st);
+  r.wait = op->ctx->team_wait;
   T* A = (T*)(p + ResTail::A);
   const unsigned grid = r.sbits ? 8u << r.sbits : 1u;
   const size_t nd = (size_t)1 << N;
@@ -1012,8 +1017,8 @@ bool res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const
     r.i_top = top;
     r.i_bot = bot;
     r.first = top == K;
-    hipLaunchKernelGGL((k_res_begin<T>), dim3(8), dim3(256), 0, s, r.st, (T*)nullptr, T(0), T(0),
-                       0);
+    hipLaunchKernelGGL((k_res_begin<T>), dim3(8), dim3(256), 0, s, r.st, r.first, (T*)nullptr,
+                       T(0), T(0), 0);
     put_coefs<T>(s, a, bot, top, A);
     r.A = A - bot;
 #define POLFED_QSUN(DG_, IT_, ND_)                                                                \
@@ -1094,9 +1099,10 @@ bool chain_dense_build(hipStream_t s, const polfed_op* op, double E_c, double dE
   r.X = X;
   r.Y = Y;
   r.st = st;
+  r.wait = op->ctx->team_wait;
   res_run<false>(s, *t, x, r, K, kResChunk, [&](ResArgs<double>& q, int top, int bot) {
-    hipLaunchKernelGGL((k_res_begin<double>), dim3(8), dim3(256), 0, s, q.st, sc, 2.0 / dE,
-                       -2.0 * E_c / dE, nb);
+    hipLaunchKernelGGL((k_res_begin<double>), dim3(8), dim3(256), 0, s, q.st, q.first, sc,
+                       2.0 / dE, -2.0 * E_c / dE, nb);
     put_coefs<double>(s, a, bot, top, A);
     q.A = A - bot;  // indexed by the step
   });
@@ -1150,7 +1156,7 @@ __global__ __launch_bounds__(kResThreads) void k_cgs2_team(
   __shared__ int s_join[4];
   __shared__ double s_red[kResWaves * 64];
   double* s_c = reinterpret_cast<double*>(smem);  // [k1]
-  TeamView tv{nullptr, 1, 0, 0, 0};
+  TeamView tv{nullptr, 1, 0, 0, 0, kResWait};
   if (!team_join(st, nm, 1, s_join, tv)) return;
   // the first team does it
   if (threadIdx.x == 0 && tv.rank == 0) {
@@ -1268,8 +1274,8 @@ bool cgs2_team(hipStream_t s, int64_t D, int k1, const double* V, double* w, dou
   static_assert(sizeof(ResState) + 32 * sizeof(double) <= 8192 * sizeof(double), "partial");
   ResState* st = reinterpret_cast<ResState*>(partial);
   double* norm = reinterpret_cast<double*>(st + 1);
-  hipLaunchKernelGGL((k_res_begin<double>), dim3(8), dim3(256), 0, s, st, (double*)nullptr, 0.0,
-                     0.0, 0);
+  hipLaunchKernelGGL((k_res_begin<double>), dim3(8), dim3(256), 0, s, st, 1, (double*)nullptr,
+                     0.0, 0.0, 0);
   hipLaunchKernelGGL(k_cgs2_team, dim3(8 * nm), dim3(kResThreads), (size_t)k1 * sizeof(double), s,
                      st, D, k1, nm, V, w, c, norm, flag, alpha, beta, v_next);
   HIPC(hipGetLastError());
@@ -1317,9 +1323,10 @@ void chain_res_batch(hipStream_t s, const ChainBatch& bt, const T* A, int K, con
   r.X = bufA;
   r.Y = bufB;
   r.st = bt.res_state.template as<ResState>();
+  r.wait = op0->ctx->team_wait;
   res_run<false>(s, *t, x, r, K, kResChunk, [&](ResArgs<T>& q, int, int) {
-    hipLaunchKernelGGL((k_res_begin<T>), dim3(8), dim3(256), 0, s, q.st, (T*)nullptr, T(0), T(0),
-                       0);
+    hipLaunchKernelGGL((k_res_begin<T>), dim3(8), dim3(256), 0, s, q.st, q.first, (T*)nullptr,
+                       T(0), T(0), 0);
     HIPC(hipGetLastError());
   });
 }
@@ -1376,11 +1383,12 @@ void chain_res_moments(hipStream_t s, const polfed_op* op, double E_c, double dE
   r.X = X;
   r.Y = Y;
   r.st = st;
+  r.wait = op->ctx->team_wait;
   r.part = (double*)(base + pl.part);
   r.i_all = M - 1;
   res_run<true>(s, *t, x, r, M, kResChunk, [&](ResArgs<double>& q, int, int) {
-    hipLaunchKernelGGL((k_res_begin<double>), dim3(8), dim3(256), 0, s, q.st, sc, 2.0 / dE,
-                       -2.0 * E_c / dE, nb);
+    hipLaunchKernelGGL((k_res_begin<double>), dim3(8), dim3(256), 0, s, q.st, q.first, sc,
+                       2.0 / dE, -2.0 * E_c / dE, nb);
     HIPC(hipGetLastError());
   });
   hipLaunchKernelGGL(k_res_sum, dim3((unsigned)((count + 3) / 4)), dim3(256), 0, s, r.part,

@@ -95,3 +95,21 @@ int main() {
     }
 }
 """)
+
+
+def test_a_given_up_barrier_is_not_cleared_between_launches(tmp_path):
+    """Before a call's first launch the whole team state is cleared, before
+    the ones that go on with its recurrence everything but err."""
+    run_host(tmp_path, """
+int main() {
+  ResState st;
+  int* p = reinterpret_cast<int*>(&st);
+  for (bool first : {true, false}) {
+    for (size_t i = 0; i < sizeof st / 4; ++i) p[i] = 7;
+    for (size_t i = 0; i < sizeof st / 4; ++i)
+      if (res_clears(i, first)) p[i] = 0;
+    for (size_t i = 0; i < sizeof st / 4; ++i)
+      if (p[i] != (&p[i] == &st.err && !first ? 7 : 0)) return 1;
+  }
+}
+""")
