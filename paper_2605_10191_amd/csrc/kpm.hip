@@ -130,7 +130,7 @@ void kpm_moments(polfed_ctx* ctx, const polfed_op* op, double E_c, double dE, in
     const int g = dot_blocks(D);
     DevBuf part((size_t)cols * 2 * g * sizeof(double)), d0((size_t)cols * 2 * sizeof(double));
     if (!rvecs) v.alloc(nd * cols * sizeof(double));
-    std::vector<double> dots((size_t)M * 2 * cols), h0((size_t)2 * cols);
+    std::vector<double> dots((size_t)M * 2 * cols + 1), h0((size_t)2 * cols);
     for (int c0 = 0; c0 < R; c0 += cols) {
       const int nb = std::min(cols, R - c0);
       const double* vc = rvecs ? rvecs + (size_t)c0 * D : v.as<double>();

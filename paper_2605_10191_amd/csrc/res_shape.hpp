@@ -112,7 +112,7 @@ struct ResTail {
 
 // M steps of the Chebyshev vectors of nb columns out of groups of width
 // columns (kpm.hip): the byte offsets of the scales, the sums and the partial
-// products behind the team state, and the bytes in all.  Every group takes the
+// products behind the team state (the sums have one element more), and the bytes in all.  Every group takes the
 // slabs of a full one, so that a shorter last group needs no more room and
 // reads the same tables (its own best shape can have more slabs than there are
 // columns fewer: D = 5,005 4 slabs for 64 columns, 16 for 32).
@@ -129,7 +129,7 @@ inline ResMomentsPlan res_moments_plan(int64_t D, int M, int width, int nb) {
   p.count = (int64_t)M * 2 * nb;
   p.sc = res_align(sizeof(ResState));
   p.sums = res_align(p.sc + (size_t)2 * nb * sizeof(double));
-  p.part = p.sums + (size_t)p.count * sizeof(double);
+  p.part = p.sums + (size_t)(p.count + 1) * sizeof(double);
   p.bytes = p.part + (size_t)p.count * nslab * kResWaves * sizeof(double);
   return p;
 }

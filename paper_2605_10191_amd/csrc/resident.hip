@@ -1331,9 +1331,10 @@ void chain_res_batch(hipStream_t s, const ChainBatch& bt, const T* A, int K, con
   });
 }
 
-// out[k] = sum of part[k * n .. k * n + n), one wave a sum.
+// out[k] = sum of part[k * n .. k * n + n), one wave a sum; out[count] = err.
 __global__ __launch_bounds__(256) void k_res_sum(const double* part, int n, int64_t count,
-                                                 double* out) {
+                                                 const ResState* st, double* out) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) out[count] = st->err;
   const int64_t k = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (k >= count) return;
   double x = 0;
@@ -1351,7 +1352,7 @@ size_t chain_res_moments_bytes(const polfed_op* op, int M, int width) {
 }
 
 // dots[n - 1][0] = <t_n|t_n>, dots[n - 1][1] = <t_{n-1}|t_n> of every column
-// for n = 1 .. M (host, [M][2][nb]); v: D x nb, X and Y: its two buffers; nb
+// for n = 1 .. M (host, [M][2][nb] and one more, used here); v: D x nb, X and Y: its two buffers; nb
 // <= width columns, ws chain_res_moments_bytes of the width.
 void chain_res_moments(hipStream_t s, const polfed_op* op, double E_c, double dE, int M, int width,
                        int nb, const double* v, double* X, double* Y, const DevBuf& ws,
@@ -1392,10 +1393,12 @@ void chain_res_moments(hipStream_t s, const polfed_op* op, double E_c, double dE
     HIPC(hipGetLastError());
   });
   hipLaunchKernelGGL(k_res_sum, dim3((unsigned)((count + 3) / 4)), dim3(256), 0, s, r.part,
-                     t->nslab * kResWaves, count, sums);
+                     t->nslab * kResWaves, count, st, sums);
   HIPC(hipGetLastError());
-  HIPC(hipMemcpyAsync(dots, sums, (size_t)count * sizeof(double), hipMemcpyDeviceToHost, s));
+  HIPC(hipMemcpyAsync(dots, sums, (size_t)(count + 1) * sizeof(double), hipMemcpyDeviceToHost, s));
   HIPC(hipStreamSynchronize(s));
+  if (dots[count] != 0)
+    fail(POLFED_ERR_HIP, "kpm: a barrier of the resident recurrence gave up (device without progress?)");
 }
 
 template void chain_res_batch<double>(hipStream_t, const ChainBatch&, const double*, int,

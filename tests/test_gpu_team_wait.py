@@ -49,3 +49,16 @@ def test_filter_of_a_quantum_sun(pk, own):
     q, H = qsun_case(N, L, 3)
     op = pk.Operator.qsun(own, N, L, q["A"], 1.0, 1.0, 0.75, q["u"], q["n_of_j"], q["h"])
     filter_gives_up(pk, own, op, H, 1.2 * L + 8.0, 47)
+
+
+@pytest.mark.parametrize("L,N,R", [(14, 7, 5), (16, 8, 40)])
+def test_kpm_moments(pk, own, L, N, R):
+    say(f"team wait 0, kpm L={L} R={R}")
+    op = pk.Operator.xxz(own, L, N, 1.0, 0.7, wl.xxz_fields(L, 3.0, 5), True)
+    good = pk.kpm_moments(op, 0.0, 2.6 * L, 60, R, seed=3)
+    own.set_team_wait(0)
+    with pytest.raises(pk.PolfedError) as e:
+        pk.kpm_moments(op, 0.0, 2.6 * L, 60, R, seed=3)
+    assert "gave up" in str(e.value)
+    own.set_team_wait(30)
+    assert np.array_equal(pk.kpm_moments(op, 0.0, 2.6 * L, 60, R, seed=3), good)

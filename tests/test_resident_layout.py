@@ -56,9 +56,9 @@ int main() {
         ++n;
         bool ok = p.shape.nslab == full.shape.nslab;
         if (ok && p.shape.nslab) {
-          const size_t sums = (size_t)M * 2 * nb * 8;
+          const size_t sums = (size_t)M * 2 * nb * 8;  // and the error word
           ok = p.shape.ngrp + p.shape.pairs == nb && p.sc >= sizeof(ResState) &&
-               p.sums >= p.sc + 16 * (size_t)nb && p.part >= p.sums + sums &&
+               p.sums >= p.sc + 16 * (size_t)nb && p.part >= p.sums + sums + 8 &&
                p.part + sums * p.shape.nslab * kResWaves <= full.bytes;
         }
         if (!ok) {
