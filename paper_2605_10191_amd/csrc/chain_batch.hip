@@ -618,15 +618,19 @@ template <typename T>
 int batch_variant(hipStream_t s, const ChainBatch& bt) {
   const polfed_op* op0 = bt.ops[0];
   const int key = bt.nb * 2 + (sizeof(T) == 8 ? 0 : 1);
+  // The resident recurrence needs the pattern's tables, which live as long as
+  // the operators that hold them and are not built under capture: a choice of
+  // it is taken only with them (false: it is timed anew).
+  auto usable = [&](int v) { return v != 5 || chain_res_batch_fits(s, op0, bt.nb); };
   {
     auto it = op0->batch_tuned.find(key);
-    if (it != op0->batch_tuned.end()) return it->second;
+    if (it != op0->batch_tuned.end() && usable(it->second)) return it->second;
   }
   // an earlier choice for this chain pattern (any operator of it)
   const std::string pkey = "batch" + std::to_string(bt.nb) + (sizeof(T) == 8 ? "|64" : "|32");
   {
     const int v = pattern_choice(op0, pkey);
-    if (v >= 0) return op0->batch_tuned[key] = v;
+    if (v >= 0 && usable(v)) return op0->batch_tuned[key] = v;
   }
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   HIPC(hipStreamIsCapturing(s, &cs));
