@@ -430,8 +430,7 @@ polfed_status polfed_block_lanczos_step(polfed_ctx* ctx, const polfed_op* op,
                                         double* Bn, int precision);
 /* Kernel polynomial method (Sec. 4.1 eq. dos_kpm, App. B): mu[n] for
  * n < N, the mean over R vectors r of <r| T_n(H~) |r> with H~ = (H - E_c)/dE,
- * by the three-term Chebyshev recurrence for the vectors, two moments a
- * step from <t_n|t_n> and <t_{n-1}|t_n> (FP64).
+ * by the three-term Chebyshev recurrence for the vectors (FP64).
  * r: device D x R column-major, or NULL: then vector c (0 <= c < R) has
  * entries sqrt(3) (2 u - 1), u = (z >> 11) / 2^53 for the splitmix64 output
  * z of seed + c at counter i + 1 (zero mean, unit variance).  mu: host [N].

@@ -4,15 +4,16 @@
 // density rho_KPM(x) = [mu_0 g_0 + 2 sum_{n>=1} mu_n g_n T_n(x)] /
 // (pi sqrt(1 - x^2)).
 //
-// With t_n = T_n(H~) r, the product rules of the Chebyshev polynomials (2 T_m
-// T_n = T_{m+n} + T_{m-n}) give two moments of a vector per step,
-//     <r|t_{2n}> = 2 <t_n|t_n> - <r|r>,
-//     <r|t_{2n+1}> = 2 <t_{n+1}|t_n> - <r|t_1>,
-// so N moments take N / 2 steps.  On short chains all vectors go through the
-// resident recurrence at once, with the products formed in it: 200 moments of
-// 32 vectors at L = 17 take 0.76 ms; with a step and two product launches per
-// moment and vector they took 71 ms.  Elsewhere the recurrence is the fused step kernel
-// (a = 0, written over t_{n-1}) followed by one launch for both products.
+// With t_n = T_n(H~) r, moment n of a vector is <r|t_n>.  (Two moments a step
+// from <t_n|t_n> and <t_{n+1}|t_n>, by the product rules of the Chebyshev
+// polynomials, take half the steps, 0.75 ms instead of 0.96 below, but 2
+// <t_n|t_n> - <r|r> doubles the rounding: relative error of t-V chains against
+// 80-bit arithmetic 2.2e-16 at L = 12 and 2.8e-16 at L = 16, from <r|t_n>
+// 1.1e-16 at both.)  On short chains all vectors go through the resident
+// recurrence at once, with the products formed in it: 200 moments of 32 vectors
+// at L = 17 take 0.96 ms, with a step and two product launches per moment and
+// vector 71.  Elsewhere the recurrence is the fused step kernel (a = 0, written
+// over t_{n-1}) followed by a product.
 #include <algorithm>
 #include <cmath>
 
@@ -23,7 +24,7 @@ namespace polfed {
 namespace {
 
 constexpr int kKpmCols = 64;       // vectors of one resident launch
-constexpr int kDotBlocks = 512;    // partial sums of a product
+constexpr int kDotBlocks = 1024;   // partial sums of a product
 
 // vector c: uniform on [-sqrt 3, sqrt 3) (zero mean, unit variance), drawn as
 // dev_random does from seed + c
@@ -41,41 +42,39 @@ __global__ void k_kpm_vectors(int64_t D, int nb, uint64_t seed, double* y) {
   }
 }
 
-// part[0][block] = sums of x x, part[1][block] = of x y (y may be null).
-__global__ __launch_bounds__(256) void k_dot_pair(int64_t n, const double* __restrict__ x,
-                                                  const double* __restrict__ y, double* part) {
-  __shared__ double red[8];
-  double a = 0, b = 0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const double t = x[i];
-    a += t * t;
-    if (y) b += t * y[i];
-  }
-  for (int off = 32; off > 0; off >>= 1) {
-    a += __shfl_down(a, off, 64);
-    b += __shfl_down(b, off, 64);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    red[threadIdx.x >> 6] = a;
-    red[4 + (threadIdx.x >> 6)] = b;
-  }
+// Sum over a workgroup of 256, valid in thread 0.
+__device__ __forceinline__ double sum_256(double a) {
+  __shared__ double red[4];
+  for (int off = 32; off > 0; off >>= 1) a += __shfl_down(a, off, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
   __syncthreads();
-  if (threadIdx.x < 2) {
-    double t = 0;
-    for (int i = 0; i < 4; ++i) t += red[4 * threadIdx.x + i];
-    part[threadIdx.x * gridDim.x + blockIdx.x] = t;
-  }
+  double t = 0;
+  if (threadIdx.x == 0)
+    for (int i = 0; i < 4; ++i) t += red[i];
+  return t;
 }
 
-// out[k] = sum of part[k n .. k n + n), one wave a sum
-__global__ __launch_bounds__(256) void k_sum_rows(const double* part, int n, int64_t count,
-                                                  double* out) {
-  const int64_t k = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (k >= count) return;
-  double t = 0;
-  for (int i = threadIdx.x & 63; i < n; i += 64) t += part[k * n + i];
-  for (int off = 32; off > 0; off >>= 1) t += __shfl_down(t, off, 64);
-  if ((threadIdx.x & 63) == 0) out[k] = t;
+// part[block] = sums of x y.
+__global__ __launch_bounds__(256) void k_dot_part(int64_t n, const double* __restrict__ x,
+                                                  const double* __restrict__ y, double* part) {
+  double a = 0;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+    a += x[i] * y[i];
+  a = sum_256(a);
+  if (threadIdx.x == 0) part[blockIdx.x] = a;
+}
+
+// out[block] = sum of part[block n .. block n + n)
+__global__ __launch_bounds__(256) void k_sum_rows(const double* part, int n, double* out) {
+  double a = 0;
+  for (int i = threadIdx.x; i < n; i += 256) a += part[(int64_t)blockIdx.x * n + i];
+  a = sum_256(a);
+  if (threadIdx.x == 0) out[blockIdx.x] = a;
+}
+
+void sum_rows(hipStream_t s, const double* part, int n, int count, double* out) {
+  hipLaunchKernelGGL(k_sum_rows, dim3((unsigned)count), dim3(256), 0, s, part, n, out);
+  HIPC(hipGetLastError());
 }
 
 void draw_vectors(hipStream_t s, int64_t D, int nb, uint64_t seed, double* y) {
@@ -90,17 +89,17 @@ int dot_blocks(int64_t D) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(kDotBlocks, (D + 1023) / 1024));
 }
 
-void dot_pair(hipStream_t s, int64_t D, const double* x, const double* y, double* part) {
-  hipLaunchKernelGGL(k_dot_pair, dim3((unsigned)dot_blocks(D)), dim3(256), 0, s, D, x, y, part);
+void dot_part(hipStream_t s, int64_t D, const double* x, const double* y, double* part) {
+  hipLaunchKernelGGL(k_dot_part, dim3((unsigned)dot_blocks(D)), dim3(256), 0, s, D, x, y, part);
   HIPC(hipGetLastError());
 }
 
 }  // namespace
 
 size_t kpm_workspace(const polfed_op* op, int N, int R) {
-  const size_t D = (size_t)std::max<int64_t>(op->D, 1), M = (size_t)(N / 2);
+  const size_t D = (size_t)std::max<int64_t>(op->D, 1), M = (size_t)(N - 1);
   const size_t nb = (size_t)std::min(R, kKpmCols);
-  const size_t dots = 2 * (M + 1) * kDotBlocks * 8;
+  const size_t dots = (size_t)N * (kDotBlocks + R) * 8;
   const bool res = op->model == Model::Chain && op->L <= kResMaxL;
   return std::max(3 * D * 8 + dots,
                   res ? 3 * D * nb * 8 + dots + chain_res_moments_bytes(op, (int)M, (int)nb) : 0);
@@ -112,54 +111,42 @@ void kpm_moments(polfed_ctx* ctx, const polfed_op* op, double E_c, double dE, in
   REQUIRE(dE > 0 && std::isfinite(dE) && std::isfinite(E_c), "kpm: need finite E_c, dE > 0");
   hipStream_t s = ctx->stream;
   const int64_t D = op->D;
-  const int M = N / 2;  // steps
+  const int M = N - 1;  // steps
   const size_t nd = (size_t)std::max<int64_t>(D, 1);
+  const int g = dot_blocks(D);
   std::fill(mu, mu + N, 0.0);
-  // the moments of one vector from m0 = <t_0|t_0> and its products of step n
-  auto add = [&](double m0, auto&& same, auto&& next) {
-    const double m1 = N > 1 ? next(1) : 0.0;
-    mu[0] += m0;
-    if (N > 1) mu[1] += m1;
-    for (int n = 1; 2 * n < N; ++n) mu[2 * n] += 2.0 * same(n) - m0;
-    for (int n = 1; 2 * n + 1 < N; ++n) mu[2 * n + 1] += 2.0 * next(n + 1) - m1;
-  };
   const int cols = std::min(R, kKpmCols);
   if (M >= 4 && D >= 1 && chain_res_moments_fit(s, op, cols)) {
     DevBuf v, X(nd * cols * sizeof(double)), Y(nd * cols * sizeof(double)),
         ws(chain_res_moments_bytes(op, M, cols));
-    const int g = dot_blocks(D);
-    DevBuf part((size_t)cols * 2 * g * sizeof(double)), d0((size_t)cols * 2 * sizeof(double));
+    DevBuf part((size_t)cols * g * sizeof(double)), d0((size_t)cols * sizeof(double));
     if (!rvecs) v.alloc(nd * cols * sizeof(double));
-    std::vector<double> dots((size_t)M * 2 * cols + 1), h0((size_t)2 * cols);
+    std::vector<double> dots((size_t)M * cols + 1), h0((size_t)cols);
     for (int c0 = 0; c0 < R; c0 += cols) {
       const int nb = std::min(cols, R - c0);
       const double* vc = rvecs ? rvecs + (size_t)c0 * D : v.as<double>();
       if (!rvecs) draw_vectors(s, D, nb, seed + (uint64_t)c0, v.as<double>());
       for (int c = 0; c < nb; ++c)
-        dot_pair(s, D, vc + (size_t)c * D, nullptr, part.as<double>() + (size_t)c * 2 * g);
-      hipLaunchKernelGGL(k_sum_rows, dim3((unsigned)((2 * nb + 3) / 4)), dim3(256), 0, s,
-                         part.as<double>(), g, (int64_t)2 * nb, d0.as<double>());
-      HIPC(hipGetLastError());
-      HIPC(hipMemcpyAsync(h0.data(), d0.get(), (size_t)2 * nb * sizeof(double),
-                          hipMemcpyDeviceToHost, s));
+        dot_part(s, D, vc + (size_t)c * D, vc + (size_t)c * D, part.as<double>() + (size_t)c * g);
+      sum_rows(s, part.as<double>(), g, nb, d0.as<double>());
+      HIPC(hipMemcpyAsync(h0.data(), d0.get(), (size_t)nb * sizeof(double), hipMemcpyDeviceToHost,
+                          s));
       chain_res_moments(s, op, E_c, dE, M, cols, nb, vc, X.as<double>(), Y.as<double>(), ws,
                         dots.data());
-      for (int c = 0; c < nb; ++c)
-        add(h0[2 * c], [&](int n) { return dots[((size_t)(n - 1) * 2) * nb + c]; },
-            [&](int n) { return dots[((size_t)(n - 1) * 2 + 1) * nb + c]; });
+      for (int c = 0; c < nb; ++c) {
+        mu[0] += h0[c];
+        for (int n = 1; n < N; ++n) mu[n] += dots[(size_t)(n - 1) * nb + c];
+      }
     }
   } else {
-    const int g = dot_blocks(D);
-    const size_t row = (size_t)2 * g;
     DevBuf r, ta(nd * sizeof(double)), tb(nd * sizeof(double)),
-        part((size_t)(M + 1) * row * sizeof(double)),
-        sums((size_t)(M + 1) * 2 * R * sizeof(double));
+        part((size_t)N * g * sizeof(double)), sums((size_t)N * R * sizeof(double));
     if (!rvecs) r.alloc(nd * sizeof(double));
     for (int c = 0; c < R; ++c) {
       const double* rv = rvecs ? rvecs + (size_t)c * D : r.as<double>();
       if (!rvecs) draw_vectors(s, D, 1, seed + (uint64_t)c, r.as<double>());
       double* pr = part.as<double>();
-      dot_pair(s, D, rv, nullptr, pr);
+      dot_part(s, D, rv, rv, pr);
       // cur = t_n, prev = t_{n-1} (overwritten; t_0 is r itself, so the first
       // update writes to tb)
       const double* cur = rv;
@@ -169,22 +156,17 @@ void kpm_moments(polfed_ctx* ctx, const polfed_op* op, double E_c, double dE, in
         double* nxt = n == 1 ? ta.as<double>()
                              : (prev == rv ? tb.as<double>() : const_cast<double*>(prev));
         op_step<double>(s, op, f / dE, -f * E_c / dE, 0.0, nullptr, cur, prev, nxt);
-        dot_pair(s, D, nxt, cur, pr + (size_t)n * row);
+        dot_part(s, D, rv, nxt, pr + (size_t)n * g);
         prev = cur;
         cur = nxt;
       }
-      const int64_t count = (int64_t)(M + 1) * 2;
-      hipLaunchKernelGGL(k_sum_rows, dim3((unsigned)((count + 3) / 4)), dim3(256), 0, s, pr, g,
-                         count, sums.as<double>() + (size_t)c * count);
-      HIPC(hipGetLastError());
+      sum_rows(s, pr, g, N, sums.as<double>() + (size_t)c * N);
     }
-    std::vector<double> h((size_t)(M + 1) * 2 * R);
+    std::vector<double> h((size_t)N * R);
     HIPC(hipMemcpyAsync(h.data(), sums.get(), h.size() * sizeof(double), hipMemcpyDeviceToHost, s));
     HIPC(hipStreamSynchronize(s));
-    for (int c = 0; c < R; ++c) {
-      const double* q = h.data() + (size_t)c * (M + 1) * 2;
-      add(q[0], [&](int n) { return q[2 * n]; }, [&](int n) { return q[2 * n + 1]; });
-    }
+    for (int c = 0; c < R; ++c)
+      for (int n = 0; n < N; ++n) mu[n] += h[(size_t)c * N + n];
   }
   for (int n = 0; n < N; ++n) mu[n] /= R;
 }

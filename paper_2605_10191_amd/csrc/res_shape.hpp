@@ -118,7 +118,7 @@ struct ResTail {
 // columns fewer: D = 5,005 4 slabs for 64 columns, 16 for 32).
 struct ResMomentsPlan {
   ResShape shape;
-  int64_t count = 0;  // products: M x 2 x nb
+  int64_t count = 0;  // products: M x nb
   size_t sc = 0, sums = 0, part = 0, bytes = 0;
 };
 inline ResMomentsPlan res_moments_plan(int64_t D, int M, int width, int nb) {
@@ -126,7 +126,7 @@ inline ResMomentsPlan res_moments_plan(int64_t D, int M, int width, int nb) {
   const int nslab = res_shape(D, width).nslab;
   if (nslab == 0 || nb > width) return p;
   p.shape = res_shape_at(D, nb, nslab);
-  p.count = (int64_t)M * 2 * nb;
+  p.count = (int64_t)M * nb;
   p.sc = res_align(sizeof(ResState));
   p.sums = res_align(p.sc + (size_t)2 * nb * sizeof(double));
   p.part = p.sums + (size_t)(p.count + 1) * sizeof(double);

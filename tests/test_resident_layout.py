@@ -56,7 +56,7 @@ int main() {
         ++n;
         bool ok = p.shape.nslab == full.shape.nslab;
         if (ok && p.shape.nslab) {
-          const size_t sums = (size_t)M * 2 * nb * 8;  // and the error word
+          const size_t sums = (size_t)M * nb * 8;  // and the error word
           ok = p.shape.ngrp + p.shape.pairs == nb && p.sc >= sizeof(ResState) &&
                p.sums >= p.sc + 16 * (size_t)nb && p.part >= p.sums + sums + 8 &&
                p.part + sums * p.shape.nslab * kResWaves <= full.bytes;
