@@ -549,7 +549,7 @@ struct ResArgs {
   T *w, *X, *Y;
   ResState* st;
   long long wait;  // of a barrier
-  double* part;  // moments: partial products; i_all: the last step's index
+  double* part;  // moments: partial products; i_all: the launch's first step
   int i_all;
 };
 
@@ -700,9 +700,11 @@ namespace polfed {
 // mu[0..N) = mean over R vectors of <r|T_n(H~)|r>; rvecs: device D x R, or
 // null for vectors drawn from the counter-based generator of dev_random
 // (vector c with seed + c), scaled to unit variance.
+// Holds at most room bytes on the device (besides rvecs) or, where that is less,
+// kpm_workspace.
 void kpm_moments(polfed_ctx* ctx, const polfed_op* op, double E_c, double dE, int N, int R,
-                 const double* rvecs, uint64_t seed, double* mu);
-// Device bytes kpm_moments holds for R vectors of op (besides rvecs).
+                 const double* rvecs, uint64_t seed, double* mu, size_t room = SIZE_MAX);
+// Device bytes of the moments of R vectors of op, one vector after another.
 size_t kpm_workspace(const polfed_op* op, int N, int R);
 void kpm_density(const double* mu, int N, const double* x, int nx, double* rho);
 // argmax of the KPM density over the Chebyshev nodes of 4096 that lie in [lo, hi]

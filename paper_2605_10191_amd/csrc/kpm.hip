@@ -25,6 +25,7 @@ namespace {
 
 constexpr int kKpmCols = 64;       // vectors of one resident launch
 constexpr int kDotBlocks = 1024;   // partial sums of a product
+constexpr int kDotPartials = 8192; // and of all that wait to be added up
 
 // vector c: uniform on [-sqrt 3, sqrt 3) (zero mean, unit variance), drawn as
 // dev_random does from seed + c
@@ -97,16 +98,49 @@ void dot_part(hipStream_t s, int64_t D, const double* x, const double* y, double
 }  // namespace
 
 size_t kpm_workspace(const polfed_op* op, int N, int R) {
-  const size_t D = (size_t)std::max<int64_t>(op->D, 1), M = (size_t)(N - 1);
-  const size_t nb = (size_t)std::min(R, kKpmCols);
-  const size_t dots = (size_t)N * (kDotBlocks + R) * 8;
-  const bool res = op->model == Model::Chain && op->L <= kResMaxL;
-  return std::max(3 * D * 8 + dots,
-                  res ? 3 * D * nb * 8 + dots + chain_res_moments_bytes(op, (int)M, (int)nb) : 0);
+  const size_t nd = (size_t)std::max<int64_t>(op->D, 1);
+  return (3 * nd + kDotPartials + (size_t)N * R) * sizeof(double);
+}
+
+// The buffers of the resident recurrence of cols vectors at a time.
+struct ResidentVectors {
+  DevBuf v, X, Y, ws, part, d0;
+  static size_t bytes(const polfed_op* op, int M, int cols) {
+    return ((size_t)3 * op->D * cols + (size_t)cols * (dot_blocks(op->D) + 1)) * sizeof(double) +
+           chain_res_moments_bytes(op, M, cols);
+  }
+  void alloc(const polfed_op* op, int M, int cols, bool draw) {
+    const size_t n = (size_t)op->D * cols * sizeof(double);
+    X.alloc(n);
+    Y.alloc(n);
+    ws.alloc(chain_res_moments_bytes(op, M, cols));
+    part.alloc((size_t)cols * dot_blocks(op->D) * sizeof(double));
+    d0.alloc((size_t)cols * sizeof(double));
+    if (draw) v.alloc(n);
+  }
+};
+
+// How many vectors go through the resident recurrence at a time: all, up to
+// 64, or as many as there is room and memory for; 0: none (or not faster).
+static int resident_width(hipStream_t s, const polfed_op* op, int M, int R, bool draw, size_t room,
+                          ResidentVectors& r) {
+  if (M < 4 || op->D < 1) return 0;
+  for (int cols = std::min(R, kKpmCols); cols >= 1; cols /= 2) {
+    if (ResidentVectors::bytes(op, M, cols) > room) continue;
+    if (!chain_res_moments_fit(s, op, cols)) return 0;
+    try {
+      r.alloc(op, M, cols, draw);
+      return cols;
+    } catch (const Error& e) {
+      if (e.code != POLFED_ERR_OOM) throw;
+      r = ResidentVectors{};
+    }
+  }
+  return 0;
 }
 
 void kpm_moments(polfed_ctx* ctx, const polfed_op* op, double E_c, double dE, int N, int R,
-                 const double* rvecs, uint64_t seed, double* mu) {
+                 const double* rvecs, uint64_t seed, double* mu, size_t room) {
   REQUIRE(N >= 1 && R >= 1, "kpm: need N >= 1 moments and R >= 1 vectors");
   REQUIRE(dE > 0 && std::isfinite(dE) && std::isfinite(E_c), "kpm: need finite E_c, dE > 0");
   hipStream_t s = ctx->stream;
@@ -115,24 +149,22 @@ void kpm_moments(polfed_ctx* ctx, const polfed_op* op, double E_c, double dE, in
   const size_t nd = (size_t)std::max<int64_t>(D, 1);
   const int g = dot_blocks(D);
   std::fill(mu, mu + N, 0.0);
-  const int cols = std::min(R, kKpmCols);
-  if (M >= 4 && D >= 1 && chain_res_moments_fit(s, op, cols)) {
-    DevBuf v, X(nd * cols * sizeof(double)), Y(nd * cols * sizeof(double)),
-        ws(chain_res_moments_bytes(op, M, cols));
-    DevBuf part((size_t)cols * g * sizeof(double)), d0((size_t)cols * sizeof(double));
-    if (!rvecs) v.alloc(nd * cols * sizeof(double));
+  ResidentVectors res;
+  const int cols = resident_width(s, op, M, R, !rvecs, room, res);
+  if (cols > 0) {
     std::vector<double> dots((size_t)M * cols + 1), h0((size_t)cols);
     for (int c0 = 0; c0 < R; c0 += cols) {
       const int nb = std::min(cols, R - c0);
-      const double* vc = rvecs ? rvecs + (size_t)c0 * D : v.as<double>();
-      if (!rvecs) draw_vectors(s, D, nb, seed + (uint64_t)c0, v.as<double>());
+      const double* vc = rvecs ? rvecs + (size_t)c0 * D : res.v.as<double>();
+      if (!rvecs) draw_vectors(s, D, nb, seed + (uint64_t)c0, res.v.as<double>());
       for (int c = 0; c < nb; ++c)
-        dot_part(s, D, vc + (size_t)c * D, vc + (size_t)c * D, part.as<double>() + (size_t)c * g);
-      sum_rows(s, part.as<double>(), g, nb, d0.as<double>());
-      HIPC(hipMemcpyAsync(h0.data(), d0.get(), (size_t)nb * sizeof(double), hipMemcpyDeviceToHost,
+        dot_part(s, D, vc + (size_t)c * D, vc + (size_t)c * D,
+                 res.part.as<double>() + (size_t)c * g);
+      sum_rows(s, res.part.as<double>(), g, nb, res.d0.as<double>());
+      HIPC(hipMemcpyAsync(h0.data(), res.d0.get(), (size_t)nb * sizeof(double), hipMemcpyDeviceToHost,
                           s));
-      chain_res_moments(s, op, E_c, dE, M, cols, nb, vc, X.as<double>(), Y.as<double>(), ws,
-                        dots.data());
+      chain_res_moments(s, op, E_c, dE, M, cols, nb, vc, res.X.as<double>(), res.Y.as<double>(),
+                        res.ws, dots.data());
       for (int c = 0; c < nb; ++c) {
         mu[0] += h0[c];
         for (int n = 1; n < N; ++n) mu[n] += dots[(size_t)(n - 1) * nb + c];
@@ -140,13 +172,22 @@ void kpm_moments(polfed_ctx* ctx, const polfed_op* op, double E_c, double dE, in
     }
   } else {
     DevBuf r, ta(nd * sizeof(double)), tb(nd * sizeof(double)),
-        part((size_t)N * g * sizeof(double)), sums((size_t)N * R * sizeof(double));
+        part(kDotPartials * sizeof(double)), sums((size_t)N * R * sizeof(double));
     if (!rvecs) r.alloc(nd * sizeof(double));
     for (int c = 0; c < R; ++c) {
       const double* rv = rvecs ? rvecs + (size_t)c * D : r.as<double>();
       if (!rvecs) draw_vectors(s, D, 1, seed + (uint64_t)c, r.as<double>());
-      double* pr = part.as<double>();
-      dot_part(s, D, rv, rv, pr);
+      // the products of as many moments as there is room for partial sums
+      double* out = sums.as<double>() + (size_t)c * N;
+      int have = 0;
+      auto product = [&](const double* t) {
+        dot_part(s, D, rv, t, part.as<double>() + (size_t)have * g);
+        if (++have < kDotPartials / g) return;
+        sum_rows(s, part.as<double>(), g, have, out);
+        out += have;
+        have = 0;
+      };
+      product(rv);
       // cur = t_n, prev = t_{n-1} (overwritten; t_0 is r itself, so the first
       // update writes to tb)
       const double* cur = rv;
@@ -156,11 +197,11 @@ void kpm_moments(polfed_ctx* ctx, const polfed_op* op, double E_c, double dE, in
         double* nxt = n == 1 ? ta.as<double>()
                              : (prev == rv ? tb.as<double>() : const_cast<double*>(prev));
         op_step<double>(s, op, f / dE, -f * E_c / dE, 0.0, nullptr, cur, prev, nxt);
-        dot_part(s, D, rv, nxt, pr + (size_t)n * g);
+        product(nxt);
         prev = cur;
         cur = nxt;
       }
-      sum_rows(s, pr, g, N, sums.as<double>() + (size_t)c * N);
+      if (have) sum_rows(s, part.as<double>(), g, have, out);
     }
     std::vector<double> h((size_t)N * R);
     HIPC(hipMemcpyAsync(h.data(), sums.get(), h.size() * sizeof(double), hipMemcpyDeviceToHost, s));

@@ -110,6 +110,10 @@ struct ResTail {
   static constexpr size_t bytes = 255 + end;
 };
 
+// Steps of the moments form in one launch: their partial products are summed
+// before the next one, so that they take no more room with more moments.
+constexpr int kResMomentSteps = 256;
+
 // M steps of the Chebyshev vectors of nb columns out of groups of width
 // columns (kpm.hip): the byte offsets of the scales, the sums and the partial
 // products behind the team state (the sums have one element more), and the bytes in all.  Every group takes the
@@ -130,7 +134,7 @@ inline ResMomentsPlan res_moments_plan(int64_t D, int M, int width, int nb) {
   p.sc = res_align(sizeof(ResState));
   p.sums = res_align(p.sc + (size_t)2 * nb * sizeof(double));
   p.part = p.sums + (size_t)(p.count + 1) * sizeof(double);
-  p.bytes = p.part + (size_t)p.count * nslab * kResWaves * sizeof(double);
+  p.bytes = p.part + (size_t)std::min(M, kResMomentSteps) * nb * nslab * kResWaves * sizeof(double);
   return p;
 }
 

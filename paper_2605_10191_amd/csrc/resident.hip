@@ -389,8 +389,8 @@ __device__ __forceinline__ double wave_sums(double (&x)[n]) {
 }
 
 // MOM: the Chebyshev vectors t_0 = v, t_1 = H~ t_0, t_{n+1} = 2 H~ t_n -
-// t_{n-1} instead of the filter (no coefficients), n = i_top - i steps done
-// after step i, with the product <t_0|t_n> of each step: a wave's sums go to
+// t_{n-1} instead of the filter (no coefficients), n = i_top - i steps of the
+// launch done after step i, with the product <t_0|t_n> of each step: a wave's sums go to
 // part[n][column][slab][wave] while the team's other members reach the barrier.
 template <typename T, int NL, int NH, int R, int G, bool MOM>
 __device__ __forceinline__ void res_group(const ResArgs<T>& p, int c0, TeamView& tv,
@@ -893,11 +893,12 @@ bool res_chain(const polfed_op* op) {
          op->L <= kResMaxL && op->D >= 1 && !op->pattern_key.empty();
 }
 
-// One chunk after another of a recurrence of order K; put(c) supplies the
-// coefficients A of steps i0 .. i1 (and clears the state).
-template <bool MOM = false, typename T, class Put>
+// One chunk after another of a recurrence of order K; put supplies the
+// coefficients A of a chunk's steps (and clears the state), done(top, bot)
+// follows its launch.
+template <bool MOM = false, typename T, class Put, class Done>
 void res_run(hipStream_t s, const ResTable& t, const ResShape& x, ResArgs<T> a, int K, int chunk,
-             Put&& put) {
+             Put&& put, Done&& done) {
   a.sep = t.sep;
   a.nslab = t.nslab;
   a.R = t.R;
@@ -919,9 +920,15 @@ void res_run(hipStream_t s, const ResTable& t, const ResShape& x, ResArgs<T> a, 
     a.first = top == K;
     put(a, top, bot);
     res_launch<T, MOM>(s, t, grid, shm, a);
+    done(top, bot);
     if ((top - bot) % 2) std::swap(a.X, a.Y);
     top = bot;
   }
+}
+template <bool MOM = false, typename T, class Put>
+void res_run(hipStream_t s, const ResTable& t, const ResShape& x, const ResArgs<T>& a, int K,
+             int chunk, Put&& put) {
+  res_run<MOM>(s, t, x, a, K, chunk, put, [](int, int) {});
 }
 
 }  // namespace
@@ -1342,10 +1349,10 @@ void chain_res_batch(hipStream_t s, const ChainBatch& bt, const T* A, int K, con
   });
 }
 
-// out[k] = sum of part[k * n .. k * n + n), one wave a sum; out[count] = err.
+// out[k] = sum of part[k * n .. k * n + n), one wave a sum; err = st->err.
 __global__ __launch_bounds__(256) void k_res_sum(const double* part, int n, int64_t count,
-                                                 const ResState* st, double* out) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) out[count] = st->err;
+                                                 const ResState* st, double* out, double* err) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) err[0] = st->err;
   const int64_t k = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (k >= count) return;
   double x = 0;
@@ -1397,15 +1404,21 @@ void chain_res_moments(hipStream_t s, const polfed_op* op, double E_c, double dE
   r.st = st;
   r.wait = op->ctx->team_wait;
   r.part = (double*)(base + pl.part);
-  r.i_all = M - 1;
-  res_run<true>(s, *t, x, r, M, kResChunk, [&](ResArgs<double>& q, int, int) {
-    hipLaunchKernelGGL((k_res_begin<double>), dim3(8), dim3(256), 0, s, q.st, q.first, sc,
-                       2.0 / dE, -2.0 * E_c / dE, nb);
-    HIPC(hipGetLastError());
-  });
-  hipLaunchKernelGGL(k_res_sum, dim3((unsigned)((count + 3) / 4)), dim3(256), 0, s, r.part,
-                     t->nslab * kResWaves, count, st, sums);
-  HIPC(hipGetLastError());
+  res_run<true>(
+      s, *t, x, r, M, kResMomentSteps,
+      [&](ResArgs<double>& q, int top, int) {
+        q.i_all = top - 1;
+        hipLaunchKernelGGL((k_res_begin<double>), dim3(8), dim3(256), 0, s, q.st, q.first, sc,
+                           2.0 / dE, -2.0 * E_c / dE, nb);
+        HIPC(hipGetLastError());
+      },
+      [&](int top, int bot) {
+        const int64_t n = (int64_t)(top - bot) * nb;
+        hipLaunchKernelGGL(k_res_sum, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, r.part,
+                           t->nslab * kResWaves, n, st, sums + (int64_t)(M - top) * nb,
+                           sums + count);
+        HIPC(hipGetLastError());
+      });
   HIPC(hipMemcpyAsync(dots, sums, (size_t)(count + 1) * sizeof(double), hipMemcpyDeviceToHost, s));
   HIPC(hipStreamSynchronize(s));
   if (dots[count] != 0)

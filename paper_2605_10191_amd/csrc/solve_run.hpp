@@ -136,6 +136,9 @@ int block_orth(hipStream_t st, int64_t D, int k, int s, double* V, double* W, do
 void block_start(hipStream_t st, int64_t D, int s, const double* X0, double* V, double* w,
                  double* c, double* partial, int64_t nseg, int* flag, double* scal);
 
+// What setup() holds for the trace moments.
+constexpr size_t kSetupBytes = (2 + 2 * 4096) * sizeof(double);
+
 struct SolveRun {
   // device bytes held by this solve's own buffers (declared first, so it
   // outlives every buffer member that counts toward it)

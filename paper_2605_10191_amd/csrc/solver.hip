@@ -471,7 +471,7 @@ void SolveRun::setup(polfed_ctx* c, const polfed_op* o, const polfed_params& prm
 
   // 2-3. trace moments, DOS, window, K, coefficients
   t0 = now_seconds();
-  DevBuf two(2 * sizeof(double)), mpart(2 * 4096 * sizeof(double));
+  DevBuf two(2 * sizeof(double)), mpart(kSetupBytes - 2 * sizeof(double));
   op_moments(s, op, two.as<double>(), mpart.as<double>(), 4096);
   double tr[2];
   HIPC(hipMemcpyAsync(tr, two.get(), sizeof tr, hipMemcpyDeviceToHost, s));
@@ -486,7 +486,7 @@ void SolveRun::setup(polfed_ctx* c, const polfed_op* o, const polfed_params& prm
     const double Ec = 0.5 * (hi + lo), dEk = 0.5 * (hi - lo);
     kmu.resize(p.kpm_moments);
     kpm_moments(ctx, op, Ec, dEk, p.kpm_moments, p.kpm_vectors > 0 ? p.kpm_vectors : 100,
-                nullptr, kKpmSeed, kmu.data());
+                nullptr, kKpmSeed, kmu.data(), take ? footprint(op, p) - kSetupBytes : SIZE_MAX);
     peak = Ec + dEk * kpm_maxdos(kmu.data(), p.kpm_moments, (E_min + 0.05 * w - Ec) / dEk,
                                  (E_max - 0.05 * w - Ec) / dEk);
   }
@@ -570,8 +570,11 @@ size_t SolveRun::footprint(const polfed_op* op, const polfed_params& p) {
   const int n_want = (int)std::min<int64_t>(op->D, n_ev + g);
   const int M = (int)std::min<int64_t>(op->D, expected_krylov_dim(n_want, 1, p.eta > 0 ? p.eta : 1.5));
   size_t b = bytes_at(op->D, M, n_want, f32);
-  if (p.kpm_moments > 0)  // before the basis is allocated
-    b = std::max(b, kpm_workspace(op, p.kpm_moments, p.kpm_vectors > 0 ? p.kpm_vectors : 100));
+  // the moments come before the basis is allocated; setup() gives them the
+  // room of the rest
+  if (p.kpm_moments > 0)
+    b = std::max(b, kSetupBytes + kpm_workspace(op, p.kpm_moments,
+                                                p.kpm_vectors > 0 ? p.kpm_vectors : 100));
   if (!(p.E_max > p.E_min)) {
     // the bounds Lanczos before it: its basis of up to 300 steps, w and the
     // two recurrence buffers of its work space

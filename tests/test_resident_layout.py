@@ -59,7 +59,8 @@ int main() {
           const size_t sums = (size_t)M * nb * 8;  // and the error word
           ok = p.shape.ngrp + p.shape.pairs == nb && p.sc >= sizeof(ResState) &&
                p.sums >= p.sc + 16 * (size_t)nb && p.part >= p.sums + sums + 8 &&
-               p.part + sums * p.shape.nslab * kResWaves <= full.bytes;
+               p.part + (size_t)std::min(M, kResMomentSteps) * nb * 8 * p.shape.nslab *
+                            kResWaves <= full.bytes;
         }
         if (!ok) {
           std::printf("D = %%ld, %%d of %%d columns\\n", (long)D, nb, width);
