@@ -590,8 +590,7 @@ polfed_status serve_submit(polfed_ctx* ctx, const polfed_op* op, const polfed_pa
     if (p->precision != prec && p->precision != POLFED_PRECISION_AUTO) continue;
     polfed_params q = *p;
     q.precision = prec;
-    const size_t tb = prec == POLFED_FP32 ? 4 : 8;
-    fp = std::max(fp, SolveRun::footprint(op, q) + 4 * (size_t)op->D * tb);
+    fp = std::max(fp, SolveRun::footprint(op, q));
   }
   if (fp > s->budget)
     fail(POLFED_ERR_REJECTED, "serve: request needs " + std::to_string(fp) +

@@ -31,7 +31,15 @@ struct Ws {
   DevBuf w, c, partial, scal, flag, alpha, beta, bA, bB, v32, w32;
   int64_t nseg = 0, parts = 0;
   int coef_cap = 0;
-  void init(hipStream_t s, int64_t D, int max_cols, bool fp32) {
+  // Device bytes of init(); filter: with the recurrence buffers.
+  static size_t bytes(int64_t D_, int max_cols, bool fp32, bool filter) {
+    const size_t D = (size_t)std::max<int64_t>(D_, 1), n = (size_t)max_cols;
+    size_t b = D * 8 + 64 * 8 + sizeof(int) + (3 * n + 4) * 8 +
+               ((size_t)gs_parts(D_) * (n + 1) + 8192) * 8;
+    if (filter) b += filter_buf_bytes(D_, fp32 ? 4 : 8) + (fp32 ? 3 * D * 4 : D * 8);
+    return b;
+  }
+  void init(hipStream_t s, int64_t D, int max_cols, bool fp32, bool filter = true) {
     w.alloc(std::max<int64_t>(D, 1) * sizeof(double));
     nseg = std::max<int64_t>(1, std::min<int64_t>(256, (D + 8191) / 8192));
     parts = gs_parts(D);
@@ -39,6 +47,7 @@ struct Ws {
     scal.alloc(64 * sizeof(double));
     flag.alloc(sizeof(int));
     HIPC(hipMemsetAsync(flag.get(), 0, sizeof(int), s));
+    if (!filter) return;
     const size_t tb = fp32 ? sizeof(float) : sizeof(double);
     bA.alloc(filter_buf_bytes(D, tb));
     bB.alloc(std::max<int64_t>(D, 1) * tb);

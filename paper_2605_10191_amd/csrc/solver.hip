@@ -244,10 +244,11 @@ void bounds(polfed_ctx* ctx, const polfed_op* op, const double* x0, double tol,
   if (!(tol > 0)) tol = 1e-10;
   if (max_iter <= 0) max_iter = 300;
   const int cap = (int)std::min<int64_t>(max_iter, D);
+  op_tune(s, op, false);  // its vectors are gone before the basis is there
   Basis B;
   B.ensure(s, D, cap, 0);
   Ws ws;
-  ws.init(s, D, cap + 1, false);
+  ws.init(s, D, cap + 1, false, false);
   normalize_into(s, D, x0, ws, B.col(0));
   std::vector<double> al(cap + 1), be(cap + 2);
   double lo = 0, hi = 0;
@@ -547,19 +548,17 @@ void SolveRun::setup(polfed_ctx* c, const polfed_op* o, const polfed_params& prm
 size_t SolveRun::bytes_at(int64_t D_, int m, int n, bool f32) {
   const size_t D = (size_t)std::max<int64_t>(D_, 1), vec = D * 8, M = (size_t)m, N = (size_t)n;
   const size_t nseg = (size_t)std::max<int64_t>(1, std::min<int64_t>(256, (D_ + 8191) / 8192));
-  // basis (M + 2 columns) and the coefficient and partial-sum arrays
-  size_t b = (M + 2) * vec + ((size_t)gs_parts(D_) * (M + 1) + 8192 + 3 * (M + 2)) * 8;
-  // w, the filter's two recurrence buffers, the FP32 copies of v and w,
-  // and the fixed graph input (FP64)
-  b += vec + (f32 ? 4 * D * 4 : 3 * vec) + ResTail::bytes;
+  // basis and work space
+  size_t b = (M + 2) * vec + Ws::bytes(D_, m + 2, f32, true);
   // check and extraction: the tridiagonal eigenvectors (M x M), the chosen
-  // ones (M x n), the projected matrix and its eigenvectors, partial sums,
-  // the split sums of the projection product
-  b += (M * M + M * N + 2 * N * N + nseg * N + 8192) * 8 + gemm_tn_workspace(D_, n, n);
+  // ones (M x n), the projected matrix and its eigenvectors, partial sums
+  b += (M * M + M * N + 2 * N * N + nseg * N + 8192) * 8;
   // FP64: U, HU, U2, HU2.  FP32 refinement: the extracted U2, HU2, four
   // FP32 blocks, five FP64 blocks and the next Rayleigh-Ritz generation;
-  // then the two FP64 recurrence buffers of the FP64 fallback.
-  b += f32 ? 11 * N * vec + 2 * vec : 4 * N * vec;
+  // then the two FP64 recurrence buffers of the FP64 fallback.  The split sums
+  // of the projection product are gone before the last two are allocated.
+  const size_t last = std::max(2 * N * vec, gemm_tn_workspace(D_, n, n));
+  b += f32 ? 9 * N * vec + last + 2 * vec : 2 * N * vec + last;
   return b;
 }
 
@@ -569,18 +568,18 @@ size_t SolveRun::footprint(const polfed_op* op, const polfed_params& p) {
   const int g = (f32 ? 2 : 1) * buffer_size(n_ev);
   const int n_want = (int)std::min<int64_t>(op->D, n_ev + g);
   const int M = (int)std::min<int64_t>(op->D, expected_krylov_dim(n_want, 1, p.eta > 0 ? p.eta : 1.5));
-  size_t b = bytes_at(op->D, M, n_want, f32);
-  // the moments come before the basis is allocated; setup() gives them the
-  // room of the rest
+  const size_t D = (size_t)std::max<int64_t>(op->D, 1);
+  // the solve's own buffers and its columns of the group's filter
+  size_t b = bytes_at(op->D, M, n_want, f32) + 4 * D * (f32 ? 4 : 8);
+  // the moments come before either; setup() gives them the room of the rest
   if (p.kpm_moments > 0)
     b = std::max(b, kSetupBytes + kpm_workspace(op, p.kpm_moments,
                                                 p.kpm_vectors > 0 ? p.kpm_vectors : 100));
   if (!(p.E_max > p.E_min)) {
-    // the bounds Lanczos before it: its basis of up to 300 steps, w and the
-    // two recurrence buffers of its work space
-    const size_t D = (size_t)std::max<int64_t>(op->D, 1);
-    const size_t cap = (size_t)std::min<int64_t>(300, op->D);
-    b = std::max(b, (cap + 2 + 3) * D * 8 + (cap + 2) * 8 * 3 + 8192 * 8 * 2);
+    // and so does the bounds Lanczos: its basis of up to 300 steps and its work
+    // space
+    const int cap = (int)std::min<int64_t>(300, op->D);
+    b = std::max(b, (cap + 1) * D * 8 + Ws::bytes(op->D, cap + 1, false, false));
   }
   return b;
 }

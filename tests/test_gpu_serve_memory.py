@@ -40,3 +40,13 @@ def test_kpm_moments_in_the_room_of_the_solve(pk, own, prec):
     got, rep = served(pk, own, op, budget, 2, kpm_moments=64, kpm_vectors=64, **kw)
     say(f"   with moments: peak {rep['mem_peak'] / 1e6:.2f} MB")
     assert np.max(np.abs(got - plain)) <= 1e-9
+
+
+# few pairs: the bounds before the iteration hold the most, up to 300 vectors
+# and a partial sum of every column for each of up to 768 workgroups
+@pytest.mark.parametrize("L,N", [(12, 6), (16, 7), (16, 8), (18, 9)])
+def test_bounds_within_the_reservation(pk, own, L, N):
+    say(f"served bounds L={L} N={N}")
+    op = pk.Operator.xxz(own, L, N, 1.0, 1.0, wl.xxz_fields(L, 1.0, 2), True)
+    _, rep = served(pk, own, op, 1 << 30, 2)
+    say(f"   reserved {rep['mem_reserved'] / 1e6:.2f} MB, peak {rep['mem_peak'] / 1e6:.2f} MB")
