@@ -494,8 +494,10 @@ typedef struct {
   int K, M_alloc, iters, n_want, n_converged, checks, restarts, refine_sweeps;
   double t_bounds, t_plan, t_filter, t_reorth, t_check, t_extract, t_refine,
       t_total;           /* seconds */
-  double filter_steps;   /* Clenshaw steps executed */
-  double filter_bytes;   /* algorithmic HBM bytes of those steps */
+  double filter_steps;   /* Clenshaw steps executed, each on one vector (of a
+                            filter computed as a matrix: D columns, once) */
+  double filter_bytes;   /* algorithmic HBM bytes of those steps and of the
+                            products with such a matrix */
   double filter_GBps;    /* filter_bytes / t_filter / 1e9 */
   double t_queue;        /* served requests: submission to admission (s) */
   double t_latency;      /* served requests: submission to result (s) */

@@ -641,6 +641,7 @@ void SolveRun::filter_self() {
   HIPC(hipEventCreate(&e0));
   HIPC(hipEventCreate(&e1));
   HIPC(hipEventRecord(e0, s));
+  bool built = false;  // the matrix, now
   if (dense_mode == kDenseAsk) {
     // not where the launch mode was chosen by the caller, nor in the server,
     // whose admissions count the vectors only
@@ -664,6 +665,7 @@ void SolveRun::filter_self() {
         dense_mode = kDenseYes;
       else
         dense.release();
+      built = dense_mode == kDenseYes;
     }
   }
   if (fp32) dev_copy_d2f(s, D, B.col(k), ws.v32.as<float>());
@@ -684,8 +686,11 @@ void SolveRun::filter_self() {
   if (fp32) dev_copy_f2d(s, D, ws.w32.as<float>(), ws.w.as<double>());
   HIPC(hipEventRecord(e1, s));
   fev.emplace_back(e0, e1);
-  R.filter_steps += pl.K;
-  R.filter_bytes += pl.K * step_bytes(op, fp32 ? POLFED_FP32 : POLFED_FP64);
+  // the steps that ran: of the matrix those of its columns, when it was built
+  const double steps = built ? (double)pl.K * D : dense_mode == kDenseYes ? 0.0 : (double)pl.K;
+  R.filter_steps += steps;
+  R.filter_bytes += steps * step_bytes(op, fp32 ? POLFED_FP32 : POLFED_FP64);
+  if (dense_mode == kDenseYes) R.filter_bytes += 8.0 * D * D + 16.0 * D;
   // autotuning: the first application runs direct, the second as a graph;
   // the faster way serves the rest of the solve
   if (mode == kTimeDirect || mode == kTimeGraph) {
