@@ -1058,26 +1058,41 @@ int resolve_precision(hipStream_t s, const polfed_op* op, int precision) {
     const auto it = by_pattern.find(key);
     if (it != by_pattern.end()) return op->auto_precision = it->second;
   }
+  // what the solve's filter runs: the step kernel, or the resident recurrence,
+  // of which a step takes a fraction of a launch (so that FP32 gains less)
   const int64_t D = op->D;
   const size_t nd = (size_t)std::max<int64_t>(D, 1);
-  DevBuf v(nd * 8), b1(nd * 8), b2(nd * 8);
+  constexpr int K = 256;
+  const std::vector<double> a(K + 1, 0.0);
+  DevBuf v(nd * 8), w(nd * 8), b1(filter_buf_bytes(D, 8)), b2(nd * 8);
   HIPC(hipMemsetAsync(v.get(), 0, nd * 8, s));
   HIPC(hipMemsetAsync(b1.get(), 0, nd * 8, s));
   HIPC(hipMemsetAsync(b2.get(), 0, nd * 8, s));
-  auto step = [&](hipStream_t st, bool f32) {
-    if (f32)
+  auto run = [&](hipStream_t st, bool f32) {
+    if (res_applies(op, f32)) {
+      if (f32)
+        filter_apply_on<float>(st, op, 0.0, 1.0, a.data(), K, v.as<float>(), w.as<float>(),
+                               b1.as<float>(), b2.as<float>());
+      else
+        filter_apply_on<double>(st, op, 0.0, 1.0, a.data(), K, v.as<double>(), w.as<double>(),
+                                b1.as<double>(), b2.as<double>());
+    } else if (f32) {
       op_step<float>(st, op, 0.1f, 0.0f, 0.0f, v.as<float>(), b1.as<float>(), b2.as<float>(),
                      b2.as<float>());
-    else
+    } else {
       op_step<double>(st, op, 0.1, 0.0, 0.0, v.as<double>(), b1.as<double>(), b2.as<double>(),
                       b2.as<double>());
+    }
   };
-  // the first steps pick the kernel variants (timed on s, outside any capture)
-  step(s, false);
-  step(s, true);
+  // the first ones pick the kernel variants (timed on s, outside any capture)
+  run(s, false);
+  run(s, true);
   HIPC(hipStreamSynchronize(s));
-  const float t64 = replay_time_us([&](hipStream_t st) { step(st, false); }, 20);
-  const float t32 = replay_time_us([&](hipStream_t st) { step(st, true); }, 20);
+  auto step_us = [&](bool f32) {
+    const bool res = res_applies(op, f32);
+    return replay_time_us([&](hipStream_t st) { run(st, f32); }, res ? 2 : 20) / (res ? K : 1);
+  };
+  const float t64 = step_us(false), t32 = step_us(true);
   op->auto_precision = t32 < 0.7f * t64 ? POLFED_FP32 : POLFED_FP64;
   if (!key.empty()) {
     std::lock_guard<std::mutex> lk(mu);
