@@ -125,6 +125,7 @@ struct ResidentVectors {
 static int resident_width(hipStream_t s, const polfed_op* op, int M, int R, bool draw, size_t room,
                           ResidentVectors& r) {
   if (M < 4 || op->D < 1) return 0;
+  op_tune(s, op, false);  // as the steps of the other way do
   for (int cols = std::min(R, kKpmCols); cols >= 1; cols /= 2) {
     if (ResidentVectors::bytes(op, M, cols) > room) continue;
     if (!chain_res_moments_fit(s, op, cols)) return 0;

@@ -201,8 +201,10 @@ void apply_H(hipStream_t s, const polfed_op* op, const double* x, double* y) {
   op_step<double>(s, op, 1.0, 0.0, 0.0, nullptr, x, nullptr, y);
 }
 
-// Y = H X for n vectors (D x n).
+// Y = H X for n vectors (D x n).  Chooses the operator's step kernel as one
+// application does.
 void apply_H_block(hipStream_t s, const polfed_op* op, int n, const double* X, double* Y) {
+  op_tune(s, op, false);
   if (chain_apply_block(s, op, n, X, Y)) return;
   for (int j = 0; j < n; ++j) apply_H(s, op, X + (size_t)j * op->D, Y + (size_t)j * op->D);
 }
