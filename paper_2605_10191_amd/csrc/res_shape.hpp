@@ -53,18 +53,21 @@ inline int res_r(int64_t D, int nslab) {
   return (res_rows(D, nslab) + kResThreads - 1) / kResThreads;
 }
 
-// Measured on an MI355X (FP64, us a step): slabs 1, 8, 16, 32 with one row a
-// thread 1.0 (two rows), 1.4, 1.6, 2.0; another row a thread adds 0.75, with
-// a pair of columns 1.2.  The model below follows these within 15% and picks
-// the cheapest shape: one workgroup up to 1,024 rows, one row a thread as
-// long as 32 slabs allow it, pairs once there are more columns than teams.
-// (nslab 0: none.)
+// Measured on an MI355X (FP64, us a step): one workgroup with one row a thread
+// 0.68, with two 0.97 (two slabs of one row 1.15), pairs of columns with two
+// rows 2.2; 8, 16, 32 slabs with one row 1.4, 1.6, 2.0, where another row a
+// thread adds 0.75 and one of a pair of columns is 1.2.  The model below follows
+// these within 15% and picks the cheapest shape: one workgroup up to 1,024
+// rows, one row a thread as long as 32 slabs allow it, pairs once there are
+// more columns than teams.  (nslab 0: none.)
 inline ResShape res_shape_at(int64_t D, int nb, int nslab) {
   ResShape best;
   const int R = res_r(D, nslab);
   if (R > kResMaxRows || (nslab == 1 && R > 2)) return best;
   const int teams = nslab == 1 ? 256 : 8 * std::min(kResMaxSlabs / nslab, kResTeamsPerXcd);
-  const double base = nslab == 1 ? 0.3 : 0.5 + 0.0235 * nslab;
+  const bool alone = nslab == 1;  // no barriers between workgroups
+  const double base = alone ? 0.39 : 0.5 + 0.0235 * nslab;
+  const double row = alone ? 0.29 : 0.75, pair_row = alone ? 0.9 : 1.2;
   for (int pair = 0; pair < 2; ++pair) {
     ResShape x;
     x.nslab = nslab;
@@ -79,7 +82,7 @@ inline ResShape res_shape_at(int64_t D, int nb, int nslab) {
       if (x.pairs == 0) continue;
     }
     x.ngrp = nb - x.pairs;
-    x.us = rounds * (base + (pair ? 1.2 : 0.75) * R);
+    x.us = rounds * (base + (pair ? pair_row : row) * R);
     if (x.us < best.us) best = x;
   }
   return best;

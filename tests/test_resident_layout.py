@@ -114,3 +114,20 @@ int main() {
   }
 }
 """)
+
+
+def test_one_column_takes_one_workgroup_up_to_1024_rows(tmp_path):
+    """Two rows a thread of one workgroup measured faster than two slabs with
+    a barrier between them; above that, slabs of one row a thread."""
+    run_host(tmp_path, """
+int main() {
+  for (int64_t D = 1; D <= 16384; ++D) {
+    const ResShape x = res_shape(D, 1);
+    if ((x.nslab == 1) != (D <= 1024) || x.pairs != 0 || x.ngrp != 1 ||
+        (x.nslab > 1 && x.R != 1)) {
+      std::printf("D = %ld: %d slabs, %d rows\\n", (long)D, x.nslab, x.R);
+      return 1;
+    }
+  }
+}
+""")
