@@ -425,6 +425,7 @@ polfed_status polfed_create(int device, void* hip_stream, polfed_ctx** out) {
     HIPC(hipGetDeviceProperties(&prop, device));
     ctx->n_cu = prop.multiProcessorCount;
     (void)resolve_scratch(device);  // device is current here
+    ctx->noalloc_tail.alloc(ResTail::bytes);
     *out = ctx.release();
     return POLFED_OK;
   });
@@ -441,6 +442,7 @@ polfed_status polfed_destroy(polfed_ctx* ctx) {
       ctx->scratch_scalar.release();
       ctx->binom.release();
       for (auto& b : ctx->ws) b.release();
+      ctx->noalloc_tail.release();
       unregister_stream(ctx->device, ctx->stream);
       if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
       if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
@@ -918,11 +920,11 @@ polfed_status polfed_filter_apply_noalloc(polfed_ctx* ctx, const polfed_op* op, 
     if (precision == POLFED_FP64)
       filter_apply<double>(ctx, op, E_c, dE, a, K, static_cast<const double*>(v),
                            static_cast<double*>(w), reinterpret_cast<double*>(base),
-                           reinterpret_cast<double*>(base + half));
+                           reinterpret_cast<double*>(base + half), ctx->noalloc_tail.get());
     else
       filter_apply<float>(ctx, op, E_c, dE, a, K, static_cast<const float*>(v),
                           static_cast<float*>(w), reinterpret_cast<float*>(base),
-                          reinterpret_cast<float*>(base + half));
+                          reinterpret_cast<float*>(base + half), ctx->noalloc_tail.get());
     return POLFED_OK;
   });
 }

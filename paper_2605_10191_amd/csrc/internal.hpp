@@ -339,6 +339,9 @@ struct polfed_ctx {
   polfed::DevBuf scratch_scalar;
   polfed::DevBuf binom;  // binomial table for the basis calls
   polfed::DevBuf ws[8];  // scratch of the single-step entry points
+  // team state of the allocation-free filter, whose vectors lie in an array
+  // that all contexts of a device share
+  polfed::DevBuf noalloc_tail;
   polfed::Server* server = nullptr;
 };
 
@@ -568,10 +571,11 @@ inline size_t filter_buf_bytes(int64_t n, size_t elem) {
   return (size_t)std::max<int64_t>(n, 1) * elem + ResTail::bytes;
 }
 // The filter as one resident launch; false (nothing done) where it does not
-// apply or K is small.
+// apply or K is small.  tail: ResTail::bytes for its state (null: behind bufA's
+// D elements).
 template <typename T>
 bool res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const double* a,
-                      int K, const T* v, T* w, T* bufA, T* bufB);
+                int K, const T* v, T* w, T* bufA, T* bufB, void* tail);
 bool chain_res_batch_fits(hipStream_t s, const polfed_op* op0, int nb);
 // The filter as a matrix, for solves of short chains (see there).
 bool chain_dense_pays(const polfed_op* op, int K, int M);
@@ -726,10 +730,12 @@ int expected_krylov_dim(int howmany, int blocksize, double eta);
 // as filter_apply, on an explicit stream (graph capture)
 template <typename T>
 void filter_apply_on(hipStream_t s, const polfed_op* op, double E_c, double dE,
-                     const double* a, int K, const T* v, T* w, T* bufA, T* bufB);
+                     const double* a, int K, const T* v, T* w, T* bufA, T* bufB,
+                     void* tail = nullptr);
 template <typename T>
 void filter_apply(polfed_ctx* ctx, const polfed_op* op, double E_c, double dE,
-                  const double* a, int K, const T* v, T* w, T* bufA, T* bufB);
+                  const double* a, int K, const T* v, T* w, T* bufA, T* bufB,
+                  void* tail = nullptr);
 void bounds(polfed_ctx* ctx, const polfed_op* op, const double* x0, double tol,
             int max_iter, double* E_min, double* E_max, int* iters);
 polfed_status solve(polfed_ctx* ctx, const polfed_op* op, const polfed_params& p,

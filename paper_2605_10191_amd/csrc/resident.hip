@@ -67,11 +67,19 @@ struct TeamView {
   int step;  // barriers passed
   int failed;
   long long wait;  // of a barrier at most, in ticks
+  int* fail;       // LDS: a barrier of this workgroup gave up
 };
 
-// All members have stored what they wrote before; afterwards all see it.  A
-// barrier that gives up sets err and lets its member run on to the end: what
-// the call returns is then NaN or an error, never a number.
+// Every wait is bounded, so that a kernel ends whatever happens to its team's
+// state: a barrier that gives up sets err and lets its member run on to the end
+// of the columns it is at, and what the call returns is NaN or an error.
+// What a member that cannot go on leaves of n elements of a result.
+template <typename T>
+__device__ __forceinline__ void poison(T* w, int64_t n) {
+  for (int64_t i = threadIdx.x; i < n; i += kResThreads) w[i] = T(NAN);
+}
+
+// All members have stored what they wrote before; afterwards all see it.
 // between() runs once the workgroup's own LDS reads are done, while the other
 // members arrive.  Every member raises its own flag and one wave polls all of
 // them with one load.
@@ -89,6 +97,7 @@ __device__ __forceinline__ void team_barrier(TeamView& tv, int* err, F&& between
     while (__ballot(res_load(f) < tv.step)) {
       if (wall_clock64() - t0 >= tv.wait) {
         tv.failed = 1;
+        *tv.fail = 1;
         res_store(err, 1);
         break;
       }
@@ -98,9 +107,11 @@ __device__ __forceinline__ void team_barrier(TeamView& tv, int* err, F&& between
 }
 
 // Joins the next team of this workgroup's XCD (nslab members); false for a
-// workgroup that came too late or is not needed.
+// workgroup that came too late or is not needed, or (*tv.fail) that waited too
+// long for its team to close.
 __device__ __forceinline__ bool team_join(ResState* st, int nslab, int teams_per_xcd, int* s_join,
                                           TeamView& tv) {
+  if (threadIdx.x == 0) *tv.fail = 0;
   if (nslab <= 1) return true;
   if (threadIdx.x == 0) {
     const int x = xcc_id();
@@ -119,7 +130,13 @@ __device__ __forceinline__ bool team_join(ResState* st, int nslab, int teams_per
         res_store(&t->n, n);
       } else if (rank < kResClosed) {
         // the first member runs and closes the team within 100 us
-        while ((n = res_load(&t->n)) == 0) __builtin_amdgcn_s_sleep(1);
+        const long long t0 = wall_clock64();
+        while ((n = res_load(&t->n)) == 0 && wall_clock64() - t0 < kResWait)
+          __builtin_amdgcn_s_sleep(1);
+        if (n == 0) {
+          *tv.fail = 1;
+          res_store(&st->err, 1);
+        }
       }
     }
     s_join[0] = n;
@@ -538,9 +555,16 @@ template <typename T, int NL, int NH, int R, bool MOM>
 __global__ __launch_bounds__(kResThreads) void k_chain_res(ResArgs<T> p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ double s_field[2 * kFieldStride];
-  __shared__ int s_join[4];
-  TeamView tv{nullptr, 1, 0, 0, 0, p.wait};
-  if (!team_join(p.st, p.nslab, p.teams_per_xcd, s_join, tv)) return;
+  __shared__ int s_join[4], s_fail;
+  TeamView tv{nullptr, 1, 0, 0, 0, p.wait, &s_fail};
+  // all columns' rows, as the ones that are this member's are not known
+  auto give_up = [&] {
+    if (!MOM) poison(p.w, p.D * p.nb);  // moments: err fails the call
+  };
+  if (!team_join(p.st, p.nslab, p.teams_per_xcd, s_join, tv)) {
+    if (s_fail) give_up();
+    return;
+  }
   for (int round = 0;; ++round) {
     if (threadIdx.x == 0 && tv.rank == 0) {
       const int g = res_add(&p.st->queue, 1);
@@ -550,6 +574,10 @@ __global__ __launch_bounds__(kResThreads) void k_chain_res(ResArgs<T> p) {
         s_join[3] = g;
     }
     team_barrier(tv, &p.st->err, [] {});
+    if (s_fail) {
+      give_up();
+      return;
+    }
     const int g = uniform(tv.n > 1 ? res_load(&tv.t->group[round & 1]) : s_join[3]);
     if (g >= p.ngrp) return;
     // pairs of columns first, then single ones
@@ -592,13 +620,16 @@ constexpr int kDenseMaxRows = 2048;  // of a filter applied as a matrix
 template <typename T, int DG, int ITEMS, int ND>
 __global__ __launch_bounds__(kResThreads) void k_qsun_res(QsunRes<T> p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  __shared__ int s_join[4];
+  __shared__ int s_join[4], s_fail;
   __shared__ T s_amp[kQsunMaxL];
   constexpr uint32_t TB = sizeof(T);
   const int L = p.q.L, nd = 1 << p.q.N, nslab = 1 << p.sbits;
   const int lo = L - p.sbits, nob = 1 << lo;  // outer bits inside a slab
-  TeamView tv{nullptr, 1, 0, 0, 0, p.wait};
-  if (!team_join(p.st, nslab, 1, s_join, tv)) return;
+  TeamView tv{nullptr, 1, 0, 0, 0, p.wait, &s_fail};
+  if (!team_join(p.st, nslab, 1, s_join, tv)) {
+    if (s_fail) poison(p.w, p.q.D);
+    return;
+  }
   // the first team takes the column
   if (threadIdx.x == 0 && tv.rank == 0) {
     const int g = res_add(&p.st->queue, 1);
@@ -945,13 +976,14 @@ void chain_res_prepare(hipStream_t s, const polfed_op* op, bool fp32) {
 }
 
 template <typename T>
-static bool chain_res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const double* a,
-                      int K, const T* v, T* w, T* bufA, T* bufB) {
+static bool chain_res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE,
+                             const double* a, int K, const T* v, T* w, T* bufA, T* bufB,
+                             void* tail) {
   if (K < kResMinSteps || !chain_res_applies(op, sizeof(T) == 4)) return false;
   const ResShape x = res_shape(op->D, 1);
   const auto t = res_table(s, op, x.nslab, false);
   if (!t || !res_instance(*t)) return false;
-  const uintptr_t p = res_align((uintptr_t)(bufA + op->D));
+  const uintptr_t p = res_align(tail ? (uintptr_t)tail : (uintptr_t)(bufA + op->D));
   ResState* st = (ResState*)(p + ResTail::st);
   T* sc = (T*)(p + ResTail::sc);
   T* A = (T*)(p + ResTail::A);
@@ -1010,8 +1042,8 @@ bool res_applies(const polfed_op* op, bool fp32) {
 
 template <typename T>
 bool res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const double* a, int K,
-                const T* v, T* w, T* bufA, T* bufB) {
-  if (chain_res_filter<T>(s, op, E_c, dE, a, K, v, w, bufA, bufB)) return true;
+                const T* v, T* w, T* bufA, T* bufB, void* tail) {
+  if (chain_res_filter<T>(s, op, E_c, dE, a, K, v, w, bufA, bufB, tail)) return true;
   if (K < kResMinSteps || !qsun_res_applies(op, sizeof(T) == 4)) return false;
   const int items = qsun_items(op), N = op->N_dot;
   QsunRes<T> r{};
@@ -1023,7 +1055,7 @@ bool res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const
   r.w = w;
   r.X = bufA;
   r.Y = bufB;
-  const uintptr_t p = res_align((uintptr_t)(bufA + op->D));
+  const uintptr_t p = res_align(tail ? (uintptr_t)tail : (uintptr_t)(bufA + op->D));
   r.st = (ResState*)(p + ResTail::st);
   r.wait = op->ctx->team_wait;
   T* A = (T*)(p + ResTail::A);
@@ -1171,11 +1203,14 @@ __global__ __launch_bounds__(kResThreads) void k_cgs2_team(
     ResState* st, int64_t D, int k1, int nm, const double* V, double* w, double* c, double* norm,
     int* flag, double* alpha, double* beta, double* v_next) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  __shared__ int s_join[4];
+  __shared__ int s_join[4], s_fail;
   __shared__ double s_red[kResWaves * 64];
   double* s_c = reinterpret_cast<double*>(smem);  // [k1]
-  TeamView tv{nullptr, 1, 0, 0, 0, kResWait};
-  if (!team_join(st, nm, 1, s_join, tv)) return;
+  TeamView tv{nullptr, 1, 0, 0, 0, kResWait, &s_fail};
+  if (!team_join(st, nm, 1, s_join, tv)) {
+    if (s_fail) poison(v_next, D);
+    return;
+  }
   // the first team does it
   if (threadIdx.x == 0 && tv.rank == 0) {
     const int g = res_add(&st->queue, 1);
@@ -1301,9 +1336,9 @@ bool cgs2_team(hipStream_t s, int64_t D, int k1, const double* V, double* w, dou
 }
 
 template bool res_filter<double>(hipStream_t, const polfed_op*, double, double, const double*, int,
-                                 const double*, double*, double*, double*);
+                                 const double*, double*, double*, double*, void*);
 template bool res_filter<float>(hipStream_t, const polfed_op*, double, double, const double*, int,
-                                const float*, float*, float*, float*);
+                                const float*, float*, float*, float*, void*);
 
 bool chain_res_batch_fits(hipStream_t s, const polfed_op* op0, int nb) {
   if (!res_chain(op0)) return false;

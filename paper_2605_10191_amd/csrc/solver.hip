@@ -86,7 +86,7 @@ static void scale_t(hipStream_t s, int64_t n, T a, const T* x, T* y) {
 // carry the recurrence.
 template <typename T>
 void filter_apply_on(hipStream_t s, const polfed_op* op, double E_c, double dE,
-                     const double* a, int K, const T* v, T* w, T* bufA, T* bufB) {
+                     const double* a, int K, const T* v, T* w, T* bufA, T* bufB, void* tail) {
   const int64_t D = op->D;
   const T sigma = (T)(2.0 / dE), tau = (T)(-2.0 * E_c / dE);
   if (K == 0) {
@@ -99,7 +99,7 @@ void filter_apply_on(hipStream_t s, const polfed_op* op, double E_c, double dE,
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     HIPC(hipStreamIsCapturing(s, &cs));
     if (cs == hipStreamCaptureStatusNone) op_tune(s, op, sizeof(T) == 4);
-    if (res_filter<T>(s, op, E_c, dE, a, K, v, w, bufA, bufB)) return;
+    if (res_filter<T>(s, op, E_c, dE, a, K, v, w, bufA, bufB, tail)) return;
   }
   scale_t<T>(s, D, (T)a[K], v, bufA);  // b_K
   const T* cur = bufA;                  // b_{i+1}
@@ -115,22 +115,22 @@ void filter_apply_on(hipStream_t s, const polfed_op* op, double E_c, double dE,
 
 template <typename T>
 void filter_apply(polfed_ctx* ctx, const polfed_op* op, double E_c, double dE,
-                  const double* a, int K, const T* v, T* w, T* bufA, T* bufB) {
-  filter_apply_on<T>(ctx->stream, op, E_c, dE, a, K, v, w, bufA, bufB);
+                  const double* a, int K, const T* v, T* w, T* bufA, T* bufB, void* tail) {
+  filter_apply_on<T>(ctx->stream, op, E_c, dE, a, K, v, w, bufA, bufB, tail);
 }
 
 template void filter_apply_on<double>(hipStream_t, const polfed_op*, double, double,
                                       const double*, int, const double*, double*, double*,
-                                      double*);
+                                      double*, void*);
 template void filter_apply_on<float>(hipStream_t, const polfed_op*, double, double,
                                      const double*, int, const float*, float*, float*,
-                                     float*);
+                                     float*, void*);
 template void filter_apply<double>(polfed_ctx*, const polfed_op*, double, double,
                                    const double*, int, const double*, double*,
-                                   double*, double*);
+                                   double*, double*, void*);
 template void filter_apply<float>(polfed_ctx*, const polfed_op*, double, double,
                                   const double*, int, const float*, float*, float*,
-                                  float*);
+                                  float*, void*);
 
 // ------------------------------------------------------------ Lanczos ----
 
