@@ -46,6 +46,7 @@ void hip_check(hipError_t e, const char* what, const char* file, int line) {
 
 thread_local MemTally* g_mem_tally = nullptr;
 thread_local bool g_no_capture = false;
+thread_local bool g_shared_device = false;
 
 struct DeviceGuard {
   int prev = -1;
@@ -707,7 +708,10 @@ polfed_status polfed_op_set_batch_kernel(polfed_op* op, int B, int precision, in
                                        : chain_lds_filter_fits<float>(op),
               "variant 5: two vectors of this chain do not fit the LDS");
     const int key = B * 2 + (precision == POLFED_FP64 ? 0 : 1);
-    if (variant == -1) op->batch_tuned.erase(key);
+    if (variant == -1) {
+      op->batch_tuned.erase(key);
+      op->batch_set.erase(key);
+    }
     if (variant >= 0) {
       if (variant >= 2)
         REQUIRE((uint64_t)op->D * (uint64_t)B * (precision == POLFED_FP64 ? 8 : 4) <
@@ -719,6 +723,7 @@ polfed_status polfed_op_set_batch_kernel(polfed_op* op, int B, int precision, in
                               "columns)");
       }
       op->batch_tuned[key] = variant;
+      op->batch_set.insert(key);
     }
     if (chosen) {
       const auto it = op->batch_tuned.find(key);

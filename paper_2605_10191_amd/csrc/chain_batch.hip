@@ -622,15 +622,25 @@ int batch_variant(hipStream_t s, const ChainBatch& bt) {
   // the operators that hold them and are not built under capture: a choice of
   // it is taken only with them (false: it is timed anew).
   auto usable = [&](int v) { return v != 5 || chain_res_batch_fits(s, op0, bt.nb); };
+  const std::string pkey = "batch" + std::to_string(bt.nb) + (sizeof(T) == 8 ? "|64" : "|32");
+  // Beside other streams a resident launch that fills an XCD gives way to the
+  // fastest of the other variants, unless the caller set it.
+  const bool no_res = g_shared_device && !chain_res_batch_shares(op0, bt.nb);
   {
     auto it = op0->batch_tuned.find(key);
-    if (it != op0->batch_tuned.end() && usable(it->second)) return it->second;
+    if (it != op0->batch_tuned.end() && (it->second != 5 || !no_res || op0->batch_set.count(key)) &&
+        usable(it->second))
+      return it->second;
   }
   // an earlier choice for this chain pattern (any operator of it)
-  const std::string pkey = "batch" + std::to_string(bt.nb) + (sizeof(T) == 8 ? "|64" : "|32");
   {
     const int v = pattern_choice(op0, pkey);
-    if (v >= 0 && usable(v)) return op0->batch_tuned[key] = v;
+    if (v == 5 && no_res) {
+      const int w = pattern_choice(op0, pkey + "|shared");
+      if (w >= 0) return w;
+    } else if (v >= 0 && usable(v)) {
+      return op0->batch_tuned[key] = v;
+    }
   }
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   HIPC(hipStreamIsCapturing(s, &cs));
@@ -643,8 +653,8 @@ int batch_variant(hipStream_t s, const ChainBatch& bt) {
   HIPC(hipMemsetAsync(b2.get(), 0, n * sizeof(T), s));
   HIPC(hipMemsetAsync(ac.get(), 0, bt.nb * sizeof(T), s));
   HIPC(hipStreamSynchronize(s));
-  int best = 0;
-  float best_us = 1e30f;
+  int best = 0, other = 0;  // of all, of those but the resident one
+  float best_us = 1e30f, other_us = 1e30f;
   for (int var = 0; var < kBatchVariants; ++var) {
     if ((var == 2 || var == 3) && !interleaved_fits(bt, sizeof(T))) continue;
     if ((var == 6 || var == 7) && !rows_fit(bt, sizeof(T))) continue;
@@ -687,6 +697,10 @@ int batch_variant(hipStream_t s, const ChainBatch& bt) {
     if (verbose())
       std::fprintf(stderr, "[polfed] batch step L=%d nb=%d %s variant %d: %.2f us\n", op0->L,
                    bt.nb, sizeof(T) == 8 ? "fp64" : "fp32", var, us);
+    if (us < other_us) {
+      other_us = us;
+      other = var;
+    }
     if (us < best_us) {
       best_us = us;
       best = var;
@@ -694,8 +708,9 @@ int batch_variant(hipStream_t s, const ChainBatch& bt) {
   }
   HIPC(hipStreamSynchronize(s));
   pattern_choice_set(op0, pkey, best);
+  pattern_choice_set(op0, pkey + "|shared", other);
   op0->batch_tuned[key] = best;
-  return best;
+  return best == 5 && no_res ? other : best;
 }
 
 template <typename T>

@@ -12,6 +12,7 @@
 #include <shared_mutex>
 #include <stdexcept>
 #include <map>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -137,6 +138,10 @@ class GraphExec {
 // one thread can be invalidated by HIP calls other threads make meanwhile,
 // and the server's rounds run side by side on several threads.
 extern thread_local bool g_no_capture;
+
+// Set on the server's threads while several groups of solves are in flight:
+// what they launch leaves room for the others (see res_shares).
+extern thread_local bool g_shared_device;
 
 // Average run time in microseconds of one call of launch(stream), taken from
 // a replay of a graph of `reps` calls on a private stream (on a thread that
@@ -434,6 +439,7 @@ struct polfed_op {
   mutable std::map<int, WTiles> wtiles;
   // multi-column step variant per (batch width, precision), by timing
   mutable std::map<int, int> batch_tuned;
+  std::set<int> batch_set;  // of them, those set by the caller
   // step-kernel variant picked by timing on first use, per precision
   // (-1: not tuned yet, 0: segment kernel, 1 + i: tile kernel tiles[i])
   mutable int tuned[2] = {-1, -1};
@@ -577,6 +583,8 @@ template <typename T>
 bool res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const double* a,
                 int K, const T* v, T* w, T* bufA, T* bufB, void* tail);
 bool chain_res_batch_fits(hipStream_t s, const polfed_op* op0, int nb);
+// Whether that launch leaves room for other streams'.
+bool chain_res_batch_shares(const polfed_op* op0, int nb);
 // The filter as a matrix, for solves of short chains (see there).
 bool chain_dense_pays(const polfed_op* op, int K, int M);
 size_t chain_dense_bytes(const polfed_op* op);

@@ -981,6 +981,7 @@ static bool chain_res_filter(hipStream_t s, const polfed_op* op, double E_c, dou
                              void* tail) {
   if (K < kResMinSteps || !chain_res_applies(op, sizeof(T) == 4)) return false;
   const ResShape x = res_shape(op->D, 1);
+  if (g_shared_device && !res_shares(x)) return false;
   const auto t = res_table(s, op, x.nslab, false);
   if (!t || !res_instance(*t)) return false;
   const uintptr_t p = res_align(tail ? (uintptr_t)tail : (uintptr_t)(bufA + op->D));
@@ -1045,6 +1046,7 @@ bool res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const
                 const T* v, T* w, T* bufA, T* bufB, void* tail) {
   if (chain_res_filter<T>(s, op, E_c, dE, a, K, v, w, bufA, bufB, tail)) return true;
   if (K < kResMinSteps || !qsun_res_applies(op, sizeof(T) == 4)) return false;
+  if (g_shared_device && (1 << qsun_slab_bits(op)) > kResSharedPerXcd) return false;
   const int items = qsun_items(op), N = op->N_dot;
   QsunRes<T> r{};
   r.q = op->qsun();
@@ -1339,6 +1341,10 @@ template bool res_filter<double>(hipStream_t, const polfed_op*, double, double, 
                                  const double*, double*, double*, double*, void*);
 template bool res_filter<float>(hipStream_t, const polfed_op*, double, double, const double*, int,
                                 const float*, float*, float*, float*, void*);
+
+bool chain_res_batch_shares(const polfed_op* op0, int nb) {
+  return res_shares(res_shape(op0->D, nb));
+}
 
 bool chain_res_batch_fits(hipStream_t s, const polfed_op* op0, int nb) {
   if (!res_chain(op0)) return false;

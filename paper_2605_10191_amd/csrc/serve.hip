@@ -124,7 +124,7 @@ struct Server {
   ~Server();
   void loop();
   void admit();
-  void round(Group* g, const std::string& key, std::vector<polfed_req*> members);
+  void round(Group* g, const std::string& key, std::vector<polfed_req*> members, bool alone);
   void settle(Done& d);
   void complete(polfed_req* r, polfed_status st, const std::string& err);
   void evict(polfed_req* r);
@@ -338,8 +338,9 @@ void Server::admit() {
 
 // One round of a group, on a pool thread: the filter application for every
 // member, then each member's Lanczos step.  Members that finish are handed
-// to the scheduler thread, which retires them.
-void Server::round(Group* g, const std::string& key, std::vector<polfed_req*> members) {
+// to the scheduler thread, which retires them.  alone: there is no other group.
+void Server::round(Group* g, const std::string& key, std::vector<polfed_req*> members, bool alone) {
+  g_shared_device = !alone;
   Done d;
   d.g = g;
   d.members = std::move(members);
@@ -452,6 +453,7 @@ void Server::settle(Done& d) {
 void Server::loop() {
   (void)hipSetDevice(ctx->device);
   g_no_capture = true;
+  g_shared_device = true;  // set-ups and restarts, beside the groups
   for (;;) {
     std::deque<Done> ended;
     {
@@ -522,7 +524,8 @@ void Server::loop() {
       Group* g = gp.get();
       std::string key = kv.first;
       std::vector<polfed_req*> mem = kv.second;
-      post([this, g, key, mem]() { round(g, key, mem); });
+      const bool alone = groups.size() == 1 && by_key.size() == 1;
+      post([this, g, key, mem, alone]() { round(g, key, mem, alone); });
       launched = true;
     }
     // solves waiting for budget: granted now if others have released bytes

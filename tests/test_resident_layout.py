@@ -131,3 +131,25 @@ int main() {
   }
 }
 """)
+
+
+def test_resident_launches_that_share_the_device(tmp_path):
+    """Beside other streams: chains up to 8,192 rows for up to 8 columns (16 up to
+    4,096 rows) leave half of every XCD free, longer ones do not go resident."""
+    run_host(tmp_path, """
+int main() {
+  for (int64_t D = 1; D <= 98304; ++D)
+    for (int nb : {1, 3, 8, 9, 16, 17, 64}) {
+      const ResShape x = res_shape(D, nb);
+      if (!x.nslab) continue;
+      // the workgroups of all teams that the launch asks for on one XCD
+      const int wgs = x.nslab == 1 ? (x.ngrp + 7) / 8 : ((x.ngrp + 7) / 8) * x.nslab;
+      if (res_shares(x) && std::min(wgs, 32) > 16) return 1;
+      if (!res_shares(x) && wgs <= 16) return 2;
+      if (D <= 1024 && nb <= 64 && !res_shares(x)) return 3;
+      if (D > 1024 && D <= 4096 && nb <= 16 && !res_shares(x)) return 4;
+      if (D > 4096 && D <= 8192 && nb <= 8 && !res_shares(x)) return 5;
+      if (D > 16384 && res_shares(x)) return 6;
+    }
+}
+""")
