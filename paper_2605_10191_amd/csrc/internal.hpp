@@ -318,11 +318,18 @@ struct ResTable;
 }
 
 struct polfed_ctx {
+  // 0 .. 7 in turn, so that contexts that are used side by side prefer
+  // different XCDs
+  static int next_home() {
+    static std::atomic<unsigned> n{0};
+    return (int)(n++ % 8);
+  }
   int device = 0;
   hipStream_t stream = nullptr;
   bool own_stream = false;
   hipStream_t cap_stream = nullptr;  // private stream for graph capture
   int n_cu = 256;
+  int home = next_home();  // where its resident launches for one column go
   // how long the teams' barriers wait (polfed_set_team_wait)
   std::atomic<long long> team_wait{polfed::kResWait};
   std::mutex mu;  // serializes calls that use the shared workspaces
@@ -557,6 +564,7 @@ struct ResArgs {
   const T* v;
   T *w, *X, *Y;
   ResState* st;
+  int home;        // workgroup whose XCD is preferred, see team_join
   long long wait;  // of a barrier
   double* part;  // moments: partial products; i_all: the launch's first step
   int i_all;

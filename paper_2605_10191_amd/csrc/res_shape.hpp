@@ -27,7 +27,8 @@ struct ResTeam {
 struct ResState {
   int slots[16 * 16];  // workgroups that joined, per XCD, a cache line apart
   int queue, err;
-  int pad[14];
+  int home;  // 1 + the XCD of a launch for one column group, see team_join
+  int pad[13];
   ResTeam teams[16 * kResTeamsPerXcd];
 };
 

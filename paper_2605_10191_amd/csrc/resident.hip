@@ -24,8 +24,8 @@
 //
 // Teams form from the workgroups that are running: a workgroup reads the XCD
 // it is on and joins that XCD's next team; the first member closes the team
-// when it is full or after a bounded time, and a workgroup that comes later
-// leaves at once.  So a barrier only ever waits for workgroups that run, no
+// when it is full or after a bounded time (see team_join), and a workgroup that
+// comes later leaves at once.  So a barrier only ever waits for workgroups that run, no
 // matter what else the device executes, and a team with fewer members than
 // slabs walks several slabs a member (reloading their state) instead.  Column
 // groups are handed out by a counter, so any set of teams finishes them all.
@@ -109,12 +109,25 @@ __device__ __forceinline__ void team_barrier(TeamView& tv, int* err, F&& between
 // Joins the next team of this workgroup's XCD (nslab members); false for a
 // workgroup that came too late or is not needed, or (*tv.fail) that waited too
 // long for its team to close.
+//
+// A launch for one column group (steps > 0 of it) needs one team out of the
+// eight that its workgroups could form.  Beside other such launches every XCD
+// gets a few workgroups of each, and a team that closes with a quarter of its
+// members walks four slabs a member, ten times slower (L = 18, four contexts,
+// 1,500 steps each: 34 ms a filter instead of 4).  So the teams that are not full
+// in time leave, all but that of the home XCD, the one where workgroup `home`
+// runs (contexts take different ones): it waits as long as it could lose that
+// way, and what the others leave makes room for the rest of its members.  As
+// long as the home XCD is not known nobody leaves, and its team is never the one
+// to leave, so one team always goes on.
 __device__ __forceinline__ bool team_join(ResState* st, int nslab, int teams_per_xcd, int* s_join,
-                                          TeamView& tv) {
+                                          TeamView& tv, int home = 0, int steps = 0) {
   if (threadIdx.x == 0) *tv.fail = 0;
   if (nslab <= 1) return true;
   if (threadIdx.x == 0) {
+    constexpr long long kJoin = 10000, kHomeMost = 200000;  // 0.1 and 2 ms
     const int x = xcc_id();
+    if (steps > 0 && (int)blockIdx.x == home) res_store(&st->home, x + 1);
     const int slot = res_add(&st->slots[16 * x], 1);
     const int team = slot / nslab;
     int n = 0, rank = 0;
@@ -123,10 +136,22 @@ __device__ __forceinline__ bool team_join(ResState* st, int nslab, int teams_per
       rank = res_add(&t->joined, 1);
       if (rank == 0) {
         const long long t0 = wall_clock64();
-        while (res_load(&t->joined) < nslab && wall_clock64() - t0 < 10000) {
+        const long long most =
+            steps > 0 ? min(max((long long)steps * 200, kJoin), kHomeMost) : kJoin;
+        bool leave = false;
+        while (res_load(&t->joined) < nslab) {
+          const long long dt = wall_clock64() - t0;
+          if (dt >= most) break;
+          if (dt < kJoin) continue;
+          const int h = res_load(&st->home);
+          if (h != 0 && h != x + 1) {
+            leave = true;
+            break;
+          }
         }
         n = __hip_atomic_fetch_or(&t->joined, kResClosed, __ATOMIC_RELAXED,
                                   __HIP_MEMORY_SCOPE_AGENT);
+        if (leave && n < nslab) n = -1;
         res_store(&t->n, n);
       } else if (rank < kResClosed) {
         // the first member runs and closes the team within 100 us
@@ -139,7 +164,7 @@ __device__ __forceinline__ bool team_join(ResState* st, int nslab, int teams_per
         }
       }
     }
-    s_join[0] = n;
+    s_join[0] = max(n, 0);
     s_join[1] = rank;
     s_join[2] = x * kResTeamsPerXcd + team;
   }
@@ -561,7 +586,8 @@ __global__ __launch_bounds__(kResThreads) void k_chain_res(ResArgs<T> p) {
   auto give_up = [&] {
     if (!MOM) poison(p.w, p.D * p.nb);  // moments: err fails the call
   };
-  if (!team_join(p.st, p.nslab, p.teams_per_xcd, s_join, tv)) {
+  if (!team_join(p.st, p.nslab, p.teams_per_xcd, s_join, tv, p.home,
+                 p.ngrp == 1 ? p.i_top - p.i_bot : 0)) {
     if (s_fail) give_up();
     return;
   }
@@ -611,6 +637,7 @@ struct QsunRes {
   const T *A, *v;
   T *w, *X, *Y;
   ResState* st;
+  int home;
   long long wait;
 };
 
@@ -626,7 +653,7 @@ __global__ __launch_bounds__(kResThreads) void k_qsun_res(QsunRes<T> p) {
   const int L = p.q.L, nd = 1 << p.q.N, nslab = 1 << p.sbits;
   const int lo = L - p.sbits, nob = 1 << lo;  // outer bits inside a slab
   TeamView tv{nullptr, 1, 0, 0, 0, p.wait, &s_fail};
-  if (!team_join(p.st, nslab, 1, s_join, tv)) {
+  if (!team_join(p.st, nslab, 1, s_join, tv, p.home, p.i_top - p.i_bot)) {
     if (s_fail) poison(p.w, p.q.D);
     return;
   }
@@ -1007,6 +1034,7 @@ static bool chain_res_filter(hipStream_t s, const polfed_op* op, double E_c, dou
   r.Y = bufB;
   r.st = st;
   r.wait = op->ctx->team_wait;
+  r.home = op->ctx->home;
   const T sigma = (T)(2.0 / dE), tau = (T)(-2.0 * E_c / dE);
   res_run<false>(s, *t, x, r, K, kResChunk, [&](ResArgs<T>& q, int top, int bot) {
     hipLaunchKernelGGL((k_res_begin<T>), dim3(8), dim3(256), 0, s, st, q.first, sc, sigma, tau, 1);
@@ -1060,6 +1088,7 @@ bool res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const
   const uintptr_t p = res_align(tail ? (uintptr_t)tail : (uintptr_t)(bufA + op->D));
   r.st = (ResState*)(p + ResTail::st);
   r.wait = op->ctx->team_wait;
+  r.home = op->ctx->home;
   T* A = (T*)(p + ResTail::A);
   const unsigned grid = r.sbits ? 8u << r.sbits : 1u;
   const size_t nd = (size_t)1 << N;
@@ -1152,6 +1181,7 @@ bool chain_dense_build(hipStream_t s, const polfed_op* op, double E_c, double dE
   r.Y = Y;
   r.st = st;
   r.wait = op->ctx->team_wait;
+  r.home = op->ctx->home;
   res_run<false>(s, *t, x, r, K, kResChunk, [&](ResArgs<double>& q, int top, int bot) {
     hipLaunchKernelGGL((k_res_begin<double>), dim3(8), dim3(256), 0, s, q.st, q.first, sc,
                        2.0 / dE, -2.0 * E_c / dE, nb);
@@ -1383,6 +1413,7 @@ void chain_res_batch(hipStream_t s, const ChainBatch& bt, const T* A, int K, con
   r.Y = bufB;
   r.st = bt.res_state.template as<ResState>();
   r.wait = op0->ctx->team_wait;
+  r.home = bt.ctx->home;
   res_run<false>(s, *t, x, r, K, kResChunk, [&](ResArgs<T>& q, int, int) {
     hipLaunchKernelGGL((k_res_begin<T>), dim3(8), dim3(256), 0, s, q.st, q.first, (T*)nullptr,
                        T(0), T(0), 0);
@@ -1444,6 +1475,7 @@ void chain_res_moments(hipStream_t s, const polfed_op* op, double E_c, double dE
   r.Y = Y;
   r.st = st;
   r.wait = op->ctx->team_wait;
+  r.home = op->ctx->home;
   r.part = (double*)(base + pl.part);
   res_run<true>(
       s, *t, x, r, M, kResMomentSteps,
