@@ -89,6 +89,8 @@ struct DevicePool {
   std::multimap<size_t, CachedBlock> blocks;  // by bucket size
   std::vector<Fence> spare;                  // events of reused blocks (s: last stream)
   size_t cached = 0, cap = 0;
+  std::mutex whole_mu;               // see WholeDevice; taken before mu
+  Fence whole{nullptr, nullptr};     // after the last such launches
 };
 
 DevicePool& device_pool(int dev) {
@@ -169,9 +171,44 @@ void register_stream(int dev, hipStream_t s) {
   P.streams.push_back(s);
 }
 
+WholeDevice::WholeDevice(int dev, hipStream_t s) : dev_(dev), s_(s) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  HIPC(hipStreamIsCapturing(s, &cs));
+  if (cs != hipStreamCaptureStatusNone) return;
+  DevicePool& P = device_pool(dev);
+  std::unique_lock<std::mutex> lk(P.whole_mu);
+  {
+    std::lock_guard<std::mutex> pl(P.mu);
+    bool ours = false, others = false;
+    for (hipStream_t t : P.streams) (t == s ? ours : others) = true;
+    if (!ours || !others) return;  // (a private stream's event would outlive it)
+  }
+  if (P.whole.e && P.whole.s != s) HIPC(hipStreamWaitEvent(s, P.whole.e, 0));
+  lk_ = std::move(lk);
+}
+
+WholeDevice::~WholeDevice() {
+  if (!lk_.owns_lock()) return;
+  Fence& f = device_pool(dev_).whole;
+  if (f.e || hipEventCreateWithFlags(&f.e, hipEventDisableTiming) == hipSuccess) {
+    f.s = s_;
+    (void)hipEventRecord(f.e, s_);
+  } else {
+    f.e = nullptr;
+  }
+  (void)hipGetLastError();
+}
+
 void unregister_stream(int dev, hipStream_t s) {
   QuietDevice g(dev);
   DevicePool& P = device_pool(dev);
+  {
+    std::lock_guard<std::mutex> wl(P.whole_mu);
+    if (P.whole.e && P.whole.s == s) {
+      (void)hipEventDestroy(P.whole.e);
+      P.whole = Fence{nullptr, nullptr};
+    }
+  }
   std::lock_guard<std::mutex> lk(P.mu);
   auto it = std::find(P.streams.begin(), P.streams.end(), s);
   if (it != P.streams.end()) P.streams.erase(it);

@@ -101,6 +101,23 @@ class DevBuf {
 void register_stream(int dev, hipStream_t s);
 void unregister_stream(int dev, hipStream_t s);
 
+// For the scope of one call's launches that need a whole device (a resident
+// batch takes every compute unit for milliseconds): they start after those of the
+// call before, whichever registered stream it was on.  Side by side, teams of
+// both would close with a part of their members.  No effect while the stream is
+// captured or is the device's only one.
+class WholeDevice {
+ public:
+  WholeDevice(int dev, hipStream_t s);
+  ~WholeDevice();
+  WholeDevice(const WholeDevice&) = delete;
+  WholeDevice& operator=(const WholeDevice&) = delete;
+ private:
+  int dev_;
+  hipStream_t s_;
+  std::unique_lock<std::mutex> lk_;
+};
+
 // A sequence of launches recorded once on a capture stream and replayed as
 // one HIP graph on any stream.  The recorded launches keep their arguments,
 // so everything they touch must stay at the same addresses between replays.

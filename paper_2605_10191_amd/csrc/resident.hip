@@ -37,6 +37,7 @@
 
 #include <iterator>
 #include <memory>
+#include <optional>
 
 #include "chain_dev.hpp"
 #include "internal.hpp"
@@ -971,6 +972,13 @@ void res_run(hipStream_t s, const ResTable& t, const ResShape& x, ResArgs<T> a, 
   const unsigned grid = t.nslab == 1 ? (unsigned)std::min(x.ngrp, 1024)
                                      : (unsigned)(8 * a.teams_per_xcd * t.nslab);
   const size_t shm = ((size_t)(t.rows + 1) * (x.pairs ? 2 : 1) * sizeof(T) + 15) / 16 * 16;
+  // columns on every XCD, side by side with another such launch 2 to 6 times
+  // slower than one after the other (four contexts, 13 columns at L = 18 each:
+  // 231 to 400 ms, 58)
+  int dev = 0;
+  HIPC(hipGetDevice(&dev));
+  std::optional<WholeDevice> whole;
+  if (x.ngrp > 1 && !res_shares(x)) whole.emplace(dev, s);
   for (int top = K; top > 0;) {
     const int bot = std::max(0, top - chunk);
     a.i_top = top;
