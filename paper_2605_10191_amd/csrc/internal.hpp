@@ -472,7 +472,8 @@ struct polfed_op {
   bool forced[2] = {false, false};
   // tables of the resident recurrence by slab count (guarded by ctx->tune_mu)
   mutable std::map<int, std::shared_ptr<polfed::ResTable>> res_tables;
-  polfed::DevBuf d_fields;  // 32 site terms and the constant (FP64)
+  // 32 site terms and the constant (FP64), behind the field tables
+  const double* fields() const { return d_ftab.as<double>() + 1024; }
   // POLFED_PRECISION_AUTO resolved for this operator (-1: not timed yet)
   mutable int auto_precision = -1;
   std::vector<double> split_dseg;  // uniform diagonal part of each segment

@@ -815,6 +815,10 @@ static polfed_op* make_chain(polfed_ctx* ctx, int L, int N, int periodic,
   op->pattern_key = key;
   std::vector<double> tab;
   field_tables(f, L, tab);
+  // the 32 site terms and the constant behind them, in the same copy
+  tab.insert(tab.end(), f.begin(), f.end());
+  tab.resize(1024 + 32, 0.0);
+  tab.push_back(c0);
   upload_tables(op.get(), tab);
   hipStream_t s = ctx->stream;
   upload(op->d_binom, host_binom(), (size_t)kBinomN * kBinomN, s);
@@ -822,10 +826,6 @@ static polfed_op* make_chain(polfed_ctx* ctx, int L, int N, int periodic,
   build_split_rank_tables(L, N, L / 2, hi, lo);
   upload(op->d_hi_off, hi.data(), hi.size(), s);
   upload(op->d_lo_rank, lo.data(), lo.size(), s);
-  std::vector<double> fl(33, 0.0);
-  std::copy(f.begin(), f.end(), fl.begin());
-  fl[32] = c0;
-  upload(op->d_fields, fl.data(), fl.size(), s);
   HIPC(hipStreamSynchronize(s));
   if (L >= 4 && L <= 28) build_chain_split(op.get());
   return op.release();

@@ -1034,7 +1034,7 @@ static bool chain_res_filter(hipStream_t s, const polfed_op* op, double E_c, dou
   r.t_in = op->t_in;
   r.t_pb = op->t_pb;
   r.vzz = op->vzz;
-  r.fields = op->d_fields.template as<double>();
+  r.fields = op->fields();
   r.sc = sc;
   r.v = v;
   r.w = w;
@@ -1182,7 +1182,7 @@ bool chain_dense_build(hipStream_t s, const polfed_op* op, double E_c, double dE
   r.t_in = op->t_in;
   r.t_pb = op->t_pb;
   r.vzz = op->vzz;
-  r.fields = op->d_fields.as<double>();
+  r.fields = op->fields();
   r.sc = sc;
   r.w = P;
   r.X = X;
@@ -1476,7 +1476,7 @@ void chain_res_moments(hipStream_t s, const polfed_op* op, double E_c, double dE
   r.t_in = op->t_in;
   r.t_pb = op->t_pb;
   r.vzz = op->vzz;
-  r.fields = op->d_fields.as<double>();
+  r.fields = op->fields();
   r.sc = sc;
   r.v = v;
   r.X = X;
