@@ -337,6 +337,34 @@ __device__ __forceinline__ void res_setup(const ResArgs<T>& p, SlabState<T, NL, 
   constexpr uint32_t RB = G * sizeof(T);
   const int64_t row0 = slab_row(p.D, p.nslab, m), row1 = slab_row(p.D, p.nslab, m + 1);
   const uint32_t zero = (uint32_t)p.rows_cap;
+  // the diagonals first: their sums take registers that the rows' tables fill
+  // later (six rows a thread: with the sums among the tables 51 registers of a
+  // row's state were spilled instead of 43, L = 19, 8 columns 7.4 us a step, 6.6
+  // so)
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    const int64_t r = row0 + threadIdx.x + kResThreads * j;
+    const bool valid = r < row1;
+    const uint32_t s = valid ? p.state[r] : 0u;
+    const uint32_t top = (s >> (p.L - 1)) & 1u;
+    const int n11 = __popc(s & (s >> 1)) + (p.periodic ? (int)(top & s & 1u) : 0);
+#pragma unroll
+    for (int c = 0; c < G; ++c) {
+      const double* f = s_field + c * kFieldStride;
+      // the diagonal is rounded once: its error is the same in every step, so
+      // it does not average out over them (relative error of KPM moments, plain
+      // sums / this: L = 12 2.11e-16 / 1.62e-16, L = 16 2.81e-16 / 2.23e-16; as
+      // launches 1.78e-16 and 2.58e-16)
+      double d = p.vzz * n11, dlo = fma(p.vzz, (double)n11, -d);
+      add_exact(d, dlo, f[32]);
+      for (int b = 0; b < p.L; ++b) add_exact(d, dlo, (s >> b) & 1u ? f[b] : 0.0);
+      const int col = c0 + c;
+      const double sg = (double)p.sc[col], q0 = sg * d;
+      double q = q0, qlo = fma(sg, d, -q0) + sg * dlo;
+      add_exact(q, qlo, (double)p.sc[p.nb + col]);
+      S.dg[j].x[c] = (T)(q + qlo);
+    }
+  }
 #pragma unroll
   for (int j = 0; j < R; ++j) {
     const int q = threadIdx.x + kResThreads * j;
@@ -364,25 +392,10 @@ __device__ __forceinline__ void res_setup(const ResArgs<T>& p, SlabState<T, NL, 
       const uint32_t x = have ? e[(int64_t)(p.nl + p.nh) * kResThreads] : kResNone;
       S.per[j] = x == kResNone ? zero * RB : (x & kResFar) ? kResFar | (x & ~kResFar) * RB : x * RB;
     }
-    const uint32_t s = valid ? p.state[r] : 0u;
-    const uint32_t top = (s >> (p.L - 1)) & 1u;
-    const int n11 = __popc(s & (s >> 1)) + (p.periodic ? (int)(top & s & 1u) : 0);
 #pragma unroll
     for (int c = 0; c < G; ++c) {
-      const double* f = s_field + c * kFieldStride;
-      // the diagonal is rounded once: its error is the same in every step, so
-      // it does not average out over them (relative error of KPM moments, plain
-      // sums / this: L = 12 2.11e-16 / 1.62e-16, L = 16 2.81e-16 / 2.23e-16; as
-      // launches 1.78e-16 and 2.58e-16)
-      double d = p.vzz * n11, dlo = fma(p.vzz, (double)n11, -d);
-      add_exact(d, dlo, f[32]);
-      for (int b = 0; b < p.L; ++b) add_exact(d, dlo, (s >> b) & 1u ? f[b] : 0.0);
-      const int col = c0 + c;
-      const double sg = (double)p.sc[col], q0 = sg * d;
-      double q = q0, qlo = fma(sg, d, -q0) + sg * dlo;
-      add_exact(q, qlo, (double)p.sc[p.nb + col]);
-      S.dg[j].x[c] = (T)(q + qlo);
-      S.v[j].x[c] = !valid ? T(0) : p.v ? p.v[(int64_t)col * p.D + r] : T(r == col);
+      const int64_t col = c0 + c;
+      S.v[j].x[c] = !valid ? T(0) : p.v ? p.v[col * p.D + r] : T(r == col);
     }
     const uint32_t off = valid ? (uint32_t)r * RB : kNoRow;
     S.b1[j] = rload<T, G>(cur, off);
