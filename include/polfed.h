@@ -234,8 +234,10 @@ polfed_status polfed_op_set_kernel(polfed_op* op, int precision, int variant, in
  * kernels, L >= 22), 5 = the resident recurrence (a column's whole filter in
  * one launch, its rows kept by a team of workgroups of one XCD; the timing
  * may pick it up to D = 98,304, it can be set for chains of which two vectors
- * fit the LDS of a compute unit: FP64 to L = 14, FP32 to L = 16 at half
- * filling), 6 / 7 = row-group kernel on the interleaved
+ * fit the LDS of a compute unit: FP64 to L = 14, FP32 to L = 15 at half
+ * filling; a server with more than one group of solves takes the fastest
+ * other variant where the timing's pick would fill more than half of the
+ * compute units of an XCD), 6 / 7 = row-group kernel on the interleaved
  * blocks (the 16-byte column groups of a row on neighbouring lanes, so a
  * wavefront reads whole rows; up to 32 FP64 or 64 FP32 columns; 4 / 8
  * workgroups per compute unit); -2 only reports.  A batch whose pattern was

@@ -973,11 +973,11 @@ constexpr int kWtXcds = 8;
 // With DB the next tile is staged into a second LDS buffer while the current
 // one is processed.
 //
-// What bounds it at L = 24 to 26 is what the L2s fetch: at L = 24 145 MB a
-// step, 86 of them the vectors themselves, which a plain pass over the same
-// vectors moves at 7.5 TB/s (19 us of 26.5); at L = 26 about 590 MB of 730 go
-// through when the order of the tiles is kept.  Below that it is the work of a
-// segment: a bond without a hop is passed by with a branch where it is loaded
+// What bounds it at L = 24 to 26 is what the L2s fetch and write (counters):
+// at L = 24 154 MB a step with two buffers (137 with one, which is slower), 86
+// of them the vectors themselves; at the 7.5 TB/s of a plain pass over the same
+// vectors that is 20 us of 25.5.  At L = 26 637 MB (333 the vectors), 85 us of
+// 100.  Below that it is the work of a segment: a bond without a hop is passed by with a branch where it is loaded
 // and where it is added, the low part and the number of its idle bonds come
 // with the neighbour positions, a hop that a row does not have reads a zero,
 // and FP32 is held to 64 registers, for two workgroups a CU.

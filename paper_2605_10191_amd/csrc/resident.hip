@@ -16,7 +16,7 @@
 //   - a step ends with a barrier of the team's members (0.9 us for 32 of
 //     them; a launch in a replayed graph takes 1.6 us before it does
 //     anything) instead of a kernel boundary.
-// Measured (FP64, us a step, before -> here): one column at L = 12 3.6 -> 1.2,
+// Measured (FP64, us a step, before -> here): one column at L = 12 3.6 -> 1.0,
 // L = 16 3.9 -> 1.9, L = 18 4.5 -> 3.0; 13 columns at L = 14 4.2 -> 1.7; 13 columns
 // at L = 18 17.3 -> 4.5, of which the barrier and the gathers' round trip are
 // 1.3 and the LDS reads of the hops most of the rest.
@@ -1150,8 +1150,8 @@ bool res_filter(hipStream_t s, const polfed_op* op, double E_c, double dE, const
 // P(H~) as a matrix: its columns are the filter of the unit vectors, a batch
 // that fills the chip, and an application is then one product with it.  A
 // short chain's filter runs on one workgroup or one XCD however idle the rest
-// of the chip is; at L = 12 (D = 924, K = 181) an application takes 222 us,
-// the matrix of all 924 columns 0.89 ms and a product 3.4 to 4.7 us; at L = 13
+// of the chip is; at L = 12 (D = 924, K = 181) an application takes 195 us,
+// the matrix of all 924 columns 0.79 ms and a product 3.4 to 4.7 us; at L = 13
 // (D = 1,716, K = 489) 590 us against 9.3 ms and 8 us.  The error of an
 // application is that of the columns, each a Clenshaw sum of the same order,
 // weighted with v (norm of the error against an 80-bit evaluation, recurrence
