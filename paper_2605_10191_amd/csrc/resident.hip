@@ -74,6 +74,7 @@ struct TeamView {
 // Every wait is bounded, so that a kernel ends whatever happens to its team's
 // state: a barrier that gives up sets err and lets its member run on to the end
 // of the columns it is at, and what the call returns is NaN or an error.
+
 // What a member that cannot go on leaves of n elements of a result.
 template <typename T>
 __device__ __forceinline__ void poison(T* w, int64_t n) {
@@ -155,7 +156,7 @@ __device__ __forceinline__ bool team_join(ResState* st, int nslab, int teams_per
         if (leave && n < nslab) n = -1;
         res_store(&t->n, n);
       } else if (rank < kResClosed) {
-        // the first member runs and closes the team within 100 us
+        // the first member runs and closes the team within 2 ms
         const long long t0 = wall_clock64();
         while ((n = res_load(&t->n)) == 0 && wall_clock64() - t0 < kResWait)
           __builtin_amdgcn_s_sleep(1);
